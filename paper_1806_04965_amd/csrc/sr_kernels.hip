@@ -332,7 +332,8 @@ __device__ __forceinline__ bool sr_head_body(const SrCtx* __restrict__ ctx, cons
         if (threadIdx.x == 0) {
           const int old = __hip_atomic_fetch_add(&h.counters[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           *flag = (old == h.splits - 1);
-          if (old == h.splits - 1) h.counters[b] = 0;
+          // an agent-scope store: a launch may cover several frames, whose slabs count on from here on other XCDs
+          if (old == h.splits - 1) __hip_atomic_store(&h.counters[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
         if (!*flag) return false;

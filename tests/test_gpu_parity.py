@@ -430,3 +430,21 @@ def test_depth_ordered_launches_of_other_lengths(frames_per_launch):
     c = gpu_rollout(g, w, b, x, 13, options={5: 0})
     assert np.array_equal(a, c)
     assert np.abs(a[-1]).max() > 0
+
+
+@pytest.mark.parametrize("batch", [1, 4, 37])
+def test_pooled_slabs_of_several_frames_in_one_launch(batch):
+    # a GAP read-out over 12 x 12 pixels is summed in three slabs whose arrival counter is reset by the last one:
+    # in a launch that covers several frames the next frame's slabs, on other XCDs, must see the reset
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    nodes = [Node("in", 3, 24, 24, ACT_IDENTITY), Node("a", 40, 24, 24), Node("b", 64, 12, 12), Node("out", 43, 1, 1, ACT_IDENTITY)]
+    edges = [Edge(0, 1), Edge(1, 1), Edge(1, 2, "conv", 3, 3, 2, 1), Edge(2, 2), Edge(2, 3, "gap_dense", 1, 1, 1, 0)]
+    g0 = Graph("slabs", nodes, edges, batch, 16, "bf16", out_node=3)
+    g = g0.with_pattern(W.sequential_pattern(g0))
+    w, b, x = W.make_case(g, seed=63, bias_scale=0.1, frames=16)
+    a, dev = gpu_rollout(g, w, b, x, 16, return_dev=True, options={6: 4096})
+    h = dev.health()
+    dev.close()
+    assert h["dependency_driven"] and h["dependency_timeouts"] == 0
+    assert np.array_equal(a, gpu_rollout(g, w, b, x, 16, options={5: 0}))
+    assert np.abs(a[-1]).max() > 0

@@ -113,10 +113,10 @@ typedef enum {
                                   frames that do not depend on one another run side by side;
                                   0: frame after frame */
   SR_OPT_TRAIN_TALL_TILES_FROM = 8
-                               /* training window (sr_window_gradients): a contraction takes the taller of its two
-                                  tile shapes when that launch has at least this many workgroups, else the shorter
-                                  one (default 2048; 0: always the taller, 2^30: never).  Same results either way
-                                  up to the order of no sum; for tests of both shapes and for tuning. */
+                               /* fp32 contractions (training window, fp32 frames): a contraction takes the taller of its
+                                  tile shapes when that launch has at least this many workgroups, else a shorter
+                                  one (default 2048; 0: always the taller, 2^30: never).  Same results either way up to
+                                  the order of float sums; for tests of both shapes and for tuning. */
 } sr_option;
 
 /* ---------------------------------------------------------------------------
@@ -254,7 +254,7 @@ sr_status sr_frame_index(const sr_graph* g, int64_t* frame);
 /* Run one frame with plain launches, bracketing every kernel of the frame with HIP events on
  * the graph's stream, and wait for it.  kernel_ms (host, capacity `cap`) receives the
  * duration of each launch in launch order, kernel_kind (host, may be NULL) a tag per launch:
- * 0 input staging, 1 MFMA convolution tiles, 2 direct (one thread per output) nodes, 3 GAP+dense
+ * 0 input staging, 1 MFMA convolution tiles, 2 fp32 and one-thread-per-output nodes, 3 GAP+dense
  * head, 4 bookkeeping; n_launches the number written.  Synchronous. */
 sr_status sr_frame_step_timed(sr_graph* g, const void* const* inputs_t, float* kernel_ms,
                               int32_t* kernel_kind, int32_t cap, int32_t* n_launches);
@@ -293,9 +293,10 @@ sr_status sr_graph_health(sr_graph* g, int64_t* dependency_timeouts, int32_t* de
  * that has not happened yet): kinds[v] (host, n_nodes ints) =
  *   0 input node (its state is staged from the caller's frame),
  *   1 matrix-core tile kernel with 4 waves per workgroup, 2 matrix-core tile kernel with 8 waves,
- *   3 one-thread-per-output kernel (fp32 graphs; nodes neither tile kernel takes: an edge with stride
- *     or upsampling outside {1,2,4}, a source patch larger than the LDS budget),
- *   4 head item (1x1 node fed by dense / GAP+dense edges only).
+ *   3 fp32 kernels (row tiles on the fp32 matrix cores; one thread per output with SR_OPT_FORCE_DIRECT and for bf16
+ *     nodes neither tile kernel takes: an edge with stride or upsampling outside {1,2,4}, a source patch larger than
+ *     the LDS budget),
+ *   4 1x1 node fed by dense / GAP+dense edges only.
  * Errors: SR_ERR_ARG, and what planning can return (SR_ERR_STATE: weights missing, SR_ERR_OOM, SR_ERR_DEVICE). */
 sr_status sr_graph_node_kernels(const sr_graph* g, int32_t* kinds);
 

@@ -1,0 +1,258 @@
+// Tiled fp32 contractions of whole update steps (fp32 graphs): descriptor tables, the index arithmetic shared by
+// the kernels (sr_f32.hip) and their planner (sr_f32_plan.cpp), and the launchers.
+//
+// Two kernels.  A ROW tile computes a rectangle (pixels x channels) of one node's tensor as the sum over all
+// contributing edges ("segments") of a contraction whose left operand is gathered from another tensor:
+//   forward         x_v = m * sigma(b_v + sum_e f_e(x_u)):    rows = pixels of v, columns = channels of v,
+//                   reduction = (tap, source channel) of every incoming edge
+//   state gradient  da_u = m * sigma' * sum_e f_e^T(da_w):    rows = pixels of u (of one stride phase), columns =
+//                   channels of u, reduction = (tap, target channel) of every outgoing edge
+// A GRADIENT tile computes a rectangle of dtheta_e: rows = (tap, source channel), columns = target channels,
+// reduction = (frame, pixel).  Work items of many nodes, edges and frames ride in one launch.
+#ifndef SR_F32_H_
+#define SR_F32_H_
+
+#include <hip/hip_runtime_api.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include <vector>
+
+#include "sr_internal.h"
+
+#ifdef __HIPCC__
+#define SR_HD __host__ __device__ __forceinline__
+#else
+#define SR_HD inline
+#endif
+
+// n / d for n < 2^31 with the pair made for d (Granlund & Montgomery: l = ceil(log2 d),
+// m = floor(2^32 (2^l - d) / d) + 1, q = (mulhi(m, n) + n) >> l; no overflow while n < 2^31)
+struct SrDiv { uint32_t mul, sh; };
+inline SrDiv sr_div_for(uint32_t d) {
+  SrDiv q;
+  q.sh = 0;
+  while ((1ull << q.sh) < d) ++q.sh;
+  q.mul = (uint32_t)((((1ull << q.sh) - d) << 32) / d + 1);
+  return q;
+}
+SR_HD int sr_divide(int n, SrDiv d) {
+  const uint32_t hi = (uint32_t)(((uint64_t)(uint32_t)n * d.mul) >> 32);
+  return (int)((hi + (uint32_t)n) >> d.sh);
+}
+
+// A tensor that has a copy per frame (or per parity of the frame): copy s starts at base + s * stride bytes.
+// base = null: the tensor does not exist (no dropout mask, no loss term).
+struct SrTensor {
+  char* base;
+  long long stride;
+};
+
+#define SR_SEG_LAG 1      // reads the gathered tensor one frame away from the rows' own frame
+#define SR_SEG_ZERO0 2    // ... and that copy is known to be all zero when it lies outside the window
+#define SR_SEG_IMAGE 4    // the gathered row depends on the image only (mean over pixels + dense, backwards)
+#define SR_SEG_QUADS 8    // channel counts are multiples of four: 16-byte gathers
+struct SrSeg {
+  const float* w;         // weights theta_e
+  int32_t tensor, flags;
+  int32_t GH, GW, GC;     // gathered image and its channels
+  int32_t rs, r0h, r0w;   // first gathered row / column of a pixel: (hh / up) * rs + r0
+  int32_t dir;            // gathered row of tap row vi: first + dir * vi
+  int32_t ntj, R;         // taps per tap row; length of the reduction: taps * GC
+  int32_t wt0, wti, wtj;  // backwards: tap of theta = wt0 + vi * wti + vj * wtj
+  int32_t ldw;            // forward: columns of theta (= J); backwards: rows of theta per tap (= J)
+  int32_t step0;          // first reduction step of this segment in the phase
+  SrDiv d_gc, d_ntj, d_up;
+  int32_t pad_[3];
+};
+
+// What a row tile's rows are: the pixels h = hh * S + ph, w = ww * S + pw of a node (S = 1: all of them).
+struct SrPhase {
+  int32_t node;                   // SrRowNode
+  int32_t seg_begin, seg_image, seg_end;   // segments; [seg_begin, seg_image) are the SR_SEG_IMAGE ones
+  int32_t steps;                  // reduction steps of all segments
+  int32_t I, Hp, Wp;              // rows, and the phase's pixel grid
+  int32_t S, ph, pw;
+  float image_scale;              // 1 / pixels: factor of the SR_SEG_IMAGE segments
+  SrDiv d_wp, d_hpwp;
+};
+
+struct SrRowNode {
+  int32_t out, x, seed, mask;     // tensors: result; state (backwards: gate of the rectifier); term added to the sum; dropout
+  const float* bias;              // forward
+  int32_t C, H, W, act;
+  int32_t gnode;                  // graph node (recording of rollout outputs)
+  int32_t pad_[3];
+};
+
+// tile shapes: TI x TJ, of four waves; SR_F32_SMALL: each wave takes every fourth reduction step of a 32 x 32 tile
+enum { SR_F32_128x128 = 0, SR_F32_128x64 = 1, SR_F32_64x64 = 2, SR_F32_128x32 = 3, SR_F32_SMALL = 4 };
+struct SrRowTile {
+  int32_t phase;                  // < 0: empty slot
+  int32_t shape, i0, j0;
+  int32_t step_begin, step_end;   // part of the phase's reduction steps
+  int32_t split_slot, part;       // K-split as in SrMfmaTile: slot of part 0 (-1: none), part index | parts << 16
+};
+
+// A launch over several (tile list, frame) pairs: pair k takes the workgroups from block0 on.
+struct SrRun {
+  int32_t block0, tile0, frame, pad_;
+};
+
+#define SR_F32_KS 16              // reduction indices per step
+#define SR_F32_STAGES 3           // steps of operands in LDS at a time
+
+// k-th group of four reduction indices of row `row` of an operand that lies in LDS row by row (64 bytes a row):
+// sixteen rows read together hit sixteen different 16-byte columns of the 256-byte LDS line
+SR_HD int sr_f32_piece(int row, int k4) { return k4 ^ ((row >> 2) & 3); }
+
+// A row of a row tile, seen by one segment: where tap (0, 0) lands in the gathered image
+struct SrRowAt { int h, w; uint32_t off; };   // h < -2^20: no such row
+#define SR_FAR (1 << 21)
+SR_HD SrRowAt sr_row_at(const SrPhase& p, const SrSeg& g, int i, int b0) {
+  SrRowAt r;
+  const int b = sr_divide(i, p.d_hpwp), rem = i - b * (p.Hp * p.Wp);
+  const int hh = sr_divide(rem, p.d_wp), ww = rem - hh * p.Wp;
+  if (g.flags & SR_SEG_IMAGE) {
+    r.h = 0;
+    r.w = 0;
+    r.off = (uint32_t)((b - b0) * g.GC) * 4u;
+  } else {
+    r.h = sr_divide(hh, g.d_up) * g.rs + g.r0h;
+    r.w = sr_divide(ww, g.d_up) * g.rs + g.r0w;
+    r.off = (uint32_t)((((b - b0) * g.GH + r.h) * g.GW + r.w) * g.GC) * 4u;
+  }
+  if (i >= p.I) r.h = -SR_FAR;
+  return r;
+}
+
+// Reduction index r of a segment: tap row and column, channel
+struct SrTapAt { int vi, vj, c; };
+SR_HD SrTapAt sr_tap_at(const SrSeg& g, int r) {
+  SrTapAt t;
+  const int tap = sr_divide(r, g.d_gc);
+  t.c = r - tap * g.GC;
+  t.vi = sr_divide(tap, g.d_ntj);
+  t.vj = tap - t.vi * g.ntj;
+  if (r >= g.R) t.vi = 2 * SR_FAR;   // past the end: outside every image
+  return t;
+}
+SR_HD bool sr_gather_ok(const SrSeg& g, const SrRowAt& a, const SrTapAt& t) {
+  return (unsigned)(a.h + g.dir * t.vi) < (unsigned)g.GH && (unsigned)(a.w + g.dir * t.vj) < (unsigned)g.GW;
+}
+SR_HD uint32_t sr_gather_off(const SrSeg& g, const SrTapAt& t) {   // added to SrRowAt::off
+  return (uint32_t)(g.dir * (t.vi * g.GW + t.vj) * g.GC + t.c) * 4u;
+}
+// weights, backwards: theta[tap][j][c]
+SR_HD uint32_t sr_weight_off(const SrSeg& g, const SrTapAt& t, int j) {
+  return (uint32_t)(((g.wt0 + t.vi * g.wti + t.vj * g.wtj) * g.ldw + j) * g.GC + t.c) * 4u;
+}
+
+// ---------------------------------------------------------------------------
+// gradient tiles
+// ---------------------------------------------------------------------------
+struct SrGradEdge {
+  int32_t x, dy;                  // tensors: source state, target gradient
+  int32_t lag, first_frame;       // the source is read at frame - lag; earlier frames contribute nothing
+  int32_t H, W, Cin, Ho, Wo, Cout;
+  int32_t kw, stride, pad, up;
+  int32_t I, M;                   // rows = taps * Cin; pixels per frame
+  int32_t steps_per_frame;        // ceil(M / SR_F32_KS)
+  int32_t quads_in, quads_out;    // channel counts that are multiples of four
+  int32_t slices;                 // parts the reduction is cut into
+  long long part_at;              // first float of this edge's partial sums
+  SrDiv d_cin, d_kw, d_wo, d_howo, d_up;
+};
+// kind 0: gradient tile; 1: column sums of a gradient tensor (bias gradient), 64 channels x a range of rows
+struct SrGradTile {
+  int32_t edge, shape, i0, j0;
+  int32_t step_begin, step_end;   // steps counted over the edge's frames
+  int32_t slice, kind;
+};
+struct SrGradBias {
+  int32_t dy, C, M;               // rows per frame
+  int32_t slices;
+  long long part_at;
+};
+// dst[k] (+)= sum over the slices of part[s][k], in slice order
+struct SrGradSum {
+  long long part_at, n;
+  int32_t slices, dst;            // dst: index into the launch's destination pointers
+  int32_t block0, pad_;
+};
+
+// pixel of a gradient tile's reduction: row of the gathered source image
+struct SrPixAt { int b, h, w; };
+SR_HD SrPixAt sr_pix_at(const SrGradEdge& e, int m) {
+  SrPixAt p;
+  p.b = sr_divide(m, e.d_howo);
+  const int rem = m - p.b * (e.Ho * e.Wo);
+  const int ho = sr_divide(rem, e.d_wo), wo = rem - ho * e.Wo;
+  p.h = sr_divide(ho, e.d_up) * e.stride - e.pad;
+  p.w = sr_divide(wo, e.d_up) * e.stride - e.pad;
+  if (m >= e.M) p.h = -SR_FAR;
+  return p;
+}
+
+// ---------------------------------------------------------------------------
+// launches
+// ---------------------------------------------------------------------------
+struct SrRowArgs {
+  const SrTensor* tensors;
+  const SrRowNode* nodes;
+  const SrPhase* phases;
+  const SrSeg* segs;
+  const SrRowTile* tiles;
+  const SrRun* runs;              // null: the launch is one tile list of the frame path (slots by the frame's parity)
+  int32_t n_runs, n_tiles;
+  int32_t frame0;                 // training: frame of a run = frame0 + run.frame
+  int32_t frames;                 // training: W
+  int32_t ring;                   // backwards: gradient tensors keep `ring` frames (slot = frame % ring)
+  int32_t rec_node;               // frame path: node whose values also go to the rollout output (-1: none)
+  SrSplitScratch split;
+};
+struct SrGradArgs {
+  const SrTensor* tensors;
+  const SrGradEdge* edges;
+  const SrGradBias* biases;
+  const SrGradTile* tiles;
+  float* part;
+  int32_t frame_lo, ring;         // first frame of the chunk; ring of the gradient tensors
+};
+
+// frame path: the level's tiles, direct blocks of other nodes and auxiliary items in one launch
+hipError_t sr_launch_rows_frame(hipStream_t s, SrCtx* ctx, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
+                                const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
+                                int aux_smem_bytes, int is_last);
+
+// ---------------------------------------------------------------------------
+// planner (sr_f32_plan.cpp)
+// ---------------------------------------------------------------------------
+inline void sr_f32_shape(int shape, int* ti, int* tj) {
+  static const int t[5][2] = {{128, 128}, {128, 64}, {64, 64}, {128, 32}, {32, 32}};
+  *ti = t[shape][0];
+  *tj = t[shape][1];
+}
+inline int sr_f32_lds_bytes(int shape) {
+  int ti, tj;
+  sr_f32_shape(shape, &ti, &tj);
+  return SR_F32_STAGES * (ti + tj) * SR_F32_KS * 4 * (shape == SR_F32_SMALL ? 4 : 1);
+}
+struct sr_graph;
+struct SrRowPlan {
+  std::vector<SrSeg> segs;
+  std::vector<SrPhase> phases;
+  std::vector<SrRowNode> nodes;
+};
+// can node v be computed by row tiles (no incoming GAP edge, offsets in 32 bits)?
+bool sr_rows_take_forward(const sr_graph* g, int v);
+// appends node v's descriptors; state tensors are numbered like the nodes
+void sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v);
+// Tiles of phases that one launch covers, in the order of the list (workgroup i runs on XCD i % 8; padded to a
+// multiple of 8 with empty tiles).  work_cycles: compute-unit cycles of the whole launch if it covers more than
+// these phases (0: just these).  tall_from: SR_OPT_TRAIN_TALL_TILES_FROM; split: SR_OPT_K_SPLIT.
+void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split,
+                   int* split_slots, std::vector<SrRowTile>* out, int* lds_bytes);
+double sr_rows_work(const SrRowPlan& p, int phase);   // compute-unit cycles of a phase at the fp32 matrix rate
+
+#endif  // SR_F32_H_

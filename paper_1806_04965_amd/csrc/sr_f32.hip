@@ -1,0 +1,506 @@
+// Tiled contractions of fp32 graphs on the fp32 matrix cores (v_mfma_f32_32x32x2_f32): whole update steps of the
+// frame path, and the forward pass, state gradients and weight gradients of a training window (see sr_f32.h).
+//
+// A workgroup of four waves owns a TI x TJ tile and walks its reduction in steps of 16 indices.  The operands of a
+// step are brought into LDS by direct-to-LDS loads whose lane addresses do the gathering (taps, strides, padding;
+// elements that do not exist are read from a line of zeros), two steps ahead of the one being multiplied: one barrier
+// per step, no registers between global memory and LDS.  fp32 matrix instructions are slow (a 32x32x2 product takes
+// 64 cycles of its SIMD), so a step's operand traffic (at most 16 bytes per cycle and CU) and address arithmetic hide
+// behind them; what bounds a tile is the fp32 matrix rate, 157 TFLOP/s, once the launch fills the chip.
+//
+// Measured, DSR2 as an fp32 graph (batch 64, 6.4 GFLOP per frame): 1350 us per frame with a thread per output (weights
+// and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s); MNIST SR, batch 128: 29 -> 15 us.
+//
+// Every sum has a fixed order (reduction index by index within a part, parts in order, waves in order): the same call
+// gives the same bits.
+#include "sr_device.h"
+#include "sr_f32.h"
+
+namespace {
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+#define SR_CONST4(T) const __attribute__((address_space(4))) T*
+template <typename T>
+__device__ __forceinline__ SR_CONST4(T) sr_k(const T* p) { return (SR_CONST4(T))(unsigned long long)p; }
+#define SR_UNI(x) __builtin_amdgcn_readfirstlane(x)
+__device__ __forceinline__ const char* sr_uni_ptr(const char* p) {
+  const unsigned long long v = (unsigned long long)p;
+  return (const char*)(((unsigned long long)(unsigned)SR_UNI((int)(v >> 32)) << 32) | (unsigned)SR_UNI((int)v));
+}
+
+__device__ __align__(64) const float sr_zero_line[16] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+// One direct-to-LDS load: lane l's 16 (4) bytes go to lds + 16 l (4 l).
+__device__ __forceinline__ void sr_to_lds16(const char* g, unsigned lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)(unsigned long long)lds, 16, 0, 0);
+}
+__device__ __forceinline__ void sr_to_lds4(const char* g, unsigned lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)(unsigned long long)lds, 4, 0, 0);
+}
+// this wave's loads but the newest N have landed, and its LDS reads are done
+template <int N>
+__device__ __forceinline__ void sr_wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+// a barrier that LDS accesses are not moved across (the waits stand before it)
+__device__ __forceinline__ void sr_step_barrier() {
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ unsigned sr_lds_at(const void* p) {
+  return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) char*)p;
+}
+
+__device__ __forceinline__ SrDiv sr_load_div(SR_CONST4(SrDiv) d) { return SrDiv{d->mul, d->sh}; }
+__device__ __forceinline__ SrSeg sr_load_seg(SR_CONST4(SrSeg) s) {
+  SrSeg g;
+  g.w = s->w;
+  g.tensor = s->tensor; g.flags = s->flags;
+  g.GH = s->GH; g.GW = s->GW; g.GC = s->GC;
+  g.rs = s->rs; g.r0h = s->r0h; g.r0w = s->r0w;
+  g.dir = s->dir; g.ntj = s->ntj; g.R = s->R;
+  g.wt0 = s->wt0; g.wti = s->wti; g.wtj = s->wtj;
+  g.ldw = s->ldw; g.step0 = s->step0;
+  g.d_gc = sr_load_div(&s->d_gc); g.d_ntj = sr_load_div(&s->d_ntj); g.d_up = sr_load_div(&s->d_up);
+  return g;
+}
+__device__ __forceinline__ SrPhase sr_load_phase(SR_CONST4(SrPhase) s) {
+  SrPhase p;
+  p.node = s->node; p.seg_begin = s->seg_begin; p.seg_image = s->seg_image; p.seg_end = s->seg_end; p.steps = s->steps;
+  p.I = s->I; p.Hp = s->Hp; p.Wp = s->Wp; p.S = s->S; p.ph = s->ph; p.pw = s->pw;
+  p.image_scale = s->image_scale;
+  p.d_wp = sr_load_div(&s->d_wp); p.d_hpwp = sr_load_div(&s->d_hpwp);
+  return p;
+}
+
+// which copies of its tensors a tile works on
+struct SrSlots {
+  int lag0, lag1;      // gathered tensors, without and with SR_SEG_LAG
+  int own;             // result
+  int frame;           // state, mask, loss term
+  bool outside;        // the lagged copy lies outside the window (segments with SR_SEG_ZERO0 contribute nothing)
+};
+
+// The operands of a tile: a TI x 16 and a 16 x TJ piece per step, NW waves fetching them together.
+//   rows:  TI (TJ) rows of 16 reduction indices, 64 bytes a row, pieces of four permuted (sr_f32_piece)
+//   k-major: 16 lines of TI (TJ) elements
+// A is rows when the gathered channel count is a multiple of four (16-byte loads), else k-major (4-byte loads); B is
+// k-major in the forward direction, where theta's columns are contiguous, and like A backwards.
+template <int TI, int TJ, int NW, bool BACK>
+struct SrRowOperands {
+  static constexpr int NA = TI / (16 * NW);                        // 16-byte loads of A per wave and step
+  static constexpr int NB = TJ / (16 * NW) > 0 ? TJ / (16 * NW) : 1;   // ... of B (TJ = 32 of four waves: half the lanes)
+  static constexpr int STAGE = (TI + TJ) * 64;                     // bytes of one step in LDS
+  static constexpr int LOADS = NA + NB;                            // fewest loads a wave issues per step
+  static constexpr bool HALF_B = TJ / (16 * NW) == 0;
+
+  SrSeg g;
+  const char* src;           // gathered tensor, image of the tile's first row
+  SrRowAt row[NA];
+  int wv, lane, i0, j0;
+  int quads, quads_w;
+
+  // a new segment: where this lane's rows are in its image
+  __device__ __forceinline__ void enter(const SrPhase& p, const SrTensor* tensors, const SrSlots& sl) {
+    SR_CONST4(SrTensor) t = sr_k(tensors) + g.tensor;
+    const int slot = (g.flags & SR_SEG_LAG) ? sl.lag1 : sl.lag0;
+    const int b0 = SR_UNI(sr_divide(i0, p.d_hpwp));
+    const long long image = (g.flags & SR_SEG_IMAGE) ? (long long)g.GC * 4 : (long long)g.GH * g.GW * g.GC * 4;
+    src = sr_uni_ptr((const char*)(unsigned long long)t->base + slot * t->stride + b0 * image);
+    quads = SR_UNI((g.flags & SR_SEG_QUADS) && ((unsigned)(unsigned long long)src & 15u) == 0);
+    quads_w = SR_UNI((g.ldw & 3) == 0);
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      const int r = quads ? n * 16 * NW + wv * 16 + (lane >> 2)
+                          : (TI >= 64 ? (TI == 128 ? (wv & 1) * 64 + lane : lane) : (lane & 31));
+      row[n] = sr_row_at(p, g, i0 + r, b0);
+    }
+  }
+
+  // loads of the 16 reduction indices from r0 on, into LDS at `at`
+  __device__ __forceinline__ void issue(int r0, unsigned at) {
+    const char* zero = (const char*)sr_zero_line;
+    const unsigned bt = at + TI * 64;
+    if (quads) {
+      const int k4 = sr_f32_piece(lane >> 2, lane & 3);
+      SrTapAt t;
+      if ((g.GC & 15) == 0) {   // the step lies inside one tap: its decoding runs on the scalar unit
+        t = sr_tap_at(g, SR_UNI(r0));
+        t.c += 4 * k4;
+      } else {
+        t = sr_tap_at(g, r0 + 4 * k4);
+      }
+      const uint32_t toff = sr_gather_off(g, t);
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+        const char* p = sr_gather_ok(g, row[n], t) ? src + (uint32_t)(row[n].off + toff) : zero;
+        sr_to_lds16(p, at + (n * NW + wv) * 1024);
+      }
+      if (BACK) {
+        const bool r_ok = t.vi < SR_FAR;
+        const uint32_t woff = sr_weight_off(g, t, 0);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const int jr = HALF_B ? wv * 8 + (lane >> 2) : n * 16 * NW + wv * 16 + (lane >> 2);
+          const int k4b = HALF_B ? sr_f32_piece(jr, lane & 3) : k4;
+          const int j = j0 + jr;
+          // (a half-filled wave's rows start at a multiple of eight: its permutation differs from A's)
+          const uint32_t o = woff + (uint32_t)(j * g.GC) * 4u + (uint32_t)((k4b - k4) * 16);
+          const char* p = (r_ok && j < g.ldw) ? (const char*)g.w + o : zero;
+          if (HALF_B) {
+            if (lane < 32) sr_to_lds16(p, bt + wv * 512);
+          } else {
+            sr_to_lds16(p, bt + (n * NW + wv) * 1024);
+          }
+        }
+        return;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < TI / 4 / NW; ++q) {
+        const int id = q * NW + wv;
+        const int k = TI >= 64 ? id * 64 / TI : 2 * id + (lane >> 5);
+        const SrTapAt t = sr_tap_at(g, TI >= 64 ? SR_UNI(r0 + k) : r0 + k);
+        const char* p = sr_gather_ok(g, row[0], t) ? src + (uint32_t)(row[0].off + sr_gather_off(g, t)) : zero;
+        sr_to_lds4(p, at + id * 256);
+      }
+      if (BACK) {
+#pragma unroll
+        for (int q = 0; q < TJ / 4 / NW; ++q) {
+          const int id = q * NW + wv;
+          const int k = TJ >= 64 ? id * 64 / TJ : 2 * id + (lane >> 5);
+          const int j = j0 + (TJ >= 64 ? (TJ == 128 ? (id & 1) * 64 + lane : lane) : (lane & 31));
+          const SrTapAt t = sr_tap_at(g, TJ >= 64 ? SR_UNI(r0 + k) : r0 + k);
+          const char* p = (t.vi < SR_FAR && j < g.ldw) ? (const char*)g.w + sr_weight_off(g, t, j) : zero;
+          sr_to_lds4(p, bt + id * 256);
+        }
+        return;
+      }
+    }
+    // forward: 16 lines of theta
+    if (quads_w) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int id = HALF_B ? wv * 32 + lane : (n * NW + wv) * 64 + lane;
+        const int r = r0 + id / (TJ / 4), j = j0 + 4 * (id % (TJ / 4));
+        const char* p = (r < g.R && j < g.ldw) ? (const char*)g.w + (uint32_t)(r * g.ldw + j) * 4u : zero;
+        if (HALF_B) {
+          if (lane < 32) sr_to_lds16(p, bt + wv * 512);
+        } else {
+          sr_to_lds16(p, bt + (n * NW + wv) * 1024);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < TJ / 4 / NW; ++q) {
+        const int id = q * NW + wv;
+        const int r = r0 + (id * 64 + lane) / TJ, j = j0 + (id * 64 + lane) % TJ;
+        const char* p = (r < g.R && j < g.ldw) ? (const char*)g.w + (uint32_t)(r * g.ldw + j) * 4u : zero;
+        sr_to_lds4(p, bt + id * 256);
+      }
+    }
+  }
+};
+
+// operand fragments of one 32-row (32-column) block for the eight products of a step: reduction index 8 (lane / 32) + kk
+__device__ __forceinline__ void sr_frag_rows(const unsigned char* lds, int row, int half, float (&f)[8]) {
+  const unsigned char* p = lds + row * 64;
+  const f32x4_t lo = *(const f32x4_t*)(p + sr_f32_piece(row, 2 * half) * 16);
+  const f32x4_t hi = *(const f32x4_t*)(p + sr_f32_piece(row, 2 * half + 1) * 16);
+  f[0] = lo.x; f[1] = lo.y; f[2] = lo.z; f[3] = lo.w;
+  f[4] = hi.x; f[5] = hi.y; f[6] = hi.z; f[7] = hi.w;
+}
+template <int T>
+__device__ __forceinline__ void sr_frag_lines(const unsigned char* lds, int row, int half, float (&f)[8]) {
+  const float* p = (const float*)lds + half * 8 * T + row;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) f[k] = p[k * T];
+}
+
+template <int TI, int TJ, int MI, int MJ>
+__device__ __forceinline__ void sr_step_products(const unsigned char* st, int iw, int jw, int lane, bool a_rows, bool b_rows,
+                                                 f32x16_t (&acc)[MI][MJ]) {
+  const int l = lane & 31, half = lane >> 5;
+  float a[MI][8], b[MJ][8];
+  if (a_rows) {
+#pragma unroll
+    for (int x = 0; x < MI; ++x) sr_frag_rows(st, iw + 32 * x + l, half, a[x]);
+  } else {
+#pragma unroll
+    for (int x = 0; x < MI; ++x) sr_frag_lines<TI>(st, iw + 32 * x + l, half, a[x]);
+  }
+  if (b_rows) {
+#pragma unroll
+    for (int y = 0; y < MJ; ++y) sr_frag_rows(st + TI * 64, jw + 32 * y + l, half, b[y]);
+  } else {
+#pragma unroll
+    for (int y = 0; y < MJ; ++y) sr_frag_lines<TJ>(st + TI * 64, jw + 32 * y + l, half, b[y]);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+#pragma unroll
+    for (int x = 0; x < MI; ++x)
+#pragma unroll
+      for (int y = 0; y < MJ; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x][k], b[y][k], acc[x][y], 0, 0, 0);
+}
+
+// K-split: every part leaves its registers in its slab, the part that arrives last adds them up in part order.
+// Agent-scope accesses throughout: the parts run on different XCDs.
+template <int N>
+__device__ __forceinline__ bool sr_row_split(float (&o)[N], const SrSplitScratch& split, int slot, int part_info, int tid, int* flag) {
+  constexpr int UNITS = N * 256 / 1024;   // slots are counted in 1024 floats
+  const int n_parts = part_info >> 16;
+  float* mine = split.slabs + ((size_t)slot + (size_t)(part_info & 0xffff) * UNITS) * 1024 + tid;
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    __hip_atomic_store((unsigned*)(mine + q * 256), __float_as_uint(o[q]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    int* counter = split.counters + slot;
+    const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = (old == n_parts - 1);
+    if (old == n_parts - 1) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!*flag) return false;
+#pragma unroll
+  for (int q = 0; q < N; ++q) o[q] = 0.f;
+  const float* all = split.slabs + (size_t)slot * 1024 + tid;
+  for (int p = 0; p < n_parts; ++p) {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      o[q] += __uint_as_float(__hip_atomic_load((const unsigned*)(all + (size_t)p * UNITS * 1024 + q * 256), __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT));
+  }
+  return true;
+}
+
+// where a recorded node's values go as well (frame path)
+struct SrRecord { float* out; };
+
+// A row tile.  SMALL: every wave takes every fourth step of a 32 x 32 tile through LDS of its own (no barriers); the
+// four waves' sums are added in order at the end.
+template <int TI, int TJ, int WJN, bool BACK, bool SMALL>
+__device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p, int i0, int j0, int step_begin, int step_end,
+                                            int split_slot, int part_info, const SrSlots& sl, float* record, int rec_node,
+                                            unsigned char* lds) {
+  constexpr int NW = SMALL ? 1 : 4, WIN = NW / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
+  typedef SrRowOperands<TI, TJ, NW, BACK> Ops;
+  const int tid = threadIdx.x, lane = tid & 63, wave = SR_UNI(tid >> 6);
+  const int iw = (wave / WJN) * 32 * MI * (SMALL ? 0 : 1), jw = (wave % WJN) * 32 * MJ * (SMALL ? 0 : 1);
+  unsigned char* base = SMALL ? lds + wave * (SR_F32_STAGES * Ops::STAGE) : lds;
+  const unsigned at0 = sr_lds_at(base);
+
+  Ops op;
+  op.wv = SMALL ? 0 : wave; op.lane = lane; op.i0 = i0; op.j0 = j0;
+  f32x16_t acc[MI][MJ];
+#pragma unroll
+  for (int x = 0; x < MI; ++x)
+#pragma unroll
+    for (int y = 0; y < MJ; ++y)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+
+  // two groups of segments: those that depend on the image only, whose sum is scaled, then the others
+  for (int group = (p.seg_image > p.seg_begin) ? 0 : 1; group < 2; ++group) {
+    int seg = (group == 0 ? p.seg_begin : p.seg_image) - 1;
+    const int seg_end = group == 0 ? p.seg_image : p.seg_end;
+    int r = 0, r_stop = 0;   // next step's first index, end of the segment's share
+    // the next step of this workgroup (wave): false when there is none
+    auto next = [&]() -> bool {
+      r += SMALL ? 4 * SR_F32_KS : SR_F32_KS;
+      while (r >= r_stop) {
+        if (++seg >= seg_end) return false;
+        op.g = sr_load_seg(sr_k(A.segs) + seg);
+        if (sl.outside && (op.g.flags & SR_SEG_LAG) && (op.g.flags & SR_SEG_ZERO0)) continue;
+        const int n = (op.g.R + SR_F32_KS - 1) / SR_F32_KS;
+        int lo = max(step_begin - op.g.step0, 0);
+        const int hi = min(step_end - op.g.step0, n);
+        if (SMALL) lo += (wave - (op.g.step0 + lo)) & 3;
+        r = lo * SR_F32_KS;
+        r_stop = hi * SR_F32_KS;
+        if (r < r_stop) op.enter(p, A.tensors, sl);
+      }
+      return true;
+    };
+    int issued = 0, done = 0, wr = 0, rd = 0;
+    unsigned rows = 0;   // per stage: the gathered operand (backwards: both) lies row by row
+    auto issue = [&]() {
+      op.issue(r, at0 + wr * Ops::STAGE);
+      const unsigned bit = 1u << wr;
+      rows = op.quads ? rows | bit : rows & ~bit;
+      wr = wr == SR_F32_STAGES - 1 ? 0 : wr + 1;
+      ++issued;
+    };
+    bool more = next();
+    for (int k = 0; k < SR_F32_STAGES - 1 && more; ++k) {
+      issue();
+      more = next();
+    }
+    while (done < issued) {
+      if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
+      else sr_wait_loads<0>();
+      if (!SMALL) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
+      if (more) {
+        issue();
+        more = next();
+      }
+      sr_step_products<TI, TJ, MI, MJ>(base + rd * Ops::STAGE, iw, jw, lane, (rows >> rd) & 1, BACK && ((rows >> rd) & 1), acc);
+      rd = rd == SR_F32_STAGES - 1 ? 0 : rd + 1;
+      ++done;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (!SMALL) sr_step_barrier();   // the stages are free again
+    if (group == 0) {
+#pragma unroll
+      for (int x = 0; x < MI; ++x)
+#pragma unroll
+        for (int y = 0; y < MJ; ++y)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[x][y][v] *= p.image_scale;
+    }
+  }
+
+  constexpr int NREG = SMALL ? 4 : MI * MJ * 16;
+  float o[NREG];
+  if (SMALL) {
+    __syncthreads();
+    float* red = (float*)lds;   // [wave][register][lane]
+#pragma unroll
+    for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float* s = red + (4 * wave + q) * 64 + lane;
+      o[q] = ((s[0] + s[16 * 64]) + s[32 * 64]) + s[48 * 64];
+    }
+  } else {
+#pragma unroll
+    for (int x = 0; x < MI; ++x)
+#pragma unroll
+      for (int y = 0; y < MJ; ++y)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[((x * MJ + y) * 16 + v) % NREG] = acc[x][y][v];
+  }
+  if ((part_info >> 16) > 1) {
+    __syncthreads();
+    if (!sr_row_split<NREG>(o, A.split, split_slot, part_info, tid, (int*)lds)) return;
+  }
+
+  // ---- epilogue.  Register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its block.
+  SR_CONST4(SrRowNode) nd = sr_k(A.nodes) + p.node;
+  const int C = nd->C, act = nd->act;
+  auto tensor_at = [&](int id, int slot) -> float* {
+    if (id < 0) return nullptr;
+    SR_CONST4(SrTensor) t = sr_k(A.tensors) + id;
+    char* b = (char*)(unsigned long long)t->base;
+    return b ? (float*)(b + slot * t->stride) : nullptr;
+  };
+  float* out = tensor_at(nd->out, sl.own);
+  const float* mask = tensor_at(nd->mask, sl.frame);
+  const float* gate = (BACK && act == 1) ? tensor_at(nd->x, sl.frame) : nullptr;
+  const float* seed = BACK ? tensor_at(nd->seed, sl.frame) : nullptr;
+  const float* bias = nd->bias;
+  if (rec_node < 0 || nd->gnode != rec_node) record = nullptr;
+  constexpr int XB = SMALL ? 1 : MI, YB = SMALL ? 1 : MJ, VB = SMALL ? 4 : 16;
+#pragma unroll
+  for (int x = 0; x < XB; ++x) {
+    size_t at[VB];
+    bool ok[VB];
+#pragma unroll
+    for (int q = 0; q < VB; ++q) {
+      const int v = SMALL ? 4 * wave + q : q;
+      const int i = i0 + iw + x * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      ok[q] = i < p.I;
+      size_t px = ok[q] ? (size_t)i : 0;
+      if (p.S != 1 && ok[q]) {
+        const int b = sr_divide(i, p.d_hpwp), rem = i - b * (p.Hp * p.Wp);
+        const int hh = sr_divide(rem, p.d_wp), ww = rem - hh * p.Wp;
+        px = ((size_t)b * nd->H + hh * p.S + p.ph) * nd->W + ww * p.S + p.pw;
+      }
+      at[q] = px * C;
+    }
+#pragma unroll
+    for (int y = 0; y < YB; ++y) {
+      const int j = j0 + jw + y * 32 + (lane & 31);
+      if (j >= C) continue;
+      const float bj = (!BACK && bias) ? bias[j] : 0.f;
+      float val[VB];
+#pragma unroll
+      for (int q = 0; q < VB; ++q) val[q] = o[(x * YB + y) * VB + q] + bj;
+      if (seed) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q) val[q] += seed[at[q] + j];
+      }
+      if (BACK) {
+        if (gate) {
+#pragma unroll
+          for (int q = 0; q < VB; ++q) val[q] = gate[at[q] + j] > 0.f ? val[q] : 0.f;
+        }
+      } else if (act == 1) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q) val[q] = fmaxf(val[q], 0.f);
+      }
+      if (mask) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q) val[q] *= mask[at[q] + j];
+      }
+#pragma unroll
+      for (int q = 0; q < VB; ++q)
+        if (ok[q]) {
+          out[at[q] + j] = val[q];
+          if (record) record[at[q] + j] = val[q];
+        }
+    }
+  }
+}
+
+template <bool BACK>
+__device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowTile) t, const SrSlots& sl, float* record, int rec_node,
+                                            unsigned char* lds) {
+  const int phase = t->phase;
+  if (phase < 0) return;
+  const SrPhase p = sr_load_phase(sr_k(A.phases) + phase);
+  const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = t->split_slot, part = t->part;
+  if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+  else if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+  else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+  else if (shape == SR_F32_128x32) sr_row_tile<128, 32, 1, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+  else sr_row_tile<32, 32, 1, BACK, true>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+}
+
+}  // namespace
+
+__global__ __launch_bounds__(256, 2) void sr_rows_frame_kernel(SrCtx* __restrict__ ctx, SrRowArgs A,
+                                                               const SrAux* __restrict__ aux, int n_aux, int aux_at,
+                                                               const SrHead* __restrict__ heads,
+                                                               const SrHeadEdge* __restrict__ head_edges,
+                                                               const SrStageNode* __restrict__ stage_nodes, int vec_floats,
+                                                               int is_last) {
+  extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
+  const int item = blockIdx.x;
+  const int frame = SR_UNI(ctx->frame);
+  if (item >= aux_at && item < aux_at + n_aux) {
+    sr_aux_item<float>(ctx, aux[item - aux_at], heads, head_edges, stage_nodes, (float*)sr_rows_lds, vec_floats, frame,
+                       SrFlow{nullptr, nullptr, 0, 0, nullptr});
+  } else {
+    const int cur = frame & 1;
+    const SrSlots sl{cur, cur ^ 1, cur, 0, false};
+    char* rec = A.rec_node >= 0 ? (char*)ctx->out_ptr : nullptr;
+    if (rec) rec += (int64_t)(frame - ctx->out_base) * ctx->out_stride;
+    sr_row_item<false>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
+  }
+  if (is_last) sr_block_done(ctx, gridDim.x, 1);
+}
+
+hipError_t sr_launch_rows_frame(hipStream_t s, SrCtx* ctx, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
+                                const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
+                                int aux_smem_bytes, int is_last) {
+  if (a.n_tiles + n_aux == 0) return hipSuccess;
+  hipLaunchKernelGGL(sr_rows_frame_kernel, dim3(a.n_tiles + n_aux), dim3(256), lds_bytes, s, ctx, a, aux, n_aux, a.n_tiles / 2, heads,
+                     head_edges, stage_nodes, (aux_smem_bytes - 16 - 4096) / 4, is_last);
+  return hipGetLastError();
+}

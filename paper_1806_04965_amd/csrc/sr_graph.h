@@ -28,7 +28,8 @@ struct NodeRt {
   void* state[2] = {nullptr, nullptr};
   float* bias_dev = nullptr;  // [Cp] float
   std::vector<float> bias;
-  int kind = 0;               // 0 input, 1 mfma, 2 direct, 3 head
+  int kind = 0;               // 0 input, 1 mfma, 2 direct, 3 head, 4 fp32 row tiles
+  bool head_like = false;     // fed by dense / GAP+dense edges only, of a size a head item takes
   int input_slot = -1;
 };
 
@@ -46,6 +47,7 @@ struct LevelPlan {
   int tile_begin = 0, n_tiles = 0;
   int block_begin = 0, n_blocks = 0;
   int head_begin = 0, n_heads = 0;
+  int row_begin = 0, n_rows = 0, row_lds = 0;   // fp32 graphs: row tiles of the level, LDS they need
   int aux_begin = 0, n_aux = 0;     // head and input-staging items that ride along in this level's launch
 };
 
@@ -112,6 +114,13 @@ struct sr_graph {
   int n_split_slots = 0;
   bool allow_split = true;
   int tile_version = 0;       // 1: 4-wave tile kernel, 2: 8-wave tile kernel (both operands through LDS); 0: choose
+  // fp32 graphs: tables of the row tiles (sr_f32.h)
+  struct SrTensor* row_tensors = nullptr;
+  struct SrRowNode* row_nodes = nullptr;
+  struct SrPhase* row_phases = nullptr;
+  struct SrSeg* row_segs = nullptr;
+  struct SrRowTile* row_tiles = nullptr;
+  SrSplitScratch row_split{nullptr, nullptr};
   SrHead* heads = nullptr;
   SrHeadEdge* head_edges = nullptr;
   int lds_bytes = 0;

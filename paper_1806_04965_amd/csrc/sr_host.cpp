@@ -16,6 +16,7 @@
 #include "../../include/sr.h"
 #include "sr_internal.h"
 #include "sr_graph.h"
+#include "sr_f32.h"
 
 namespace {
 
@@ -478,7 +479,9 @@ sr_status finalize(sr_graph* g) {
       if (e.d.kind == SR_EDGE_DENSE && (int64_t)sd.height * sd.width * sd.channels > SR_HEAD_MAX_K) head_ok = false;
       if (e.d.kind == SR_EDGE_GAP_DENSE && sd.channels > SR_HEAD_MAX_K) head_ok = false;
     }
+    n.head_like = head_ok;
     if (mfma_eligible(g, v)) n.kind = 1;
+    else if (!bf16 && !g->force_direct && sr_rows_take_forward(g, v)) n.kind = 4;
     else if (head_ok) n.kind = 3;
     else n.kind = 2;
   }
@@ -552,6 +555,10 @@ sr_status finalize(sr_graph* g) {
     g->flops += 2.0 * B * macs;
   }
 
+  // fp32 graphs: descriptors of the nodes on row tiles; a node's state is tensor v, its two copies are the slots
+  SrRowPlan rows;
+  std::vector<SrRowTile> row_tiles;
+  int row_slots = 0;
   std::vector<SrAux> aux, stage_aux;
   for (size_t i = 0; i < stage.size(); ++i) {
     const int total = stage[i].elems_px;
@@ -583,6 +590,17 @@ sr_status finalize(sr_graph* g) {
     if (L == F && g->stage_mode == 1)
       for (SrAux it : stage_aux) { it.c = 1; level_aux.push_back(it); }
 
+    {
+      std::vector<int> phases;
+      for (int v = 0; v < g->n_nodes; ++v)
+        if (g->an.level[v] == L && g->nodes[v].kind == 4) {
+          phases.push_back((int)rows.phases.size());
+          sr_rows_forward(&rows, g, v);
+        }
+      lp.row_begin = (int)row_tiles.size();
+      if (!phases.empty()) sr_rows_tiles(rows, phases, 0, g->train_tall_from, g->allow_split, &row_slots, &row_tiles, &lp.row_lds);
+      lp.n_rows = (int)row_tiles.size() - lp.row_begin;
+    }
     for (int v = 0; v < g->n_nodes; ++v) {
       NodeRt& n = g->nodes[v];
       if (g->an.level[v] != L || n.kind == 0) continue;
@@ -1180,6 +1198,22 @@ sr_status finalize(sr_graph* g) {
     flow_stage_begin = (int)aux.size();
     aux.insert(aux.end(), stage_aux.begin(), stage_aux.end());
   }
+  if (!row_tiles.empty()) {
+    std::vector<SrTensor> tensors;
+    for (const NodeRt& n : g->nodes) tensors.push_back(SrTensor{(char*)n.state[0], (char*)n.state[1] - (char*)n.state[0]});
+    if ((st = upload(g, &g->row_tensors, tensors)) != SR_OK) return st;
+    if ((st = upload(g, &g->row_nodes, rows.nodes)) != SR_OK) return st;
+    if ((st = upload(g, &g->row_phases, rows.phases)) != SR_OK) return st;
+    if ((st = upload(g, &g->row_segs, rows.segs)) != SR_OK) return st;
+    if ((st = upload(g, &g->row_tiles, row_tiles)) != SR_OK) return st;
+    if (row_slots > 0) {
+      void* sp = nullptr;
+      if ((st = dev_alloc(g, &sp, (size_t)row_slots * (1024 + 1) * sizeof(float))) != SR_OK) return st;
+      g->row_split.slabs = (float*)sp;
+      g->row_split.counters = (int32_t*)sp + (size_t)row_slots * 1024;
+      SR_HIP(g, sr_launch_fill_zero(g->stream, g->row_split.counters, (size_t)row_slots * sizeof(int32_t)));
+    }
+  }
   if ((st = upload(g, &g->stage_nodes, stage)) != SR_OK) return st;
   if ((st = upload(g, &g->d_nodes, dn)) != SR_OK) return st;
   if ((st = upload(g, &g->d_edges, de)) != SR_OK) return st;
@@ -1389,7 +1423,7 @@ sr_status finalize(sr_graph* g) {
   int launches = g->stage_mode == 2 ? 1 : 0;
   for (int L = 1; L <= F; ++L) {
     const LevelPlan& lp = g->levels[L];
-    const bool has_tiles = lp.n_tiles > 0, has_blocks = lp.n_blocks > 0;
+    const bool has_tiles = lp.n_tiles > 0 || lp.n_rows > 0, has_blocks = lp.n_blocks > 0;   // (bf16 tiles or fp32 row tiles)
     const bool aux_ride = has_tiles;   // the tile kernels take the auxiliary items along
     launches += has_tiles + (has_blocks || (!aux_ride && lp.n_aux > 0));
   }
@@ -1421,7 +1455,7 @@ sr_status set_record_node(sr_graph* g, int node) {
 }
 
 bool record_needs_copy(const sr_graph* g) {
-  if (g->rec_node < 0) return false;
+  if (g->rec_node < 0 || g->nodes[g->rec_node].kind == 4) return false;   // row tiles record what they store
   for (int v : g->head_node)
     if (v == g->rec_node) return false;
   return true;
@@ -1502,7 +1536,7 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
   int last_level = 0, last_is_direct = 0;
   for (int L = 1; L <= g->an.factor; ++L) {
     const LevelPlan& lp = g->levels[L];
-    const bool has_tiles = lp.n_tiles > 0;
+    const bool has_tiles = lp.n_tiles > 0 || lp.n_rows > 0;
     const bool aux_ride = has_tiles;
     const bool direct_launch = lp.n_blocks > 0 || (!aux_ride && lp.n_aux > 0);
     if (has_tiles || direct_launch) { last_level = L; last_is_direct = direct_launch; }
@@ -1514,13 +1548,22 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
   }
   for (int L = 1; L <= g->an.factor; ++L) {
     const LevelPlan& lp = g->levels[L];
-    const bool has_tiles = lp.n_tiles > 0;
+    const bool has_tiles = lp.n_tiles > 0 || lp.n_rows > 0;
     const bool aux_ride = has_tiles;
     const bool direct_launch = lp.n_blocks > 0 || (!aux_ride && lp.n_aux > 0);
     if (has_tiles) {
       const int is_last = (!copy_out && L == last_level && !last_is_direct) ? 1 : 0;
-      SR_HIP(g, mark(1));
-      if (g->tile_version == 2)
+      SR_HIP(g, mark(lp.n_rows > 0 ? 2 : 1));
+      if (lp.n_rows > 0) {   // fp32 graphs have no bf16 tiles
+        SrRowArgs a{};
+        a.tensors = g->row_tensors; a.nodes = g->row_nodes; a.phases = g->row_phases; a.segs = g->row_segs;
+        a.tiles = g->row_tiles + lp.row_begin;
+        a.n_tiles = lp.n_rows;
+        a.rec_node = record ? g->rec_node : -1;
+        a.split = g->row_split;
+        SR_HIP(g, sr_launch_rows_frame(s, g->ctx, a, std::max(lp.row_lds, g->aux_smem_bytes), g->aux + lp.aux_begin, lp.n_aux, g->heads,
+                                       g->head_edges, g->stage_nodes, g->aux_smem_bytes, is_last));
+      } else if (g->tile_version == 2)
         SR_HIP(g, sr_launch_mfma8(s, g->ctx, g->m_nodes, g->m_edges, g->m_tiles + lp.tile_begin, lp.n_tiles,
                                   g->aux + lp.aux_begin, lp.n_aux, g->heads, g->head_edges, g->stage_nodes,
                                   g->aux_smem_bytes, is_last, split));
@@ -2216,8 +2259,8 @@ sr_status sr_graph_node_kernels(const sr_graph* g, int32_t* kinds) {
   sr_status st = finalize(const_cast<sr_graph*>(g));
   if (st != SR_OK) return st;
   for (int v = 0; v < g->n_nodes; ++v) {
-    const int k = g->nodes[v].kind;   // 0 input, 1 tile kernel, 2 direct, 3 head
-    kinds[v] = (k == 0) ? 0 : (k == 1 ? (g->tile_version == 2 ? 2 : 1) : (k == 2 ? 3 : 4));
+    const int k = g->nodes[v].kind;   // 0 input, 1 tile kernel, 2 direct, 3 head, 4 fp32 row tiles
+    kinds[v] = (k == 0) ? 0 : (k == 1 ? (g->tile_version == 2 ? 2 : 1) : (k == 2 ? 3 : (k == 3 || g->nodes[v].head_like ? 4 : 3)));
   }
   return SR_OK;
 }

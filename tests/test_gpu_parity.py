@@ -448,3 +448,26 @@ def test_pooled_slabs_of_several_frames_in_one_launch(batch):
     assert h["dependency_driven"] and h["dependency_timeouts"] == 0
     assert np.array_equal(a, gpu_rollout(g, w, b, x, 16, options={5: 0}))
     assert np.abs(a[-1]).max() > 0
+
+
+@pytest.mark.parametrize("tall_from", [0, 2048, 1 << 30])
+@pytest.mark.parametrize("channels", [(4, 32, 64), (31, 33, 65), (36, 100, 130)])
+def test_fp32_row_tiles_at_tile_edges(channels, tall_from):
+    # fp32 nodes run as row tiles: channel counts at, below and above the 32- / 64- / 128-wide column tiles, with
+    # 16-byte and 4-byte gathers; 17 x 17 images (ragged row tiles over several images), a stride-2 edge, up-sampling,
+    # a dense edge whose long sum is cut into parts.  tall_from (option 8) picks the tile shapes: 0 the tall ones.
+    # Bound: a sum of K terms in float32 is off by about sqrt(K) * 2^-24 of the sum of magnitudes, which for these
+    # inputs is a few times the tensor's largest element; K <= 5780: 5e-6 a frame, fed back over three frames.
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    ca, cb, cc = channels
+    nodes = [Node("in", 3, 17, 17, ACT_IDENTITY), Node("a", ca, 17, 17), Node("b", cb, 9, 9), Node("c", cc, 9, 9),
+             Node("d", 20, 17, 17), Node("out", 7, 1, 1, ACT_IDENTITY)]
+    edges = [Edge(0, 1, "conv", 5, 5, 1, 2), Edge(1, 1), Edge(1, 2, "conv", 3, 3, 2, 1), Edge(2, 3), Edge(3, 2, "conv", 1, 1, 1, 0),
+             Edge(1, 4), Edge(3, 3), Edge(4, 5, "dense", 17, 17, 1, 0)]
+    g0 = Graph("edges", nodes, edges, 5, 3, "f32", out_node=5)
+    g = g0.with_pattern(W.hybrid_pattern(g0))
+    w, b, x = W.make_case(g, seed=71, bias_scale=0.1, frames=3, recipe="uniform")
+    got, _, _ = gpu_states_by_steps(g, w, b, x, 3, {8: tall_from})
+    compare_all(got, oracle_states(g, w, b, x, 3, "f64"), 2e-5, f"row tiles {channels} tall_from={tall_from}")
+    rec = gpu_rollout(g, w, b, x, 3, options={8: tall_from})
+    assert np.array_equal(rec, np.stack(got[5]))     # recorded by the tiles themselves

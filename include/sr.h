@@ -112,11 +112,14 @@ typedef enum {
                                   taken over update steps of all the frames), so that update steps of consecutive
                                   frames that do not depend on one another run side by side;
                                   0: frame after frame */
-  SR_OPT_TRAIN_TALL_TILES_FROM = 8
+  SR_OPT_TRAIN_TALL_TILES_FROM = 8,
                                /* fp32 contractions (training window, fp32 frames): a contraction takes the taller of its
                                   tile shapes when that launch has at least this many workgroups, else a shorter
                                   one (default 2048; 0: always the taller, 2^30: never).  Same results either way up to
                                   the order of float sums; for tests of both shapes and for tuning. */
+  SR_OPT_TRAIN_FRAMES_KEPT = 9 /* training window: frames whose state gradients are kept at a time; a longer window is swept
+                                  in chunks of that many (default 0: as many as 16 GiB hold).  Same results up to the
+                                  order of float sums. */
 } sr_option;
 
 /* ---------------------------------------------------------------------------
@@ -327,11 +330,10 @@ sr_status sr_graph_node_kernels(const sr_graph* g, int32_t* kinds);
  *             of input nodes are ignored, a NULL entry skips that node
  * fp32 arithmetic; every sum is taken in a fixed order (no floating-point atomics): the same call
  * gives the same bits.  Device memory for the window's states and
- * gradients (about (W + 3) x the graph's node states, plus scratch) is allocated by the call, kept by
- * the graph and reused by later calls.  Asynchronous: the results are complete in the order of the
- * graph's stream (inside the call three more streams of the library's own, of default priority, run
- * work that does not depend on each other; they are joined to the graph's stream before the call's
- * last kernel); the host arrays are consumed before the call returns.  Every kernel is launched by the
+ * gradients (about (2 W + 1) x the graph's node states, plus scratch; see SR_OPT_TRAIN_FRAMES_KEPT) is allocated by
+ * the call, kept by the graph and reused by later calls; a window size or out_node other than the last call's makes
+ * the call wait for the stream while its plan is made.  Asynchronous: the results are complete in the order of the
+ * graph's stream; the host arrays are consumed before the call returns.  Every kernel is launched by the
  * call itself (SR_OPT_USE_HIPGRAPH concerns the frame path only).  No optimiser step is taken.
  * Errors: SR_ERR_ARG, SR_ERR_STATE (weights missing), SR_ERR_OOM, SR_ERR_DEVICE. */
 sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs, const float* const* masks,

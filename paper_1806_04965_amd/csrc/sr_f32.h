@@ -49,7 +49,7 @@ struct SrTensor {
 };
 
 #define SR_SEG_LAG 1      // reads the gathered tensor one frame away from the rows' own frame
-#define SR_SEG_ZERO0 2    // ... and that copy is known to be all zero when it lies outside the window
+#define SR_SEG_ZERO0 2    // forward, with SR_SEG_LAG: the tensor's frame 0 is all zero (the window's initial state)
 #define SR_SEG_IMAGE 4    // the gathered row depends on the image only (mean over pixels + dense, backwards)
 #define SR_SEG_QUADS 8    // channel counts are multiples of four: 16-byte gathers
 struct SrSeg {
@@ -59,11 +59,12 @@ struct SrSeg {
   int32_t rs, r0h, r0w;   // first gathered row / column of a pixel: (hh / up) * rs + r0
   int32_t dir;            // gathered row of tap row vi: first + dir * vi
   int32_t ntj, R;         // taps per tap row; length of the reduction: taps * GC
-  int32_t wt0, wti, wtj;  // backwards: tap of theta = wt0 + vi * wti + vj * wtj
+  int32_t wt0, wti, wtj;  // backwards: tap of theta = wt0 + (vi / wup) * wti + (vj / wup) * wtj
   int32_t ldw;            // forward: columns of theta (= J); backwards: rows of theta per tap (= J)
   int32_t step0;          // first reduction step of this segment in the phase
   SrDiv d_gc, d_ntj, d_up;
-  int32_t pad_[3];
+  SrDiv d_wup;            // backwards: gathered positions per tap of an up-sampled edge
+  int32_t dist;           // backwards: the gathered node's gradient is zero after frame W - dist
 };
 
 // What a row tile's rows are: the pixels h = hh * S + ph, w = ww * S + pw of a node (S = 1: all of them).
@@ -96,7 +97,8 @@ struct SrRowTile {
 
 // A launch over several (tile list, frame) pairs: pair k takes the workgroups from block0 on.
 struct SrRun {
-  int32_t block0, tile0, frame, pad_;
+  int32_t block0, tile0, frame;
+  int32_t slot0;          // added to the split slots of its tiles
 };
 
 #define SR_F32_KS 16              // reduction indices per step
@@ -107,7 +109,7 @@ struct SrRun {
 SR_HD int sr_f32_piece(int row, int k4) { return k4 ^ ((row >> 2) & 3); }
 
 // A row of a row tile, seen by one segment: where tap (0, 0) lands in the gathered image
-struct SrRowAt { int h, w; uint32_t off; };   // h < -2^20: no such row
+struct SrRowAt { int h, w; uint32_t off; };   // off in floats; h = -SR_FAR: no such row
 #define SR_FAR (1 << 21)
 SR_HD SrRowAt sr_row_at(const SrPhase& p, const SrSeg& g, int i, int b0) {
   SrRowAt r;
@@ -116,11 +118,11 @@ SR_HD SrRowAt sr_row_at(const SrPhase& p, const SrSeg& g, int i, int b0) {
   if (g.flags & SR_SEG_IMAGE) {
     r.h = 0;
     r.w = 0;
-    r.off = (uint32_t)((b - b0) * g.GC) * 4u;
+    r.off = (uint32_t)((b - b0) * g.GC);
   } else {
     r.h = sr_divide(hh, g.d_up) * g.rs + g.r0h;
     r.w = sr_divide(ww, g.d_up) * g.rs + g.r0w;
-    r.off = (uint32_t)((((b - b0) * g.GH + r.h) * g.GW + r.w) * g.GC) * 4u;
+    r.off = (uint32_t)(((b - b0) * g.GH + r.h) * g.GW + r.w) * (uint32_t)g.GC;
   }
   if (i >= p.I) r.h = -SR_FAR;
   return r;
@@ -141,11 +143,12 @@ SR_HD bool sr_gather_ok(const SrSeg& g, const SrRowAt& a, const SrTapAt& t) {
   return (unsigned)(a.h + g.dir * t.vi) < (unsigned)g.GH && (unsigned)(a.w + g.dir * t.vj) < (unsigned)g.GW;
 }
 SR_HD uint32_t sr_gather_off(const SrSeg& g, const SrTapAt& t) {   // added to SrRowAt::off
-  return (uint32_t)(g.dir * (t.vi * g.GW + t.vj) * g.GC + t.c) * 4u;
+  return (uint32_t)(g.dir * (t.vi * g.GW + t.vj)) * (uint32_t)g.GC + (uint32_t)t.c;
 }
 // weights, backwards: theta[tap][j][c]
 SR_HD uint32_t sr_weight_off(const SrSeg& g, const SrTapAt& t, int j) {
-  return (uint32_t)(((g.wt0 + t.vi * g.wti + t.vj * g.wtj) * g.ldw + j) * g.GC + t.c) * 4u;
+  const int tap = g.wt0 + sr_divide(t.vi, g.d_wup) * g.wti + sr_divide(t.vj, g.d_wup) * g.wtj;
+  return ((uint32_t)tap * (uint32_t)g.ldw + (uint32_t)j) * (uint32_t)g.GC + (uint32_t)t.c;
 }
 
 // ---------------------------------------------------------------------------
@@ -153,35 +156,36 @@ SR_HD uint32_t sr_weight_off(const SrSeg& g, const SrTapAt& t, int j) {
 // ---------------------------------------------------------------------------
 struct SrGradEdge {
   int32_t x, dy;                  // tensors: source state, target gradient
-  int32_t lag, first_frame;       // the source is read at frame - lag; earlier frames contribute nothing
-  int32_t H, W, Cin, Ho, Wo, Cout;
-  int32_t kw, stride, pad, up;
+  int32_t lag, frame0;            // the source is read at frame - lag; first frame that contributes
+  int32_t H, W, Cin, Ho, Wo, Cout;   // Ho, Wo: the target's own (up-sampled) image
+  int32_t kw, stride, pad;
   int32_t I, M;                   // rows = taps * Cin; pixels per frame
-  int32_t steps_per_frame;        // ceil(M / SR_F32_KS)
   int32_t quads_in, quads_out;    // channel counts that are multiples of four
-  int32_t slices;                 // parts the reduction is cut into
+  int32_t slices;                 // parts the reduction is cut into (1: straight to the destination)
+  int32_t dst;                    // destination pointer
   long long part_at;              // first float of this edge's partial sums
-  SrDiv d_cin, d_kw, d_wo, d_howo, d_up;
+  SrDiv d_cin, d_kw, d_wo, d_howo, d_up, d_steps;   // d_steps: steps per frame, ceil(M / SR_F32_KS)
+  int32_t steps_per_frame, pad_;
 };
 // kind 0: gradient tile; 1: column sums of a gradient tensor (bias gradient), 64 channels x a range of rows
 struct SrGradTile {
   int32_t edge, shape, i0, j0;
-  int32_t step_begin, step_end;   // steps counted over the edge's frames
+  int32_t step_begin, step_end;   // steps counted over the edge's frames (kind 1: rows counted over the frames)
   int32_t slice, kind;
 };
 struct SrGradBias {
-  int32_t dy, C, M;               // rows per frame
-  int32_t slices;
+  int32_t dy, C, M, frame0;       // rows per frame; first frame
+  SrDiv d_m;
   long long part_at;
 };
-// dst[k] (+)= sum over the slices of part[s][k], in slice order
+// dst[k] (+)= sum over the slices of part[s][k], in slice order; no slices: zero
 struct SrGradSum {
   long long part_at, n;
   int32_t slices, dst;            // dst: index into the launch's destination pointers
-  int32_t block0, pad_;
+  int32_t block0, pad_;           // first workgroup (64 elements each)
 };
 
-// pixel of a gradient tile's reduction: row of the gathered source image
+// pixel of a gradient tile's reduction: first row and column of its window in the source image
 struct SrPixAt { int b, h, w; };
 SR_HD SrPixAt sr_pix_at(const SrGradEdge& e, int m) {
   SrPixAt p;
@@ -203,11 +207,11 @@ struct SrRowArgs {
   const SrPhase* phases;
   const SrSeg* segs;
   const SrRowTile* tiles;
-  const SrRun* runs;              // null: the launch is one tile list of the frame path (slots by the frame's parity)
-  int32_t n_runs, n_tiles;
+  const SrRun* runs;              // training: (tile list, frame) pairs of the launch
+  int32_t n_runs, n_tiles;        // n_tiles: workgroups
   int32_t frame0;                 // training: frame of a run = frame0 + run.frame
-  int32_t frames;                 // training: W
-  int32_t ring;                   // backwards: gradient tensors keep `ring` frames (slot = frame % ring)
+  int32_t window;                 // training: W
+  int32_t ring;                   // training: gradient tensors keep `ring` frames (slot = frame % ring)
   int32_t rec_node;               // frame path: node whose values also go to the rollout output (-1: none)
   SrSplitScratch split;
 };
@@ -216,14 +220,52 @@ struct SrGradArgs {
   const SrGradEdge* edges;
   const SrGradBias* biases;
   const SrGradTile* tiles;
+  float* const* dst;
   float* part;
-  int32_t frame_lo, ring;         // first frame of the chunk; ring of the gradient tensors
+  int32_t n_tiles, ring, accumulate;
+};
+struct SrLossArgs {
+  const SrTensor* tensors;
+  const int32_t* labels;
+  float* terms;                   // [W][B]
+  int32_t frame0, frames;         // of the window, and of this launch
+  int32_t B, C, act;
+  int32_t x, out, mask;           // tensors: scores, where their gradient goes, dropout (out of the node itself)
+  int32_t ring, gate;             // gate: `out` is the node's own gradient (apply rectifier and dropout)
+  float scale;
+};
+#define SR_PATCH_MAX 96
+struct SrPatch {                  // entries of the tensor / destination tables that a call brings along
+  int32_t index[SR_PATCH_MAX];    // >= 0: tensor; < 0: destination -1 - index
+  SrTensor value[SR_PATCH_MAX];
+  int32_t n;
+};
+struct SrPool {                   // channel means of a node's state
+  int32_t x, mean, lag, HW, C, zero0;
+};
+#define SR_RMS_MAX 64
+struct SrRmsBatch {
+  float *theta[SR_RMS_MAX], *mean[SR_RMS_MAX];
+  const float* grad[SR_RMS_MAX];
+  long long n[SR_RMS_MAX];
+  int32_t block0[SR_RMS_MAX + 1];
+  int32_t count;
 };
 
-// frame path: the level's tiles, direct blocks of other nodes and auxiliary items in one launch
+// frame path: the level's tiles and the auxiliary items in one launch
 hipError_t sr_launch_rows_frame(hipStream_t s, SrCtx* ctx, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
                                 const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
                                 int aux_smem_bytes, int is_last);
+// training window
+hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int lds_bytes);
+hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int lds_bytes);
+// destination sums, and (loss != null) loss = scale * sum of the n_terms loss terms
+hipError_t sr_launch_grad_sum(hipStream_t s, const SrGradSum* sums, int n_sums, int n_blocks, const float* part, float* const* dst,
+                              int accumulate, const float* terms, int n_terms, float scale, float* loss);
+hipError_t sr_launch_loss(hipStream_t s, const SrLossArgs& a);
+hipError_t sr_launch_patch(hipStream_t s, SrTensor* tensors, float** dst, const SrPatch& p);
+hipError_t sr_launch_pool(hipStream_t s, const SrTensor* tensors, const SrPool& p, int B, int frame0, int frames);
+hipError_t sr_launch_rmsprop(hipStream_t s, const SrRmsBatch& b, float lr, float rho, float eps);
 
 // ---------------------------------------------------------------------------
 // planner (sr_f32_plan.cpp)
@@ -244,15 +286,38 @@ struct SrRowPlan {
   std::vector<SrPhase> phases;
   std::vector<SrRowNode> nodes;
 };
+// Tensor numbers of a training window: node v's state is v, its gradient grad0 + v, its dropout multipliers mask0 + v;
+// mean[e]: channel means that the GAP edge e reads; seed: loss term of the out node (-1: stored as its gradient)
+struct SrTrainIds {
+  int grad0, mask0, seed, out_node;
+  std::vector<int> mean;
+  std::vector<int> dist;   // per node: fewest bridging edges on a path to the out node (-1: no path, the loss does not see it)
+};
 // can node v be computed by row tiles (no incoming GAP edge, offsets in 32 bits)?
 bool sr_rows_take_forward(const sr_graph* g, int v);
-// appends node v's descriptors; state tensors are numbered like the nodes
-void sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v);
+// are all tensors of the graph small enough for the tiled kernels of a training window?
+bool sr_rows_take_training(const sr_graph* g);
+// Append node v's descriptors; returns its first phase (a forward node has one).  ids = null: frame path, tensors
+// numbered like the nodes.
+int sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds* ids);
+int sr_rows_backward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds& ids);
 // Tiles of phases that one launch covers, in the order of the list (workgroup i runs on XCD i % 8; padded to a
 // multiple of 8 with empty tiles).  work_cycles: compute-unit cycles of the whole launch if it covers more than
 // these phases (0: just these).  tall_from: SR_OPT_TRAIN_TALL_TILES_FROM; split: SR_OPT_K_SPLIT.
 void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split,
                    int* split_slots, std::vector<SrRowTile>* out, int* lds_bytes);
 double sr_rows_work(const SrRowPlan& p, int phase);   // compute-unit cycles of a phase at the fp32 matrix rate
+// Weight and bias gradients of the frames lo..hi of a window of W frames: descriptors, tiles, partial sums.  Destination
+// pointers: edge e is e, node v's bias n_edges + v.  first: the first chunk of the window that is worked on (it
+// overwrites the destinations, later ones add).
+struct SrGradPlan {
+  std::vector<SrGradEdge> edges;
+  std::vector<SrGradBias> biases;
+  std::vector<SrGradTile> tiles;
+  std::vector<SrGradSum> sums;
+  int sum_blocks = 0, lds = 0;
+  long long part_floats = 0;
+};
+void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from);
 
 #endif  // SR_F32_H_

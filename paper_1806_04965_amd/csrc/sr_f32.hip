@@ -64,6 +64,7 @@ __device__ __forceinline__ SrSeg sr_load_seg(SR_CONST4(SrSeg) s) {
   g.wt0 = s->wt0; g.wti = s->wti; g.wtj = s->wtj;
   g.ldw = s->ldw; g.step0 = s->step0;
   g.d_gc = sr_load_div(&s->d_gc); g.d_ntj = sr_load_div(&s->d_ntj); g.d_up = sr_load_div(&s->d_up);
+  g.d_wup = sr_load_div(&s->d_wup); g.dist = s->dist;
   return g;
 }
 __device__ __forceinline__ SrPhase sr_load_phase(SR_CONST4(SrPhase) s) {
@@ -75,13 +76,23 @@ __device__ __forceinline__ SrPhase sr_load_phase(SR_CONST4(SrPhase) s) {
   return p;
 }
 
+// float `off` of the tensor at p
+__device__ __forceinline__ const char* sr_at(const char* p, uint32_t off) { return p + ((unsigned long long)off << 2); }
+
 // which copies of its tensors a tile works on
 struct SrSlots {
   int lag0, lag1;      // gathered tensors, without and with SR_SEG_LAG
   int own;             // result
   int frame;           // state, mask, loss term
-  bool outside;        // the lagged copy lies outside the window (segments with SR_SEG_ZERO0 contribute nothing)
+  int left;            // training, backwards: frames from here to the window's last (W - frame); forward: frame; else large
 };
+// Does a segment contribute?  Forward: not if it reads the window's initial state, which is zero.  Backwards: not if
+// it reads a gradient that no loss term of the window depends on.
+template <bool BACK>
+__device__ __forceinline__ bool sr_seg_counts(const SrSeg& g, const SrSlots& sl) {
+  const int lag = (g.flags & SR_SEG_LAG) ? 1 : 0;
+  return BACK ? sl.left >= lag + g.dist : !(lag && (g.flags & SR_SEG_ZERO0) && sl.left == 1);
+}
 
 // The operands of a tile: a TI x 16 and a 16 x TJ piece per step, NW waves fetching them together.
 //   rows:  TI (TJ) rows of 16 reduction indices, 64 bytes a row, pieces of four permuted (sr_f32_piece)
@@ -105,7 +116,7 @@ struct SrRowOperands {
   // a new segment: where this lane's rows are in its image
   __device__ __forceinline__ void enter(const SrPhase& p, const SrTensor* tensors, const SrSlots& sl) {
     SR_CONST4(SrTensor) t = sr_k(tensors) + g.tensor;
-    const int slot = (g.flags & SR_SEG_LAG) ? sl.lag1 : sl.lag0;
+    const int slot = sl.lag0 + ((g.flags & SR_SEG_LAG) ? sl.lag1 - sl.lag0 : 0);   // (a select between the fields would go through memory)
     const int b0 = SR_UNI(sr_divide(i0, p.d_hpwp));
     const long long image = (g.flags & SR_SEG_IMAGE) ? (long long)g.GC * 4 : (long long)g.GH * g.GW * g.GC * 4;
     src = sr_uni_ptr((const char*)(unsigned long long)t->base + slot * t->stride + b0 * image);
@@ -135,20 +146,18 @@ struct SrRowOperands {
       const uint32_t toff = sr_gather_off(g, t);
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
-        const char* p = sr_gather_ok(g, row[n], t) ? src + (uint32_t)(row[n].off + toff) : zero;
+        const char* p = sr_gather_ok(g, row[n], t) ? sr_at(src, row[n].off + toff) : zero;
         sr_to_lds16(p, at + (n * NW + wv) * 1024);
       }
       if (BACK) {
-        const bool r_ok = t.vi < SR_FAR;
-        const uint32_t woff = sr_weight_off(g, t, 0);
+        // (a half-filled wave's rows start at a multiple of eight: its pieces are permuted differently from A's)
+        const SrTapAt tb = HALF_B ? sr_tap_at(g, r0 + 4 * sr_f32_piece(wv * 8 + (lane >> 2), lane & 3)) : t;
+        const bool r_ok = tb.vi < SR_FAR;
+        const uint32_t woff = sr_weight_off(g, tb, 0);
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
-          const int jr = HALF_B ? wv * 8 + (lane >> 2) : n * 16 * NW + wv * 16 + (lane >> 2);
-          const int k4b = HALF_B ? sr_f32_piece(jr, lane & 3) : k4;
-          const int j = j0 + jr;
-          // (a half-filled wave's rows start at a multiple of eight: its permutation differs from A's)
-          const uint32_t o = woff + (uint32_t)(j * g.GC) * 4u + (uint32_t)((k4b - k4) * 16);
-          const char* p = (r_ok && j < g.ldw) ? (const char*)g.w + o : zero;
+          const int j = j0 + (HALF_B ? wv * 8 + (lane >> 2) : n * 16 * NW + wv * 16 + (lane >> 2));
+          const char* p = (r_ok && j < g.ldw) ? sr_at((const char*)g.w, woff + (uint32_t)j * (uint32_t)g.GC) : zero;
           if (HALF_B) {
             if (lane < 32) sr_to_lds16(p, bt + wv * 512);
           } else {
@@ -163,7 +172,7 @@ struct SrRowOperands {
         const int id = q * NW + wv;
         const int k = TI >= 64 ? id * 64 / TI : 2 * id + (lane >> 5);
         const SrTapAt t = sr_tap_at(g, TI >= 64 ? SR_UNI(r0 + k) : r0 + k);
-        const char* p = sr_gather_ok(g, row[0], t) ? src + (uint32_t)(row[0].off + sr_gather_off(g, t)) : zero;
+        const char* p = sr_gather_ok(g, row[0], t) ? sr_at(src, row[0].off + sr_gather_off(g, t)) : zero;
         sr_to_lds4(p, at + id * 256);
       }
       if (BACK) {
@@ -173,7 +182,7 @@ struct SrRowOperands {
           const int k = TJ >= 64 ? id * 64 / TJ : 2 * id + (lane >> 5);
           const int j = j0 + (TJ >= 64 ? (TJ == 128 ? (id & 1) * 64 + lane : lane) : (lane & 31));
           const SrTapAt t = sr_tap_at(g, TJ >= 64 ? SR_UNI(r0 + k) : r0 + k);
-          const char* p = (t.vi < SR_FAR && j < g.ldw) ? (const char*)g.w + sr_weight_off(g, t, j) : zero;
+          const char* p = (t.vi < SR_FAR && j < g.ldw) ? sr_at((const char*)g.w, sr_weight_off(g, t, j)) : zero;
           sr_to_lds4(p, bt + id * 256);
         }
         return;
@@ -185,7 +194,7 @@ struct SrRowOperands {
       for (int n = 0; n < NB; ++n) {
         const int id = HALF_B ? wv * 32 + lane : (n * NW + wv) * 64 + lane;
         const int r = r0 + id / (TJ / 4), j = j0 + 4 * (id % (TJ / 4));
-        const char* p = (r < g.R && j < g.ldw) ? (const char*)g.w + (uint32_t)(r * g.ldw + j) * 4u : zero;
+        const char* p = (r < g.R && j < g.ldw) ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
         if (HALF_B) {
           if (lane < 32) sr_to_lds16(p, bt + wv * 512);
         } else {
@@ -197,7 +206,7 @@ struct SrRowOperands {
       for (int q = 0; q < TJ / 4 / NW; ++q) {
         const int id = q * NW + wv;
         const int r = r0 + (id * 64 + lane) / TJ, j = j0 + (id * 64 + lane) % TJ;
-        const char* p = (r < g.R && j < g.ldw) ? (const char*)g.w + (uint32_t)(r * g.ldw + j) * 4u : zero;
+        const char* p = (r < g.R && j < g.ldw) ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
         sr_to_lds4(p, bt + id * 256);
       }
     }
@@ -315,7 +324,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
       while (r >= r_stop) {
         if (++seg >= seg_end) return false;
         op.g = sr_load_seg(sr_k(A.segs) + seg);
-        if (sl.outside && (op.g.flags & SR_SEG_LAG) && (op.g.flags & SR_SEG_ZERO0)) continue;
+        if (!sr_seg_counts<BACK>(op.g, sl)) continue;
         const int n = (op.g.R + SR_F32_KS - 1) / SR_F32_KS;
         int lo = max(step_begin - op.g.step0, 0);
         const int hi = min(step_end - op.g.step0, n);
@@ -459,12 +468,12 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
 }
 
 template <bool BACK>
-__device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowTile) t, const SrSlots& sl, float* record, int rec_node,
-                                            unsigned char* lds) {
+__device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowTile) t, int slot0, const SrSlots& sl, float* record,
+                                            int rec_node, unsigned char* lds) {
   const int phase = t->phase;
   if (phase < 0) return;
   const SrPhase p = sr_load_phase(sr_k(A.phases) + phase);
-  const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = t->split_slot, part = t->part;
+  const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = slot0 + t->split_slot, part = t->part;
   if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
   else if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
   else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
@@ -488,10 +497,10 @@ __global__ __launch_bounds__(256, 2) void sr_rows_frame_kernel(SrCtx* __restrict
                        SrFlow{nullptr, nullptr, 0, 0, nullptr});
   } else {
     const int cur = frame & 1;
-    const SrSlots sl{cur, cur ^ 1, cur, 0, false};
+    const SrSlots sl{cur, cur ^ 1, cur, 0, 1 << 30};
     char* rec = A.rec_node >= 0 ? (char*)ctx->out_ptr : nullptr;
     if (rec) rec += (int64_t)(frame - ctx->out_base) * ctx->out_stride;
-    sr_row_item<false>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
+    sr_row_item<false>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), 0, sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
   }
   if (is_last) sr_block_done(ctx, gridDim.x, 1);
 }
@@ -502,5 +511,424 @@ hipError_t sr_launch_rows_frame(hipStream_t s, SrCtx* ctx, const SrRowArgs& a, i
   if (a.n_tiles + n_aux == 0) return hipSuccess;
   hipLaunchKernelGGL(sr_rows_frame_kernel, dim3(a.n_tiles + n_aux), dim3(256), lds_bytes, s, ctx, a, aux, n_aux, a.n_tiles / 2, heads,
                      head_edges, stage_nodes, (aux_smem_bytes - 16 - 4096) / 4, is_last);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// training window
+// ---------------------------------------------------------------------------
+template <bool BACK>
+__global__ __launch_bounds__(256, 2) void sr_rows_train_kernel(SrRowArgs A) {
+  extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
+  // the run (tile list, frame) this workgroup belongs to: runs are in order of their first workgroup
+  const int lane = threadIdx.x & 63;
+  int k = 0;
+  for (int base = 0; base < A.n_runs; base += 64) {
+    const int b0 = base + lane < A.n_runs ? A.runs[base + lane].block0 : 0x7fffffff;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= (int)blockIdx.x);
+    k += __popcll(m);
+    if (m != ~0ull) break;
+  }
+  SR_CONST4(SrRun) run = sr_k(A.runs) + SR_UNI(k - 1);
+  const int frame = A.frame0 + run->frame;
+  SrSlots sl;
+  if (BACK) {
+    sl.lag0 = frame % A.ring;
+    sl.lag1 = (frame + 1) % A.ring;
+    sl.own = sl.lag0;
+    sl.left = A.window - frame;
+  } else {
+    sl.lag0 = frame;
+    sl.lag1 = frame - 1;
+    sl.own = frame;
+    sl.left = frame;
+  }
+  sl.frame = frame;
+  sr_row_item<BACK>(A, sr_k(A.tiles) + run->tile0 + (blockIdx.x - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
+}
+
+namespace {
+
+// The operands of a weight gradient tile: 16 lines of TI (source channels of the taps' pixels) and of TJ (target
+// channels) elements per step; a pixel's channels are contiguous.
+template <int TI, int TJ>
+struct SrGradOperands {
+  static constexpr int NA = TI / 64, NB = TJ >= 64 ? TJ / 64 : 1, STAGE = (TI + TJ) * 64, LOADS = NA + NB;
+  static constexpr bool HALF_B = TJ < 64;
+  SrGradEdge e;
+  const char *xb0, *yb0;
+  long long xs, ys, image;
+  int quads_a, quads_b, ring;
+  int wv, lane, j0;
+  int ti, tj;          // this lane's row (rows i .. i + 3) of A: tap and ...
+  uint32_t aoff;       // ... offset from the window's first element
+
+  __device__ __forceinline__ void enter(SR_CONST4(SrGradEdge) ek, const SrTensor* tensors, int ring_, int i0, int j0_) {
+    e.x = ek->x; e.dy = ek->dy; e.lag = ek->lag; e.frame0 = ek->frame0;
+    e.H = ek->H; e.W = ek->W; e.Cin = ek->Cin; e.Ho = ek->Ho; e.Wo = ek->Wo; e.Cout = ek->Cout;
+    e.kw = ek->kw; e.stride = ek->stride; e.pad = ek->pad; e.I = ek->I; e.M = ek->M;
+    e.d_cin = sr_load_div(&ek->d_cin); e.d_kw = sr_load_div(&ek->d_kw); e.d_wo = sr_load_div(&ek->d_wo);
+    e.d_howo = sr_load_div(&ek->d_howo); e.d_up = sr_load_div(&ek->d_up); e.d_steps = sr_load_div(&ek->d_steps);
+    e.steps_per_frame = ek->steps_per_frame;
+    SR_CONST4(SrTensor) tx = sr_k(tensors) + e.x;
+    SR_CONST4(SrTensor) ty = sr_k(tensors) + e.dy;
+    xb0 = (const char*)(unsigned long long)tx->base;
+    yb0 = (const char*)(unsigned long long)ty->base;
+    xs = tx->stride;
+    ys = ty->stride;
+    image = (long long)e.H * e.W * e.Cin * 4;
+    quads_a = SR_UNI(ek->quads_in && (((unsigned)(unsigned long long)xb0 | (unsigned)xs | (unsigned)image) & 15u) == 0);
+    quads_b = SR_UNI(ek->quads_out && (((unsigned)(unsigned long long)yb0 | (unsigned)ys) & 15u) == 0);
+    ring = ring_;
+    j0 = j0_;
+    const int i = quads_a ? i0 + 4 * (lane % (TI / 4)) : i0 + (TI == 128 ? (wv & 1) * 64 + lane : lane);
+    const int tap = sr_divide(i, e.d_cin), ci = i - tap * e.Cin;
+    ti = sr_divide(tap, e.d_kw);
+    tj = tap - ti * e.kw;
+    aoff = (uint32_t)(ti * e.W + tj) * (uint32_t)e.Cin + (uint32_t)ci;
+    if (i >= e.I) ti = 2 * SR_FAR;
+  }
+
+  __device__ __forceinline__ void issue(int step, unsigned at) {
+    const char* zero = (const char*)sr_zero_line;
+    const int fi = sr_divide(step, e.d_steps), m0 = (step - fi * e.steps_per_frame) * SR_F32_KS;
+    const int frame = e.frame0 + fi;
+    const int b0 = sr_divide(m0, e.d_howo);
+    const char* xb = xb0 + (frame - e.lag) * xs + b0 * image;
+    const char* yb = yb0 + (frame % ring) * ys + (long long)m0 * e.Cout * 4;
+    if (quads_a) {
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+        const SrPixAt p = sr_pix_at(e, m0 + (n * 4 + wv) * (256 / TI) + lane / (TI / 4));
+        const bool ok = (unsigned)(p.h + ti) < (unsigned)e.H && (unsigned)(p.w + tj) < (unsigned)e.W;
+        const uint32_t off = (uint32_t)(((p.b - b0) * e.H + p.h) * e.W + p.w) * (uint32_t)e.Cin + aoff;
+        sr_to_lds16(ok ? sr_at(xb, off) : zero, at + (n * 4 + wv) * 1024);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < TI / 16; ++q) {
+        const int id = q * 4 + wv;
+        const SrPixAt p = sr_pix_at(e, SR_UNI(m0 + id * 64 / TI));
+        const bool ok = (unsigned)(p.h + ti) < (unsigned)e.H && (unsigned)(p.w + tj) < (unsigned)e.W;
+        const uint32_t off = (uint32_t)(((p.b - b0) * e.H + p.h) * e.W + p.w) * (uint32_t)e.Cin + aoff;
+        sr_to_lds4(ok ? sr_at(xb, off) : zero, at + id * 256);
+      }
+    }
+    const unsigned bt = at + TI * 64;
+    if (quads_b) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int id = HALF_B ? wv * 32 + lane : (n * 4 + wv) * 64 + lane;
+        const int k = id / (TJ / 4), j = j0 + 4 * (id % (TJ / 4));
+        const char* p = (m0 + k < e.M && j < e.Cout) ? sr_at(yb, (uint32_t)(k * e.Cout + j)) : zero;
+        if (HALF_B) {
+          if (lane < 32) sr_to_lds16(p, bt + wv * 512);
+        } else {
+          sr_to_lds16(p, bt + (n * 4 + wv) * 1024);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < TJ / 16; ++q) {
+        const int id = (q * 4 + wv) * 64 + lane;
+        const int k = id / TJ, j = j0 + id % TJ;
+        sr_to_lds4((m0 + k < e.M && j < e.Cout) ? sr_at(yb, (uint32_t)(k * e.Cout + j)) : zero, bt + (q * 4 + wv) * 256);
+      }
+    }
+  }
+};
+
+// Weight gradient: rows i = (tap, source channel), columns j = target channel, reduction over the pixels of the
+// edge's frames, 16 pixels of one frame per step.  The sum over a tile's steps is taken in blocks of 128 steps, so that
+// it stays as accurate as the sums of short slices that a second pass would add up.
+template <int TI, int TJ, int WJN>
+__device__ __forceinline__ void sr_grad_tile(const SrGradArgs& A, SR_CONST4(SrGradEdge) ek, int i0, int j0, int step_begin, int step_end,
+                                             int slice, unsigned char* lds) {
+  constexpr int WIN = 4 / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
+  typedef SrGradOperands<TI, TJ> Ops;
+  const int tid = threadIdx.x, lane = tid & 63, wv = SR_UNI(tid >> 6);
+  const unsigned at0 = sr_lds_at(lds);
+  Ops op;
+  op.wv = wv;
+  op.lane = lane;
+  op.enter(ek, A.tensors, A.ring, i0, j0);
+
+  f32x16_t acc[MI][MJ], sum[MI][MJ];
+#pragma unroll
+  for (int x = 0; x < MI; ++x)
+#pragma unroll
+    for (int y = 0; y < MJ; ++y)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[x][y][v] = sum[x][y][v] = 0.f;
+  const int iw = (wv / WJN) * 32 * MI, jw = (wv % WJN) * 32 * MJ;
+  int wr = 0, rd = 0, next = step_begin;
+  for (int k = 0; k < SR_F32_STAGES - 1 && next < step_end; ++k) {
+    op.issue(next++, at0 + wr * Ops::STAGE);
+    wr = wr == SR_F32_STAGES - 1 ? 0 : wr + 1;
+  }
+  for (int s = step_begin; s < step_end; ++s) {
+    if (s + 1 < step_end) sr_wait_loads<Ops::LOADS>();
+    else sr_wait_loads<0>();
+    sr_step_barrier();
+    if (next < step_end) {
+      op.issue(next++, at0 + wr * Ops::STAGE);
+      wr = wr == SR_F32_STAGES - 1 ? 0 : wr + 1;
+    }
+    sr_step_products<TI, TJ, MI, MJ>(lds + rd * Ops::STAGE, iw, jw, lane, false, false, acc);
+    rd = rd == SR_F32_STAGES - 1 ? 0 : rd + 1;
+    if (((s - step_begin) & 127) == 127) {
+#pragma unroll
+      for (int x = 0; x < MI; ++x)
+#pragma unroll
+        for (int y = 0; y < MJ; ++y)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            sum[x][y][v] += acc[x][y][v];
+            acc[x][y][v] = 0.f;
+          }
+    }
+  }
+  const int slices = ek->slices;
+  const int I = op.e.I, J = op.e.Cout;
+  float* out = slices == 1 ? A.dst[ek->dst] : A.part + ek->part_at + (size_t)slice * I * J;
+  const bool add = slices == 1 && A.accumulate;
+#pragma unroll
+  for (int x = 0; x < MI; ++x)
+#pragma unroll
+    for (int y = 0; y < MJ; ++y)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int i = i0 + iw + x * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), j = j0 + jw + y * 32 + (lane & 31);
+        if (i < I && j < J) {
+          float* d = out + (size_t)i * J + j;
+          const float r = sum[x][y][v] + acc[x][y][v];
+          *d = add ? *d + r : r;
+        }
+      }
+}
+
+// Column sums of a gradient tensor over a range of rows (frame, pixel): 64 channels, four row lanes per channel (each
+// adds every fourth row in order, eight loads in flight, then the four in order)
+__device__ __forceinline__ void sr_grad_bias(const SrGradArgs& A, SR_CONST4(SrGradBias) bk, int j0, int row_begin, int row_end, int slice,
+                                             float* lds) {
+  const int C = bk->C, M = bk->M, frame0 = bk->frame0;
+  const SrDiv d_m = sr_load_div(&bk->d_m);
+  SR_CONST4(SrTensor) t = sr_k(A.tensors) + bk->dy;
+  const char* base = (const char*)(unsigned long long)t->base;
+  const long long stride = t->stride;
+  const int c = j0 + (threadIdx.x & 63), rl = threadIdx.x >> 6;
+  float acc = 0.f;
+  if (c < C)
+    for (int r = row_begin + rl; r < row_end; r += 32) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int q = min(r + 4 * u, row_end - 1);
+        const int fi = sr_divide(q, d_m), m = q - fi * M;
+        v[u] = *(const float*)(base + ((frame0 + fi) % A.ring) * stride + ((size_t)m * C + c) * 4);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += r + 4 * u < row_end ? v[u] : 0.f;
+    }
+  lds[rl * 64 + (threadIdx.x & 63)] = acc;
+  __syncthreads();
+  if (rl == 0 && c < C)
+    A.part[bk->part_at + (size_t)slice * C + c] =
+        ((lds[threadIdx.x] + lds[64 + threadIdx.x]) + lds[128 + threadIdx.x]) + lds[192 + threadIdx.x];
+}
+
+}  // namespace
+
+__global__ __launch_bounds__(256, 2) void sr_grad_kernel(SrGradArgs A) {
+  extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
+  SR_CONST4(SrGradTile) t = sr_k(A.tiles) + blockIdx.x;
+  const int kind = t->kind, shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slice = t->slice;
+  if (kind == 1) {
+    sr_grad_bias(A, sr_k(A.biases) + t->edge, j0, sb, se, slice, (float*)sr_rows_lds);
+    return;
+  }
+  SR_CONST4(SrGradEdge) e = sr_k(A.edges) + t->edge;
+  if (shape == SR_F32_128x128) sr_grad_tile<128, 128, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
+  else if (shape == SR_F32_128x64) sr_grad_tile<128, 64, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
+  else if (shape == SR_F32_64x64) sr_grad_tile<64, 64, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
+  else sr_grad_tile<128, 32, 1>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
+}
+
+// The partial sums of gradients cut into slices, added in slice order: a workgroup takes 64 elements, four slice lanes
+// per element (each adds every fourth slice in order, eight loads in flight; then the four in order).  The last
+// workgroup adds up the loss.
+__global__ __launch_bounds__(256) void sr_grad_sum_kernel(const SrGradSum* __restrict__ sums, int n_sums, const float* __restrict__ part,
+                                                          float* const* __restrict__ dst, int accumulate,
+                                                          const float* __restrict__ terms, int n_terms, float scale,
+                                                          float* __restrict__ loss) {
+  __shared__ float lanes[256];
+  const int t = threadIdx.x;
+  if (loss && blockIdx.x == gridDim.x - 1) {
+    float acc = 0.f;
+    for (int i = t; i < n_terms; i += 256) acc += terms[i];
+    lanes[t] = acc;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+      if (t < s) lanes[t] += lanes[t + s];
+      __syncthreads();
+    }
+    if (t == 0) loss[0] = lanes[0] * scale;
+    return;
+  }
+  int k = 0;
+  for (int base = 0; base < n_sums; base += 64) {
+    const int q = base + (t & 63);
+    const int b0 = q < n_sums ? sums[q].block0 : 0x7fffffff;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= (int)blockIdx.x);
+    k += __popcll(m);
+    if (m != ~0ull) break;
+  }
+  SR_CONST4(SrGradSum) s = sr_k(sums) + SR_UNI(k - 1);
+  const long long n = s->n, e = (long long)(blockIdx.x - s->block0) * 64 + (t & 63);
+  const int slices = s->slices, sl = t >> 6;
+  const float* p = part + s->part_at;
+  float acc = 0.f;
+  if (e < n)
+    for (int s0 = sl; s0 < slices; s0 += 32) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[(size_t)min(s0 + 4 * u, slices - 1) * n + e];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += s0 + 4 * u < slices ? v[u] : 0.f;
+    }
+  lanes[t] = acc;
+  __syncthreads();
+  if (sl == 0 && e < n) {
+    const float r = ((lanes[t] + lanes[64 + t]) + lanes[128 + t]) + lanes[192 + t];
+    float* d = dst[s->dst];
+    if (!d) return;   // a gradient the caller did not ask for
+    d += e;
+    *d = accumulate ? *d + r : r;
+  }
+}
+
+// Softmax cross-entropy of every frame of the window (App. A2), a wave per (frame, sample): its term of the loss and
+// the gradient of the scores, (softmax - [class == label]) * scale
+__global__ __launch_bounds__(256) void sr_loss_kernel(SrLossArgs A) {
+  const int lane = threadIdx.x & 63, idx = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (idx >= A.frames * A.B) return;   // a whole wave
+  const int fi = idx / A.B, frame = A.frame0 + fi, b = idx - fi * A.B, C = A.C;
+  auto at = [&](int id, int slot) -> float* {
+    const SrTensor t = A.tensors[id];
+    return t.base ? (float*)(t.base + slot * t.stride) + (size_t)b * C : nullptr;
+  };
+  const float* z = at(A.x, frame);
+  float* d = at(A.out, A.gate ? frame % A.ring : frame);
+  const float* mask = A.gate ? at(A.mask, frame) : nullptr;
+  float zmax = -INFINITY;
+  for (int c = lane; c < C; c += 64) zmax = fmaxf(zmax, z[c]);
+  for (int m = 32; m > 0; m >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, m, 64));
+  float sum = 0.f;
+  for (int c = lane; c < C; c += 64) sum += expf(z[c] - zmax);
+  for (int m = 32; m > 0; m >>= 1) sum += __shfl_xor(sum, m, 64);
+  const float lse = zmax + logf(sum);
+  int lab = A.labels[b];
+  lab = lab < 0 ? 0 : (lab >= C ? C - 1 : lab);   // the host checks nothing on the device: stay in bounds
+  if (lane == 0) A.terms[(frame - 1) * A.B + b] = lse - z[lab];
+  for (int c = lane; c < C; c += 64) {
+    float v = (expf(z[c] - lse) - (c == lab ? 1.f : 0.f)) * A.scale;
+    if (A.gate) {
+      if (A.act == 1 && !(z[c] > 0.f)) v = 0.f;
+      if (mask) v *= mask[c];
+    }
+    d[c] = v;
+  }
+}
+
+__global__ void sr_patch_kernel(SrTensor* __restrict__ tensors, float** __restrict__ dst, SrPatch p) {
+  for (int k = threadIdx.x; k < p.n; k += blockDim.x) {
+    const int i = p.index[k];
+    if (i >= 0) tensors[i] = p.value[k];
+    else dst[-1 - i] = (float*)p.value[k].base;
+  }
+}
+
+// channel means of a node's state at the frames frame0 .. (the mean read at frame f is that of frame f - lag), a
+// workgroup per 64 channels of one image: four pixel lanes per channel, eight loads in flight
+__global__ __launch_bounds__(256) void sr_pool_kernel(const SrTensor* __restrict__ tensors, SrPool q, int frame0) {
+  __shared__ float lanes[256];
+  const int frame = frame0 + blockIdx.z, b = blockIdx.y, t = threadIdx.x, c = blockIdx.x * 64 + (t & 63), pl = t >> 6;
+  const SrTensor x = tensors[q.x], mean = tensors[q.mean];
+  float acc = 0.f;
+  if (c < q.C && !(q.zero0 && frame - q.lag == 0)) {
+    const float* p = (const float*)(x.base + (frame - q.lag) * x.stride) + (size_t)b * q.HW * q.C + c;
+    for (int i = pl; i < q.HW; i += 32) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[(size_t)min(i + 4 * u, q.HW - 1) * q.C];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += i + 4 * u < q.HW ? v[u] : 0.f;
+    }
+  }
+  lanes[t] = acc;
+  __syncthreads();
+  if (pl == 0 && c < q.C)
+    ((float*)(mean.base + frame * mean.stride))[(size_t)b * q.C + c] =
+        (((lanes[t] + lanes[64 + t]) + lanes[128 + t]) + lanes[192 + t]) / (float)q.HW;
+}
+
+// RMSprop of many parameters in one launch: a <- rho a + (1 - rho) g^2;  theta <- theta - lr g / (sqrt(a) + eps)
+__global__ __launch_bounds__(256) void sr_rmsprop_kernel(SrRmsBatch b, float lr, float rho, float eps) {
+  int k = 0;
+  while (k + 1 < b.count && (int)blockIdx.x >= b.block0[k + 1]) ++k;
+  const long long i = (long long)(blockIdx.x - b.block0[k]) * 256 + threadIdx.x;
+  if (i >= b.n[k]) return;
+  const float gi = b.grad[k][i];
+  const float ai = rho * b.mean[k][i] + (1.f - rho) * gi * gi;
+  b.mean[k][i] = ai;
+  b.theta[k][i] -= lr * gi / (sqrtf(ai) + eps);
+}
+
+hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int lds_bytes) {
+  if (a.n_tiles == 0) return hipSuccess;
+  if (backward) hipLaunchKernelGGL(sr_rows_train_kernel<true>, dim3(a.n_tiles), dim3(256), lds_bytes, s, a);
+  else hipLaunchKernelGGL(sr_rows_train_kernel<false>, dim3(a.n_tiles), dim3(256), lds_bytes, s, a);
+  return hipGetLastError();
+}
+
+hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int lds_bytes) {
+  if (a.n_tiles == 0) return hipSuccess;
+  hipLaunchKernelGGL(sr_grad_kernel, dim3(a.n_tiles), dim3(256), lds_bytes, s, a);
+  return hipGetLastError();
+}
+
+hipError_t sr_launch_grad_sum(hipStream_t s, const SrGradSum* sums, int n_sums, int n_blocks, const float* part, float* const* dst,
+                              int accumulate, const float* terms, int n_terms, float scale, float* loss) {
+  const int blocks = n_blocks + (loss ? 1 : 0);
+  if (blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(sr_grad_sum_kernel, dim3(blocks), dim3(256), 0, s, sums, n_sums, part, dst, accumulate, terms, n_terms, scale, loss);
+  return hipGetLastError();
+}
+
+hipError_t sr_launch_loss(hipStream_t s, const SrLossArgs& a) {
+  hipLaunchKernelGGL(sr_loss_kernel, dim3((a.frames * a.B + 3) / 4), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t sr_launch_patch(hipStream_t s, SrTensor* tensors, float** dst, const SrPatch& p) {
+  if (p.n == 0) return hipSuccess;
+  hipLaunchKernelGGL(sr_patch_kernel, dim3(1), dim3(64), 0, s, tensors, dst, p);
+  return hipGetLastError();
+}
+
+hipError_t sr_launch_pool(hipStream_t s, const SrTensor* tensors, const SrPool& p, int B, int frame0, int frames) {
+  // frames and images as grid rows, some thousands at a time (grid y and z are limited to 65535)
+  for (int f = 0; f < frames; f += 4096) {
+    const int nf = frames - f < 4096 ? frames - f : 4096;
+    hipLaunchKernelGGL(sr_pool_kernel, dim3((p.C + 63) / 64, B, nf), dim3(256), 0, s, tensors, p, frame0 + f);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t sr_launch_rmsprop(hipStream_t s, const SrRmsBatch& b, float lr, float rho, float eps) {
+  if (b.count == 0 || b.block0[b.count] == 0) return hipSuccess;
+  hipLaunchKernelGGL(sr_rmsprop_kernel, dim3(b.block0[b.count]), dim3(256), 0, s, b, lr, rho, eps);
   return hipGetLastError();
 }

@@ -26,27 +26,38 @@ Geometry geometry(const sr_graph* g, const EdgeRt& e) {
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
+// 32-bit offsets (in floats) from the image of a tile's first row, which may touch `images` of them
+bool fits(const sr_graph* g, const sr_node_desc& rows, const sr_node_desc& gathered) {
+  const int64_t pixels = (int64_t)rows.height * rows.width;
+  const int64_t images = std::min<int64_t>(g->batch, 128 / pixels + 2);
+  return (int64_t)g->batch * pixels < ((int64_t)1 << 30) && images * image_floats(gathered) < ((int64_t)1 << 31);
+}
+
 }  // namespace
 
 bool sr_rows_take_forward(const sr_graph* g, int v) {
-  const sr_node_desc& d = g->nodes[v].d;
-  const int64_t pixels = (int64_t)d.height * d.width;
-  if ((int64_t)g->batch * pixels >= ((int64_t)1 << 30) || pixels * d.channels * 4 >= ((int64_t)1 << 31)) return false;
-  const int64_t images = std::min<int64_t>(g->batch, 128 / pixels + 2);   // that the rows of a tile can touch
   for (const EdgeRt& e : g->edges) {
     if (e.d.dst != v) continue;
-    if (e.d.kind == SR_EDGE_GAP_DENSE) return false;
-    if (images * image_floats(g->nodes[e.d.src].d) * 4 >= ((int64_t)1 << 31)) return false;
-    if ((int64_t)e.w_count * 4 >= ((int64_t)1 << 31)) return false;
+    if (e.d.kind == SR_EDGE_GAP_DENSE || (int64_t)e.w_count >= ((int64_t)1 << 31)) return false;
+    if (!fits(g, g->nodes[v].d, g->nodes[e.d.src].d)) return false;
   }
   return true;
 }
 
-void sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v) {
+bool sr_rows_take_training(const sr_graph* g) {
+  for (const EdgeRt& e : g->edges) {
+    const sr_node_desc &s = g->nodes[e.d.src].d, &d = g->nodes[e.d.dst].d;
+    if ((int64_t)e.w_count >= ((int64_t)1 << 31) || !fits(g, d, s) || !fits(g, s, d)) return false;
+  }
+  return true;
+}
+
+int sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds* ids) {
   const NodeRt& n = g->nodes[v];
   SrRowNode node{};
   node.out = v;
-  node.x = node.seed = node.mask = -1;
+  node.x = node.seed = -1;
+  node.mask = ids ? ids->mask0 + v : -1;
   node.bias = n.bias_dev;
   node.C = n.d.channels;
   node.H = n.d.height;
@@ -63,13 +74,19 @@ void sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v) {
   ph.image_scale = 1.f;
   ph.d_wp = sr_div_for(ph.Wp);
   ph.d_hpwp = sr_div_for(ph.Hp * ph.Wp);
-  for (const EdgeRt& e : g->edges) {
+  for (int ei = 0; ei < g->n_edges; ++ei) {
+    const EdgeRt& e = g->edges[ei];
     if (e.d.dst != v) continue;
     const Geometry q = geometry(g, e);
     SrSeg s{};
     s.w = e.w_dev;
-    s.tensor = e.d.src;
-    s.flags = (e.d.bridge ? SR_SEG_LAG : 0) | (g->an.is_input[e.d.src] ? 0 : SR_SEG_ZERO0) | (q.Cin % 4 == 0 ? SR_SEG_QUADS : 0);
+    if (e.d.kind == SR_EDGE_GAP_DENSE) {
+      s.tensor = ids->mean[ei];   // of the frame the rows belong to: the lag was applied when the means were taken
+    } else {
+      s.tensor = e.d.src;
+      s.flags = (e.d.bridge ? SR_SEG_LAG : 0) | (g->an.is_input[e.d.src] ? 0 : SR_SEG_ZERO0);
+    }
+    if (q.Cin % 4 == 0) s.flags |= SR_SEG_QUADS;
     s.GH = q.H; s.GW = q.W; s.GC = q.Cin;
     s.rs = q.stride; s.r0h = s.r0w = -q.pad;
     s.dir = 1;
@@ -80,12 +97,128 @@ void sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v) {
     s.d_gc = sr_div_for(q.Cin);
     s.d_ntj = sr_div_for(q.kw);
     s.d_up = sr_div_for(q.up);
+    s.d_wup = sr_div_for(1);
     ph.steps += ceil_div(s.R, SR_F32_KS);
     p->segs.push_back(s);
   }
   ph.seg_end = (int)p->segs.size();
   p->nodes.push_back(node);
   p->phases.push_back(ph);
+  return (int)p->phases.size() - 1;
+}
+
+// State gradient of node v from the gradients of all its readers.  A stride-s edge pairs a source pixel only with the
+// taps of its own residues, so the pixels are cut into S x S phases, S the common multiple of the strides of v's
+// outgoing convolutions, each with its own tap lists.  A dense edge pairs a pixel with a slice of theta of its own: a
+// node all of whose outgoing edges are dense is one row per image over all its elements, and one that has convolutions
+// as well gets a phase per pixel.
+int sr_rows_backward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds& ids) {
+  const NodeRt& n = g->nodes[v];
+  const int H = n.d.height, W = n.d.width, C = n.d.channels;
+  std::vector<int> gap, dense, conv;
+  int64_t S = 1;
+  for (int ei = 0; ei < g->n_edges; ++ei) {
+    const EdgeRt& e = g->edges[ei];
+    if (e.d.src != v || ids.dist[e.d.dst] < 0) continue;
+    if (e.d.kind == SR_EDGE_GAP_DENSE) gap.push_back(ei);
+    else if (e.d.kind == SR_EDGE_DENSE) dense.push_back(ei);
+    else {
+      conv.push_back(ei);
+      int64_t a = S, b = e.d.stride;
+      while (b) { const int64_t t = a % b; a = b; b = t; }
+      S = S / a * e.d.stride;
+    }
+  }
+  const bool flat = !dense.empty() && conv.empty() && gap.empty();
+  if (!flat && !dense.empty()) S = std::max(H, W);
+  S = std::min<int64_t>(S, std::max(H, W));   // from there on every phase is a single pixel
+  // (a single pixel pairs through stride s with the taps of its residue whatever S is)
+  SrRowNode node{};
+  node.out = ids.grad0 + v;
+  node.x = v;
+  node.seed = v == ids.out_node ? ids.seed : -1;
+  node.mask = ids.mask0 + v;
+  node.C = flat ? H * W * C : C;
+  node.H = flat ? 1 : H;
+  node.W = flat ? 1 : W;
+  node.act = n.d.act;
+  node.gnode = v;
+  const int node_index = (int)p->nodes.size(), first = (int)p->phases.size();
+  p->nodes.push_back(node);
+  for (int phh = 0; phh < (flat ? 1 : std::min<int64_t>(S, H)); ++phh)
+    for (int pww = 0; pww < (flat ? 1 : std::min<int64_t>(S, W)); ++pww) {
+      SrPhase ph{};
+      ph.node = node_index;
+      ph.S = flat ? 1 : (int)S;
+      ph.ph = phh;
+      ph.pw = pww;
+      ph.Hp = flat ? 1 : ceil_div(H - phh, S);
+      ph.Wp = flat ? 1 : ceil_div(W - pww, S);
+      ph.I = g->batch * ph.Hp * ph.Wp;
+      ph.image_scale = 1.f / (float)(H * W);
+      ph.d_wp = sr_div_for(ph.Wp);
+      ph.d_hpwp = sr_div_for(ph.Hp * ph.Wp);
+      ph.seg_begin = (int)p->segs.size();
+      auto add = [&](const EdgeRt& e, SrSeg s, int nti, int ntj) {
+        s.w = e.w_dev;
+        s.tensor = ids.grad0 + e.d.dst;
+        s.flags |= (e.d.bridge ? SR_SEG_LAG : 0) | (s.GC % 4 == 0 ? SR_SEG_QUADS : 0);
+        s.dir = -1;
+        s.ntj = ntj;
+        s.R = nti * ntj * s.GC;
+        s.ldw = node.C;
+        s.dist = ids.dist[e.d.dst];
+        s.step0 = ph.steps;
+        s.d_gc = sr_div_for(s.GC);
+        s.d_ntj = sr_div_for(ntj);
+        s.d_up = sr_div_for(1);
+        ph.steps += ceil_div(s.R, SR_F32_KS);
+        p->segs.push_back(s);
+      };
+      for (int ei : gap) {
+        const EdgeRt& e = g->edges[ei];
+        SrSeg s{};
+        s.flags = SR_SEG_IMAGE;
+        s.GH = s.GW = 1;
+        s.GC = g->nodes[e.d.dst].d.channels;
+        s.d_wup = sr_div_for(1);
+        add(e, s, 1, 1);
+      }
+      ph.seg_image = (int)p->segs.size();
+      for (int ei : dense) {
+        const EdgeRt& e = g->edges[ei];
+        SrSeg s{};
+        s.GH = s.GW = 1;
+        s.GC = g->nodes[e.d.dst].d.channels;
+        s.wt0 = flat ? 0 : phh * W + pww;   // the pixel's slice of theta
+        s.d_wup = sr_div_for(1);
+        add(e, s, 1, 1);
+      }
+      for (int ei : conv) {
+        const EdgeRt& e = g->edges[ei];
+        const Geometry q = geometry(g, e);
+        const int ti0 = (phh + q.pad) % q.stride, tj0 = (pww + q.pad) % q.stride;
+        const int nti = ti0 < q.kh ? ceil_div(q.kh - ti0, q.stride) : 0, ntj = tj0 < q.kw ? ceil_div(q.kw - tj0, q.stride) : 0;
+        if (nti * ntj == 0) continue;
+        // pixel (hh S + ph) pairs through the tap ti0 + a s with row (hh S + ph + pad - ti0) / s - a of the edge's
+        // result, each row of which stands for `up` rows of the target
+        SrSeg s{};
+        s.GH = g->nodes[e.d.dst].d.height;
+        s.GW = g->nodes[e.d.dst].d.width;
+        s.GC = q.Cout;
+        s.rs = ph.Hp > 1 || ph.Wp > 1 ? (int)(S / q.stride) * q.up : 0;
+        s.r0h = (phh + q.pad - ti0) / q.stride * q.up + q.up - 1;
+        s.r0w = (pww + q.pad - tj0) / q.stride * q.up + q.up - 1;
+        s.wt0 = ti0 * q.kw + tj0;
+        s.wti = q.stride * q.kw;
+        s.wtj = q.stride;
+        s.d_wup = sr_div_for(q.up);
+        add(e, s, nti * q.up, ntj * q.up);
+      }
+      ph.seg_end = (int)p->segs.size();
+      p->phases.push_back(ph);
+    }
+  return first;
 }
 
 double sr_rows_work(const SrRowPlan& p, int phase) {
@@ -173,4 +306,136 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
   none.phase = -1;
   for (size_t k = 0; k < longest; ++k)
     for (int x = 0; x < SR_XCDS; ++x) out->push_back(k < per_xcd[x].size() ? per_xcd[x][k].t : none);
+}
+
+void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from) {
+  // columns of work: per edge its shape, tiles, steps
+  struct Item { int edge, shape, n_i, n_j, steps; double step_cycles; };
+  std::vector<Item> items;
+  double work = 0;
+  int64_t n_short = 0;
+  for (int ei = 0; ei < g->n_edges; ++ei) {
+    const EdgeRt& e = g->edges[ei];
+    const int w = e.d.dst;
+    // frames in which the target has a gradient and the source is not the window's zero initial state
+    const int f0 = std::max(lo, e.d.bridge && !g->an.is_input[e.d.src] ? 2 : 1);
+    const int f1 = ids.dist[w] < 0 ? 0 : std::min(hi, W - ids.dist[w]);
+    if (f1 < f0) {
+      if (first) {
+        p->sums.push_back(SrGradSum{0, (long long)e.w_count, 0, ei, p->sum_blocks, 0});
+        p->sum_blocks += ceil_div(e.w_count, 64);
+      }
+      continue;
+    }
+    const Geometry q = geometry(g, e);
+    SrGradEdge d{};
+    d.x = e.d.kind == SR_EDGE_GAP_DENSE ? ids.mean[ei] : e.d.src;
+    d.dy = ids.grad0 + w;
+    d.lag = e.d.kind == SR_EDGE_GAP_DENSE ? 0 : (int)e.d.bridge;
+    d.frame0 = f0;
+    d.H = q.H; d.W = q.W; d.Cin = q.Cin;
+    d.Ho = q.Ho * q.up; d.Wo = q.Wo * q.up; d.Cout = q.Cout;
+    d.kw = q.kw; d.stride = q.stride; d.pad = q.pad;
+    d.I = q.kh * q.kw * q.Cin;
+    d.M = g->batch * d.Ho * d.Wo;
+    d.quads_in = q.Cin % 4 == 0;
+    d.quads_out = q.Cout % 4 == 0;
+    d.dst = ei;
+    d.steps_per_frame = ceil_div(d.M, SR_F32_KS);
+    d.d_cin = sr_div_for(q.Cin);
+    d.d_kw = sr_div_for(q.kw);
+    d.d_wo = sr_div_for(d.Wo);
+    d.d_howo = sr_div_for(d.Ho * d.Wo);
+    d.d_up = sr_div_for(q.up);
+    d.d_steps = sr_div_for(d.steps_per_frame);
+    Item it{(int)p->edges.size(), 0, 0, 0, d.steps_per_frame * (f1 - f0 + 1), 0};
+    p->edges.push_back(d);
+    items.push_back(it);
+    n_short += (int64_t)ceil_div(d.I, 64) * ceil_div(d.Cout, 64) * std::max(1, it.steps / 64);
+  }
+  const bool tall = n_short >= tall_from;
+  for (Item& it : items) {
+    const SrGradEdge& d = p->edges[it.edge];
+    if (d.Cout <= 32) it.shape = SR_F32_128x32;
+    else if (!tall || d.I <= 64) it.shape = SR_F32_64x64;
+    else it.shape = (d.Cout <= 64 || (d.Cout + 127) / 128 * 128 - d.Cout >= 64) ? SR_F32_128x64 : SR_F32_128x128;
+    int ti, tj;
+    sr_f32_shape(it.shape, &ti, &tj);
+    it.n_i = ceil_div(d.I, ti);
+    it.n_j = ceil_div(d.Cout, tj);
+    it.step_cycles = std::max(ti * tj / 8.0, 700.0);
+    work += it.step_cycles * it.steps * it.n_i * it.n_j;
+    p->lds = std::max(p->lds, sr_f32_lds_bytes(it.shape));
+  }
+  // The pixel sums are cut into slices so that the launch has about six work items of equal length per compute unit,
+  // none shorter than 16 steps: shorter ones are dominated by filling the pipeline and by their partial sums.
+  const double item_cycles = work / (SR_CUS * 6.0);
+  struct Keyed { double cost; SrGradTile t; };
+  std::vector<Keyed> list;
+  for (const Item& it : items) {
+    SrGradEdge& d = p->edges[it.edge];
+    const int64_t most = std::max(1, it.steps / 16);
+    const int64_t want = (int64_t)std::ceil(it.step_cycles * it.steps / std::max(item_cycles, 1.0));
+    d.slices = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(want, most), 1024));
+    if (d.slices > 1) {
+      d.part_at = p->part_floats;
+      p->part_floats += ((long long)d.I * d.Cout * d.slices + 63) / 64 * 64;
+      p->sums.push_back(SrGradSum{d.part_at, (long long)d.I * d.Cout, d.slices, d.dst, p->sum_blocks, 0});
+      p->sum_blocks += ceil_div((int64_t)d.I * d.Cout, 64);
+    }
+    int ti, tj;
+    sr_f32_shape(it.shape, &ti, &tj);
+    for (int s = 0; s < d.slices; ++s)
+      for (int a = 0; a < it.n_i; ++a)
+        for (int b = 0; b < it.n_j; ++b) {
+          SrGradTile t{};
+          t.edge = it.edge;
+          t.shape = it.shape;
+          t.i0 = a * ti;
+          t.j0 = b * tj;
+          t.step_begin = (int)((int64_t)it.steps * s / d.slices);
+          t.step_end = (int)((int64_t)it.steps * (s + 1) / d.slices);
+          t.slice = s;
+          list.push_back(Keyed{it.step_cycles * (t.step_end - t.step_begin), t});
+        }
+  }
+  for (int v = 0; v < g->n_nodes; ++v) {
+    if (g->an.is_input[v]) continue;
+    const sr_node_desc& d = g->nodes[v].d;
+    const int f1 = ids.dist[v] < 0 ? 0 : std::min(hi, W - ids.dist[v]);
+    SrGradSum sum{0, d.channels, 0, g->n_edges + v, p->sum_blocks, 0};
+    if (f1 >= lo) {
+      SrGradBias b{};
+      b.dy = ids.grad0 + v;
+      b.C = d.channels;
+      b.M = g->batch * d.height * d.width;
+      b.frame0 = lo;
+      b.d_m = sr_div_for(b.M);
+      const int64_t rows = (int64_t)b.M * (f1 - lo + 1);
+      const int slices = (int)std::max<int64_t>(1, std::min<int64_t>(512, rows / 256));
+      b.part_at = p->part_floats;
+      p->part_floats += ((long long)d.channels * slices + 63) / 64 * 64;
+      sum.part_at = b.part_at;
+      sum.slices = slices;
+      for (int s = 0; s < slices; ++s)
+        for (int j = 0; j < d.channels; j += 64) {
+          SrGradTile t{};
+          t.edge = (int)p->biases.size();
+          t.j0 = j;
+          t.step_begin = (int)(rows * s / slices);
+          t.step_end = (int)(rows * (s + 1) / slices);
+          t.slice = s;
+          t.kind = 1;
+          list.push_back(Keyed{(t.step_end - t.step_begin) * 8.0, t});
+        }
+      p->biases.push_back(b);
+      p->lds = std::max(p->lds, 1024);
+    } else if (!first) {
+      continue;
+    }
+    p->sums.push_back(sum);
+    p->sum_blocks += ceil_div(d.channels, 64);
+  }
+  std::stable_sort(list.begin(), list.end(), [](const Keyed& a, const Keyed& b) { return a.cost > b.cost; });
+  for (const Keyed& k : list) p->tiles.push_back(k.t);
 }

@@ -594,8 +594,7 @@ sr_status finalize(sr_graph* g) {
       std::vector<int> phases;
       for (int v = 0; v < g->n_nodes; ++v)
         if (g->an.level[v] == L && g->nodes[v].kind == 4) {
-          phases.push_back((int)rows.phases.size());
-          sr_rows_forward(&rows, g, v);
+          phases.push_back(sr_rows_forward(&rows, g, v, nullptr));
         }
       lp.row_begin = (int)row_tiles.size();
       if (!phases.empty()) sr_rows_tiles(rows, phases, 0, g->train_tall_from, g->allow_split, &row_slots, &row_tiles, &lp.row_lds);
@@ -2028,6 +2027,10 @@ sr_status sr_graph_configure(sr_graph* g, int32_t option, int64_t value) {
     case SR_OPT_TRAIN_TALL_TILES_FROM:
       if (value < 0 || value > (1 << 30)) return gfail(g, SR_ERR_ARG, "tall-tile threshold must be in 0..2^30");
       g->train_tall_from = (int)value;
+      return SR_OK;
+    case SR_OPT_TRAIN_FRAMES_KEPT:
+      if (value < 0 || value > 4096) return gfail(g, SR_ERR_ARG, "frames kept by a training window must be in 0..4096");
+      g->train_frames_kept = (int)value;
       return SR_OK;
     case SR_OPT_DEP_SPIN_LIMIT:
       if (value < 0 || value > (1 << 24)) return gfail(g, SR_ERR_ARG, "spin limit of dependency waits must be in 0..2^24");

@@ -421,3 +421,20 @@ def test_gtsrb_shaped_window_at_full_width():
     g = g0.with_pattern(W.hybrid_pattern(g0))
     got, data = run_case(g, 3, seed=5)
     check_against_oracle(g, 3, got, data, "gtsrb_sr B=8/hybrid")
+
+
+@pytest.mark.parametrize("kept", [1, 2, 3])
+@pytest.mark.parametrize("pattern", list(PATTERNS))
+def test_reverse_sweep_in_chunks_of_frames(pattern, kept):
+    # SR_OPT_TRAIN_FRAMES_KEPT (option 9): the state gradients of `kept` frames at a time; the weight gradients of the
+    # chunks add up, the last frame of one chunk feeds the first of the next
+    import paper_1806_04965_amd as sr
+    g0 = small_sr_graph(batch=3)
+    g = g0.with_pattern(PATTERNS[pattern](g0))
+    w, b, _ = W.make_case(g, seed=41, bias_scale=0.1, frames=7, recipe="uniform")
+    dev = sr.SrGraph(g, options={9: kept})
+    dev.set_parameters(w, b)
+    for Wn in (1, kept, kept + 1, 7):
+        got, data = run_case(g, Wn, seed=41, dev=dev)
+        check_against_oracle(g, Wn, got, data, f"small_sr/{pattern} W={Wn}, {kept} frames at a time", may_be_zero=Wn < 4)
+    dev.close()

@@ -51,18 +51,26 @@ template <> struct Store<uint16_t> {
   static __device__ __forceinline__ void store(uint16_t* p, float v) { *p = float_to_bf16_bits(v); }
 };
 
-// Called by every workgroup of the last launch of a frame once its work is stored: the workgroup
-// that arrives last advances the frame counter by the frames the launch covers (all others have
-// read it long before).
-__device__ __forceinline__ void sr_block_done(SrCtx* ctx, int n_blocks, int frames) {
+// The call's values (see SrFrame): in the launch's own arguments, of which the SrFrame is the first, or in memory.
+// Read with scalar loads; constant while the launch runs (the last workgroup advances the frame counter when all others
+// have read it).
+typedef const __attribute__((address_space(4))) SrCtx* sr_call_t;
+__device__ __forceinline__ sr_call_t sr_call(const SrFrame& f) {
+  return f.here.frame > 0 ? (sr_call_t)__builtin_amdgcn_kernarg_segment_ptr() : (sr_call_t)(unsigned long long)f.ctx;
+}
+
+// Called by every workgroup of a launch once its work is stored.  If the launch advances the frame counter, the
+// workgroup that arrives last does so (all others have read it long before).
+__device__ __forceinline__ void sr_block_done(const SrFrame& f, int n_blocks) {
   // no fence: the counter only orders "everyone has read the frame counter" (done at kernel start)
   // before its update, and the next launch sees the update through the kernel boundary
+  if (f.advance <= 0) return;
   __syncthreads();
   if (threadIdx.x == 0) {
-    const int old = __hip_atomic_fetch_add(&ctx->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int old = __hip_atomic_fetch_add(&f.ctx->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (old == n_blocks - 1) {
-      ctx->done = 0;
-      ctx->frame = ctx->frame + frames;
+      f.ctx->done = 0;
+      f.ctx->frame = f.ctx->frame + f.advance;
     }
   }
 }
@@ -152,14 +160,14 @@ __device__ __forceinline__ void sr_store16_agent(void* p, u32x4_t v) {
 // in place before frame t's first launch.  Frames the caller has given no input for are skipped
 // (the item still counts as completed for its dependants).
 template <typename T>
-__device__ __forceinline__ void sr_stage_item(SrCtx* __restrict__ ctx, const SrStageNode& nd, int chunk, int ahead,
+__device__ __forceinline__ void sr_stage_item(SrCtx* __restrict__ ctx, sr_call_t call, const SrStageNode& nd, int chunk, int ahead,
                                               int frame_now, const SrFlow& flow) {
   const int frame = frame_now + ahead;
-  const char* base = (const char*)ctx->in_ptr[nd.input_slot];
+  const char* base = (const char*)(unsigned long long)call->in_ptr[nd.input_slot];
   // the copy written was last read two frames ago (one frame ago, by bridging edges): wait for those readers
   sr_wait_deps(flow, nd.dep_begin, nd.dep_count, frame, ctx);
-  if (base != nullptr && frame <= ctx->in_last) {
-    const T* in = (const T*)(base + (int64_t)(frame - ctx->in_base) * ctx->in_stride[nd.input_slot]);
+  if (base != nullptr && frame <= call->in_last) {
+    const T* in = (const T*)(base + (int64_t)(frame - call->in_base) * call->in_stride[nd.input_slot]);
     T* out = (T*)nd.state[frame & 1];
     const int end = min(nd.elems_px, (chunk + 1) * SR_STAGE_CHUNK);
     constexpr int V = 16 / sizeof(T);
@@ -211,7 +219,7 @@ __device__ __forceinline__ void sr_stage_item(SrCtx* __restrict__ ctx, const SrS
 // the parts are added in a fixed order, then bias, activation, store and, if this node is being
 // recorded, the rollout output.  smem: SR_HEAD_MAX_K floats, one int, 4*64*4 floats.
 template <typename T>
-__device__ __forceinline__ bool sr_head_body(const SrCtx* __restrict__ ctx, const SrHead& h,
+__device__ __forceinline__ bool sr_head_body(sr_call_t call, const SrHead& h,
                                              const SrHeadEdge* __restrict__ head_edges, int b, int split,
                                              float* smem, int vec_floats, int frame) {
   const int cur = frame & 1;
@@ -330,8 +338,8 @@ __device__ __forceinline__ bool sr_head_body(const SrCtx* __restrict__ ctx, cons
       }
     }
   }
-  char* rec = h.record ? (char*)ctx->out_ptr : nullptr;
-  T* recp = rec ? (T*)(rec + (int64_t)(frame - ctx->out_base) * ctx->out_stride) : nullptr;
+  char* rec = h.record ? (char*)(unsigned long long)call->out_ptr : nullptr;
+  T* recp = rec ? (T*)(rec + (int64_t)(frame - call->out_base) * call->out_stride) : nullptr;
   if (narrow) {
     red[slice * CO + co_n] = acc[0];
     __syncthreads();
@@ -362,21 +370,21 @@ __device__ __forceinline__ bool sr_head_body(const SrCtx* __restrict__ ctx, cons
 // ... as a work item: wait for the source nodes (and for the readers of the copy about to be
 // overwritten), compute, and count the image as done once its outputs are in memory
 template <typename T>
-__device__ __forceinline__ void sr_head_item(SrCtx* __restrict__ ctx, const SrHead& h,
+__device__ __forceinline__ void sr_head_item(SrCtx* __restrict__ ctx, sr_call_t call, const SrHead& h,
                                              const SrHeadEdge* __restrict__ head_edges, int b, int split,
                                              float* smem, int vec_floats, int frame, const SrFlow& flow) {
   sr_wait_deps(flow, h.dep_begin, h.dep_count, frame, ctx);
-  const bool wrote = sr_head_body<T>(ctx, h, head_edges, b, split, smem, vec_floats, frame);
+  const bool wrote = sr_head_body<T>(call, h, head_edges, b, split, smem, vec_floats, frame);
   if (wrote) sr_signal_done(flow, h.gnode);
 }
 
 
 template <typename T>
-__device__ __forceinline__ void sr_aux_item(SrCtx* __restrict__ ctx, const SrAux& it,
+__device__ __forceinline__ void sr_aux_item(SrCtx* __restrict__ ctx, sr_call_t call, const SrAux& it,
                                             const SrHead* __restrict__ heads,
                                             const SrHeadEdge* __restrict__ head_edges,
                                             const SrStageNode* __restrict__ stage_nodes, float* smem, int vec_floats,
                                             int frame, const SrFlow& flow) {
-  if (it.kind == SR_AUX_HEAD) sr_head_item<T>(ctx, heads[it.a], head_edges, it.b, it.c, smem, vec_floats, frame, flow);
-  else if (it.kind == SR_AUX_STAGE) sr_stage_item<T>(ctx, stage_nodes[it.a], it.b, it.c, frame, flow);
+  if (it.kind == SR_AUX_HEAD) sr_head_item<T>(ctx, call, heads[it.a], head_edges, it.b, it.c, smem, vec_floats, frame, flow);
+  else if (it.kind == SR_AUX_STAGE) sr_stage_item<T>(ctx, call, stage_nodes[it.a], it.b, it.c, frame, flow);
 }

@@ -253,9 +253,9 @@ struct SrRmsBatch {
 };
 
 // frame path: the level's tiles and the auxiliary items in one launch
-hipError_t sr_launch_rows_frame(hipStream_t s, SrCtx* ctx, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
+hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
                                 const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
-                                int aux_smem_bytes, int is_last);
+                                int aux_smem_bytes);
 // training window
 hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int lds_bytes);
 hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int lds_bytes);

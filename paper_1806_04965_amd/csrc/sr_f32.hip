@@ -483,34 +483,34 @@ __device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowT
 
 }  // namespace
 
-__global__ __launch_bounds__(256, 2) void sr_rows_frame_kernel(SrCtx* __restrict__ ctx, SrRowArgs A,
+__global__ __launch_bounds__(256, 2) void sr_rows_frame_kernel(SrFrame f, SrRowArgs A,
                                                                const SrAux* __restrict__ aux, int n_aux, int aux_at,
                                                                const SrHead* __restrict__ heads,
                                                                const SrHeadEdge* __restrict__ head_edges,
-                                                               const SrStageNode* __restrict__ stage_nodes, int vec_floats,
-                                                               int is_last) {
+                                                               const SrStageNode* __restrict__ stage_nodes, int vec_floats) {
   extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
   const int item = blockIdx.x;
-  const int frame = SR_UNI(ctx->frame);
+  const sr_call_t call = sr_call(f);
+  const int frame = call->frame + f.offset;
   if (item >= aux_at && item < aux_at + n_aux) {
-    sr_aux_item<float>(ctx, aux[item - aux_at], heads, head_edges, stage_nodes, (float*)sr_rows_lds, vec_floats, frame,
+    sr_aux_item<float>(f.ctx, call, aux[item - aux_at], heads, head_edges, stage_nodes, (float*)sr_rows_lds, vec_floats, frame,
                        SrFlow{nullptr, nullptr, 0, 0, nullptr});
   } else {
     const int cur = frame & 1;
     const SrSlots sl{cur, cur ^ 1, cur, 0, 1 << 30};
-    char* rec = A.rec_node >= 0 ? (char*)ctx->out_ptr : nullptr;
-    if (rec) rec += (int64_t)(frame - ctx->out_base) * ctx->out_stride;
+    char* rec = A.rec_node >= 0 ? (char*)(unsigned long long)call->out_ptr : nullptr;
+    if (rec) rec += (int64_t)(frame - call->out_base) * call->out_stride;
     sr_row_item<false>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), 0, sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
   }
-  if (is_last) sr_block_done(ctx, gridDim.x, 1);
+  sr_block_done(f, gridDim.x);
 }
 
-hipError_t sr_launch_rows_frame(hipStream_t s, SrCtx* ctx, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
+hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
                                 const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
-                                int aux_smem_bytes, int is_last) {
+                                int aux_smem_bytes) {
   if (a.n_tiles + n_aux == 0) return hipSuccess;
-  hipLaunchKernelGGL(sr_rows_frame_kernel, dim3(a.n_tiles + n_aux), dim3(256), lds_bytes, s, ctx, a, aux, n_aux, a.n_tiles / 2, heads,
-                     head_edges, stage_nodes, (aux_smem_bytes - 16 - 4096) / 4, is_last);
+  hipLaunchKernelGGL(sr_rows_frame_kernel, dim3(a.n_tiles + n_aux), dim3(256), lds_bytes, s, f, a, aux, n_aux, a.n_tiles / 2, heads,
+                     head_edges, stage_nodes, (aux_smem_bytes - 16 - 4096) / 4);
   return hipGetLastError();
 }
 

@@ -138,9 +138,11 @@ struct sr_graph {
   int train_tall_from = 2048;   // SR_OPT_TRAIN_TALL_TILES_FROM
   int train_frames_kept = 0;    // SR_OPT_TRAIN_FRAMES_KEPT
 
-  hipGraph_t graph1 = nullptr, graphN = nullptr;
-  hipGraphExec_t exec1 = nullptr, execN = nullptr;
-  int graph_rec_node = -2;   // out_node the captured graphs record
+  hipGraph_t graph = nullptr;      // frames_per_graph frames
+  hipGraphExec_t exec = nullptr;
+  int graph_rec_node = -2;   // out_node the captured graph records
+  SrResetItem* reset_items = nullptr;   // what sr_reset clears or fills
+  int n_reset_items = 0, n_reset_blocks = 0;
 };
 
 void sr_train_state_release(struct SrTrainState* t);

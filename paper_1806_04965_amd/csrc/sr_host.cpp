@@ -1419,6 +1419,19 @@ sr_status finalize(sr_graph* g) {
   g->heads_host = hd;
   g->lds_bytes = std::max(g->lds_bytes, g->aux_smem_bytes);
 
+  {
+    std::vector<SrResetItem> items;
+    auto item = [&](void* p, size_t bytes, int slot, int px, int C, int Cp) {
+      items.push_back(SrResetItem{p, (int64_t)bytes, slot, px, C, Cp, g->n_reset_blocks, 0});
+      g->n_reset_blocks += (int)((bytes + SR_RESET_BYTES - 1) / SR_RESET_BYTES);
+    };
+    for (const NodeRt& n : g->nodes)
+      item(n.state[0], n.state_bytes, n.input_slot, B * n.d.height * n.d.width, n.d.channels, n.Cp);
+    // frames are counted from the reset: so are the nodes' completed work items
+    if (g->done_counters) item(g->done_counters, (size_t)g->n_nodes * SR_DONE_STRIDE * sizeof(int32_t), -1, 0, 0, 0);
+    g->n_reset_items = (int)items.size();
+    if ((st = upload(g, &g->reset_items, items)) != SR_OK) return st;
+  }
   int launches = g->stage_mode == 2 ? 1 : 0;
   for (int L = 1; L <= F; ++L) {
     const LevelPlan& lp = g->levels[L];
@@ -1460,13 +1473,17 @@ bool record_needs_copy(const sr_graph* g) {
   return true;
 }
 
-// Start of a call that computes frames: the per-call values go into the device context, and a graph
-// whose input staging runs one frame ahead gets the call's first frame staged here.
+// a launch that brings its call's values along (frame = c.frame) ...
+SrFrame plain_frame(const sr_graph* g, const SrCtx& c) { return SrFrame{c, g->ctx, 0, 0}; }
+// ... and one recorded into a HIP graph: frame `offset` after the device context's
+SrFrame recorded_frame(const sr_graph* g, int offset, int advance) { return SrFrame{SrCtx{}, g->ctx, offset, advance}; }
+
+// Start of a call that computes frames: a graph whose input staging runs one frame ahead gets the call's first frame
+// (c.frame) staged here.
 sr_status begin_frames(sr_graph* g, const SrCtx& c) {
-  SR_HIP(g, sr_launch_set_ctx(g->stream, g->ctx, c, 0));
   if (g->stage_mode == 1 && !g->dataflow)
-    SR_HIP(g, sr_launch_aux(g->stream, g->ctx, g->aux + g->stage_aux_begin, g->n_stage_aux, g->heads, g->head_edges,
-                            g->stage_nodes, g->aux_smem_bytes, g->dtype == SR_BF16, 0));
+    SR_HIP(g, sr_launch_aux(g->stream, plain_frame(g, c), g->aux + g->stage_aux_begin, g->n_stage_aux, g->heads, g->head_edges,
+                            g->stage_nodes, g->aux_smem_bytes, g->dtype == SR_BF16));
   return SR_OK;
 }
 
@@ -1486,17 +1503,20 @@ sr_status ensure_split_scratch(sr_graph* g) {
 }
 
 // Dependency-driven graphs: `frames` frames, every update step of each, in one launch.
-sr_status enqueue_flow(sr_graph* g, int frames, bool advance, SrSplitScratch split) {
+sr_status enqueue_flow(sr_graph* g, int frames, const SrFrame& f, SrSplitScratch split) {
   const bool by_depth = g->flow_order && frames == g->flow_order_frames && g->flow_depth_order;
   const SrFlow flow{g->deps, g->done_counters, g->dep_spin_limit, frames, by_depth ? g->flow_order : nullptr};
-  SR_HIP(g, sr_launch_mfma(g->stream, g->ctx,
+  SR_HIP(g, sr_launch_mfma(g->stream, f,
                            SrTables4{g->nodes4, g->planes4, (const SrPlanRef*)g->plan_index, g->plan_tables, g->tap_table},
                            flow, frames, g->n_flow_order, g->flow_items, g->n_flow_items, g->lds_bytes, g->aux, 0, g->heads, g->head_edges,
-                           g->stage_nodes, g->aux_smem_bytes, advance ? 1 : 0, split));
+                           g->stage_nodes, g->aux_smem_bytes, split));
   return SR_OK;
 }
 
-sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch split) {
+// The launches of one frame; the last one advances the device's frame counter by f.advance.
+sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch split, const SrFrame& f) {
+  SrFrame still = f;   // of all launches but the last
+  still.advance = 0;
   hipStream_t s = g->stream;
   const int bf16 = g->dtype == SR_BF16;
   if (g->dataflow) {
@@ -1509,13 +1529,13 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
       SR_HIP(g, hipEventRecord(e0, s));
     }
     const bool copy = record && record_needs_copy(g);
-    sr_status st = enqueue_flow(g, 1, !copy, split);
+    sr_status st = enqueue_flow(g, 1, copy ? still : f, split);
     if (st != SR_OK) return st;
     if (copy) {
       const NodeRt& n = g->nodes[g->rec_node];
-      SR_HIP(g, sr_launch_record_output(s, g->ctx, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
+      SR_HIP(g, sr_launch_record_output(s, still, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
                                         n.d.channels, n.Cp, bf16));
-      SR_HIP(g, sr_launch_tick(s, g->ctx));
+      if (f.advance > 0) SR_HIP(g, sr_launch_tick(s, g->ctx, f.advance));
     }
     if (ft) SR_HIP(g, hipEventRecord(e1, s));
     return SR_OK;
@@ -1542,8 +1562,8 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
   }
   if (g->stage_mode == 2) {
     SR_HIP(g, mark(0));
-    SR_HIP(g, sr_launch_aux(s, g->ctx, g->aux + g->stage_aux_begin, g->n_stage_aux, g->heads, g->head_edges, g->stage_nodes,
-                            g->aux_smem_bytes, bf16, 0));
+    SR_HIP(g, sr_launch_aux(s, still, g->aux + g->stage_aux_begin, g->n_stage_aux, g->heads, g->head_edges, g->stage_nodes,
+                            g->aux_smem_bytes, bf16));
   }
   for (int L = 1; L <= g->an.factor; ++L) {
     const LevelPlan& lp = g->levels[L];
@@ -1551,7 +1571,7 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
     const bool aux_ride = has_tiles;
     const bool direct_launch = lp.n_blocks > 0 || (!aux_ride && lp.n_aux > 0);
     if (has_tiles) {
-      const int is_last = (!copy_out && L == last_level && !last_is_direct) ? 1 : 0;
+      const SrFrame& fl = (!copy_out && L == last_level && !last_is_direct) ? f : still;
       SR_HIP(g, mark(lp.n_rows > 0 ? 2 : 1));
       if (lp.n_rows > 0) {   // fp32 graphs have no bf16 tiles
         SrRowArgs a{};
@@ -1560,133 +1580,106 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
         a.n_tiles = lp.n_rows;
         a.rec_node = record ? g->rec_node : -1;
         a.split = g->row_split;
-        SR_HIP(g, sr_launch_rows_frame(s, g->ctx, a, std::max(lp.row_lds, g->aux_smem_bytes), g->aux + lp.aux_begin, lp.n_aux, g->heads,
-                                       g->head_edges, g->stage_nodes, g->aux_smem_bytes, is_last));
+        SR_HIP(g, sr_launch_rows_frame(s, fl, a, std::max(lp.row_lds, g->aux_smem_bytes), g->aux + lp.aux_begin, lp.n_aux, g->heads,
+                                       g->head_edges, g->stage_nodes, g->aux_smem_bytes));
       } else if (g->tile_version == 2)
-        SR_HIP(g, sr_launch_mfma8(s, g->ctx, g->m_nodes, g->m_edges, g->m_tiles + lp.tile_begin, lp.n_tiles,
+        SR_HIP(g, sr_launch_mfma8(s, fl, g->m_nodes, g->m_edges, g->m_tiles + lp.tile_begin, lp.n_tiles,
                                   g->aux + lp.aux_begin, lp.n_aux, g->heads, g->head_edges, g->stage_nodes,
-                                  g->aux_smem_bytes, is_last, split));
+                                  g->aux_smem_bytes, split));
       else
-        SR_HIP(g, sr_launch_mfma(s, g->ctx,
+        SR_HIP(g, sr_launch_mfma(s, fl,
                                  SrTables4{g->nodes4, g->planes4, (const SrPlanRef*)g->plan_index, g->plan_tables, g->tap_table},
                                  SrFlow{nullptr, nullptr, 0, 0, nullptr}, 1, 0, g->tiles4 + lp.tile_begin, lp.n_tiles, g->lds_bytes,
                                  g->aux + lp.aux_begin, lp.n_aux, g->heads, g->head_edges, g->stage_nodes,
-                                 g->aux_smem_bytes, is_last, split));
+                                 g->aux_smem_bytes, split));
     }
     if (direct_launch) {
-      const int is_last = (!copy_out && L == last_level) ? 1 : 0;
+      const SrFrame& fl = (!copy_out && L == last_level) ? f : still;
       const int n_aux = aux_ride ? 0 : lp.n_aux;   // aux items already went with the tiles
       SR_HIP(g, mark(2));
       if (lp.n_blocks == 0)   // auxiliary items only
-        SR_HIP(g, sr_launch_aux(s, g->ctx, g->aux + lp.aux_begin, n_aux, g->heads, g->head_edges, g->stage_nodes,
-                                g->aux_smem_bytes, bf16, is_last));
+        SR_HIP(g, sr_launch_aux(s, fl, g->aux + lp.aux_begin, n_aux, g->heads, g->head_edges, g->stage_nodes,
+                                g->aux_smem_bytes, bf16));
       else
-        SR_HIP(g, sr_launch_direct(s, g->ctx, g->d_nodes, g->d_edges, g->d_blocks + lp.block_begin, lp.n_blocks, bf16,
+        SR_HIP(g, sr_launch_direct(s, fl, g->d_nodes, g->d_edges, g->d_blocks + lp.block_begin, lp.n_blocks, bf16,
                                    g->batch, g->aux + lp.aux_begin, n_aux, g->heads, g->head_edges, g->stage_nodes,
-                                   g->aux_smem_bytes, is_last));
+                                   g->aux_smem_bytes));
     }
   }
   if (copy_out) {
     SR_HIP(g, mark(4));
     const NodeRt& n = g->nodes[g->rec_node];
-    SR_HIP(g, sr_launch_record_output(s, g->ctx, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
+    SR_HIP(g, sr_launch_record_output(s, still, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
                                       n.d.channels, n.Cp, bf16));
-    SR_HIP(g, sr_launch_tick(s, g->ctx));
+    if (f.advance > 0) SR_HIP(g, sr_launch_tick(s, g->ctx, f.advance));
   }
   SR_HIP(g, mark(-1));
   return SR_OK;
 }
 
 void drop_graphs(sr_graph* g) {
-  if (g->exec1) hipGraphExecDestroy(g->exec1);
-  if (g->execN) hipGraphExecDestroy(g->execN);
-  if (g->graph1) hipGraphDestroy(g->graph1);
-  if (g->graphN) hipGraphDestroy(g->graphN);
-  g->exec1 = g->execN = nullptr;
-  g->graph1 = g->graphN = nullptr;
+  if (g->exec) hipGraphExecDestroy(g->exec);
+  if (g->graph) hipGraphDestroy(g->graph);
+  g->exec = nullptr;
+  g->graph = nullptr;
   g->graph_rec_node = -2;
 }
 
-sr_status capture(sr_graph* g, int frames, hipGraph_t* graph, hipGraphExec_t* exec) {
+// frames_per_graph frames as one HIP graph
+sr_status ensure_graph(sr_graph* g) {
+  if (g->exec && g->graph_rec_node == g->rec_node) return SR_OK;
+  drop_graphs(g);
   SR_HIP(g, hipStreamBeginCapture(g->stream, hipStreamCaptureModeThreadLocal));
   sr_status st = SR_OK;
   const SrSplitScratch own{g->split_scratch, g->split_counters};
-  if (g->dataflow && !record_needs_copy(g))
-    st = enqueue_flow(g, frames, true, own);   // all the frames in one launch
-  else
-    for (int f = 0; f < frames && st == SR_OK; ++f) st = enqueue_frame(g, true, nullptr, own);
-  hipError_t e = hipStreamEndCapture(g->stream, graph);
+  const int n = g->frames_per_graph;
+  for (int k = 0; k < n && st == SR_OK; ++k) st = enqueue_frame(g, true, nullptr, own, recorded_frame(g, k, k == n - 1 ? n : 0));
+  hipError_t e = hipStreamEndCapture(g->stream, &g->graph);
   if (st != SR_OK) return st;
   SR_HIP(g, e);
-  SR_HIP(g, hipGraphInstantiate(exec, *graph, nullptr, nullptr, 0));
-  return SR_OK;
-}
-
-sr_status ensure_graphs(sr_graph* g) {
-  if (g->exec1 && g->graph_rec_node == g->rec_node) return SR_OK;
-  drop_graphs(g);
-  sr_status st = capture(g, 1, &g->graph1, &g->exec1);
-  if (st != SR_OK) return st;
-  if (g->frames_per_graph > 1) {
-    st = capture(g, g->frames_per_graph, &g->graphN, &g->execN);
-    if (st != SR_OK) return st;
-  }
+  SR_HIP(g, hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0));
   g->graph_rec_node = g->rec_node;
   return SR_OK;
 }
 
-sr_status run_frames(sr_graph* g, int64_t frames) {
-  {
-    sr_status st = ensure_split_scratch(g);
-    if (st != SR_OK) return st;
+// `frames` frames from c.frame on.  ctx_set: the device context already holds c.
+sr_status run_frames(sr_graph* g, int64_t frames, SrCtx c, bool ctx_set) {
+  sr_status st = ensure_split_scratch(g);
+  if (st != SR_OK) return st;
+  const SrSplitScratch own{g->split_scratch, g->split_counters};
+  int64_t left = frames;
+  const bool flow = g->dataflow && !record_needs_copy(g);   // several frames are one launch anyway
+  // A replayed launch costs the host 1.5 us instead of up to 9 and starts later on the device: frames of one launch
+  // take longer replayed (16 streaming frames: 500 us for 486, CIFAR-shaped; 289 for 282, MNIST SR), of two or four
+  // too (453 for 417, MNIST SR hybrid; 1214 for 1140, DSR4 hybrid), and with eight (DSR4 sequential) the time is the
+  // same within 2 % while the host is busy for 209 us instead of 1222.
+  if (g->use_hipgraph && !flow && g->launches_per_frame > 4 && left >= g->frames_per_graph && g->frames_per_graph > 1) {
+    if ((st = ensure_graph(g)) != SR_OK) return st;
+    if (!ctx_set) SR_HIP(g, sr_launch_set_ctx(g->stream, g->ctx, c, 0));
+    for (; left >= g->frames_per_graph; left -= g->frames_per_graph) {
+      SR_HIP(g, hipGraphLaunch(g->exec, g->stream));
+      c.frame += g->frames_per_graph;
+    }
   }
-  if (!g->use_hipgraph) {
-    const SrSplitScratch own{g->split_scratch, g->split_counters};
-    if (g->dataflow && !record_needs_copy(g)) {
-      for (int64_t left = frames; left > 0;) {
-        const int n = (int)std::min<int64_t>(left, g->frames_per_graph);
-        sr_status st = enqueue_flow(g, n, true, own);
-        if (st != SR_OK) return st;
-        left -= n;
-      }
-    } else {
-      for (int64_t f = 0; f < frames; ++f) {
-        sr_status st = enqueue_frame(g, true, nullptr, own);
-        if (st != SR_OK) return st;
-      }
-    }
-  } else {
-    sr_status st = ensure_graphs(g);
+  while (left > 0) {
+    const int n = flow ? (int)std::min<int64_t>(left, g->frames_per_graph) : 1;
+    st = flow ? enqueue_flow(g, n, plain_frame(g, c), own) : enqueue_frame(g, true, nullptr, own, plain_frame(g, c));
     if (st != SR_OK) return st;
-    int64_t left = frames;
-    while (g->execN && left >= g->frames_per_graph) {
-      SR_HIP(g, hipGraphLaunch(g->execN, g->stream));
-      left -= g->frames_per_graph;
-    }
-    for (; left > 0; --left) SR_HIP(g, hipGraphLaunch(g->exec1, g->stream));
+    left -= n;
+    c.frame += n;
   }
   g->host_frame += frames;
   return SR_OK;
 }
 
-sr_status do_reset(sr_graph* g, const void* const* input_frame0) {
+// Frame 0, in one launch: states, completion counters, and the device context := c (frame 1).
+sr_status do_reset(sr_graph* g, const void* const* input_frame0, SrCtx c) {
   sr_status st = finalize(g);
   if (st != SR_OK) return st;
-  const int bf16 = g->dtype == SR_BF16;
-  for (int v = 0; v < g->n_nodes; ++v) {
-    NodeRt& n = g->nodes[v];
-    int slot = n.input_slot;
-    const void* src = (slot >= 0 && input_frame0) ? input_frame0[slot] : nullptr;
-    if (src)
-      SR_HIP(g, sr_launch_pack(g->stream, n.state[0], src, g->batch * n.d.height * n.d.width, n.d.channels, n.Cp, bf16, 0));
-    else
-      SR_HIP(g, sr_launch_fill_zero(g->stream, n.state[0], n.state_bytes));
-  }
-  if (g->done_counters)   // frames are counted from the reset: so are the nodes' completed work items
-    SR_HIP(g, sr_launch_fill_zero(g->stream, g->done_counters, (size_t)g->n_nodes * SR_DONE_STRIDE * sizeof(int32_t)));
-  SrCtx c{};
   c.frame = 1;
-  SR_HIP(g, sr_launch_set_ctx(g->stream, g->ctx, c, 1));
+  const void* frame0[SR_MAX_INPUTS] = {nullptr};
+  for (size_t i = 0; input_frame0 && i < g->inputs.size(); ++i) frame0[i] = input_frame0[i];
+  SR_HIP(g, sr_launch_reset(g->stream, g->ctx, c, g->reset_items, g->n_reset_items, g->n_reset_blocks, frame0, g->dtype == SR_BF16));
   g->host_frame = 0;
   g->was_reset = true;
   return SR_OK;
@@ -2063,7 +2056,7 @@ sr_status sr_graph_info(const sr_graph* g, int32_t* inference_factor, int32_t* l
 
 sr_status sr_reset(sr_graph* g, const void* const* input_frame0) {
   if (!g) return fail(nullptr, SR_ERR_ARG, "null graph");
-  return do_reset(g, input_frame0);
+  return do_reset(g, input_frame0, SrCtx{});
 }
 
 sr_status sr_frame_step(sr_graph* g, const void* const* inputs_t) {
@@ -2076,12 +2069,12 @@ sr_status sr_frame_step(sr_graph* g, const void* const* inputs_t) {
     c.in_stride[i] = 0;
   }
   c.out_ptr = nullptr;
-  c.in_last = (int32_t)(g->host_frame + 1);   // the frame computed now is the last one with input
+  c.frame = c.in_last = (int32_t)(g->host_frame + 1);   // the frame computed now is the last one with input
   {
     sr_status st = begin_frames(g, c);
     if (st != SR_OK) return st;
   }
-  return run_frames(g, 1);
+  return run_frames(g, 1, c, false);
 }
 
 sr_status sr_frame_step_static(sr_graph* g, const void* const* inputs_t) {
@@ -2102,7 +2095,7 @@ sr_status sr_frame_step_static(sr_graph* g, const void* const* inputs_t) {
     c.in_stride[i] = 0;
   }
   c.out_ptr = nullptr;
-  c.in_last = (int32_t)(g->host_frame + 1);
+  c.frame = c.in_last = (int32_t)(g->host_frame + 1);
   SrSplitScratch split{nullptr, nullptr};
   if (g->n_split_slots > 0) {
     void* base = nullptr;
@@ -2115,7 +2108,7 @@ sr_status sr_frame_step_static(sr_graph* g, const void* const* inputs_t) {
   }
   sr_status st = begin_frames(g, c);
   if (st != SR_OK) return st;
-  st = enqueue_frame(g, true, nullptr, split);   // plain launches: nothing is captured or instantiated
+  st = enqueue_frame(g, true, nullptr, split, plain_frame(g, c));   // plain launches: nothing is captured or instantiated
   if (st != SR_OK) return st;
   g->host_frame += 1;
   return SR_OK;
@@ -2129,29 +2122,26 @@ sr_status sr_rollout(sr_graph* g, const void* const* inputs, int32_t T, int32_t 
     if (!inputs[i]) return gfail(g, SR_ERR_ARG, "input " + std::to_string(i) + " is null");
     frame0[i] = inputs[i];
   }
-  sr_status st = do_reset(g, frame0);
-  if (st != SR_OK) return st;
   SrCtx c{};
   for (size_t i = 0; i < g->inputs.size(); ++i) {
     const sr_node_desc& d = g->nodes[g->inputs[i]].d;
     c.in_ptr[i] = inputs[i];
     c.in_stride[i] = (int64_t)g->batch * d.height * d.width * d.channels * (int64_t)elem_size(g);
   }
+  c.frame = 1;
   c.in_base = 0;    // frame t reads inputs[t]
   c.in_last = T;
   c.out_base = 1;   // frame t is recorded in slot t-1
-  {
-    sr_status st2 = set_record_node(g, outputs ? out_node : -1);
-    if (st2 != SR_OK) return st2;
-  }
   if (outputs) {
     const sr_node_desc& d = g->nodes[out_node].d;
     c.out_ptr = outputs;
     c.out_stride = (int64_t)g->batch * d.height * d.width * d.channels * (int64_t)elem_size(g);
   }
-  st = begin_frames(g, c);
+  sr_status st = do_reset(g, frame0, c);
   if (st != SR_OK) return st;
-  return run_frames(g, T);
+  if ((st = set_record_node(g, outputs ? out_node : -1)) != SR_OK) return st;
+  if ((st = begin_frames(g, c)) != SR_OK) return st;
+  return run_frames(g, T, c, true);
 }
 
 sr_status sr_get_state(const sr_graph* g, int32_t node, void* dst_device, size_t bytes) {
@@ -2190,13 +2180,13 @@ sr_status sr_frame_step_timed(sr_graph* g, const void* const* inputs_t, float* k
     if (!inputs_t[i]) return gfail(g, SR_ERR_ARG, "input " + std::to_string(i) + " is null");
     c.in_ptr[i] = inputs_t[i];
   }
-  c.in_last = (int32_t)(g->host_frame + 1);
+  c.frame = c.in_last = (int32_t)(g->host_frame + 1);
   sr_status st = begin_frames(g, c);
   if (st != SR_OK) return st;
   FrameTimer ft;
   st = ensure_split_scratch(g);
   if (st != SR_OK) return st;
-  st = enqueue_frame(g, false, &ft, SrSplitScratch{g->split_scratch, g->split_counters});
+  st = enqueue_frame(g, false, &ft, SrSplitScratch{g->split_scratch, g->split_counters}, plain_frame(g, c));
   hipError_t he = hipStreamSynchronize(g->stream);
   int n = 0;
   if (st == SR_OK && he == hipSuccess) {

@@ -25,6 +25,17 @@ struct SrCtx {
   int64_t out_stride;                 // bytes per recorded frame
 };
 
+// Which frame a launch computes and where the call's values are.  A launch that is recorded into a HIP graph takes them
+// from the context in device memory (frame = ctx->frame + offset: one recording of n frames serves every n frames of a
+// rollout, its last launch advancing the counter by n); a plain launch brings them along (here.frame > 0), which saves
+// the launch that writes the context and, in the kernel, the round trip to it.
+struct SrFrame {
+  SrCtx here;
+  SrCtx* ctx;
+  int32_t offset;
+  int32_t advance;    // > 0: the launch's last workgroup adds this to ctx->frame
+};
+
 // ---------------------------------------------------------------------------
 // Dependency-driven execution.  In a streaming rollout a node's update at frame t needs nothing but
 // its source nodes' states of frame t-1 (an edge with R(e) = 0: of frame t, computed at an earlier
@@ -269,20 +280,32 @@ struct SrAux {
   int32_t kind, a, b, c;
 };
 
+// frame 0: memory that sr_reset clears (input nodes: fills from the caller's frame 0, channel pitch C -> Cp)
+#define SR_RESET_BYTES 32768   // of one workgroup
+struct SrResetItem {
+  void* p;
+  int64_t bytes;
+  int32_t input_slot;          // -1: not an input node
+  int32_t px, C, Cp;
+  int32_t block0, pad_;        // first workgroup
+};
+
 // launch wrappers (sr_kernels.hip); each returns the hipError_t of the launch
-hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values, int set_frame);
-hipError_t sr_launch_tick(hipStream_t s, SrCtx* ctx);
+hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values, int clear);
+// also ctx := values
+hipError_t sr_launch_reset(hipStream_t s, SrCtx* ctx, const SrCtx& values, const SrResetItem* items, int n_items, int n_blocks,
+                           const void* const* frame0, int bf16);
+hipError_t sr_launch_tick(hipStream_t s, SrCtx* ctx, int frames);
 hipError_t sr_launch_fill_zero(hipStream_t s, void* p, size_t bytes);
 hipError_t sr_launch_pack(hipStream_t s, void* dst, const void* src, int px, int C, int Cp, int bf16, int unpack);
-hipError_t sr_launch_record_output(hipStream_t s, const SrCtx* ctx, const void* state0, const void* state1,
+hipError_t sr_launch_record_output(hipStream_t s, const SrFrame& f, const void* state0, const void* state1,
                                    int px, int C, int Cp, int bf16);
-hipError_t sr_launch_aux(hipStream_t s, SrCtx* ctx, const SrAux* aux, int n_aux, const SrHead* heads,
-                         const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int smem_bytes, int bf16,
-                         int is_last);
-hipError_t sr_launch_direct(hipStream_t s, SrCtx* ctx, const SrDirectNode* nodes, const SrDirectEdge* edges,
+hipError_t sr_launch_aux(hipStream_t s, const SrFrame& f, const SrAux* aux, int n_aux, const SrHead* heads,
+                         const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int smem_bytes, int bf16);
+hipError_t sr_launch_direct(hipStream_t s, const SrFrame& f, const SrDirectNode* nodes, const SrDirectEdge* edges,
                             const SrDirectBlock* blocks, int n_blocks, int bf16, int batch, const SrAux* aux, int n_aux,
                             const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
-                            int smem_bytes, int is_last);
+                            int smem_bytes);
 struct SrTables4 {   // 4-wave kernel: the graph's device tables
   const SrNode4* nodes;
   const SrPlane4* planes;
@@ -292,14 +315,14 @@ struct SrTables4 {   // 4-wave kernel: the graph's device tables
 };
 // frames > 1 or flow.deps != null: dependency-driven launch covering `frames` frames (grid y)
 // flow.order != null: one-dimensional launch of n_order workgroups (see SrFlow)
-hipError_t sr_launch_mfma(hipStream_t s, SrCtx* ctx, SrTables4 tables, SrFlow flow, int frames, int n_order,
+hipError_t sr_launch_mfma(hipStream_t s, const SrFrame& f, SrTables4 tables, SrFlow flow, int frames, int n_order,
                           const SrTile4* tiles, int n_tiles, int lds_bytes, const SrAux* aux, int n_aux,
                           const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
-                          int aux_smem_bytes, int is_last, SrSplitScratch split);
+                          int aux_smem_bytes, SrSplitScratch split);
 int sr_mfma_max_lds_bytes();
-hipError_t sr_launch_mfma8(hipStream_t s, SrCtx* ctx, const SrMfmaNode* nodes, const SrMfmaEdge* edges,
+hipError_t sr_launch_mfma8(hipStream_t s, const SrFrame& f, const SrMfmaNode* nodes, const SrMfmaEdge* edges,
                            const SrMfmaTile* tiles, int n_tiles, const SrAux* aux, int n_aux, const SrHead* heads,
-                           const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int aux_smem_bytes, int is_last,
+                           const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int aux_smem_bytes,
                            SrSplitScratch split);
 // The library's static scratch: a file-scope device array of SR_STATIC_SCRATCH_BYTES on every GPU the
 // library runs on, for the entry point that allocates nothing.  Returns its device address on the

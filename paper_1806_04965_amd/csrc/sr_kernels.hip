@@ -12,26 +12,55 @@
 // head kernels     global average pool + dense.
 // plus input staging, state packing, output recording and the frame counter.
 //
-// Every kernel takes the frame counter from SrCtx: the copy written at frame t is t & 1.
+// Every kernel takes the frame it computes from its SrFrame: the copy written at frame t is t & 1.
 #include <atomic>
 #include "sr_device.h"
 
 // ---------------------------------------------------------------------------
 // bookkeeping kernels
 // ---------------------------------------------------------------------------
-__global__ void sr_set_ctx_kernel(SrCtx* ctx, SrCtx v, int set_frame) {
+__global__ void sr_set_ctx_kernel(SrCtx* ctx, SrCtx v, int clear) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    const int frame = ctx->frame, timeouts = ctx->dep_timeouts;
+    if (!clear) v.dep_timeouts = ctx->dep_timeouts;   // counted since the last reset
     *ctx = v;
-    if (!set_frame) {   // a reset clears both; any other call keeps them
-      ctx->frame = frame;
-      ctx->dep_timeouts = timeouts;
-    }
   }
 }
 
-__global__ void sr_tick_kernel(SrCtx* ctx) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) ctx->frame = ctx->frame + 1;
+__global__ void sr_tick_kernel(SrCtx* ctx, int frames) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) ctx->frame = ctx->frame + frames;
+}
+
+// Frame 0 of all nodes, and the device context, in one launch.
+struct SrFrame0 { const void* in[SR_MAX_INPUTS]; };
+template <typename T>
+__global__ __launch_bounds__(256) void sr_reset_kernel(SrCtx* ctx, SrCtx values, const SrResetItem* __restrict__ items, int n_items,
+                                                       SrFrame0 frame0) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ctx = values;
+  int k = 0;   // the item this workgroup belongs to
+  for (int base = 0; base < n_items; base += 64) {
+    const int q = base + (threadIdx.x & 63);
+    const int b0 = q < n_items ? items[q].block0 : 0x7fffffff;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= (int)blockIdx.x);
+    k += __popcll(m);
+    if (m != ~0ull) break;
+  }
+  const SrResetItem it = items[k - 1];
+  const int64_t begin = (int64_t)(blockIdx.x - it.block0) * SR_RESET_BYTES;
+  const int64_t end = begin + SR_RESET_BYTES < it.bytes ? begin + SR_RESET_BYTES : it.bytes;
+  const void* src = nullptr;
+  for (int i = 0; i < SR_MAX_INPUTS; ++i)
+    if (i == it.input_slot) src = frame0.in[i];
+  if (src == nullptr) {
+    const int64_t whole = begin + (end - begin) / 16 * 16;
+    for (int64_t o = begin + threadIdx.x * 16; o < whole; o += 4096) *(uint4*)((char*)it.p + o) = make_uint4(0, 0, 0, 0);
+    for (int64_t o = whole + threadIdx.x; o < end; o += 256) ((char*)it.p)[o] = 0;
+    return;
+  }
+  for (int64_t i = begin / (int64_t)sizeof(T) + threadIdx.x; i < end / (int64_t)sizeof(T); i += 256) {
+    const int64_t p = i / it.Cp;
+    const int c = (int)(i - p * it.Cp);
+    ((T*)it.p)[i] = c < it.C ? ((const T*)src)[p * it.C + c] : (T)0;
+  }
 }
 
 __global__ void sr_fill_zero_kernel(uint4* p, size_t n16, unsigned char* tail, size_t ntail) {
@@ -57,11 +86,12 @@ __global__ void sr_pack_kernel(T* __restrict__ dst, const T* __restrict__ src, i
 }
 
 template <typename T>
-__global__ void sr_record_output_kernel(const SrCtx* __restrict__ ctx, const T* s0, const T* s1, int px, int C, int Cp) {
-  char* base = (char*)ctx->out_ptr;
+__global__ void sr_record_output_kernel(SrFrame f, const T* s0, const T* s1, int px, int C, int Cp) {
+  const sr_call_t call = sr_call(f);
+  char* base = (char*)(unsigned long long)call->out_ptr;
   if (base == nullptr) return;
-  const int frame = ctx->frame;
-  T* dst = (T*)(base + (int64_t)(frame - ctx->out_base) * ctx->out_stride);
+  const int frame = call->frame + f.offset;
+  T* dst = (T*)(base + (int64_t)(frame - call->out_base) * call->out_stride);
   const T* src = (frame & 1) ? s1 : s0;
   const int total = px * C;
   for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += gridDim.x * blockDim.x) {
@@ -74,9 +104,9 @@ __global__ void sr_record_output_kernel(const SrCtx* __restrict__ ctx, const T* 
 // direct path
 // ---------------------------------------------------------------------------
 template <typename T>
-__device__ __forceinline__ void sr_direct_block(const SrCtx* __restrict__ ctx, const SrDirectNode& nd,
+__device__ __forceinline__ void sr_direct_block(int frame, const SrDirectNode& nd,
                                                 const SrDirectEdge* __restrict__ edges, int first, int batch) {
-  const int cur = ctx->frame & 1;
+  const int cur = frame & 1;
   const int idx = first + threadIdx.x;
   const int HW = nd.H * nd.W;
   if (idx >= batch * HW * nd.C) return;
@@ -130,23 +160,24 @@ __device__ __forceinline__ void sr_direct_block(const SrCtx* __restrict__ ctx, c
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void sr_direct_kernel(SrCtx* __restrict__ ctx, const SrDirectNode* __restrict__ nodes,
+__global__ __launch_bounds__(256) void sr_direct_kernel(SrFrame f, const SrDirectNode* __restrict__ nodes,
                                                         const SrDirectEdge* __restrict__ edges,
                                                         const SrDirectBlock* __restrict__ blocks, int n_blocks,
                                                         int batch, const SrAux* __restrict__ aux,
                                                         const SrHead* __restrict__ heads,
                                                         const SrHeadEdge* __restrict__ head_edges,
-                                                        const SrStageNode* __restrict__ stage_nodes, int vec_floats,
-                                                        int is_last) {
+                                                        const SrStageNode* __restrict__ stage_nodes, int vec_floats) {
   extern __shared__ float sr_aux_smem[];
+  const sr_call_t call = sr_call(f);
+  const int frame = call->frame + f.offset;
   if ((int)blockIdx.x < n_blocks) {
     const SrDirectBlock blk = blocks[blockIdx.x];
-    sr_direct_block<T>(ctx, nodes[blk.node], edges, blk.first, batch);
+    sr_direct_block<T>(frame, nodes[blk.node], edges, blk.first, batch);
   } else {
-    sr_aux_item<T>(ctx, aux[blockIdx.x - n_blocks], heads, head_edges, stage_nodes, sr_aux_smem, vec_floats, ctx->frame,
+    sr_aux_item<T>(f.ctx, call, aux[blockIdx.x - n_blocks], heads, head_edges, stage_nodes, sr_aux_smem, vec_floats, frame,
                    SrFlow{nullptr, nullptr, 0, 0, nullptr});
   }
-  if (is_last) sr_block_done(ctx, gridDim.x, 1);
+  sr_block_done(f, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -610,33 +641,35 @@ __device__ __forceinline__ void sr_mfma_tile(SrCtx* __restrict__ ctx, const SrTa
   sr_signal_done(flow, nv[15]);
 }
 
-__global__ __launch_bounds__(256, 2) void sr_mfma_kernel(SrCtx* __restrict__ ctx, SrTables4 tb, SrFlow flow,
+__global__ __launch_bounds__(256, 2) void sr_mfma_kernel(SrFrame f, SrTables4 tb, SrFlow flow,
                                                          const SrTile4* __restrict__ tiles, int n_tiles,
                                                          const SrAux* __restrict__ aux, int n_aux, int aux_at,
                                                          const SrHead* __restrict__ heads,
                                                          const SrHeadEdge* __restrict__ head_edges,
                                                          const SrStageNode* __restrict__ stage_nodes, int vec_floats,
-                                                         int is_last, SrSplitScratch split) {
+                                                         SrSplitScratch split) {
+  SrCtx* const ctx = f.ctx;
+  const sr_call_t call = sr_call(f);
   extern __shared__ __align__(16) unsigned char sr_lds[];
   // work list: tiles in decreasing cost; the auxiliary items are spliced in at position aux_at so
   // that neither the longest tiles start late nor the launch ends on an auxiliary item
   // A launch covers gridDim.y frames (more than one only when dependency-driven); the hardware hands
   // workgroups out in the order x, then y: frame by frame.
-  int item = blockIdx.x, frame = ctx->frame + (int)blockIdx.y;
-  int n_blocks = gridDim.x * gridDim.y, n_frames = gridDim.y;
+  const int frame0 = call->frame + f.offset;
+  int item = blockIdx.x, frame = frame0 + (int)blockIdx.y;
+  int n_blocks = gridDim.x * gridDim.y;
   if (flow.order) {
     const int e = ((const __attribute__((address_space(4))) int*)(unsigned long long)flow.order)[blockIdx.x];
     item = e & 0xffffff;
-    frame = ctx->frame + (int)((unsigned)e >> 24);
+    frame = frame0 + (int)((unsigned)e >> 24);
     n_blocks = gridDim.x;
-    n_frames = flow.frames;
   }
   const bool is_aux = item >= aux_at && item < aux_at + n_aux;
   if (!is_aux) {
     const SrTileK t = sr_load_tile(tiles, item < aux_at ? item : item - n_aux);
     if (t.node <= -2) {
       // an auxiliary item placed in the list itself (dependency-driven launches order all items of a frame)
-      sr_aux_item<uint16_t>(ctx, aux[-2 - t.node], heads, head_edges, stage_nodes, (float*)sr_lds, vec_floats, frame, flow);
+      sr_aux_item<uint16_t>(ctx, call, aux[-2 - t.node], heads, head_edges, stage_nodes, (float*)sr_lds, vec_floats, frame, flow);
     } else if (t.node < 0) {
       // empty slot
     } else if (t.wn_tiles == 2)
@@ -644,9 +677,9 @@ __global__ __launch_bounds__(256, 2) void sr_mfma_kernel(SrCtx* __restrict__ ctx
     else
       sr_mfma_tile<1>(ctx, tb, t, sr_lds, split, frame, flow);
   } else {
-    sr_aux_item<uint16_t>(ctx, aux[item - aux_at], heads, head_edges, stage_nodes, (float*)sr_lds, vec_floats, frame, flow);
+    sr_aux_item<uint16_t>(ctx, call, aux[item - aux_at], heads, head_edges, stage_nodes, (float*)sr_lds, vec_floats, frame, flow);
   }
-  if (is_last) sr_block_done(ctx, n_blocks, n_frames);
+  sr_block_done(f, n_blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -769,7 +802,7 @@ __device__ __forceinline__ void sr8_step(const unsigned char* rd, const int (&ab
 }
 
 template <int WN>
-__device__ __forceinline__ void sr_mfma8_tile(const SrCtx* __restrict__ ctx, const SrMfmaNode* __restrict__ nodes,
+__device__ __forceinline__ void sr_mfma8_tile(int frame, const SrMfmaNode* __restrict__ nodes,
                                               const SrMfmaEdge* __restrict__ edges, int node_index, int tile_m0,
                                               int tile_n0, int plan_begin, int stage_begin, int stage_end,
                                               int split_slot, int part_info, unsigned char* lds,
@@ -782,7 +815,7 @@ __device__ __forceinline__ void sr_mfma8_tile(const SrCtx* __restrict__ ctx, con
   const int waves_n = nd->waves_n;
   const int wm = (waves_n == 4) ? (wave >> 2) : (waves_n == 2 ? (wave >> 1) : wave);
   const int wn = wave - wm * waves_n;
-  const int cur = ctx->frame & 1;
+  const int cur = frame & 1;
   const int M = nd->M, Wo = nd->Wo, HoWo = nd->Ho * Wo;
   const int BM = 128 * nd->waves_m;
   const int m_first = tile_m0;
@@ -972,24 +1005,26 @@ __device__ __forceinline__ void sr_mfma8_tile(const SrCtx* __restrict__ ctx, con
   }
 }
 
-__global__ __launch_bounds__(512) void sr_mfma8_kernel(SrCtx* __restrict__ ctx, const SrMfmaNode* __restrict__ nodes,
+__global__ __launch_bounds__(512) void sr_mfma8_kernel(SrFrame f, const SrMfmaNode* __restrict__ nodes,
                                                        const SrMfmaEdge* __restrict__ edges,
                                                        const SrMfmaTile* __restrict__ tiles, int n_tiles,
                                                        const SrAux* __restrict__ aux, int n_aux, int aux_at,
                                                        const SrHead* __restrict__ heads,
                                                        const SrHeadEdge* __restrict__ head_edges,
                                                        const SrStageNode* __restrict__ stage_nodes, int vec_floats,
-                                                       int is_last, SrSplitScratch split) {
+                                                       SrSplitScratch split) {
   extern __shared__ __align__(16) unsigned char sr_lds8[];
+  const sr_call_t call = sr_call(f);
+  const int frame = call->frame + f.offset;
   // work list as in the 4-wave kernel: the auxiliary items are spliced in at position aux_at.  An
   // auxiliary item is written for 256 threads: the upper four waves of the workgroup leave (a
   // barrier only waits for the waves that are still there).
   const int item = blockIdx.x;
   if (item >= aux_at && item < aux_at + n_aux) {
     if (threadIdx.x >= SR_AUX_THREADS) return;
-    sr_aux_item<uint16_t>(ctx, aux[item - aux_at], heads, head_edges, stage_nodes, (float*)sr_lds8, vec_floats, ctx->frame,
+    sr_aux_item<uint16_t>(f.ctx, call, aux[item - aux_at], heads, head_edges, stage_nodes, (float*)sr_lds8, vec_floats, frame,
                           SrFlow{nullptr, nullptr, 0, 0, nullptr});
-    if (is_last) sr_block_done(ctx, gridDim.x, 1);
+    sr_block_done(f, gridDim.x);
     return;
   }
   const SrMfmaTile t = tiles[item < aux_at ? item : item - n_aux];
@@ -997,14 +1032,14 @@ __global__ __launch_bounds__(512) void sr_mfma8_kernel(SrCtx* __restrict__ ctx, 
   if (node_index < 0) {
     // empty slot
   } else if (nodes[node_index].wn_tiles == 2)
-    sr_mfma8_tile<2>(ctx, nodes, edges, node_index, SR_UNIFORM(t.m0), SR_UNIFORM(t.n0), SR_UNIFORM(t.plan_begin),
+    sr_mfma8_tile<2>(frame, nodes, edges, node_index, SR_UNIFORM(t.m0), SR_UNIFORM(t.n0), SR_UNIFORM(t.plan_begin),
                      SR_UNIFORM(t.stage_begin), SR_UNIFORM(t.stage_end), SR_UNIFORM(t.split_slot), SR_UNIFORM(t.part),
                      sr_lds8, split);
   else
-    sr_mfma8_tile<1>(ctx, nodes, edges, node_index, SR_UNIFORM(t.m0), SR_UNIFORM(t.n0), SR_UNIFORM(t.plan_begin),
+    sr_mfma8_tile<1>(frame, nodes, edges, node_index, SR_UNIFORM(t.m0), SR_UNIFORM(t.n0), SR_UNIFORM(t.plan_begin),
                      SR_UNIFORM(t.stage_begin), SR_UNIFORM(t.stage_end), SR_UNIFORM(t.split_slot), SR_UNIFORM(t.part),
                      sr_lds8, split);
-  if (is_last) sr_block_done(ctx, gridDim.x, 1);
+  sr_block_done(f, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1017,13 +1052,22 @@ static inline int blocks_for(long long n, int per) {
   return (int)b;
 }
 
-hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values, int set_frame) {
-  hipLaunchKernelGGL(sr_set_ctx_kernel, dim3(1), dim3(64), 0, s, ctx, values, set_frame);
+hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values, int clear) {
+  hipLaunchKernelGGL(sr_set_ctx_kernel, dim3(1), dim3(64), 0, s, ctx, values, clear);
   return hipGetLastError();
 }
 
-hipError_t sr_launch_tick(hipStream_t s, SrCtx* ctx) {
-  hipLaunchKernelGGL(sr_tick_kernel, dim3(1), dim3(64), 0, s, ctx);
+hipError_t sr_launch_reset(hipStream_t s, SrCtx* ctx, const SrCtx& values, const SrResetItem* items, int n_items, int n_blocks,
+                           const void* const* frame0, int bf16) {
+  SrFrame0 f;
+  for (int i = 0; i < SR_MAX_INPUTS; ++i) f.in[i] = frame0[i];
+  if (bf16) hipLaunchKernelGGL(sr_reset_kernel<uint16_t>, dim3(n_blocks), dim3(256), 0, s, ctx, values, items, n_items, f);
+  else hipLaunchKernelGGL(sr_reset_kernel<float>, dim3(n_blocks), dim3(256), 0, s, ctx, values, items, n_items, f);
+  return hipGetLastError();
+}
+
+hipError_t sr_launch_tick(hipStream_t s, SrCtx* ctx, int frames) {
+  hipLaunchKernelGGL(sr_tick_kernel, dim3(1), dim3(64), 0, s, ctx, frames);
   return hipGetLastError();
 }
 
@@ -1038,25 +1082,25 @@ hipError_t sr_launch_fill_zero(hipStream_t s, void* p, size_t bytes) {
 }
 
 template <typename T>
-__global__ void sr_aux_kernel(SrCtx* __restrict__ ctx, const SrAux* __restrict__ aux, const SrHead* __restrict__ heads,
+__global__ void sr_aux_kernel(SrFrame f, const SrAux* __restrict__ aux, const SrHead* __restrict__ heads,
                               const SrHeadEdge* __restrict__ head_edges, const SrStageNode* __restrict__ stage_nodes,
-                              int vec_floats, int is_last) {
+                              int vec_floats) {
   extern __shared__ float sr_aux_smem2[];
-  sr_aux_item<T>(ctx, aux[blockIdx.x], heads, head_edges, stage_nodes, sr_aux_smem2, vec_floats, ctx->frame,
+  const sr_call_t call = sr_call(f);
+  sr_aux_item<T>(f.ctx, call, aux[blockIdx.x], heads, head_edges, stage_nodes, sr_aux_smem2, vec_floats, call->frame + f.offset,
                  SrFlow{nullptr, nullptr, 0, 0, nullptr});
-  if (is_last) sr_block_done(ctx, gridDim.x, 1);
+  sr_block_done(f, gridDim.x);
 }
 
 // smem_bytes of the aux items: vector floats + 16 bytes + 4 KiB of partial outputs
 static inline int sr_vec_floats(int smem_bytes) { return (smem_bytes - 16 - 4096) / 4; }
 
-hipError_t sr_launch_aux(hipStream_t s, SrCtx* ctx, const SrAux* aux, int n_aux, const SrHead* heads,
-                         const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int smem_bytes, int bf16,
-                         int is_last) {
+hipError_t sr_launch_aux(hipStream_t s, const SrFrame& f, const SrAux* aux, int n_aux, const SrHead* heads,
+                         const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int smem_bytes, int bf16) {
   if (n_aux == 0) return hipSuccess;
   const int vf = sr_vec_floats(smem_bytes);
-  if (bf16) hipLaunchKernelGGL(sr_aux_kernel<uint16_t>, dim3(n_aux), dim3(256), smem_bytes, s, ctx, aux, heads, head_edges, stage_nodes, vf, is_last);
-  else hipLaunchKernelGGL(sr_aux_kernel<float>, dim3(n_aux), dim3(256), smem_bytes, s, ctx, aux, heads, head_edges, stage_nodes, vf, is_last);
+  if (bf16) hipLaunchKernelGGL(sr_aux_kernel<uint16_t>, dim3(n_aux), dim3(256), smem_bytes, s, f, aux, heads, head_edges, stage_nodes, vf);
+  else hipLaunchKernelGGL(sr_aux_kernel<float>, dim3(n_aux), dim3(256), smem_bytes, s, f, aux, heads, head_edges, stage_nodes, vf);
   return hipGetLastError();
 }
 
@@ -1070,24 +1114,24 @@ hipError_t sr_launch_pack(hipStream_t s, void* dst, const void* src, int px, int
   return hipGetLastError();
 }
 
-hipError_t sr_launch_record_output(hipStream_t s, const SrCtx* ctx, const void* state0, const void* state1,
+hipError_t sr_launch_record_output(hipStream_t s, const SrFrame& f, const void* state0, const void* state1,
                                    int px, int C, int Cp, int bf16) {
   long long total = (long long)px * C;
   int nb = blocks_for(total, 256 * 4);
   if (nb > 1024) nb = 1024;
-  if (bf16) hipLaunchKernelGGL(sr_record_output_kernel<uint16_t>, dim3(nb), dim3(256), 0, s, ctx, (const uint16_t*)state0, (const uint16_t*)state1, px, C, Cp);
-  else hipLaunchKernelGGL(sr_record_output_kernel<float>, dim3(nb), dim3(256), 0, s, ctx, (const float*)state0, (const float*)state1, px, C, Cp);
+  if (bf16) hipLaunchKernelGGL(sr_record_output_kernel<uint16_t>, dim3(nb), dim3(256), 0, s, f, (const uint16_t*)state0, (const uint16_t*)state1, px, C, Cp);
+  else hipLaunchKernelGGL(sr_record_output_kernel<float>, dim3(nb), dim3(256), 0, s, f, (const float*)state0, (const float*)state1, px, C, Cp);
   return hipGetLastError();
 }
 
-hipError_t sr_launch_direct(hipStream_t s, SrCtx* ctx, const SrDirectNode* nodes, const SrDirectEdge* edges,
+hipError_t sr_launch_direct(hipStream_t s, const SrFrame& f, const SrDirectNode* nodes, const SrDirectEdge* edges,
                             const SrDirectBlock* blocks, int n_blocks, int bf16, int batch, const SrAux* aux, int n_aux,
                             const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
-                            int smem_bytes, int is_last) {
+                            int smem_bytes) {
   if (n_blocks + n_aux == 0) return hipSuccess;
   const int vf = sr_vec_floats(smem_bytes);
-  if (bf16) hipLaunchKernelGGL(sr_direct_kernel<uint16_t>, dim3(n_blocks + n_aux), dim3(256), smem_bytes, s, ctx, nodes, edges, blocks, n_blocks, batch, aux, heads, head_edges, stage_nodes, vf, is_last);
-  else hipLaunchKernelGGL(sr_direct_kernel<float>, dim3(n_blocks + n_aux), dim3(256), smem_bytes, s, ctx, nodes, edges, blocks, n_blocks, batch, aux, heads, head_edges, stage_nodes, vf, is_last);
+  if (bf16) hipLaunchKernelGGL(sr_direct_kernel<uint16_t>, dim3(n_blocks + n_aux), dim3(256), smem_bytes, s, f, nodes, edges, blocks, n_blocks, batch, aux, heads, head_edges, stage_nodes, vf);
+  else hipLaunchKernelGGL(sr_direct_kernel<float>, dim3(n_blocks + n_aux), dim3(256), smem_bytes, s, f, nodes, edges, blocks, n_blocks, batch, aux, heads, head_edges, stage_nodes, vf);
   return hipGetLastError();
 }
 
@@ -1105,10 +1149,10 @@ static hipError_t sr_request_lds(const void* kernel, int bytes, int which) {
   return e;
 }
 
-hipError_t sr_launch_mfma(hipStream_t s, SrCtx* ctx, SrTables4 tables, SrFlow flow, int frames, int n_order,
+hipError_t sr_launch_mfma(hipStream_t s, const SrFrame& f, SrTables4 tables, SrFlow flow, int frames, int n_order,
                           const SrTile4* tiles,
                           int n_tiles, int lds_bytes, const SrAux* aux, int n_aux, const SrHead* heads,
-                          const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int aux_smem_bytes, int is_last,
+                          const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int aux_smem_bytes,
                           SrSplitScratch split) {
   if (n_tiles + n_aux == 0) return hipSuccess;
   {   // dynamic LDS above 64 KiB has to be requested once per device
@@ -1116,23 +1160,23 @@ hipError_t sr_launch_mfma(hipStream_t s, SrCtx* ctx, SrTables4 tables, SrFlow fl
     if (e != hipSuccess) return e;
   }
   const dim3 grid = flow.order ? dim3(n_order) : dim3(n_tiles + n_aux, frames);
-  hipLaunchKernelGGL(sr_mfma_kernel, grid, dim3(256), lds_bytes, s, ctx, tables, flow, tiles,
-                     n_tiles, aux, n_aux, n_tiles / 2, heads, head_edges, stage_nodes, sr_vec_floats(aux_smem_bytes), is_last,
+  hipLaunchKernelGGL(sr_mfma_kernel, grid, dim3(256), lds_bytes, s, f, tables, flow, tiles,
+                     n_tiles, aux, n_aux, n_tiles / 2, heads, head_edges, stage_nodes, sr_vec_floats(aux_smem_bytes),
                      split);
   return hipGetLastError();
 }
 
-hipError_t sr_launch_mfma8(hipStream_t s, SrCtx* ctx, const SrMfmaNode* nodes, const SrMfmaEdge* edges,
+hipError_t sr_launch_mfma8(hipStream_t s, const SrFrame& f, const SrMfmaNode* nodes, const SrMfmaEdge* edges,
                            const SrMfmaTile* tiles, int n_tiles, const SrAux* aux, int n_aux, const SrHead* heads,
-                           const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int aux_smem_bytes, int is_last,
+                           const SrHeadEdge* head_edges, const SrStageNode* stage_nodes, int aux_smem_bytes,
                            SrSplitScratch split) {
   if (n_tiles + n_aux == 0) return hipSuccess;
   {
     hipError_t e = sr_request_lds((const void*)sr_mfma8_kernel, 2 * SR8_BUF_BYTES, 1);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(sr_mfma8_kernel, dim3(n_tiles + n_aux), dim3(512), 2 * SR8_BUF_BYTES, s, ctx, nodes, edges, tiles, n_tiles,
-                     aux, n_aux, n_tiles / 2, heads, head_edges, stage_nodes, sr_vec_floats(aux_smem_bytes), is_last, split);
+  hipLaunchKernelGGL(sr_mfma8_kernel, dim3(n_tiles + n_aux), dim3(512), 2 * SR8_BUF_BYTES, s, f, nodes, edges, tiles, n_tiles,
+                     aux, n_aux, n_tiles / 2, heads, head_edges, stage_nodes, sr_vec_floats(aux_smem_bytes), split);
   return hipGetLastError();
 }
 

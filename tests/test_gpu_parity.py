@@ -1,6 +1,8 @@
 """GPU parity: the HIP library (through its C ABI) against the CPU oracle, element by element, on
 the same seeded inputs.  Tolerances: max-abs-rel <= 1e-4 for fp32 graphs (oracle in float64),
 <= 2e-2 for bf16 graphs (oracle emulating the bf16 storage points)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -131,6 +133,22 @@ def test_rollout_equals_frame_steps_and_hipgraph_equals_eager():
     ref = oracle_states(g, w, b, x, T, "bf16", nodes=[g.out_node])[g.out_node]
     for t in range(T):
         assert max_abs_rel(a[t], ref[t]) <= 2e-2
+
+
+@pytest.mark.parametrize("per_graph", [1, 2, 8])
+@pytest.mark.parametrize("T", [1, 8, 19])
+def test_recorded_frames_equal_plain_launches(per_graph, T):
+    # a sequential fp32 net of more than four launches a frame: recorded where per_graph > 1 frames fit, any remainder
+    # launched plainly; the same kernels on the same operands either way, so the same bits
+    g = dataclasses.replace(W.dsr_net(2, batch=1, frames=T), dtype="f32")
+    g = g.with_pattern(W.sequential_pattern(g))
+    w, b, x = W.make_case(g, seed=8, bias_scale=0.1, frames=T)
+    a, dev = gpu_rollout(g, w, b, x, T, options={0: 1, 2: per_graph}, return_dev=True)
+    assert dev.info()["launches_per_frame"] > 4
+    dev.close()
+    np.testing.assert_array_equal(a, gpu_rollout(g, w, b, x, T, options=OPT_EAGER))
+    steps, _, _ = gpu_states_by_steps(g, w, b, x, T, nodes=[g.out_node])
+    np.testing.assert_array_equal(a, np.stack(steps[g.out_node]))
 
 
 def test_checkpoint_restore_continues_bit_exactly():

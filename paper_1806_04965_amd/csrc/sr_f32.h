@@ -102,7 +102,21 @@ struct SrRun {
 };
 
 #define SR_F32_KS 16              // reduction indices per step
-#define SR_F32_STAGES 3           // steps of operands in LDS at a time
+// Variants of the tile kernels, by the shapes that a launch holds (bits 1 << shape):
+//   WIDE    some 128 x 128 tiles: 64 accumulator registers a lane (weight gradients: 128), 48 KiB of LDS, three workgroups per CU
+//   NARROW  none: at most 128 registers and 40 KiB of LDS, four workgroups per CU
+//   DEEP    32 x 32 tiles only: few workgroups and a chain of loads per wave, so three steps ahead instead of two
+// DSR2 window (B=64, W=8) with the weight gradients' tiles all narrow 1557 us, as planned 1575; GTSRB-shaped window without
+// 128 x 128 tiles 6640, with them 6150: the wide tiles stay where they are most of the work.  MNIST SR frame 17.5 -> 17 us (DEEP).
+enum { SR_F32_WIDE = 0, SR_F32_NARROW = 1, SR_F32_DEEP = 2 };
+inline int sr_f32_variant(int shapes) {
+  return shapes == 1 << SR_F32_SMALL ? SR_F32_DEEP : ((shapes >> SR_F32_128x128) & 1 ? SR_F32_WIDE : SR_F32_NARROW);
+}
+// steps of operands in LDS at a time (NARROW: two for the 32 x 32 tiles, whose four waves have LDS of their own)
+#define SR_F32_PAIRS 104   // four, in pairs
+SR_HD constexpr int sr_f32_stages(int variant, int shape) {
+  return shape == SR_F32_64x64 || shape == SR_F32_128x32 ? 4 : shape != SR_F32_SMALL || variant == SR_F32_WIDE ? 3 : (variant == SR_F32_DEEP ? 4 : 2);
+}
 
 // k-th group of four reduction indices of row `row` of an operand that lies in LDS row by row (64 bytes a row):
 // sixteen rows read together hit sixteen different 16-byte columns of the 256-byte LDS line
@@ -253,12 +267,12 @@ struct SrRmsBatch {
 };
 
 // frame path: the level's tiles and the auxiliary items in one launch
-hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
+hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs& a, int shapes, const SrAux* aux, int n_aux,
                                 const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
                                 int aux_smem_bytes);
 // training window
-hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int lds_bytes);
-hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int lds_bytes);
+hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int shapes);
+hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int shapes);
 // destination sums, and (loss != null) loss = scale * sum of the n_terms loss terms
 hipError_t sr_launch_grad_sum(hipStream_t s, const SrGradSum* sums, int n_sums, int n_blocks, const float* part, float* const* dst,
                               int accumulate, const float* terms, int n_terms, float scale, float* loss);
@@ -275,10 +289,16 @@ inline void sr_f32_shape(int shape, int* ti, int* tj) {
   *ti = t[shape][0];
   *tj = t[shape][1];
 }
-inline int sr_f32_lds_bytes(int shape) {
-  int ti, tj;
-  sr_f32_shape(shape, &ti, &tj);
-  return SR_F32_STAGES * (ti + tj) * SR_F32_KS * 4 * (shape == SR_F32_SMALL ? 4 : 1);
+inline int sr_f32_lds_bytes(int shapes) {   // of a workgroup of a launch with these shapes
+  int most = 0;
+  for (int shape = 0; shape < 5; ++shape) {
+    if (!((shapes >> shape) & 1)) continue;
+    int ti, tj;
+    sr_f32_shape(shape, &ti, &tj);
+    const int bytes = sr_f32_stages(sr_f32_variant(shapes), shape) * (ti + tj) * SR_F32_KS * 4 * (shape == SR_F32_SMALL ? 4 : 1);
+    if (bytes > most) most = bytes;
+  }
+  return most;
 }
 struct sr_graph;
 struct SrRowPlan {
@@ -305,7 +325,7 @@ int sr_rows_backward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds& i
 // multiple of 8 with empty tiles).  work_cycles: compute-unit cycles of the whole launch if it covers more than
 // these phases (0: just these).  tall_from: SR_OPT_TRAIN_TALL_TILES_FROM; split: SR_OPT_K_SPLIT.
 void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split,
-                   int* split_slots, std::vector<SrRowTile>* out, int* lds_bytes);
+                   int* split_slots, std::vector<SrRowTile>* out, int* shapes);
 double sr_rows_work(const SrRowPlan& p, int phase);   // compute-unit cycles of a phase at the fp32 matrix rate
 // Weight and bias gradients of the frames lo..hi of a window of W frames: descriptors, tiles, partial sums.  Destination
 // pointers: edge e is e, node v's bias n_edges + v.  first: the first chunk of the window that is worked on (it
@@ -315,7 +335,7 @@ struct SrGradPlan {
   std::vector<SrGradBias> biases;
   std::vector<SrGradTile> tiles;
   std::vector<SrGradSum> sums;
-  int sum_blocks = 0, lds = 0;
+  int sum_blocks = 0, shapes = 0;
   long long part_floats = 0;
 };
 void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from);

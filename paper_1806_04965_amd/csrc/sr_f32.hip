@@ -3,13 +3,19 @@
 //
 // A workgroup of four waves owns a TI x TJ tile and walks its reduction in steps of 16 indices.  The operands of a
 // step are brought into LDS by direct-to-LDS loads whose lane addresses do the gathering (taps, strides, padding;
-// elements that do not exist are read from a line of zeros), two steps ahead of the one being multiplied: one barrier
-// per step, no registers between global memory and LDS.  fp32 matrix instructions are slow (a 32x32x2 product takes
-// 64 cycles of its SIMD), so a step's operand traffic (at most 16 bytes per cycle and CU) and address arithmetic hide
-// behind them; what bounds a tile is the fp32 matrix rate, 157 TFLOP/s, once the launch fills the chip.
+// elements that do not exist are read from a line of zeros), ahead of the step being multiplied: no registers between
+// global memory and LDS.  fp32 matrix instructions are slow (a 32x32x2 product takes 64 cycles of its SIMD); a step's
+// operand traffic (at most 16 bytes per cycle and CU) hides behind them.  What bounds a tile is the fp32 matrix rate, 157
+// TFLOP/s, for 128 x 128 tiles, whose waves have 32 products a step (GTSRB-shaped launches: matrix cores 78 % busy).
+// 64 x 64 and 128 x 32 tiles have 8: there the step's fixed costs (some 70 vector and 120 scalar instructions, a barrier, a
+// wait) take longer than its products (matrix cores 47 % busy with three workgroups per CU).  So these fetch steps in
+// pairs, a barrier per pair and, where a pair lies in one tap, one set of addresses; and launches without 128 x 128 tiles
+// run four workgroups per CU (see the variants in sr_f32.h).
 //
 // Measured, DSR2 as an fp32 graph (batch 64, 6.4 GFLOP per frame): 1350 us per frame with a thread per output (weights
-// and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s); MNIST SR, batch 128: 29 -> 15 us.
+// and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s), 100 with pairs; MNIST SR, batch 128:
+// 29 -> 15 us.  Training windows, step by step -> pairs and variants: DSR2 B=64 W=8 1674 -> 1498 us, GTSRB-shaped
+// B=128 W=4 6270 -> 5970, MNIST SR 317 -> 302.
 //
 // Every sum has a fixed order (reduction index by index within a part, parts in order, waves in order): the same call
 // gives the same bits.
@@ -28,7 +34,7 @@ __device__ __forceinline__ const char* sr_uni_ptr(const char* p) {
   return (const char*)(((unsigned long long)(unsigned)SR_UNI((int)(v >> 32)) << 32) | (unsigned)SR_UNI((int)v));
 }
 
-__device__ __align__(64) const float sr_zero_line[16] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+__device__ __align__(128) const float sr_zero_line[32] = {};   // a lane reads 16 bytes of it, or 64 bytes further on (second step of a pair)
 
 // One direct-to-LDS load: lane l's 16 (4) bytes go to lds + 16 l (4 l).
 __device__ __forceinline__ void sr_to_lds16(const char* g, unsigned lds) {
@@ -130,7 +136,13 @@ struct SrRowOperands {
     }
   }
 
-  // loads of the 16 reduction indices from r0 on, into LDS at `at`
+  // may the steps at r0 and r0 + 16 share their addresses (one tap, 16-byte loads)?  stop: end of the segment's share
+  __device__ __forceinline__ bool pairs(int r0, int stop) const {
+    return quads && (g.GC & 31) == 0 && (r0 & 31) == 0 && r0 + SR_F32_KS < stop && (BACK || quads_w);
+  }
+
+  // loads of the 16 reduction indices from r0 on, into LDS at `at`; PAIR: and of the next 16, into the stage behind it
+  template <bool PAIR = false>
   __device__ __forceinline__ void issue(int r0, unsigned at) {
     const char* zero = (const char*)sr_zero_line;
     const unsigned bt = at + TI * 64;
@@ -148,6 +160,7 @@ struct SrRowOperands {
       for (int n = 0; n < NA; ++n) {
         const char* p = sr_gather_ok(g, row[n], t) ? sr_at(src, row[n].off + toff) : zero;
         sr_to_lds16(p, at + (n * NW + wv) * 1024);
+        if (PAIR) sr_to_lds16(p + 64, at + STAGE + (n * NW + wv) * 1024);
       }
       if (BACK) {
         // (a half-filled wave's rows start at a multiple of eight: its pieces are permuted differently from A's)
@@ -159,9 +172,13 @@ struct SrRowOperands {
           const int j = j0 + (HALF_B ? wv * 8 + (lane >> 2) : n * 16 * NW + wv * 16 + (lane >> 2));
           const char* p = (r_ok && j < g.ldw) ? sr_at((const char*)g.w, woff + (uint32_t)j * (uint32_t)g.GC) : zero;
           if (HALF_B) {
-            if (lane < 32) sr_to_lds16(p, bt + wv * 512);
+            if (lane < 32) {
+              sr_to_lds16(p, bt + wv * 512);
+              if (PAIR) sr_to_lds16(p + 64, bt + STAGE + wv * 512);
+            }
           } else {
             sr_to_lds16(p, bt + (n * NW + wv) * 1024);
+            if (PAIR) sr_to_lds16(p + 64, bt + STAGE + (n * NW + wv) * 1024);
           }
         }
         return;
@@ -194,11 +211,17 @@ struct SrRowOperands {
       for (int n = 0; n < NB; ++n) {
         const int id = HALF_B ? wv * 32 + lane : (n * NW + wv) * 64 + lane;
         const int r = r0 + id / (TJ / 4), j = j0 + 4 * (id % (TJ / 4));
-        const char* p = (r < g.R && j < g.ldw) ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
+        const bool ok = r < g.R && j < g.ldw;
+        const char* p = ok ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
+        const char* p2 = PAIR ? p + (ok ? (uint32_t)g.ldw * (4 * SR_F32_KS) : 0u) : nullptr;
         if (HALF_B) {
-          if (lane < 32) sr_to_lds16(p, bt + wv * 512);
+          if (lane < 32) {
+            sr_to_lds16(p, bt + wv * 512);
+            if (PAIR) sr_to_lds16(p2, bt + STAGE + wv * 512);
+          }
         } else {
           sr_to_lds16(p, bt + (n * NW + wv) * 1024);
+          if (PAIR) sr_to_lds16(p2, bt + STAGE + (n * NW + wv) * 1024);
         }
       }
     } else {
@@ -292,15 +315,16 @@ struct SrRecord { float* out; };
 
 // A row tile.  SMALL: every wave takes every fourth step of a 32 x 32 tile through LDS of its own (no barriers); the
 // four waves' sums are added in order at the end.
-template <int TI, int TJ, int WJN, bool BACK, bool SMALL>
+template <int TI, int TJ, int WJN, bool BACK, bool SMALL, int STAGES>
 __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p, int i0, int j0, int step_begin, int step_end,
                                             int split_slot, int part_info, const SrSlots& sl, float* record, int rec_node,
                                             unsigned char* lds) {
+  constexpr bool PAIRS = STAGES == SR_F32_PAIRS;
   constexpr int NW = SMALL ? 1 : 4, WIN = NW / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
   typedef SrRowOperands<TI, TJ, NW, BACK> Ops;
   const int tid = threadIdx.x, lane = tid & 63, wave = SR_UNI(tid >> 6);
   const int iw = (wave / WJN) * 32 * MI * (SMALL ? 0 : 1), jw = (wave % WJN) * 32 * MJ * (SMALL ? 0 : 1);
-  unsigned char* base = SMALL ? lds + wave * (SR_F32_STAGES * Ops::STAGE) : lds;
+  unsigned char* base = SMALL ? lds + wave * ((PAIRS ? 4 : STAGES) * Ops::STAGE) : lds;
   const unsigned at0 = sr_lds_at(base);
 
   Ops op;
@@ -341,16 +365,51 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
       op.issue(r, at0 + wr * Ops::STAGE);
       const unsigned bit = 1u << wr;
       rows = op.quads ? rows | bit : rows & ~bit;
-      wr = wr == SR_F32_STAGES - 1 ? 0 : wr + 1;
+      wr = wr == STAGES - 1 ? 0 : wr + 1;
       ++issued;
     };
     bool more = next();
-    for (int k = 0; k < SR_F32_STAGES - 1 && more; ++k) {
+    if constexpr (PAIRS) {
+      // two steps per barrier: a pair is fetched while the one before it is multiplied
+      auto issue_pair = [&](int to) -> int {
+        if (!more) return 0;
+        wr = to;
+        if (op.pairs(r, r_stop)) {
+          op.template issue<true>(r, at0 + wr * Ops::STAGE);
+          rows |= 3u << wr;
+          r += SR_F32_KS;
+          more = next();
+          return 2;
+        }
+        issue();
+        more = next();
+        if (!more) return 1;
+        wr = to + 1;
+        issue();
+        more = next();
+        return 2;
+      };
+      int cur = issue_pair(0);
+      while (cur > 0) {
+        sr_wait_loads<0>();
+        sr_step_barrier();   // everybody's loads of this pair; and the pair before has been read by all
+        const int following = issue_pair(rd ^ 2);
+        sr_step_products<TI, TJ, MI, MJ>(base + rd * Ops::STAGE, iw, jw, lane, (rows >> rd) & 1, BACK && ((rows >> rd) & 1), acc);
+        if (cur == 2)
+          sr_step_products<TI, TJ, MI, MJ>(base + (rd + 1) * Ops::STAGE, iw, jw, lane, (rows >> (rd + 1)) & 1,
+                                           BACK && ((rows >> (rd + 1)) & 1), acc);
+        rd ^= 2;
+        cur = following;
+      }
+      issued = 0;
+    }
+    for (int k = 0; k < STAGES - 1 && more; ++k) {
       issue();
       more = next();
     }
     while (done < issued) {
-      if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
+      if (STAGES > 3 && issued - done >= 3) sr_wait_loads<2 * Ops::LOADS>();
+      else if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
       else sr_wait_loads<0>();
       if (!SMALL) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
       if (more) {
@@ -358,7 +417,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
         more = next();
       }
       sr_step_products<TI, TJ, MI, MJ>(base + rd * Ops::STAGE, iw, jw, lane, (rows >> rd) & 1, BACK && ((rows >> rd) & 1), acc);
-      rd = rd == SR_F32_STAGES - 1 ? 0 : rd + 1;
+      rd = rd == STAGES - 1 ? 0 : rd + 1;
       ++done;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -467,23 +526,28 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
   }
 }
 
-template <bool BACK>
+template <bool BACK, int VARIANT>
 __device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowTile) t, int slot0, const SrSlots& sl, float* record,
                                             int rec_node, unsigned char* lds) {
   const int phase = t->phase;
   if (phase < 0) return;
   const SrPhase p = sr_load_phase(sr_k(A.phases) + phase);
   const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = slot0 + t->split_slot, part = t->part;
-  if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-  else if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-  else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-  else if (shape == SR_F32_128x32) sr_row_tile<128, 32, 1, BACK, false>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-  else sr_row_tile<32, 32, 1, BACK, true>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+  if constexpr (VARIANT != SR_F32_DEEP) {
+    if constexpr (VARIANT == SR_F32_WIDE)
+      if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, BACK, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, BACK, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, BACK, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    else if (shape == SR_F32_128x32) sr_row_tile<128, 32, 1, BACK, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+  }
+  if (shape == SR_F32_SMALL)
+    sr_row_tile<32, 32, 1, BACK, true, sr_f32_stages(VARIANT, SR_F32_SMALL)>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
 }
 
 }  // namespace
 
-__global__ __launch_bounds__(256, 2) void sr_rows_frame_kernel(SrFrame f, SrRowArgs A,
+template <int VARIANT>
+__global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows_frame_kernel(SrFrame f, SrRowArgs A,
                                                                const SrAux* __restrict__ aux, int n_aux, int aux_at,
                                                                const SrHead* __restrict__ heads,
                                                                const SrHeadEdge* __restrict__ head_edges,
@@ -500,16 +564,19 @@ __global__ __launch_bounds__(256, 2) void sr_rows_frame_kernel(SrFrame f, SrRowA
     const SrSlots sl{cur, cur ^ 1, cur, 0, 1 << 30};
     char* rec = A.rec_node >= 0 ? (char*)(unsigned long long)call->out_ptr : nullptr;
     if (rec) rec += (int64_t)(frame - call->out_base) * call->out_stride;
-    sr_row_item<false>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), 0, sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
+    sr_row_item<false, VARIANT>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), 0, sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
   }
   sr_block_done(f, gridDim.x);
 }
 
-hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs& a, int lds_bytes, const SrAux* aux, int n_aux,
+hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs& a, int shapes, const SrAux* aux, int n_aux,
                                 const SrHead* heads, const SrHeadEdge* head_edges, const SrStageNode* stage_nodes,
                                 int aux_smem_bytes) {
   if (a.n_tiles + n_aux == 0) return hipSuccess;
-  hipLaunchKernelGGL(sr_rows_frame_kernel, dim3(a.n_tiles + n_aux), dim3(256), lds_bytes, s, f, a, aux, n_aux, a.n_tiles / 2, heads,
+  const int variant = sr_f32_variant(shapes), tile_lds = sr_f32_lds_bytes(shapes);
+  const auto kernel = variant == SR_F32_WIDE ? sr_rows_frame_kernel<SR_F32_WIDE>
+                                             : (variant == SR_F32_NARROW ? sr_rows_frame_kernel<SR_F32_NARROW> : sr_rows_frame_kernel<SR_F32_DEEP>);
+  hipLaunchKernelGGL(kernel, dim3(a.n_tiles + n_aux), dim3(256), tile_lds > aux_smem_bytes ? tile_lds : aux_smem_bytes, s, f, a, aux, n_aux, a.n_tiles / 2, heads,
                      head_edges, stage_nodes, (aux_smem_bytes - 16 - 4096) / 4);
   return hipGetLastError();
 }
@@ -517,8 +584,8 @@ hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs
 // ---------------------------------------------------------------------------
 // training window
 // ---------------------------------------------------------------------------
-template <bool BACK>
-__global__ __launch_bounds__(256, 2) void sr_rows_train_kernel(SrRowArgs A) {
+template <bool BACK, int VARIANT>
+__global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows_train_kernel(SrRowArgs A) {
   extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
   // the run (tile list, frame) this workgroup belongs to: runs are in order of their first workgroup
   const int lane = threadIdx.x & 63;
@@ -544,7 +611,7 @@ __global__ __launch_bounds__(256, 2) void sr_rows_train_kernel(SrRowArgs A) {
     sl.left = frame;
   }
   sl.frame = frame;
-  sr_row_item<BACK>(A, sr_k(A.tiles) + run->tile0 + (blockIdx.x - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
+  sr_row_item<BACK, VARIANT>(A, sr_k(A.tiles) + run->tile0 + (blockIdx.x - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
 }
 
 namespace {
@@ -644,7 +711,7 @@ struct SrGradOperands {
 template <int TI, int TJ, int WJN>
 __device__ __forceinline__ void sr_grad_tile(const SrGradArgs& A, SR_CONST4(SrGradEdge) ek, int i0, int j0, int step_begin, int step_end,
                                              int slice, unsigned char* lds) {
-  constexpr int WIN = 4 / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
+  constexpr int WIN = 4 / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN), STAGES = 3;
   typedef SrGradOperands<TI, TJ> Ops;
   const int tid = threadIdx.x, lane = tid & 63, wv = SR_UNI(tid >> 6);
   const unsigned at0 = sr_lds_at(lds);
@@ -662,9 +729,9 @@ __device__ __forceinline__ void sr_grad_tile(const SrGradArgs& A, SR_CONST4(SrGr
       for (int v = 0; v < 16; ++v) acc[x][y][v] = sum[x][y][v] = 0.f;
   const int iw = (wv / WJN) * 32 * MI, jw = (wv % WJN) * 32 * MJ;
   int wr = 0, rd = 0, next = step_begin;
-  for (int k = 0; k < SR_F32_STAGES - 1 && next < step_end; ++k) {
+  for (int k = 0; k < STAGES - 1 && next < step_end; ++k) {
     op.issue(next++, at0 + wr * Ops::STAGE);
-    wr = wr == SR_F32_STAGES - 1 ? 0 : wr + 1;
+    wr = wr == STAGES - 1 ? 0 : wr + 1;
   }
   for (int s = step_begin; s < step_end; ++s) {
     if (s + 1 < step_end) sr_wait_loads<Ops::LOADS>();
@@ -672,10 +739,10 @@ __device__ __forceinline__ void sr_grad_tile(const SrGradArgs& A, SR_CONST4(SrGr
     sr_step_barrier();
     if (next < step_end) {
       op.issue(next++, at0 + wr * Ops::STAGE);
-      wr = wr == SR_F32_STAGES - 1 ? 0 : wr + 1;
+      wr = wr == STAGES - 1 ? 0 : wr + 1;
     }
     sr_step_products<TI, TJ, MI, MJ>(lds + rd * Ops::STAGE, iw, jw, lane, false, false, acc);
-    rd = rd == SR_F32_STAGES - 1 ? 0 : rd + 1;
+    rd = rd == STAGES - 1 ? 0 : rd + 1;
     if (((s - step_begin) & 127) == 127) {
 #pragma unroll
       for (int x = 0; x < MI; ++x)
@@ -739,7 +806,9 @@ __device__ __forceinline__ void sr_grad_bias(const SrGradArgs& A, SR_CONST4(SrGr
 
 }  // namespace
 
-__global__ __launch_bounds__(256, 2) void sr_grad_kernel(SrGradArgs A) {
+// (WIDE: 168 registers and three workgroups per CU, four of them spilled, beat 172 and two: 1900 -> 1800 us, GTSRB-shaped window)
+template <int VARIANT>
+__global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 3) void sr_grad_kernel(SrGradArgs A) {
   extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
   SR_CONST4(SrGradTile) t = sr_k(A.tiles) + blockIdx.x;
   const int kind = t->kind, shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slice = t->slice;
@@ -748,10 +817,11 @@ __global__ __launch_bounds__(256, 2) void sr_grad_kernel(SrGradArgs A) {
     return;
   }
   SR_CONST4(SrGradEdge) e = sr_k(A.edges) + t->edge;
-  if (shape == SR_F32_128x128) sr_grad_tile<128, 128, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
-  else if (shape == SR_F32_128x64) sr_grad_tile<128, 64, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
+  if constexpr (VARIANT == SR_F32_WIDE)
+    if (shape == SR_F32_128x128) sr_grad_tile<128, 128, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
+  if (shape == SR_F32_128x64) sr_grad_tile<128, 64, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
   else if (shape == SR_F32_64x64) sr_grad_tile<64, 64, 2>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
-  else sr_grad_tile<128, 32, 1>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
+  else if (shape == SR_F32_128x32) sr_grad_tile<128, 32, 1>(A, e, i0, j0, sb, se, slice, sr_rows_lds);
 }
 
 // The partial sums of gradients cut into slices, added in slice order: a workgroup takes 64 elements, four slice lanes
@@ -884,16 +954,20 @@ __global__ __launch_bounds__(256) void sr_rmsprop_kernel(SrRmsBatch b, float lr,
   b.theta[k][i] -= lr * gi / (sqrtf(ai) + eps);
 }
 
-hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int lds_bytes) {
+hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int shapes) {
   if (a.n_tiles == 0) return hipSuccess;
-  if (backward) hipLaunchKernelGGL(sr_rows_train_kernel<true>, dim3(a.n_tiles), dim3(256), lds_bytes, s, a);
-  else hipLaunchKernelGGL(sr_rows_train_kernel<false>, dim3(a.n_tiles), dim3(256), lds_bytes, s, a);
+  static void (*const kernels[2][3])(SrRowArgs) = {
+      {sr_rows_train_kernel<false, SR_F32_WIDE>, sr_rows_train_kernel<false, SR_F32_NARROW>, sr_rows_train_kernel<false, SR_F32_DEEP>},
+      {sr_rows_train_kernel<true, SR_F32_WIDE>, sr_rows_train_kernel<true, SR_F32_NARROW>, sr_rows_train_kernel<true, SR_F32_DEEP>}};
+  hipLaunchKernelGGL(kernels[backward ? 1 : 0][sr_f32_variant(shapes)], dim3(a.n_tiles), dim3(256), sr_f32_lds_bytes(shapes), s, a);
   return hipGetLastError();
 }
 
-hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int lds_bytes) {
+hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int shapes) {
   if (a.n_tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(sr_grad_kernel, dim3(a.n_tiles), dim3(256), lds_bytes, s, a);
+  const int lds = sr_f32_lds_bytes(shapes);
+  const auto kernel = sr_f32_variant(shapes) == SR_F32_WIDE ? sr_grad_kernel<SR_F32_WIDE> : sr_grad_kernel<SR_F32_NARROW>;
+  hipLaunchKernelGGL(kernel, dim3(a.n_tiles), dim3(256), lds > 1024 ? lds : 1024 /* column sums */, s, a);
   return hipGetLastError();
 }
 

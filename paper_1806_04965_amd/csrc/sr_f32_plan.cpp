@@ -233,7 +233,7 @@ double sr_rows_work(const SrRowPlan& p, int phase) {
 // the launch's work per compute unit (or some microseconds), else the next smaller shape is tried; below that the
 // reduction is cut into parts.
 void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split,
-                   int* split_slots, std::vector<SrRowTile>* out, int* lds_bytes) {
+                   int* split_slots, std::vector<SrRowTile>* out, int* shapes) {
   double work = 0;
   int64_t n_short = 0;
   for (int f : phases) {
@@ -271,7 +271,7 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
     }
     int ti, tj;
     sr_f32_shape(shape, &ti, &tj);
-    *lds_bytes = std::max(*lds_bytes, sr_f32_lds_bytes(shape));
+    *shapes |= 1 << shape;
     const int n_i = ceil_div(ph.I, ti), n_j = ceil_div(C, tj);
     const int64_t total = (int64_t)n_i * n_j * parts;
     int64_t k = 0;
@@ -365,7 +365,7 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
     it.n_j = ceil_div(d.Cout, tj);
     it.step_cycles = std::max(ti * tj / 8.0, 700.0);
     work += it.step_cycles * it.steps * it.n_i * it.n_j;
-    p->lds = std::max(p->lds, sr_f32_lds_bytes(it.shape));
+    p->shapes |= 1 << it.shape;
   }
   // The pixel sums are cut into slices so that the launch has about six work items of equal length per compute unit,
   // none shorter than 16 steps: shorter ones are dominated by filling the pipeline and by their partial sums.
@@ -429,7 +429,6 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
           list.push_back(Keyed{(t.step_end - t.step_begin) * 8.0, t});
         }
       p->biases.push_back(b);
-      p->lds = std::max(p->lds, 1024);
     } else if (!first) {
       continue;
     }

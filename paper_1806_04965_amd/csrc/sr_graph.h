@@ -47,7 +47,7 @@ struct LevelPlan {
   int tile_begin = 0, n_tiles = 0;
   int block_begin = 0, n_blocks = 0;
   int head_begin = 0, n_heads = 0;
-  int row_begin = 0, n_rows = 0, row_lds = 0;   // fp32 graphs: row tiles of the level, LDS they need
+  int row_begin = 0, n_rows = 0, row_shapes = 0;   // fp32 graphs: row tiles of the level, their shapes
   int aux_begin = 0, n_aux = 0;     // head and input-staging items that ride along in this level's launch
 };
 

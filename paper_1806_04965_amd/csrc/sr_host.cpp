@@ -597,7 +597,7 @@ sr_status finalize(sr_graph* g) {
           phases.push_back(sr_rows_forward(&rows, g, v, nullptr));
         }
       lp.row_begin = (int)row_tiles.size();
-      if (!phases.empty()) sr_rows_tiles(rows, phases, 0, g->train_tall_from, g->allow_split, &row_slots, &row_tiles, &lp.row_lds);
+      if (!phases.empty()) sr_rows_tiles(rows, phases, 0, g->train_tall_from, g->allow_split, &row_slots, &row_tiles, &lp.row_shapes);
       lp.n_rows = (int)row_tiles.size() - lp.row_begin;
     }
     for (int v = 0; v < g->n_nodes; ++v) {
@@ -1580,7 +1580,7 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
         a.n_tiles = lp.n_rows;
         a.rec_node = record ? g->rec_node : -1;
         a.split = g->row_split;
-        SR_HIP(g, sr_launch_rows_frame(s, fl, a, std::max(lp.row_lds, g->aux_smem_bytes), g->aux + lp.aux_begin, lp.n_aux, g->heads,
+        SR_HIP(g, sr_launch_rows_frame(s, fl, a, lp.row_shapes, g->aux + lp.aux_begin, lp.n_aux, g->heads,
                                        g->head_edges, g->stage_nodes, g->aux_smem_bytes));
       } else if (g->tile_version == 2)
         SR_HIP(g, sr_launch_mfma8(s, fl, g->m_nodes, g->m_edges, g->m_tiles + lp.tile_begin, lp.n_tiles,

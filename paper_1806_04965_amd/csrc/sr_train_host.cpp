@@ -36,7 +36,7 @@ struct SrTrainState {
 
   // the plan of windows of W frames with the loss at node `out` (device tables in one allocation)
   struct Launch {
-    int run0 = 0, n_runs = 0, blocks = 0, lds = 0;
+    int run0 = 0, n_runs = 0, blocks = 0, shapes = 0;
     std::vector<std::pair<SrPool, std::pair<int, int>>> pools;   // before it: means of (first frame, number of frames)
   };
   struct Chunk {   // frames lo..hi of the reverse sweep
@@ -97,7 +97,7 @@ size_t node_floats(const sr_graph* g, int v) {
 }
 
 // (frame, node) pairs of one depth as runs over the nodes' tile lists, longest tiles first
-struct NodeTiles { int tile0 = 0, n = 0, slots = 0, lds = 0; double length = 0; };
+struct NodeTiles { int tile0 = 0, n = 0, slots = 0, shapes = 0; double length = 0; };
 
 // the launches of pairs[depth]; returns the split slots the largest one needs
 int make_launches(const std::vector<std::vector<std::pair<int, int>>>& pairs, const std::vector<NodeTiles>& tiles,
@@ -114,7 +114,7 @@ int make_launches(const std::vector<std::vector<std::pair<int, int>>>& pairs, co
       const NodeTiles& t = tiles[fv.second];
       runs->push_back(SrRun{l.blocks, t.tile0, fv.first, slots});
       l.blocks += t.n;
-      l.lds = std::max(l.lds, t.lds);
+      l.shapes |= t.shapes;
       slots += t.slots;
     }
     l.n_runs = (int)level.size();
@@ -217,7 +217,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
     for (int v : order) {
       NodeTiles& t = nf[v];
       t.tile0 = (int)tf.size();
-      sr_rows_tiles(rf, {ph[v]}, work / std::max<size_t>(1, pairs.size()), g->train_tall_from, g->allow_split, &t.slots, &tf, &t.lds);
+      sr_rows_tiles(rf, {ph[v]}, work / std::max<size_t>(1, pairs.size()), g->train_tall_from, g->allow_split, &t.slots, &tf, &t.shapes);
       t.n = (int)tf.size() - t.tile0;
       t.length = rf.phases[ph[v]].steps * (tf[t.tile0].shape <= SR_F32_128x64 ? 2.0 : 1.0);
     }
@@ -255,7 +255,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
       if (phs[v].empty()) continue;
       NodeTiles& t = nb[v];
       t.tile0 = (int)tb.size();
-      sr_rows_tiles(rb, phs[v], per_launch, g->train_tall_from, g->allow_split, &t.slots, &tb, &t.lds);
+      sr_rows_tiles(rb, phs[v], per_launch, g->train_tall_from, g->allow_split, &t.slots, &tb, &t.shapes);
       t.n = (int)tb.size() - t.tile0;
       for (int f : phs[v]) t.length = std::max(t.length, rb.phases[f].steps * (tb[t.tile0].shape <= SR_F32_128x64 ? 2.0 : 1.0));
     }
@@ -420,7 +420,7 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
     a.runs = T.runs + l.run0;
     a.n_runs = l.n_runs;
     a.n_tiles = l.blocks;
-    SR_HIP(g, sr_launch_rows_train(s, a, backward, l.lds));
+    SR_HIP(g, sr_launch_rows_train(s, a, backward, l.shapes));
     return SR_OK;
   };
   for (const SrTrainState::Launch& l : T.fwd)
@@ -456,7 +456,7 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
     ga.n_tiles = (int)c.grad.tiles.size();
     ga.ring = T.ring;
     ga.accumulate = k > 0;
-    SR_HIP(g, sr_launch_grad(s, ga, c.grad.lds));
+    SR_HIP(g, sr_launch_grad(s, ga, c.grad.shapes));
     const bool final = k + 1 == T.chunks.size();
     SR_HIP(g, sr_launch_grad_sum(s, c.sums, (int)c.grad.sums.size(), c.grad.sum_blocks, T.part, T.dst, k > 0, T.terms, W * B, scale,
                                  final ? loss : nullptr));

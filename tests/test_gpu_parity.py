@@ -489,3 +489,19 @@ def test_fp32_row_tiles_at_tile_edges(channels, tall_from):
     compare_all(got, oracle_states(g, w, b, x, 3, "f64"), 2e-5, f"row tiles {channels} tall_from={tall_from}")
     rec = gpu_rollout(g, w, b, x, 3, options={8: tall_from})
     assert np.array_equal(rec, np.stack(got[5]))     # recorded by the tiles themselves
+
+
+@pytest.mark.parametrize("channels", [(32, 64), (20, 64), (16, 40)])
+def test_fp32_64x64_tiles_in_pairs_of_steps(channels):
+    # enough rows for the 64 x 64 and 128 x 32 tiles of a launch without 128 x 128 tiles (four workgroups per CU): sums of
+    # 32 k channels (two steps share their addresses) beside 20, 16 and 3 (step by step, odd numbers of steps).
+    # Bound: as in test_fp32_row_tiles_at_tile_edges, K <= 864.
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    ca, cb = channels
+    nodes = [Node("in", 3, 40, 40, ACT_IDENTITY), Node("a", ca, 40, 40), Node("b", cb, 40, 40), Node("out", 5, 1, 1, ACT_IDENTITY)]
+    edges = [Edge(0, 1), Edge(1, 1, "conv", 1, 1, 1, 0), Edge(1, 2), Edge(2, 2, "conv", 1, 1, 1, 0), Edge(2, 3, "dense", 40, 40, 1, 0)]
+    g0 = Graph("pairs", nodes, edges, 21, 3, "f32", out_node=3)
+    g = g0.with_pattern(W.streaming_pattern(g0))
+    w, b, x = W.make_case(g, seed=73, bias_scale=0.1, frames=3, recipe="uniform")
+    got, _, _ = gpu_states_by_steps(g, w, b, x, 3)
+    compare_all(got, oracle_states(g, w, b, x, 3, "f64"), 2e-5, f"pairs {channels}")

@@ -438,3 +438,19 @@ def test_reverse_sweep_in_chunks_of_frames(pattern, kept):
         got, data = run_case(g, Wn, seed=41, dev=dev)
         check_against_oracle(g, Wn, got, data, f"small_sr/{pattern} W={Wn}, {kept} frames at a time", may_be_zero=Wn < 4)
     dev.close()
+
+
+@pytest.mark.parametrize("channels", [(32, 64, 32), (32, 16, 96), (96, 32, 20)])
+def test_steps_in_pairs_and_single_steps_of_one_tile(channels):
+    # 128 x 32 tiles fetch two reduction steps at a time where both lie in one tap of 32 k channels (shared addresses),
+    # else step by step: sums of 32 k, 16 and 20 channels follow one another in a tile, with odd numbers of steps, over
+    # ragged rows; forward and reverse.  GRAD_TOL as derived above.
+    import paper_1806_04965_amd as sr
+    g0 = ragged_graph(channels=channels)
+    g = g0.with_pattern(W.hybrid_pattern(g0))
+    w, b, _ = W.make_case(g, seed=43, bias_scale=0.1, frames=3, recipe="uniform")
+    dev = sr.SrGraph(g, options={8: 0})
+    dev.set_parameters(w, b)
+    got, data = run_case(g, 3, seed=43, dev=dev)
+    check_against_oracle(g, 3, got, data, f"pairs {channels}")
+    dev.close()

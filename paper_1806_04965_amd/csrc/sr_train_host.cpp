@@ -217,7 +217,10 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
     for (int v : order) {
       NodeTiles& t = nf[v];
       t.tile0 = (int)tf.size();
-      sr_rows_tiles(rf, {ph[v]}, work / std::max<size_t>(1, pairs.size()), g->train_tall_from, g->allow_split, &t.slots, &tf, &t.shapes);
+      // a launch's work: the average one's; scores that nothing but the loss reads have a launch of their own (DSR2: 64 x 10
+      // scores of 8192 products each, alone 75 us uncut, 23 in parts)
+      const double launch = v == out_node && T.out_is_sink ? sr_rows_work(rf, ph[v]) * W : work / std::max<size_t>(1, pairs.size());
+      sr_rows_tiles(rf, {ph[v]}, launch, g->train_tall_from, g->allow_split, &t.slots, &tf, &t.shapes);
       t.n = (int)tf.size() - t.tile0;
       t.length = rf.phases[ph[v]].steps * (tf[t.tile0].shape <= SR_F32_128x64 ? 2.0 : 1.0);
     }

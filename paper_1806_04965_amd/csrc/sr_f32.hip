@@ -806,7 +806,8 @@ __device__ __forceinline__ void sr_grad_bias(const SrGradArgs& A, SR_CONST4(SrGr
 
 }  // namespace
 
-// (WIDE: 168 registers and three workgroups per CU, four of them spilled, beat 172 and two: 1900 -> 1800 us, GTSRB-shaped window)
+// (WIDE: 168 registers, four spilled, and three workgroups per CU; two with 172.  All variants together took the GTSRB-shaped
+// window from 6270 to 6150 us.)
 template <int VARIANT>
 __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 3) void sr_grad_kernel(SrGradArgs A) {
   extern __shared__ __align__(1024) unsigned char sr_rows_lds[];

@@ -56,10 +56,32 @@ __global__ __launch_bounds__(256) void sr_reset_kernel(SrCtx* ctx, SrCtx values,
     for (int64_t o = whole + threadIdx.x; o < end; o += 256) ((char*)it.p)[o] = 0;
     return;
   }
-  for (int64_t i = begin / (int64_t)sizeof(T) + threadIdx.x; i < end / (int64_t)sizeof(T); i += 256) {
-    const int64_t p = i / it.Cp;
-    const int c = (int)(i - p * it.Cp);
-    ((T*)it.p)[i] = c < it.C ? ((const T*)src)[p * it.C + c] : (T)0;
+  // Frame 0 of an input node, 16 bytes of the state at a time: a piece of one pixel where a pixel is whole pieces (the
+  // chunk's first pixel by one 64-bit division, the rest in 32 bits), a plain copy where nothing is padded.  Element by
+  // element, each with a 64-bit division, this took most of the launch: CIFAR-shaped graph, 64 images, 25 us -> 9.
+  constexpr int E = 16 / (int)sizeof(T);
+  typedef T piece_t __attribute__((ext_vector_type(16 / sizeof(T))));
+  const T* in = (const T*)src;
+  T* out = (T*)it.p;
+  const int64_t first = begin / (int64_t)sizeof(T), last = end / (int64_t)sizeof(T);
+  if (it.C == it.Cp) {
+    const bool wide = (((unsigned long long)(in + first) | (unsigned long long)(out + first)) & 15) == 0;
+    const int64_t whole = wide ? first + (last - first) / E * E : first;
+    for (int64_t i = first + threadIdx.x * E; i < whole; i += 256 * E) *(piece_t*)(out + i) = *(const piece_t*)(in + i);
+    for (int64_t i = whole + threadIdx.x; i < last; i += 256) out[i] = in[i];
+  } else {   // bf16: Cp is a multiple of 16, the chunk begins and ends with a piece
+    const unsigned per_pixel = it.Cp / E;
+    const int64_t piece0 = first / E, pixel0 = piece0 / per_pixel;
+    const unsigned off = (unsigned)(piece0 - pixel0 * per_pixel), n = (unsigned)((last - first) / E);
+    for (unsigned q = threadIdx.x; q < n; q += 256) {
+      const unsigned l = off + q, px = l / per_pixel;
+      const int c = (int)(l - px * per_pixel) * E;
+      const T* s = in + (pixel0 + px) * it.C;
+      piece_t v;
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = c + e < it.C ? s[c + e] : (T)0;
+      *(piece_t*)(out + first + (int64_t)q * E) = v;
+    }
   }
 }
 

@@ -505,3 +505,26 @@ def test_fp32_64x64_tiles_in_pairs_of_steps(channels):
     w, b, x = W.make_case(g, seed=73, bias_scale=0.1, frames=3, recipe="uniform")
     got, _, _ = gpu_states_by_steps(g, w, b, x, 3)
     compare_all(got, oracle_states(g, w, b, x, 3, "f64"), 2e-5, f"pairs {channels}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("channels", [1, 3, 5, 16, 33, 40])
+def test_reset_copies_frame_0_of_an_input(channels, dtype):
+    # whole pieces of 16 bytes, ragged ones, more than one chunk of a workgroup, and input frames that begin at any
+    # element; frame 0 comes back bit for bit
+    import torch
+    import paper_1806_04965_amd as sr
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    nodes = [Node("in", channels, 23, 31, ACT_IDENTITY), Node("a", 7, 23, 31)]
+    g0 = Graph("reset", nodes, [Edge(0, 1)], 3, 1, dtype, out_node=1)
+    g = g0.with_pattern(W.streaming_pattern(g0))
+    w, b, _ = W.make_case(g, seed=5, frames=1, recipe="uniform")
+    dev = sr.SrGraph(g)
+    dev.set_parameters(w, b)
+    n = 3 * 23 * 31 * channels
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for start in (0, 1, 2):
+        x = torch.randn(n + 2, device="cuda").to(tdt)[start:start + n].view(3, 23, 31, channels)
+        dev.reset([x])
+        assert torch.equal(dev.get_state(0), x)
+    dev.close()

@@ -72,9 +72,9 @@ PEAK_FP32_VALU_TFLOPS = 157.3  # fp32 vector peak (the fp32 graph runs on plain 
 def train_window_bench(args, g):
     """One step = one training window (Sec. 3 rollout window of size W; loss of App. A2): forward over
     W frames, loss, gradients of every weight and bias, through sr_window_gradients on the fp32 graph.
-    The roofline is the fp32 vector one; the algorithmic work of a window is, per edge and frame, the
-    forward contraction, the weight gradient and, where one is kept (not into an input node, not into
-    frame 0), the state gradient."""
+    The roofline is the fp32 one (vector and matrix rate are the same); the algorithmic work of a window is,
+    per edge and frame, the forward contraction, the weight gradient and, where one is kept (not into an
+    input node, not into frame 0), the state gradient -- of the frames that a loss term depends on."""
     import dataclasses
     import numpy as np
     import torch
@@ -110,10 +110,15 @@ def train_window_bench(args, g):
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     ms_per_step = dt / args.steps * 1e3
-    # algorithmic work of the window: per edge and frame the forward contraction and the weight gradient, and the
-    # state gradient where one is kept (not into input nodes, not into frame 0)
+    # algorithmic work of the window: per edge and frame the forward contraction, the weight gradient and the state
+    # gradient (not into input nodes); frames of a node that no loss term depends on and the zero initial state need none
     inputs_set = set(ins)
     flop = 0.0
+    dist = {g.out_node: 0}      # fewest bridging edges from a node to the scores: the loss sees it up to frame W - dist
+    for _ in g.nodes:
+        for e in g.edges:
+            if e.dst in dist:
+                dist[e.src] = min(dist.get(e.src, Wn), dist[e.dst] + int(e.bridge))
     for e in g.edges:
         sn, dn = g.nodes[e.src], g.nodes[e.dst]
         if e.kind == "conv":
@@ -122,8 +127,8 @@ def train_window_bench(args, g):
             macs = B * dn.channels * sn.channels * sn.height * sn.width
         else:
             macs = B * dn.channels * sn.channels
-        for i in range(1, Wn + 1):
-            flop += 2.0 * macs * (2 + (1 if e.src not in inputs_set and i - int(e.bridge) >= 1 else 0))
+        for i in range(1, Wn - dist.get(e.dst, Wn) + 1):
+            flop += 2.0 * macs * (2 if e.src in inputs_set else (3 if i - int(e.bridge) >= 1 else 0))
     achieved = flop / (ev0.elapsed_time(ev1) / args.steps * 1e-3) / 1e12
     cpu = None
     if not args.no_cpu_baseline:

@@ -323,8 +323,9 @@ int sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds* id
 int sr_rows_backward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds& ids);
 // Tiles of phases that one launch covers, in the order of the list (workgroup i runs on XCD i % 8; padded to a
 // multiple of 8 with empty tiles).  work_cycles: compute-unit cycles of the whole launch if it covers more than
-// these phases (0: just these).  tall_from: SR_OPT_TRAIN_TALL_TILES_FROM; split: SR_OPT_K_SPLIT.
-void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split,
+// these phases (0: just these).  tall_from: SR_OPT_TRAIN_TALL_TILES_FROM; split: SR_OPT_K_SPLIT; ordered: forward pass of a
+// training window.
+void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split, bool ordered,
                    int* split_slots, std::vector<SrRowTile>* out, int* shapes);
 double sr_rows_work(const SrRowPlan& p, int phase);   // compute-unit cycles of a phase at the fp32 matrix rate
 // Weight and bias gradients of the frames lo..hi of a window of W frames: descriptors, tiles, partial sums.  Destination

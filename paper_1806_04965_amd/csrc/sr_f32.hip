@@ -18,7 +18,9 @@
 // B=128 W=4 6270 -> 5970, MNIST SR 317 -> 302.
 //
 // Every sum has a fixed order (reduction index by index within a part, parts in order, waves in order): the same call
-// gives the same bits.
+// gives the same bits.  The forward pass of a training window has one order for all sizes and tiles (SR_ROWS_ORDERED);
+// against tiles that take theirs as it comes, and cut long sums, that costs DSR2 1459 -> 1532 us, GTSRB-shaped 5990 -> 6130,
+// MNIST SR 302 -> 360.
 #include "sr_device.h"
 #include "sr_f32.h"
 
@@ -100,13 +102,22 @@ __device__ __forceinline__ bool sr_seg_counts(const SrSeg& g, const SrSlots& sl)
   return BACK ? sl.left >= lag + g.dist : !(lag && (g.flags & SR_SEG_ZERO0) && sl.left == 1);
 }
 
+// What a row tile is computed for.  SR_ROWS_ORDERED: the forward pass of a training window, whose sums are taken in one
+// order whatever the sizes, so that the sign of a rectifier's input, and with it the path a gradient takes, does not hang
+// on which tile shape a launch has.  Every edge's sum starts from zero and runs through its reduction indices step by step,
+// the edges' sums are added in edge order; inside a step the products go 0, 8, 1, 9, .. where all channel counts are
+// multiples of four (SR_SEG_QUADS), else 0, 1, 2, .. (line 8 h + k of its stage then holds index 2 k + h).
+enum { SR_ROWS_FRAME = 0, SR_ROWS_BACK = 1, SR_ROWS_ORDERED = 2 };
+SR_HD int sr_in_turn(int line) { return 2 * (line & 7) + (line >> 3); }
+
 // The operands of a tile: a TI x 16 and a 16 x TJ piece per step, NW waves fetching them together.
 //   rows:  TI (TJ) rows of 16 reduction indices, 64 bytes a row, pieces of four permuted (sr_f32_piece)
 //   k-major: 16 lines of TI (TJ) elements
 // A is rows when the gathered channel count is a multiple of four (16-byte loads), else k-major (4-byte loads); B is
 // k-major in the forward direction, where theta's columns are contiguous, and like A backwards.
-template <int TI, int TJ, int NW, bool BACK>
+template <int TI, int TJ, int NW, int FOR>
 struct SrRowOperands {
+  static constexpr bool BACK = FOR == SR_ROWS_BACK;
   static constexpr int NA = TI / (16 * NW);                        // 16-byte loads of A per wave and step
   static constexpr int NB = TJ / (16 * NW) > 0 ? TJ / (16 * NW) : 1;   // ... of B (TJ = 32 of four waves: half the lanes)
   static constexpr int STAGE = (TI + TJ) * 64;                     // bytes of one step in LDS
@@ -118,6 +129,7 @@ struct SrRowOperands {
   SrRowAt row[NA];
   int wv, lane, i0, j0;
   int quads, quads_w;
+  int turn;                  // ordered: the products of a step go in turn
 
   // a new segment: where this lane's rows are in its image
   __device__ __forceinline__ void enter(const SrPhase& p, const SrTensor* tensors, const SrSlots& sl) {
@@ -128,6 +140,7 @@ struct SrRowOperands {
     src = sr_uni_ptr((const char*)(unsigned long long)t->base + slot * t->stride + b0 * image);
     quads = SR_UNI((g.flags & SR_SEG_QUADS) && ((unsigned)(unsigned long long)src & 15u) == 0);
     quads_w = SR_UNI((g.ldw & 3) == 0);
+    if (FOR == SR_ROWS_ORDERED) turn = !(g.flags & SR_SEG_QUADS);
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
       const int r = quads ? n * 16 * NW + wv * 16 + (lane >> 2)
@@ -187,7 +200,8 @@ struct SrRowOperands {
 #pragma unroll
       for (int q = 0; q < TI / 4 / NW; ++q) {
         const int id = q * NW + wv;
-        const int k = TI >= 64 ? id * 64 / TI : 2 * id + (lane >> 5);
+        const int line = TI >= 64 ? id * 64 / TI : 2 * id + (lane >> 5);
+        const int k = FOR == SR_ROWS_ORDERED && turn ? sr_in_turn(line) : line;
         const SrTapAt t = sr_tap_at(g, TI >= 64 ? SR_UNI(r0 + k) : r0 + k);
         const char* p = sr_gather_ok(g, row[0], t) ? sr_at(src, row[0].off + sr_gather_off(g, t)) : zero;
         sr_to_lds4(p, at + id * 256);
@@ -206,7 +220,29 @@ struct SrRowOperands {
       }
     }
     // forward: 16 lines of theta
-    if (quads_w) {
+    if (FOR == SR_ROWS_ORDERED && turn) {
+      if (quads_w) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const int id = HALF_B ? wv * 32 + lane : (n * NW + wv) * 64 + lane;
+          const int r = r0 + sr_in_turn((id / (TJ / 4)) & 15), j = j0 + 4 * (id % (TJ / 4));
+          const char* p = (r < g.R && j < g.ldw) ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
+          if (HALF_B) {
+            if (lane < 32) sr_to_lds16(p, bt + wv * 512);
+          } else {
+            sr_to_lds16(p, bt + (n * NW + wv) * 1024);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < TJ / 4 / NW; ++q) {
+          const int id = q * NW + wv;
+          const int r = r0 + sr_in_turn((id * 64 + lane) / TJ), j = j0 + (id * 64 + lane) % TJ;
+          const char* p = (r < g.R && j < g.ldw) ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
+          sr_to_lds4(p, bt + id * 256);
+        }
+      }
+    } else if (quads_w) {
 #pragma unroll
       for (int n = 0; n < NB; ++n) {
         const int id = HALF_B ? wv * 32 + lane : (n * NW + wv) * 64 + lane;
@@ -278,6 +314,37 @@ __device__ __forceinline__ void sr_step_products(const unsigned char* st, int iw
       for (int y = 0; y < MJ; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x][k], b[y][k], acc[x][y], 0, 0, 0);
 }
 
+// The products of four steps for a 16 x 16 quarter of a 32 x 32 tile, four reduction indices per instruction, in the order
+// in which the 32x32x2 products take them: 0, 8, 1, 9, ...  Both instructions add their products one after the other, each
+// rounded like a fused multiply-add (300 000 sums compared bit for bit, denormal terms among them).
+template <bool A_ROWS>
+__device__ __forceinline__ void sr_quarter_products(const unsigned char* st, int iw, int jw, int lane, f32x4_t& acc) {
+  constexpr int STAGE = 64 * 64;
+  const int l = lane & 15, q = lane >> 4;
+  const int k0 = 8 * (q & 1) + (q >> 1);   // this lane's index of product m: k0 + 2 m
+  float a[4][4], b[4][4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    if (A_ROWS) {
+      float f[8];
+      sr_frag_rows(st + s * STAGE, iw + l, q & 1, f);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) a[s][m] = (q >> 1) ? f[2 * m + 1] : f[2 * m];
+    } else {
+      const float* p = (const float*)(st + s * STAGE) + k0 * 32 + iw + l;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) a[s][m] = p[m * 64];
+    }
+    const float* p = (const float*)(st + s * STAGE + 32 * 64) + k0 * 32 + jw + l;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) b[s][m] = p[m * 64];
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][m], b[s][m], acc, 0, 0, 0);
+}
+
 // K-split: every part leaves its registers in its slab, the part that arrives last adds them up in part order.
 // Agent-scope accesses throughout: the parts run on different XCDs.
 template <int N>
@@ -314,18 +381,21 @@ __device__ __forceinline__ bool sr_row_split(float (&o)[N], const SrSplitScratch
 struct SrRecord { float* out; };
 
 // A row tile.  SMALL: every wave takes every fourth step of a 32 x 32 tile through LDS of its own (no barriers); the
-// four waves' sums are added in order at the end.
-template <int TI, int TJ, int WJN, bool BACK, bool SMALL, int STAGES>
+// four waves' sums are added in order at the end.  Ordered, four steps go at a time: wave w fetches the w-th, then every
+// wave multiplies all four for a 16 x 16 quarter of the tile -- as long a chain of products per wave.
+template <int TI, int TJ, int WJN, int FOR, bool SMALL, int STAGES>
 __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p, int i0, int j0, int step_begin, int step_end,
                                             int split_slot, int part_info, const SrSlots& sl, float* record, int rec_node,
                                             unsigned char* lds) {
-  constexpr bool PAIRS = STAGES == SR_F32_PAIRS;
+  constexpr bool BACK = FOR == SR_ROWS_BACK, ORDERED = FOR == SR_ROWS_ORDERED;
+  constexpr bool PAIRS = STAGES == SR_F32_PAIRS, ALONE = SMALL && !ORDERED, QUARTERS = SMALL && ORDERED;
   constexpr int NW = SMALL ? 1 : 4, WIN = NW / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
-  typedef SrRowOperands<TI, TJ, NW, BACK> Ops;
+  typedef SrRowOperands<TI, TJ, NW, FOR> Ops;
   const int tid = threadIdx.x, lane = tid & 63, wave = SR_UNI(tid >> 6);
   const int iw = (wave / WJN) * 32 * MI * (SMALL ? 0 : 1), jw = (wave % WJN) * 32 * MJ * (SMALL ? 0 : 1);
-  unsigned char* base = SMALL ? lds + wave * ((PAIRS ? 4 : STAGES) * Ops::STAGE) : lds;
-  const unsigned at0 = sr_lds_at(base);
+  constexpr int PITCH = (QUARTERS ? 4 : 1) * Ops::STAGE;   // from one stage to the next
+  unsigned char* base = ALONE ? lds + wave * ((PAIRS ? 4 : STAGES) * Ops::STAGE) : lds;
+  const unsigned at0 = sr_lds_at(base) + (QUARTERS ? wave * Ops::STAGE : 0);
 
   Ops op;
   op.wv = SMALL ? 0 : wave; op.lane = lane; op.i0 = i0; op.j0 = j0;
@@ -336,6 +406,14 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
     for (int y = 0; y < MJ; ++y)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+  f32x16_t sum[ORDERED ? MI : 1][ORDERED ? MJ : 1];   // of the segments that are done
+  if constexpr (ORDERED) {
+#pragma unroll
+    for (int x = 0; x < MI; ++x)
+#pragma unroll
+      for (int y = 0; y < MJ; ++y) sum[x][y] = acc[x][y];
+  }
+  f32x4_t quarter{0.f, 0.f, 0.f, 0.f}, quarter_sum{0.f, 0.f, 0.f, 0.f};
 
   // two groups of segments: those that depend on the image only, whose sum is scaled, then the others
   for (int group = (p.seg_image > p.seg_begin) ? 0 : 1; group < 2; ++group) {
@@ -352,7 +430,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
         const int n = (op.g.R + SR_F32_KS - 1) / SR_F32_KS;
         int lo = max(step_begin - op.g.step0, 0);
         const int hi = min(step_end - op.g.step0, n);
-        if (SMALL) lo += (wave - (op.g.step0 + lo)) & 3;
+        if (ALONE) lo += (wave - (op.g.step0 + lo)) & 3;
         r = lo * SR_F32_KS;
         r_stop = hi * SR_F32_KS;
         if (r < r_stop) op.enter(p, A.tensors, sl);
@@ -361,12 +439,45 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
     };
     int issued = 0, done = 0, wr = 0, rd = 0;
     unsigned rows = 0;   // per stage: the gathered operand (backwards: both) lies row by row
-    auto issue = [&]() {
-      op.issue(r, at0 + wr * Ops::STAGE);
-      const unsigned bit = 1u << wr;
+    unsigned ends = 0;   // ordered, per stage: it is the last one of its segment
+    auto mark = [&](int stage) {   // what the step at r, about to be fetched into `stage`, is
+      const unsigned bit = 1u << stage;
       rows = op.quads ? rows | bit : rows & ~bit;
+      if constexpr (ORDERED)
+        ends = r + (QUARTERS ? 4 : 1) * SR_F32_KS >= r_stop ? ends | bit : ends & ~bit;
+    };
+    auto issue = [&]() {
+      mark(wr);
+      // (quarters: the steps of the four that are past the end of the share are zero)
+      op.issue(!QUARTERS ? r : (r + wave * SR_F32_KS < r_stop ? r + wave * SR_F32_KS : op.g.R), at0 + wr * PITCH);
       wr = wr == STAGES - 1 ? 0 : wr + 1;
       ++issued;
+    };
+    auto multiply = [&](int stage) {
+      const unsigned char* st = base + stage * PITCH;
+      const bool a_rows = (rows >> stage) & 1;
+      if constexpr (QUARTERS) {
+        if (a_rows) sr_quarter_products<true>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, quarter);
+        else sr_quarter_products<false>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, quarter);
+      } else {
+        sr_step_products<TI, TJ, MI, MJ>(st, iw, jw, lane, a_rows, BACK && a_rows, acc);
+      }
+    };
+    auto fold = [&]() {   // a segment is done
+      if constexpr (QUARTERS) {
+        quarter_sum += quarter;
+        quarter = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      } else if constexpr (ORDERED) {
+#pragma unroll
+        for (int x = 0; x < MI; ++x)
+#pragma unroll
+          for (int y = 0; y < MJ; ++y)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              sum[x][y][v] += acc[x][y][v];
+              acc[x][y][v] = 0.f;
+            }
+      }
     };
     bool more = next();
     if constexpr (PAIRS) {
@@ -375,15 +486,17 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
         if (!more) return 0;
         wr = to;
         if (op.pairs(r, r_stop)) {
+          mark(wr);
           op.template issue<true>(r, at0 + wr * Ops::STAGE);
-          rows |= 3u << wr;
           r += SR_F32_KS;
+          mark(wr + 1);
           more = next();
           return 2;
         }
         issue();
+        const bool last = ORDERED && ((ends >> to) & 1);   // a pair lies in one segment
         more = next();
-        if (!more) return 1;
+        if (!more || last) return 1;
         wr = to + 1;
         issue();
         more = next();
@@ -391,15 +504,19 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
       };
       int cur = issue_pair(0);
       while (cur > 0) {
-        sr_wait_loads<0>();
-        sr_step_barrier();   // everybody's loads of this pair; and the pair before has been read by all
-        const int following = issue_pair(rd ^ 2);
-        sr_step_products<TI, TJ, MI, MJ>(base + rd * Ops::STAGE, iw, jw, lane, (rows >> rd) & 1, BACK && ((rows >> rd) & 1), acc);
-        if (cur == 2)
-          sr_step_products<TI, TJ, MI, MJ>(base + (rd + 1) * Ops::STAGE, iw, jw, lane, (rows >> (rd + 1)) & 1,
-                                           BACK && ((rows >> (rd + 1)) & 1), acc);
-        rd ^= 2;
-        cur = following;
+        bool end;   // of the loop: ordered, of a segment
+        do {
+          sr_wait_loads<0>();
+          sr_step_barrier();   // everybody's loads of this pair; and the pair before has been read by all
+          end = ORDERED && ((ends >> (rd + cur - 1)) & 1);
+          const int following = issue_pair(rd ^ 2);
+          multiply(rd);
+          if (cur == 2) multiply(rd + 1);
+          rd ^= 2;
+          cur = following;
+          if (!ORDERED) end = cur == 0;
+        } while (!end);
+        fold();
       }
       issued = 0;
     }
@@ -408,20 +525,26 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
       more = next();
     }
     while (done < issued) {
-      if (STAGES > 3 && issued - done >= 3) sr_wait_loads<2 * Ops::LOADS>();
-      else if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
-      else sr_wait_loads<0>();
-      if (!SMALL) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
-      if (more) {
-        issue();
-        more = next();
-      }
-      sr_step_products<TI, TJ, MI, MJ>(base + rd * Ops::STAGE, iw, jw, lane, (rows >> rd) & 1, BACK && ((rows >> rd) & 1), acc);
-      rd = rd == STAGES - 1 ? 0 : rd + 1;
-      ++done;
+      bool end;
+      do {
+        if (STAGES > 3 && issued - done >= 3) sr_wait_loads<2 * Ops::LOADS>();
+        else if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
+        else sr_wait_loads<0>();
+        if (!ALONE) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
+        end = ORDERED && ((ends >> rd) & 1);
+        if (more) {
+          issue();
+          more = next();
+        }
+        multiply(rd);
+        rd = rd == STAGES - 1 ? 0 : rd + 1;
+        ++done;
+        if (!ORDERED) end = done == issued;
+      } while (!end);
+      fold();
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (!SMALL) sr_step_barrier();   // the stages are free again
+    if (!ALONE) sr_step_barrier();   // the stages are free again
     if (group == 0) {
 #pragma unroll
       for (int x = 0; x < MI; ++x)
@@ -434,7 +557,10 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
 
   constexpr int NREG = SMALL ? 4 : MI * MJ * 16;
   float o[NREG];
-  if (SMALL) {
+  if constexpr (QUARTERS) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = quarter_sum[q];
+  } else if (SMALL) {
     __syncthreads();
     float* red = (float*)lds;   // [wave][register][lane]
 #pragma unroll
@@ -451,14 +577,15 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
 #pragma unroll
       for (int y = 0; y < MJ; ++y)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[((x * MJ + y) * 16 + v) % NREG] = acc[x][y][v];
+        for (int v = 0; v < 16; ++v) o[((x * MJ + y) * 16 + v) % NREG] = ORDERED ? sum[ORDERED ? x : 0][ORDERED ? y : 0][v] : acc[x][y][v];
   }
   if ((part_info >> 16) > 1) {
     __syncthreads();
     if (!sr_row_split<NREG>(o, A.split, split_slot, part_info, tid, (int*)lds)) return;
   }
 
-  // ---- epilogue.  Register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its block.
+  // ---- epilogue.  Register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its block (a quarter:
+  // row 4 (l / 16) + v, column l % 16).
   SR_CONST4(SrRowNode) nd = sr_k(A.nodes) + p.node;
   const int C = nd->C, act = nd->act;
   auto tensor_at = [&](int id, int slot) -> float* {
@@ -481,7 +608,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
 #pragma unroll
     for (int q = 0; q < VB; ++q) {
       const int v = SMALL ? 4 * wave + q : q;
-      const int i = i0 + iw + x * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      const int i = QUARTERS ? i0 + 16 * (wave >> 1) + 4 * (lane >> 4) + q : i0 + iw + x * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
       ok[q] = i < p.I;
       size_t px = ok[q] ? (size_t)i : 0;
       if (p.S != 1 && ok[q]) {
@@ -493,7 +620,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
     }
 #pragma unroll
     for (int y = 0; y < YB; ++y) {
-      const int j = j0 + jw + y * 32 + (lane & 31);
+      const int j = QUARTERS ? j0 + 16 * (wave & 1) + (lane & 15) : j0 + jw + y * 32 + (lane & 31);
       if (j >= C) continue;
       const float bj = (!BACK && bias) ? bias[j] : 0.f;
       float val[VB];
@@ -526,7 +653,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
   }
 }
 
-template <bool BACK, int VARIANT>
+template <int FOR, int VARIANT>
 __device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowTile) t, int slot0, const SrSlots& sl, float* record,
                                             int rec_node, unsigned char* lds) {
   const int phase = t->phase;
@@ -535,13 +662,13 @@ __device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowT
   const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = slot0 + t->split_slot, part = t->part;
   if constexpr (VARIANT != SR_F32_DEEP) {
     if constexpr (VARIANT == SR_F32_WIDE)
-      if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, BACK, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-    if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, BACK, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-    else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, BACK, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-    else if (shape == SR_F32_128x32) sr_row_tile<128, 32, 1, BACK, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+      if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, FOR, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, FOR, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, FOR, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    else if (shape == SR_F32_128x32) sr_row_tile<128, 32, 1, FOR, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
   }
   if (shape == SR_F32_SMALL)
-    sr_row_tile<32, 32, 1, BACK, true, sr_f32_stages(VARIANT, SR_F32_SMALL)>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    sr_row_tile<32, 32, 1, FOR, true, sr_f32_stages(VARIANT, SR_F32_SMALL)>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
 }
 
 }  // namespace
@@ -564,7 +691,7 @@ __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows
     const SrSlots sl{cur, cur ^ 1, cur, 0, 1 << 30};
     char* rec = A.rec_node >= 0 ? (char*)(unsigned long long)call->out_ptr : nullptr;
     if (rec) rec += (int64_t)(frame - call->out_base) * call->out_stride;
-    sr_row_item<false, VARIANT>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), 0, sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
+    sr_row_item<SR_ROWS_FRAME, VARIANT>(A, sr_k(A.tiles) + (item < aux_at ? item : item - n_aux), 0, sl, (float*)rec, rec ? A.rec_node : -1, sr_rows_lds);
   }
   sr_block_done(f, gridDim.x);
 }
@@ -611,7 +738,7 @@ __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows
     sl.left = frame;
   }
   sl.frame = frame;
-  sr_row_item<BACK, VARIANT>(A, sr_k(A.tiles) + run->tile0 + (blockIdx.x - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
+  sr_row_item<BACK ? SR_ROWS_BACK : SR_ROWS_ORDERED, VARIANT>(A, sr_k(A.tiles) + run->tile0 + (blockIdx.x - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
 }
 
 namespace {
@@ -957,8 +1084,9 @@ __global__ __launch_bounds__(256) void sr_rmsprop_kernel(SrRmsBatch b, float lr,
 
 hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int shapes) {
   if (a.n_tiles == 0) return hipSuccess;
+  if (!backward && sr_f32_variant(shapes) == SR_F32_WIDE) return hipErrorInvalidValue;   // not planned: see sr_rows_tiles
   static void (*const kernels[2][3])(SrRowArgs) = {
-      {sr_rows_train_kernel<false, SR_F32_WIDE>, sr_rows_train_kernel<false, SR_F32_NARROW>, sr_rows_train_kernel<false, SR_F32_DEEP>},
+      {nullptr, sr_rows_train_kernel<false, SR_F32_NARROW>, sr_rows_train_kernel<false, SR_F32_DEEP>},
       {sr_rows_train_kernel<true, SR_F32_WIDE>, sr_rows_train_kernel<true, SR_F32_NARROW>, sr_rows_train_kernel<true, SR_F32_DEEP>}};
   hipLaunchKernelGGL(kernels[backward ? 1 : 0][sr_f32_variant(shapes)], dim3(a.n_tiles), dim3(256), sr_f32_lds_bytes(shapes), s, a);
   return hipGetLastError();

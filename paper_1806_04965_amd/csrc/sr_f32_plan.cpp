@@ -54,6 +54,8 @@ bool sr_rows_take_training(const sr_graph* g) {
 
 int sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds* ids) {
   const NodeRt& n = g->nodes[v];
+  // a window's values that a rectifier may yet read have one order of sums whatever the batch and the tiles, also inside a step
+  const bool free_order = !ids || (v == ids->out_node && ids->seed < 0);
   SrRowNode node{};
   node.out = v;
   node.x = node.seed = -1;
@@ -86,7 +88,7 @@ int sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds* id
       s.tensor = e.d.src;
       s.flags = (e.d.bridge ? SR_SEG_LAG : 0) | (g->an.is_input[e.d.src] ? 0 : SR_SEG_ZERO0);
     }
-    if (q.Cin % 4 == 0) s.flags |= SR_SEG_QUADS;
+    if (q.Cin % 4 == 0 && (free_order || q.Cout % 4 == 0)) s.flags |= SR_SEG_QUADS;
     s.GH = q.H; s.GW = q.W; s.GC = q.Cin;
     s.rs = q.stride; s.r0h = s.r0w = -q.pad;
     s.dir = 1;
@@ -232,7 +234,7 @@ double sr_rows_work(const SrRowPlan& p, int phase) {
 // give the launch more workgroups and shorter chains of dependent steps.  A tile may take as long as an even share of
 // the launch's work per compute unit (or some microseconds), else the next smaller shape is tried; below that the
 // reduction is cut into parts.
-void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split,
+void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split, bool ordered,
                    int* split_slots, std::vector<SrRowTile>* out, int* shapes) {
   double work = 0;
   int64_t n_short = 0;
@@ -258,7 +260,9 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
     const int C = p.nodes[ph.node].C;
     int tall, mid;
     if (C <= 32) { tall = SR_F32_128x32; mid = SR_F32_128x32; }
-    else if (C <= 64 || (C + 127) / 128 * 128 - C >= 64) { tall = SR_F32_128x64; mid = SR_F32_64x64; }
+    // (ordered tiles: a lane would hold 64 accumulators and 64 sums of an 128 x 128 tile, which leaves two workgroups per CU;
+    // GTSRB-shaped window 6181 us with them, 6125 without)
+    else if (ordered || C <= 64 || (C + 127) / 128 * 128 - C >= 64) { tall = SR_F32_128x64; mid = SR_F32_64x64; }
     else { tall = SR_F32_128x128; mid = SR_F32_64x64; }
     int shape = SR_F32_SMALL, parts = 1;
     if (tall_from == 0 || (n_short >= tall_from && latency(tall, ph.steps) <= std::max(share, 20000.0))) {

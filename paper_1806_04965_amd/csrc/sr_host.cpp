@@ -597,7 +597,7 @@ sr_status finalize(sr_graph* g) {
           phases.push_back(sr_rows_forward(&rows, g, v, nullptr));
         }
       lp.row_begin = (int)row_tiles.size();
-      if (!phases.empty()) sr_rows_tiles(rows, phases, 0, g->train_tall_from, g->allow_split, &row_slots, &row_tiles, &lp.row_shapes);
+      if (!phases.empty()) sr_rows_tiles(rows, phases, 0, g->train_tall_from, g->allow_split, false, &row_slots, &row_tiles, &lp.row_shapes);
       lp.n_rows = (int)row_tiles.size() - lp.row_begin;
     }
     for (int v = 0; v < g->n_nodes; ++v) {

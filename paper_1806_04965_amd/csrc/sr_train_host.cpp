@@ -219,8 +219,10 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
       t.tile0 = (int)tf.size();
       // a launch's work: the average one's; scores that nothing but the loss reads have a launch of their own (DSR2: 64 x 10
       // scores of 8192 products each, alone 75 us uncut, 23 in parts)
-      const double launch = v == out_node && T.out_is_sink ? sr_rows_work(rf, ph[v]) * W : work / std::max<size_t>(1, pairs.size());
-      sr_rows_tiles(rf, {ph[v]}, launch, g->train_tall_from, g->allow_split, &t.slots, &tf, &t.shapes);
+      const bool scores = v == out_node && T.out_is_sink;
+      const double launch = scores ? sr_rows_work(rf, ph[v]) * W : work / std::max<size_t>(1, pairs.size());
+      // the sums of all others have one order, so they are not cut into parts (SR_ROWS_ORDERED)
+      sr_rows_tiles(rf, {ph[v]}, launch, g->train_tall_from, scores && g->allow_split, true, &t.slots, &tf, &t.shapes);
       t.n = (int)tf.size() - t.tile0;
       t.length = rf.phases[ph[v]].steps * (tf[t.tile0].shape <= SR_F32_128x64 ? 2.0 : 1.0);
     }
@@ -258,7 +260,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
       if (phs[v].empty()) continue;
       NodeTiles& t = nb[v];
       t.tile0 = (int)tb.size();
-      sr_rows_tiles(rb, phs[v], per_launch, g->train_tall_from, g->allow_split, &t.slots, &tb, &t.shapes);
+      sr_rows_tiles(rb, phs[v], per_launch, g->train_tall_from, g->allow_split, false, &t.slots, &tb, &t.shapes);
       t.n = (int)tb.size() - t.tile0;
       for (int f : phs[v]) t.length = std::max(t.length, rb.phases[f].steps * (tb[t.tile0].shape <= SR_F32_128x64 ? 2.0 : 1.0));
     }

@@ -454,3 +454,73 @@ def test_steps_in_pairs_and_single_steps_of_one_tile(channels):
     got, data = run_case(g, 3, seed=43, dev=dev)
     check_against_oracle(g, 3, got, data, f"pairs {channels}")
     dev.close()
+
+
+@pytest.mark.parametrize("tall_from", [0, 2048, 1 << 30])
+@pytest.mark.parametrize("channels", [32, 52, 128])
+@pytest.mark.parametrize("batch", [1, 3, 40, 300])
+def test_sums_of_the_forward_pass_have_one_order(batch, channels, tall_from):
+    # Every edge's sum starts from zero and runs through (tap, channel) step by step of 16; inside a step the products go
+    # 0, 8, 1, 9, .. (channel counts that are multiples of four) or 0, 1, 2, ..; the edges' sums are added in edge order,
+    # whatever the batch and the tiles.  The terms are powers of two chosen so that the order decides whether the
+    # rectifier's input is 0 or 2^-24, i.e. whether any gradient passes: 1 + 2^-24 rounds to 1, 2^-24 - 1 is exact.
+    import torch
+    import paper_1806_04965_amd as sr
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    e = 2.0 ** -24
+    cases = [   # (channels of the two sources, {index: term} of each, does the gradient pass?)
+        ("edge by edge", (20, 20), {0: 1.0}, {0: e, 1: -1.0}, True),
+        ("steps in order", (80, 4), {0: 1.0, 16: e, 64: -1.0}, {}, False),
+        ("0, 8, 1 of a step", (80, 4), {16: 1.0, 24: e, 17: -1.0}, {}, False),
+        ("in turn", (81, 4), {16: 1.0, 24: e, 17: -1.0}, {}, True),
+        ("in turn, steps in order", (81, 4), {0: 1.0, 16: e, 80: -1.0}, {}, False),
+    ]
+    for name, (ca, cb), ta, tb, passes in cases:
+        nodes = [Node("a", ca, 4, 4, ACT_IDENTITY), Node("b", cb, 4, 4, ACT_IDENTITY), Node("h", channels, 4, 4),
+                 Node("out", 3, 1, 1, ACT_IDENTITY)]
+        edges = [Edge(0, 2, "conv", 1, 1, 1, 0), Edge(1, 2, "conv", 1, 1, 1, 0), Edge(2, 3, "gap_dense", 1, 1, 1, 0)]
+        g0 = Graph("order", nodes, edges, batch, 2, "f32", out_node=3)
+        g = g0.with_pattern(W.sequential_pattern(g0))
+        w, b, _ = W.make_case(g, seed=3, frames=2)
+        w = [np.ones_like(w[0]), np.ones_like(w[1]), w[2]]
+        b = [np.zeros_like(v) for v in b]
+        dev = sr.SrGraph(g, options={8: tall_from})
+        dev.set_parameters(w, b)
+        xs = []
+        for c, terms in ((ca, ta), (cb, tb)):
+            x = torch.zeros((3, batch, 4, 4, c), device="cuda")
+            for k, v in terms.items():
+                x[..., k] = v
+            xs.append(x)
+        labels = torch.zeros(batch, dtype=torch.int32, device="cuda")
+        _, _, dbs = dev.window_gradients(xs, labels, 2)
+        d = dbs[2].cpu().numpy()
+        assert (np.abs(d) > 0).all() if passes else (d == 0).all(), (name, d)
+        dev.close()
+
+
+def test_dsr2_window_at_full_size_does_not_depend_on_the_tiles():
+    # The paper's batch size and a window of 8: 5e7 rectifier inputs, some of them zero to float32 accuracy.  Their sums
+    # have one order, so tile shapes, parts and the chunks of the reverse sweep change the gradients by the rounding of
+    # float32 sums only: 2e-6 of a tensor's norm (measured 3e-7), where one rectifier that takes its other derivative is
+    # 1e-5 to 1e-3 of it.
+    import torch
+    import paper_1806_04965_amd as sr
+    g0 = replace(W.dsr_net(2, batch=64, frames=8), dtype="f32")
+    g = g0.with_pattern(W.streaming_pattern(g0))
+    w, b, _ = W.make_case(g, seed=2, bias_scale=0.1, frames=1)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((9, 64, 32, 32, 3), generator=gen, device="cuda")
+    labels = torch.randint(0, 10, (64,), generator=gen, device="cuda", dtype=torch.int32)
+    ref = None
+    for options in ({}, {8: 0}, {8: 1 << 30}, {3: 0, 9: 3}):
+        dev = sr.SrGraph(g, options=options)
+        dev.set_parameters(w, b)
+        loss, dth, dbs = dev.window_gradients([x], labels, 8)
+        got = [loss] + dth + [t for t in dbs if t is not None]
+        got = [t.double().cpu() for t in got]
+        dev.close()
+        if ref is None:
+            ref = got
+        for a, r in zip(got, ref):
+            assert float((a - r).norm()) <= 2e-6 * float(r.norm()), (options, tuple(r.shape), float((a - r).norm() / r.norm()))

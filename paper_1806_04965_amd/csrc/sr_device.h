@@ -56,7 +56,7 @@ template <> struct Store<uint16_t> {
 // have read it).
 typedef const __attribute__((address_space(4))) SrCtx* sr_call_t;
 __device__ __forceinline__ sr_call_t sr_call(const SrFrame& f) {
-  return f.here.frame > 0 ? (sr_call_t)__builtin_amdgcn_kernarg_segment_ptr() : (sr_call_t)(unsigned long long)f.ctx;
+  return f.plain ? (sr_call_t)__builtin_amdgcn_kernarg_segment_ptr() : (sr_call_t)(unsigned long long)f.ctx;
 }
 
 // Called by every workgroup of a launch once its work is stored.  If the launch advances the frame counter, the

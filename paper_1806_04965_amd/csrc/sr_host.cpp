@@ -1474,9 +1474,9 @@ bool record_needs_copy(const sr_graph* g) {
 }
 
 // a launch that brings its call's values along (frame = c.frame) ...
-SrFrame plain_frame(const sr_graph* g, const SrCtx& c) { return SrFrame{c, g->ctx, 0, 0}; }
+SrFrame plain_frame(const sr_graph* g, const SrCtx& c) { return SrFrame{c, g->ctx, 1, 0, 0}; }
 // ... and one recorded into a HIP graph: frame `offset` after the device context's
-SrFrame recorded_frame(const sr_graph* g, int offset, int advance) { return SrFrame{SrCtx{}, g->ctx, offset, advance}; }
+SrFrame recorded_frame(const sr_graph* g, int offset, int advance) { return SrFrame{SrCtx{}, g->ctx, 0, offset, advance}; }
 
 // Start of a call that computes frames: a graph whose input staging runs one frame ahead gets the call's first frame
 // (c.frame) staged here.

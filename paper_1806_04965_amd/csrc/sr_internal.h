@@ -27,11 +27,13 @@ struct SrCtx {
 
 // Which frame a launch computes and where the call's values are.  A launch that is recorded into a HIP graph takes them
 // from the context in device memory (frame = ctx->frame + offset: one recording of n frames serves every n frames of a
-// rollout, its last launch advancing the counter by n); a plain launch brings them along (here.frame > 0), which saves
-// the launch that writes the context and, in the kernel, the round trip to it.
+// rollout, its last launch advancing the counter by n); a plain launch brings them along, which saves the launch that
+// writes the context and, in the kernel, the round trip to it.  Frame numbers wrap: only their parity and their
+// differences are used.
 struct SrFrame {
   SrCtx here;
   SrCtx* ctx;
+  int32_t plain;      // 1: the values are `here`
   int32_t offset;
   int32_t advance;    // > 0: the launch's last workgroup adds this to ctx->frame
 };

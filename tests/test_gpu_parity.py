@@ -528,3 +528,49 @@ def test_reset_copies_frame_0_of_an_input(channels, dtype):
         dev.reset([x])
         assert torch.equal(dev.get_state(0), x)
     dev.close()
+
+
+def set_frame_index(dev, index, tmp_path):
+    """Count `index` frames as computed: the graph object's own counter, found by the offset that a C++ compiler gives it."""
+    import ctypes
+    import os
+    import subprocess
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src, exe = tmp_path / "at.cpp", tmp_path / "at"
+    src.write_text('#include <cstddef>\n#include <cstdio>\n#include "sr_graph.h"\n'
+                   'int main() { std::printf("%zu", offsetof(sr_graph, host_frame)); }\n')
+    subprocess.run(["g++", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", f"{root}/paper_1806_04965_amd/csrc",
+                    str(src), "-o", str(exe)], check=True, timeout=60)
+    at = int(subprocess.run([str(exe)], check=True, capture_output=True, timeout=10).stdout)
+    counter = ctypes.c_int64.from_address(dev.h.value + at)
+    assert counter.value == dev.frame_index()
+    counter.value = index
+
+
+@pytest.mark.parametrize("net", ["f32 streaming", "f32 sequential", "bf16 streaming"])
+def test_frames_past_the_32_bit_frame_counter(net, tmp_path):
+    # a stream that has run for 2^31 - 3 frames (17 hours at 29 us) goes on as one that has just begun: the kernels' 32-bit
+    # frame numbers wrap, inputs are still taken and both copies of a state still alternate
+    import paper_1806_04965_amd as sr
+    dtype, pattern = net.split()
+    g = dataclasses.replace(W.tiny_sr(batch=2, frames=8), dtype=dtype)
+    g = g.with_pattern((W.streaming_pattern if pattern == "streaming" else W.sequential_pattern)(g))
+    w, b, x = W.make_case(g, seed=17, bias_scale=0.1, frames=8)
+    ins = g.input_nodes()
+    xd = [to_device_(x[v], dtype) for v in ins]
+    runs = []
+    for start in (0, 2 ** 31 - 4, 2 ** 32 - 4):     # even: frame 0 of the reset lies in copy 0
+        dev = sr.SrGraph(g, options={5: 0})
+        dev.set_parameters(w, b)
+        dev.reset([t[0] for t in xd])
+        set_frame_index(dev, start, tmp_path)
+        states = []
+        for t in range(1, 9):
+            (dev.frame_step_static if t % 3 == 2 else dev.frame_step)([xi[t] for xi in xd])
+            states += [dev.get_state(v).float().cpu().numpy() for v in range(len(g.nodes))]
+        assert dev.frame_index() == start + 8
+        dev.close()
+        runs.append(states)
+    for other in runs[1:]:
+        for a, c in zip(runs[0], other):
+            np.testing.assert_array_equal(a, c)

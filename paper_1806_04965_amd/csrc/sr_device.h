@@ -55,7 +55,10 @@ template <> struct Store<uint16_t> {
 // Read with scalar loads; constant while the launch runs (the last workgroup advances the frame counter when all others
 // have read it).
 typedef const __attribute__((address_space(4))) SrCtx* sr_call_t;
+// A plain launch, which does not read the counter in memory, puts it right here (at its end, the values that this needs cost
+// the tile kernel registers: CIFAR-shaped frames 28.3 -> 32 us).
 __device__ __forceinline__ sr_call_t sr_call(const SrFrame& f) {
+  if (f.advance < 0 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) f.ctx->frame = f.here.frame - f.advance;
   return f.plain ? (sr_call_t)__builtin_amdgcn_kernarg_segment_ptr() : (sr_call_t)(unsigned long long)f.ctx;
 }
 

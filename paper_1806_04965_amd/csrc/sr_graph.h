@@ -67,6 +67,7 @@ struct sr_graph {
 
   // plan
   bool finalized = false, was_reset = false;
+  bool replayed = false;             // a caller has recorded frames: from then on the device alone counts them
   int64_t host_frame = 0;
   std::vector<LevelPlan> levels;
   std::vector<void*> dev_allocs;     // everything to free

@@ -1473,16 +1473,34 @@ bool record_needs_copy(const sr_graph* g) {
   return true;
 }
 
-// a launch that brings its call's values along (frame = c.frame) ...
-SrFrame plain_frame(const sr_graph* g, const SrCtx& c) { return SrFrame{c, g->ctx, 1, 0, 0}; }
+// a launch that brings its call's values along (frames c.frame ..) ...
+SrFrame plain_frame(const sr_graph* g, const SrCtx& c, int advance) { return SrFrame{c, g->ctx, 1, 0, -advance}; }
 // ... and one recorded into a HIP graph: frame `offset` after the device context's
 SrFrame recorded_frame(const sr_graph* g, int offset, int advance) { return SrFrame{SrCtx{}, g->ctx, 0, offset, advance}; }
 
-// Start of a call that computes frames: a graph whose input staging runs one frame ahead gets the call's first frame
-// (c.frame) staged here.
-sr_status begin_frames(sr_graph* g, const SrCtx& c) {
+// Is the graph's stream being recorded by the caller, or has it been?  A recording may be replayed any number of times, at
+// any time, without the library taking part, so its frames have to be the ones that follow whatever has been computed then:
+// their number, and which copy of a state is the last frame's, is known to the device only.
+bool device_counts(sr_graph* g) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (!g->replayed && g->stream != nullptr && hipStreamIsCapturing(g->stream, &st) == hipSuccess && st == hipStreamCaptureStatusActive)
+    g->replayed = true;
+  return g->replayed;
+}
+
+// Start of a call that computes frames, one at a time in `f` on return (`f` of a rollout's later frames: c.frame is theirs):
+// a graph whose input staging runs one frame ahead gets the call's first frame staged here.
+sr_status begin_frames(sr_graph* g, SrCtx c, bool next_frame, SrFrame* f) {
+  *f = plain_frame(g, c, 1);
+  if (next_frame && device_counts(g)) {
+    c.in_last = INT32_MAX;   // every replay takes what the input buffers hold then
+    SR_HIP(g, sr_launch_set_ctx(g->stream, g->ctx, c));
+    *f = recorded_frame(g, 0, 1);
+  }
+  SrFrame still = *f;
+  still.advance = 0;
   if (g->stage_mode == 1 && !g->dataflow)
-    SR_HIP(g, sr_launch_aux(g->stream, plain_frame(g, c), g->aux + g->stage_aux_begin, g->n_stage_aux, g->heads, g->head_edges,
+    SR_HIP(g, sr_launch_aux(g->stream, still, g->aux + g->stage_aux_begin, g->n_stage_aux, g->heads, g->head_edges,
                             g->stage_nodes, g->aux_smem_bytes, g->dtype == SR_BF16));
   return SR_OK;
 }
@@ -1533,9 +1551,9 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
     if (st != SR_OK) return st;
     if (copy) {
       const NodeRt& n = g->nodes[g->rec_node];
-      SR_HIP(g, sr_launch_record_output(s, still, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
+      SR_HIP(g, sr_launch_record_output(s, f, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
                                         n.d.channels, n.Cp, bf16));
-      if (f.advance > 0) SR_HIP(g, sr_launch_tick(s, g->ctx, f.advance));
+      if (!f.plain) SR_HIP(g, sr_launch_tick(s, g->ctx, f.advance));
     }
     if (ft) SR_HIP(g, hipEventRecord(e1, s));
     return SR_OK;
@@ -1609,9 +1627,9 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
   if (copy_out) {
     SR_HIP(g, mark(4));
     const NodeRt& n = g->nodes[g->rec_node];
-    SR_HIP(g, sr_launch_record_output(s, still, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
+    SR_HIP(g, sr_launch_record_output(s, f, n.state[0], n.state[1], g->batch * n.d.height * n.d.width,
                                       n.d.channels, n.Cp, bf16));
-    if (f.advance > 0) SR_HIP(g, sr_launch_tick(s, g->ctx, f.advance));
+    if (!f.plain && f.advance > 0) SR_HIP(g, sr_launch_tick(s, g->ctx, f.advance));
   }
   SR_HIP(g, mark(-1));
   return SR_OK;
@@ -1642,8 +1660,8 @@ sr_status ensure_graph(sr_graph* g) {
   return SR_OK;
 }
 
-// `frames` frames from c.frame on.  ctx_set: the device context already holds c.
-sr_status run_frames(sr_graph* g, int64_t frames, SrCtx c, bool ctx_set) {
+// A rollout's `frames` frames from c.frame on (the device context holds c), or, next_frame, the frame that `first` is.
+sr_status run_frames(sr_graph* g, int64_t frames, SrCtx c, bool next_frame, const SrFrame& first) {
   sr_status st = ensure_split_scratch(g);
   if (st != SR_OK) return st;
   const SrSplitScratch own{g->split_scratch, g->split_counters};
@@ -1653,9 +1671,8 @@ sr_status run_frames(sr_graph* g, int64_t frames, SrCtx c, bool ctx_set) {
   // take longer replayed (16 streaming frames: 500 us for 486, CIFAR-shaped; 289 for 282, MNIST SR), of two or four
   // too (453 for 417, MNIST SR hybrid; 1214 for 1140, DSR4 hybrid), and with eight (DSR4 sequential) the time is the
   // same within 2 % while the host is busy for 209 us instead of 1222.
-  if (g->use_hipgraph && !flow && g->launches_per_frame > 4 && left >= g->frames_per_graph && g->frames_per_graph > 1) {
+  if (g->use_hipgraph && !flow && !next_frame && g->launches_per_frame > 4 && left >= g->frames_per_graph && g->frames_per_graph > 1) {
     if ((st = ensure_graph(g)) != SR_OK) return st;
-    if (!ctx_set) SR_HIP(g, sr_launch_set_ctx(g->stream, g->ctx, c, 0));
     for (; left >= g->frames_per_graph; left -= g->frames_per_graph) {
       SR_HIP(g, hipGraphLaunch(g->exec, g->stream));
       c.frame += g->frames_per_graph;
@@ -1663,7 +1680,8 @@ sr_status run_frames(sr_graph* g, int64_t frames, SrCtx c, bool ctx_set) {
   }
   while (left > 0) {
     const int n = flow ? (int)std::min<int64_t>(left, g->frames_per_graph) : 1;
-    st = flow ? enqueue_flow(g, n, plain_frame(g, c), own) : enqueue_frame(g, true, nullptr, own, plain_frame(g, c));
+    const SrFrame f = next_frame ? first : plain_frame(g, c, n);
+    st = flow ? enqueue_flow(g, n, f, own) : enqueue_frame(g, true, nullptr, own, f);
     if (st != SR_OK) return st;
     left -= n;
     c.frame += n;
@@ -2070,11 +2088,9 @@ sr_status sr_frame_step(sr_graph* g, const void* const* inputs_t) {
   }
   c.out_ptr = nullptr;
   c.frame = c.in_last = (int32_t)(g->host_frame + 1);   // the frame computed now is the last one with input
-  {
-    sr_status st = begin_frames(g, c);
-    if (st != SR_OK) return st;
-  }
-  return run_frames(g, 1, c, false);
+  SrFrame f;
+  sr_status st = begin_frames(g, c, true, &f);
+  return st != SR_OK ? st : run_frames(g, 1, c, true, f);
 }
 
 sr_status sr_frame_step_static(sr_graph* g, const void* const* inputs_t) {
@@ -2106,9 +2122,10 @@ sr_status sr_frame_step_static(sr_graph* g, const void* const* inputs_t) {
     // (a fill kernel, not a memset: the caller may be capturing the stream)
     SR_HIP(g, sr_launch_fill_zero(g->stream, split.counters, (size_t)g->n_split_slots * sizeof(int32_t)));
   }
-  sr_status st = begin_frames(g, c);
+  SrFrame f;
+  sr_status st = begin_frames(g, c, true, &f);
   if (st != SR_OK) return st;
-  st = enqueue_frame(g, true, nullptr, split, plain_frame(g, c));   // plain launches: nothing is captured or instantiated
+  st = enqueue_frame(g, true, nullptr, split, f);   // plain launches: nothing is captured or instantiated
   if (st != SR_OK) return st;
   g->host_frame += 1;
   return SR_OK;
@@ -2140,8 +2157,9 @@ sr_status sr_rollout(sr_graph* g, const void* const* inputs, int32_t T, int32_t 
   sr_status st = do_reset(g, frame0, c);
   if (st != SR_OK) return st;
   if ((st = set_record_node(g, outputs ? out_node : -1)) != SR_OK) return st;
-  if ((st = begin_frames(g, c)) != SR_OK) return st;
-  return run_frames(g, T, c, true);
+  SrFrame f;
+  if ((st = begin_frames(g, c, false, &f)) != SR_OK) return st;
+  return run_frames(g, T, c, false, f);
 }
 
 sr_status sr_get_state(const sr_graph* g, int32_t node, void* dst_device, size_t bytes) {
@@ -2150,8 +2168,9 @@ sr_status sr_get_state(const sr_graph* g, int32_t node, void* dst_device, size_t
   const NodeRt& n = g->nodes[node];
   const size_t want = (size_t)g->batch * n.d.height * n.d.width * n.d.channels * elem_size(g);
   if (bytes != want) return gfail(gm, SR_ERR_ARG, "sr_get_state: expected " + std::to_string(want) + " bytes");
-  SR_HIP(gm, sr_launch_pack(g->stream, dst_device, n.state[g->host_frame & 1], g->batch * n.d.height * n.d.width,
-                            n.d.channels, n.Cp, g->dtype == SR_BF16, 1));
+  const bool by_device = device_counts(gm);
+  SR_HIP(gm, sr_launch_pack(g->stream, by_device ? g->ctx : nullptr, n.state[by_device ? 0 : g->host_frame & 1], n.state[1], dst_device,
+                            g->batch * n.d.height * n.d.width, n.d.channels, n.Cp, g->dtype == SR_BF16, 1));
   return SR_OK;
 }
 
@@ -2160,8 +2179,9 @@ sr_status sr_set_state(sr_graph* g, int32_t node, const void* src_device, size_t
   const NodeRt& n = g->nodes[node];
   const size_t want = (size_t)g->batch * n.d.height * n.d.width * n.d.channels * elem_size(g);
   if (bytes != want) return gfail(g, SR_ERR_ARG, "sr_set_state: expected " + std::to_string(want) + " bytes");
-  SR_HIP(g, sr_launch_pack(g->stream, n.state[g->host_frame & 1], src_device, g->batch * n.d.height * n.d.width,
-                           n.d.channels, n.Cp, g->dtype == SR_BF16, 0));
+  const bool by_device = device_counts(g);
+  SR_HIP(g, sr_launch_pack(g->stream, by_device ? g->ctx : nullptr, n.state[by_device ? 0 : g->host_frame & 1], n.state[1],
+                           const_cast<void*>(src_device), g->batch * n.d.height * n.d.width, n.d.channels, n.Cp, g->dtype == SR_BF16, 0));
   return SR_OK;
 }
 
@@ -2181,12 +2201,13 @@ sr_status sr_frame_step_timed(sr_graph* g, const void* const* inputs_t, float* k
     c.in_ptr[i] = inputs_t[i];
   }
   c.frame = c.in_last = (int32_t)(g->host_frame + 1);
-  sr_status st = begin_frames(g, c);
+  SrFrame f;
+  sr_status st = begin_frames(g, c, true, &f);
   if (st != SR_OK) return st;
   FrameTimer ft;
   st = ensure_split_scratch(g);
   if (st != SR_OK) return st;
-  st = enqueue_frame(g, false, &ft, SrSplitScratch{g->split_scratch, g->split_counters}, plain_frame(g, c));
+  st = enqueue_frame(g, false, &ft, SrSplitScratch{g->split_scratch, g->split_counters}, f);
   hipError_t he = hipStreamSynchronize(g->stream);
   int n = 0;
   if (st == SR_OK && he == hipSuccess) {

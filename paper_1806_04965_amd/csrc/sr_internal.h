@@ -28,14 +28,15 @@ struct SrCtx {
 // Which frame a launch computes and where the call's values are.  A launch that is recorded into a HIP graph takes them
 // from the context in device memory (frame = ctx->frame + offset: one recording of n frames serves every n frames of a
 // rollout, its last launch advancing the counter by n); a plain launch brings them along, which saves the launch that
-// writes the context and, in the kernel, the round trip to it.  Frame numbers wrap: only their parity and their
+// writes the context and, in the kernel, the round trip to it.  Either way ctx->frame is the next frame once the frame's
+// last launch is done, so that recorded frames can follow plain ones.  Frame numbers wrap: only their parity and their
 // differences are used.
 struct SrFrame {
   SrCtx here;
   SrCtx* ctx;
   int32_t plain;      // 1: the values are `here`
   int32_t offset;
-  int32_t advance;    // > 0: the launch's last workgroup adds this to ctx->frame
+  int32_t advance;    // frames that ctx->frame goes on by: > 0 recorded, the last workgroup adds them; < 0 plain
 };
 
 // ---------------------------------------------------------------------------
@@ -293,13 +294,16 @@ struct SrResetItem {
 };
 
 // launch wrappers (sr_kernels.hip); each returns the hipError_t of the launch
-hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values, int clear);
+// a call's values into the context, but for what the device counts (frame, dep_timeouts)
+hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values);
 // also ctx := values
 hipError_t sr_launch_reset(hipStream_t s, SrCtx* ctx, const SrCtx& values, const SrResetItem* items, int n_items, int n_blocks,
                            const void* const* frame0, int bf16);
 hipError_t sr_launch_tick(hipStream_t s, SrCtx* ctx, int frames);
 hipError_t sr_launch_fill_zero(hipStream_t s, void* p, size_t bytes);
-hipError_t sr_launch_pack(hipStream_t s, void* dst, const void* src, int px, int C, int Cp, int bf16, int unpack);
+// dense [px][C] -> pitched [px][Cp], unpack: the other way.  ctx: the pitched side is copy0 or copy1, whichever holds the
+// last frame computed by the device's count; null: copy0.
+hipError_t sr_launch_pack(hipStream_t s, const SrCtx* ctx, void* copy0, void* copy1, void* dense, int px, int C, int Cp, int bf16, int unpack);
 hipError_t sr_launch_record_output(hipStream_t s, const SrFrame& f, const void* state0, const void* state1,
                                    int px, int C, int Cp, int bf16);
 hipError_t sr_launch_aux(hipStream_t s, const SrFrame& f, const SrAux* aux, int n_aux, const SrHead* heads,

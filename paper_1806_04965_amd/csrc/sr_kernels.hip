@@ -19,9 +19,10 @@
 // ---------------------------------------------------------------------------
 // bookkeeping kernels
 // ---------------------------------------------------------------------------
-__global__ void sr_set_ctx_kernel(SrCtx* ctx, SrCtx v, int clear) {
+__global__ void sr_set_ctx_kernel(SrCtx* ctx, SrCtx v) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    if (!clear) v.dep_timeouts = ctx->dep_timeouts;   // counted since the last reset
+    v.frame = ctx->frame;   // both counted since the last reset
+    v.dep_timeouts = ctx->dep_timeouts;
     *ctx = v;
   }
 }
@@ -94,7 +95,11 @@ __global__ void sr_fill_zero_kernel(uint4* p, size_t n16, unsigned char* tail, s
 
 // dense [px][C]  <->  pitched [px][Cp]
 template <typename T>
-__global__ void sr_pack_kernel(T* __restrict__ dst, const T* __restrict__ src, int px, int C, int Cp, int unpack) {
+__global__ void sr_pack_kernel(const SrCtx* __restrict__ ctx, T* __restrict__ copy0, T* __restrict__ copy1, T* __restrict__ dense, int px,
+                               int C, int Cp, int unpack) {
+  T* const pitched = ctx != nullptr && ((ctx->frame - 1) & 1) ? copy1 : copy0;
+  T* const dst = unpack ? dense : pitched;
+  const T* const src = unpack ? pitched : dense;
   const int total = unpack ? px * C : px * Cp;
   for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += gridDim.x * blockDim.x) {
     if (unpack) {
@@ -1074,8 +1079,8 @@ static inline int blocks_for(long long n, int per) {
   return (int)b;
 }
 
-hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values, int clear) {
-  hipLaunchKernelGGL(sr_set_ctx_kernel, dim3(1), dim3(64), 0, s, ctx, values, clear);
+hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values) {
+  hipLaunchKernelGGL(sr_set_ctx_kernel, dim3(1), dim3(64), 0, s, ctx, values);
   return hipGetLastError();
 }
 
@@ -1126,13 +1131,13 @@ hipError_t sr_launch_aux(hipStream_t s, const SrFrame& f, const SrAux* aux, int 
   return hipGetLastError();
 }
 
-hipError_t sr_launch_pack(hipStream_t s, void* dst, const void* src, int px, int C, int Cp, int bf16, int unpack) {
+hipError_t sr_launch_pack(hipStream_t s, const SrCtx* ctx, void* copy0, void* copy1, void* dense, int px, int C, int Cp, int bf16, int unpack) {
   long long total = (long long)px * (unpack ? C : Cp);
   if (total == 0) return hipSuccess;
   int nb = blocks_for(total, 256 * 4);
   if (nb > 2048) nb = 2048;
-  if (bf16) hipLaunchKernelGGL(sr_pack_kernel<uint16_t>, dim3(nb), dim3(256), 0, s, (uint16_t*)dst, (const uint16_t*)src, px, C, Cp, unpack);
-  else hipLaunchKernelGGL(sr_pack_kernel<float>, dim3(nb), dim3(256), 0, s, (float*)dst, (const float*)src, px, C, Cp, unpack);
+  if (bf16) hipLaunchKernelGGL(sr_pack_kernel<uint16_t>, dim3(nb), dim3(256), 0, s, ctx, (uint16_t*)copy0, (uint16_t*)copy1, (uint16_t*)dense, px, C, Cp, unpack);
+  else hipLaunchKernelGGL(sr_pack_kernel<float>, dim3(nb), dim3(256), 0, s, ctx, (float*)copy0, (float*)copy1, (float*)dense, px, C, Cp, unpack);
   return hipGetLastError();
 }
 

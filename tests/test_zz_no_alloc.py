@@ -111,3 +111,89 @@ def test_static_scratch_refuses_what_does_not_fit():
     assert dev.frame_index() == 1
     assert float(dev.get_state(n_in + 1).float().abs().max()) > 0
     dev.close()
+
+
+GRAPHS = {
+    "bf16 streaming": lambda: W.cifar_sr(batch=2, frames=9),
+    "bf16 sequential, dependency-driven": lambda: _with(W.cifar_sr(batch=2, frames=9), W.sequential_pattern),
+    "bf16 hybrid, a launch per update step": lambda: _with(W.cifar_sr(batch=2, frames=9), W.hybrid_pattern),
+    "f32 streaming": lambda: W.tiny_sr(batch=2, frames=9),
+    "f32 sequential": lambda: _with(W.tiny_sr(batch=2, frames=9), W.sequential_pattern),
+}
+
+
+def _with(g, pattern):
+    return g.with_pattern(pattern(g))
+
+
+@pytest.mark.parametrize("hidden_node_recorded", [False, True])
+@pytest.mark.parametrize("calls", [1, 2])
+@pytest.mark.parametrize("name", list(GRAPHS))
+def test_replays_of_recorded_calls_go_on_with_the_stream(name, calls, hidden_node_recorded):
+    # `calls` frames recorded once and replayed, the caller's input buffer refilled before each replay, with frames of
+    # ordinary calls and other GPU work between the replays: every node after every frame as without recording, bit for bit
+    import torch
+    import paper_1806_04965_amd as sr
+    g = GRAPHS[name]()
+    T = 9
+    w, b, x = W.make_case(g, seed=21, bias_scale=0.1, frames=T)
+    xd = [to_device(x[v], g.dtype) for v in g.input_nodes()]
+    options = {5: 0} if "launch per" in name else None
+    ref, dev = sr.SrGraph(g, options=options), sr.SrGraph(g, options=options)
+    for d in (ref, dev):
+        d.set_parameters(w, b)
+        if hidden_node_recorded:     # leaves the graph with a copy launch behind every frame
+            out = torch.empty((1, g.batch, g.nodes[1].height, g.nodes[1].width, g.nodes[1].channels), dtype=d.tdtype, device="cuda")
+            d.rollout([t[:2].contiguous() for t in xd], 1, 1, out)
+            d.synchronize()
+        d.reset([t[0] for t in xd])
+    buf = [[t[0].clone() for t in xd] for _ in range(calls)]
+    recording = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(recording, stream=dev.stream):
+        for k in range(calls):
+            dev.frame_step_static(buf[k])
+    t = 0
+
+    def same(t):
+        for v in range(len(g.nodes)):
+            assert torch.equal(dev.get_state(v), ref.get_state(v)), (name, t, v)
+
+    def eager(t):
+        ref.frame_step([xi[t] for xi in xd])
+
+    while t + calls < T:
+        for k in range(calls):
+            for dst, src in zip(buf[k], xd):
+                dst.copy_(src[t + 1 + k])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(dev.stream):
+            recording.replay()
+        torch.cuda.synchronize()
+        for _ in range(calls):
+            t += 1
+            eager(t)
+        ref.synchronize()
+        same(t)
+        torch.ones(1 << 20, device="cuda").cumsum(0)
+        if t in (3, 4, 7):            # an ordinary call between two replays
+            t += 1
+            (dev.frame_step if t % 2 else dev.frame_step_static)([xi[t] for xi in xd])
+            eager(t)
+            ref.synchronize()
+            dev.synchronize()
+            same(t)
+    state = ref.get_state(1)          # set_state goes to the copy the next frame reads
+    dev.set_state(1, state)
+    ref.set_state(1, state)
+    same(t)
+    assert dev.health()["dependency_timeouts"] == 0
+    dev.reset([xi[0] for xi in xd])
+    ref.reset([xi[0] for xi in xd])
+    dev.frame_step([xi[1] for xi in xd])
+    eager(1)
+    ref.synchronize()
+    dev.synchronize()
+    same(1)
+    ref.close()
+    dev.close()

@@ -193,7 +193,9 @@ sr_status sr_graph_set_weights(sr_graph* g, int32_t edge, const float* host_w, s
 /* Channel-wise bias b_v of a node, host float [C]; default 0; kept in float. */
 sr_status sr_graph_set_bias(sr_graph* g, int32_t node, const float* host_b, size_t count);
 
-/* Options (see sr_option); must be called before the first sr_reset. */
+/* Options (see sr_option); must be called before the graph is planned (by the first sr_reset, sr_graph_info with
+ * launches_per_frame, ...): SR_ERR_STATE after that.  Training windows do not plan the graph's frames: on a graph that is
+ * only trained an option set between two windows holds from the next one on. */
 sr_status sr_graph_configure(sr_graph* g, int32_t option, int64_t value);
 
 /* Inference factor and tableau of the graph's pattern (as sr_analyze), plus the number of

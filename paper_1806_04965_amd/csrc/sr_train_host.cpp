@@ -48,7 +48,10 @@ struct SrTrainState {
     const SrGradTile* tiles = nullptr;
     const SrGradSum* sums = nullptr;
   };
-  int W = 0, out = -1, ring = 0;
+  // what the plan was made for: window size, out node, and the options that it went by
+  int W = 0, out = -1, tall_from = 0, frames_kept = 0;
+  bool split = false;
+  int ring = 0;
   std::vector<Launch> fwd;
   std::vector<Chunk> chunks;
   SrTrainIds ids;
@@ -364,6 +367,9 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
   T.ring = ring;
   T.ids = ids;
   T.out = out_node;
+  T.tall_from = g->train_tall_from;
+  T.frames_kept = g->train_frames_kept;
+  T.split = g->allow_split;
   T.W = W;
   return SR_OK;
 }
@@ -391,7 +397,7 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
   if (!sr_rows_take_training(g))
     return sr_gfail(g, SR_ERR_ARG, "sr_window_gradients: a node or weight tensor of 2^31 or more elements per tile");
   SrTrainState& T = train_state(g);
-  if (T.W != W || T.out != out_node) {
+  if (T.W != W || T.out != out_node || T.tall_from != g->train_tall_from || T.frames_kept != g->train_frames_kept || T.split != g->allow_split) {
     sr_status st = make_plan(g, T, W, out_node);
     if (st != SR_OK) return st;
   }

@@ -524,3 +524,32 @@ def test_dsr2_window_at_full_size_does_not_depend_on_the_tiles():
             ref = got
         for a, r in zip(got, ref):
             assert float((a - r).norm()) <= 2e-6 * float(r.norm()), (options, tuple(r.shape), float((a - r).norm() / r.norm()))
+
+
+@pytest.mark.parametrize("option, value", [(9, 1), (8, 0), (3, 0)])
+def test_options_set_between_two_windows(option, value):
+    # frames kept, tall tiles and parts belong to the plan that a graph keeps for its windows: set after one window they hold
+    # from the next one on, which gives the bits of a graph that had them from the start -- and not those of the first window
+    # (the sums are cut in other places)
+    import torch
+    import paper_1806_04965_amd as sr
+    g0 = W.mnist_net("SR", batch=128, frames=4)
+    g = g0.with_pattern(W.sequential_pattern(g0))
+    w, b, x = W.make_case(g, seed=41, bias_scale=0.1, frames=4, recipe="uniform")
+    xd = [to_device(x[0], "f32")]
+    labels = torch.arange(128, device="cuda", dtype=torch.int32) % 10
+
+    def window(dev):
+        loss, dth, dbs = dev.window_gradients(xd, labels, 4)
+        return torch.cat([t.flatten() for t in dth + [t for t in dbs if t is not None]])
+
+    dev, fresh = sr.SrGraph(g), sr.SrGraph(g, options={option: value})
+    for d in (dev, fresh):
+        d.set_parameters(w, b)
+    before = window(dev)
+    dev.configure(option, value)
+    after, want = window(dev), window(fresh)
+    assert torch.equal(after, want)
+    assert not torch.equal(after, before)
+    dev.close()
+    fresh.close()

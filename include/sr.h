@@ -336,10 +336,10 @@ sr_status sr_graph_node_kernels(const sr_graph* g, int32_t* kinds);
  *             of input nodes are ignored, a NULL entry skips that node
  * fp32 arithmetic; every sum is taken in a fixed order (no floating-point atomics): the same call
  * gives the same bits.  Device memory for the window's states and
- * gradients (about (2 W + 1) x the graph's node states, plus scratch; see SR_OPT_TRAIN_FRAMES_KEPT) is allocated by
- * the call, kept by the graph and reused by later calls; a window size or out_node other than the last call's makes
- * the call wait for the stream while its plan is made.  Asynchronous: the results are complete in the order of the
- * graph's stream; the host arrays are consumed before the call returns.  Every kernel is launched by the
+ * gradients (about (2 W + 1) x the graph's node states, plus scratch; see SR_OPT_TRAIN_FRAMES_KEPT) is allocated by the call, kept by the graph and reused by later calls.  The plans of the last
+ * four combinations of window size, out_node and options are kept too; another one is made, which allocates its tables,
+ * and waits for the stream if the memory has to grow or a fifth plan to go.  Asynchronous: the results are complete in the
+ * order of the graph's stream; the host arrays are consumed before the call returns.  Every kernel is launched by the
  * call itself (SR_OPT_USE_HIPGRAPH concerns the frame path only).  No optimiser step is taken.
  * Errors: SR_ERR_ARG, SR_ERR_STATE (weights missing), SR_ERR_OOM, SR_ERR_DEVICE. */
 sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs, const float* const* masks,

@@ -134,7 +134,8 @@ struct sr_graph {
   // rollout output recording (set per call)
   int rec_node = -1;
 
-  // what the training window keeps between calls (arena, plan, RMSprop's running means): made on first use and released by sr_train_state_release, both in sr_train_host.cpp
+  // what training windows keep between calls (arena, plans, RMSprop's running means): made on first use and released by
+  // sr_train_state_release, both in sr_train_host.cpp
   struct SrTrainState* train = nullptr;
   int train_tall_from = 2048;   // SR_OPT_TRAIN_TALL_TILES_FROM
   int train_frames_kept = 0;    // SR_OPT_TRAIN_FRAMES_KEPT

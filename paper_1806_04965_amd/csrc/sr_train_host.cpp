@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -27,14 +28,15 @@
 #include "sr_graph.h"
 #include "sr_internal.h"
 
-// what a graph keeps for its training windows between calls
-struct SrTrainState {
-  // one arena: the states of the frames 1..W, the state gradients of a chunk of frames, and scratch
-  float* arena = nullptr;
-  size_t arena_floats = 0;
-  std::vector<float*> rms_w, rms_b;   // RMSprop's running mean of the squared gradient, per edge / node (on first use)
-
-  // the plan of windows of W frames with the loss at node `out` (device tables in one allocation)
+// The plan of windows of W frames with the loss at node `out`: device tables in one allocation, offsets into the arena.
+struct SrTrainPlan {
+  struct Key {   // what it was made for, and the options that it went by
+    int W, out, tall_from, frames_kept;
+    bool split;
+    bool operator==(const Key& o) const {
+      return W == o.W && out == o.out && tall_from == o.tall_from && frames_kept == o.frames_kept && split == o.split;
+    }
+  };
   struct Launch {
     int run0 = 0, n_runs = 0, blocks = 0, shapes = 0;
     std::vector<std::pair<SrPool, std::pair<int, int>>> pools;   // before it: means of (first frame, number of frames)
@@ -48,9 +50,7 @@ struct SrTrainState {
     const SrGradTile* tiles = nullptr;
     const SrGradSum* sums = nullptr;
   };
-  // what the plan was made for: window size, out node, and the options that it went by
-  int W = 0, out = -1, tall_from = 0, frames_kept = 0;
-  bool split = false;
+  Key key{};
   int ring = 0;
   std::vector<Launch> fwd;
   std::vector<Chunk> chunks;
@@ -63,12 +63,29 @@ struct SrTrainState {
   float** dst = nullptr;
   const SrRun* runs = nullptr;
   SrRowArgs rows_fwd{}, rows_back{};
+  SrTrainPlan() = default;
+  SrTrainPlan(const SrTrainPlan&) = delete;
+  ~SrTrainPlan() {
+    if (tables) hipFree(tables);
+  }
 };
+
+// what a graph keeps for its training windows between calls
+struct SrTrainState {
+  // one arena: the states of the frames 1..W, the state gradients of a chunk of frames, and scratch
+  float* arena = nullptr;
+  size_t arena_floats = 0;
+  std::vector<float*> rms_w, rms_b;   // RMSprop's running mean of the squared gradient, per edge / node (on first use)
+  // Plans, the last one used first; all work in the one arena, one window at a time.  Making a plan takes up to some
+  // milliseconds of the host; programs that alternate window sizes or out nodes use a few.
+  std::vector<std::unique_ptr<SrTrainPlan>> plans;
+};
+constexpr size_t kTrainPlans = 4;
 
 void sr_train_state_release(SrTrainState* t) {
   if (!t) return;
+  t->plans.clear();
   if (t->arena) hipFree(t->arena);
-  if (t->tables) hipFree(t->tables);
   delete t;
 }
 
@@ -104,13 +121,13 @@ struct NodeTiles { int tile0 = 0, n = 0, slots = 0, shapes = 0; double length = 
 
 // the launches of pairs[depth]; returns the split slots the largest one needs
 int make_launches(const std::vector<std::vector<std::pair<int, int>>>& pairs, const std::vector<NodeTiles>& tiles,
-                  std::vector<SrRun>* runs, std::vector<SrTrainState::Launch>* out) {
+                  std::vector<SrRun>* runs, std::vector<SrTrainPlan::Launch>* out) {
   int most = 0;
   for (auto level : pairs) {   // (frame, node)
     std::stable_sort(level.begin(), level.end(), [&](const std::pair<int, int>& a, const std::pair<int, int>& b) {
       return tiles[a.second].length > tiles[b.second].length;
     });
-    SrTrainState::Launch l;
+    SrTrainPlan::Launch l;
     l.run0 = (int)runs->size();
     int slots = 0;
     for (const auto& fv : level) {
@@ -127,11 +144,8 @@ int make_launches(const std::vector<std::vector<std::pair<int, int>>>& pairs, co
   return most;
 }
 
-sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
-  const int N = g->n_nodes, E = g->n_edges, B = g->batch;
-  T.W = 0;
-  T.fwd.clear();
-  T.chunks.clear();
+sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainPlan::Key& key) {
+  const int N = g->n_nodes, E = g->n_edges, B = g->batch, W = key.W, out_node = key.out;
   SrTrainIds ids;
   ids.grad0 = N;
   ids.mask0 = 2 * N;
@@ -175,7 +189,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
     most_pixels = std::max<int64_t>(most_pixels, (int64_t)B * g->nodes[v].d.height * g->nodes[v].d.width);
   }
   int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(W, std::min<int64_t>(kGradRingBytes / 4 / frame_floats, (1 << 30) / most_pixels)));
-  if (g->train_frames_kept > 0) chunk = std::min(chunk, g->train_frames_kept);
+  if (key.frames_kept > 0) chunk = std::min(chunk, key.frames_kept);
   const int ring = chunk + 1;
   const size_t x_at = take(frame_floats * W), dx_at = take(frame_floats * ring);
   const size_t seed_at = take((size_t)W * B * g->nodes[out_node].d.channels);
@@ -225,7 +239,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
       const bool scores = v == out_node && T.out_is_sink;
       const double launch = scores ? sr_rows_work(rf, ph[v]) * W : work / std::max<size_t>(1, pairs.size());
       // the sums of all others have one order, so they are not cut into parts (SR_ROWS_ORDERED)
-      sr_rows_tiles(rf, {ph[v]}, launch, g->train_tall_from, scores && g->allow_split, true, &t.slots, &tf, &t.shapes);
+      sr_rows_tiles(rf, {ph[v]}, launch, key.tall_from, scores && key.split, true, &t.slots, &tf, &t.shapes);
       t.n = (int)tf.size() - t.tile0;
       t.length = rf.phases[ph[v]].steps * (tf[t.tile0].shape <= SR_F32_128x64 ? 2.0 : 1.0);
     }
@@ -263,13 +277,13 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
       if (phs[v].empty()) continue;
       NodeTiles& t = nb[v];
       t.tile0 = (int)tb.size();
-      sr_rows_tiles(rb, phs[v], per_launch, g->train_tall_from, g->allow_split, false, &t.slots, &tb, &t.shapes);
+      sr_rows_tiles(rb, phs[v], per_launch, key.tall_from, key.split, false, &t.slots, &tb, &t.shapes);
       t.n = (int)tb.size() - t.tile0;
       for (int f : phs[v]) t.length = std::max(t.length, rb.phases[f].steps * (tb[t.tile0].shape <= SR_F32_128x64 ? 2.0 : 1.0));
     }
     std::vector<int> rev(order.rbegin(), order.rend());   // readers of the same frame first
     for (int hi = W; hi >= 1; hi -= chunk) {
-      SrTrainState::Chunk c;
+      SrTrainPlan::Chunk c;
       c.hi = hi;
       c.lo = std::max(1, hi - chunk + 1);
       std::vector<std::vector<int>> db(c.hi - c.lo + 2, std::vector<int>(N, 0));
@@ -287,29 +301,28 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
           put(d, i, v);
         }
       slots = std::max(slots, make_launches(pairs, nb, &runs, &c.back));
-      sr_grad_plan(&c.grad, g, ids, W, c.lo, c.hi, hi == W, g->train_tall_from);
+      sr_grad_plan(&c.grad, g, ids, W, c.lo, c.hi, hi == W, key.tall_from);
       T.chunks.push_back(std::move(c));
     }
   }
   long long part_floats = 0;
-  for (const SrTrainState::Chunk& c : T.chunks) part_floats = std::max(part_floats, c.grad.part_floats);
+  for (const SrTrainPlan::Chunk& c : T.chunks) part_floats = std::max(part_floats, c.grad.part_floats);
   const size_t part_at = take((size_t)part_floats);
-  const size_t slab_at = take((size_t)slots * 1024), counter_at = take((size_t)slots);
+  const size_t slab_at = take((size_t)slots * 1024);
 
-  // what an earlier plan has in flight still uses its tables and the arena
-  SR_HIP(g, hipStreamSynchronize(g->stream));
-  if (T.tables) SR_HIP(g, hipFree(T.tables));
-  T.tables = nullptr;
-  if (at > T.arena_floats) {
-    if (T.arena) SR_HIP(g, hipFree(T.arena));
-    T.arena = nullptr;
-    T.arena_floats = 0;
+  if (at > S.arena_floats) {
+    // what is in flight still uses the arena, and the tables of the other plans hold its address
+    SR_HIP(g, hipStreamSynchronize(g->stream));
+    S.plans.clear();
+    if (S.arena) SR_HIP(g, hipFree(S.arena));
+    S.arena = nullptr;
+    S.arena_floats = 0;
     void* p = nullptr;
     SR_HIP(g, hipMalloc(&p, at * sizeof(float)));
-    T.arena = (float*)p;
-    T.arena_floats = at;
+    S.arena = (float*)p;
+    S.arena_floats = at;
   }
-  float* A = T.arena;
+  float* A = S.arena;
   auto tensor = [&](size_t offset, size_t floats_per_frame, int frame_of_slot0) {
     const long long stride = (long long)floats_per_frame * 4;
     return SrTensor{(char*)(A + offset) - stride * frame_of_slot0, stride};
@@ -329,15 +342,15 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
   const size_t o_fn = blob.add(rf.nodes), o_fp = blob.add(rf.phases), o_fs = blob.add(rf.segs), o_ft = blob.add(tf);
   const size_t o_bn = blob.add(rb.nodes), o_bp = blob.add(rb.phases), o_bs = blob.add(rb.segs), o_bt = blob.add(tb);
   std::vector<std::vector<size_t>> o_chunk;
-  for (const SrTrainState::Chunk& c : T.chunks)
+  for (const SrTrainPlan::Chunk& c : T.chunks)
     o_chunk.push_back({blob.add(c.grad.edges), blob.add(c.grad.biases), blob.add(c.grad.tiles), blob.add(c.grad.sums)});
+  const size_t o_counters = blob.add(std::vector<int32_t>(slots, 0));   // zero between launches
   SR_HIP(g, hipMalloc(&T.tables, blob.bytes.size()));
   SR_HIP(g, hipMemcpy(T.tables, blob.bytes.data(), blob.bytes.size(), hipMemcpyHostToDevice));
   unsigned char* base = (unsigned char*)T.tables;
   T.tensors = (SrTensor*)(base + o_tensors);
   T.dst = (float**)(base + o_dst);
-  SrSplitScratch split{A + slab_at, (int32_t*)(A + counter_at)};
-  if (slots > 0) SR_HIP(g, sr_launch_fill_zero(g->stream, split.counters, (size_t)slots * sizeof(int32_t)));
+  SrSplitScratch split{A + slab_at, (int32_t*)(base + o_counters)};
   SrRowArgs a{};
   a.tensors = T.tensors;
   a.window = W;
@@ -356,7 +369,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
   T.rows_back.segs = (const SrSeg*)(base + o_bs);
   T.rows_back.tiles = (const SrRowTile*)(base + o_bt);
   for (size_t k = 0; k < T.chunks.size(); ++k) {
-    SrTrainState::Chunk& c = T.chunks[k];
+    SrTrainPlan::Chunk& c = T.chunks[k];
     c.edges = (const SrGradEdge*)(base + o_chunk[k][0]);
     c.biases = (const SrGradBias*)(base + o_chunk[k][1]);
     c.tiles = (const SrGradTile*)(base + o_chunk[k][2]);
@@ -366,11 +379,27 @@ sr_status make_plan(sr_graph* g, SrTrainState& T, int W, int out_node) {
   T.part = A + part_at;
   T.ring = ring;
   T.ids = ids;
-  T.out = out_node;
-  T.tall_from = g->train_tall_from;
-  T.frames_kept = g->train_frames_kept;
-  T.split = g->allow_split;
-  T.W = W;
+  T.key = key;
+  return SR_OK;
+}
+
+// The plan of a call: one that is kept, or a new one.
+sr_status plan_for(sr_graph* g, SrTrainState& S, const SrTrainPlan::Key& key, SrTrainPlan** out) {
+  for (size_t k = 0; k < S.plans.size(); ++k)
+    if (S.plans[k]->key == key) {
+      std::rotate(S.plans.begin(), S.plans.begin() + k, S.plans.begin() + k + 1);
+      *out = S.plans[0].get();
+      return SR_OK;
+    }
+  if (S.plans.size() >= kTrainPlans) {
+    SR_HIP(g, hipStreamSynchronize(g->stream));   // its tables may still be in use
+    S.plans.pop_back();
+  }
+  std::unique_ptr<SrTrainPlan> p(new SrTrainPlan());
+  const sr_status st = make_plan(g, S, *p, key);
+  if (st != SR_OK) return st;
+  S.plans.insert(S.plans.begin(), std::move(p));
+  *out = S.plans[0].get();
   return SR_OK;
 }
 
@@ -396,11 +425,10 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
   if (W > 4096) return sr_gfail(g, SR_ERR_ARG, "sr_window_gradients: window size above 4096");
   if (!sr_rows_take_training(g))
     return sr_gfail(g, SR_ERR_ARG, "sr_window_gradients: a node or weight tensor of 2^31 or more elements per tile");
-  SrTrainState& T = train_state(g);
-  if (T.W != W || T.out != out_node || T.tall_from != g->train_tall_from || T.frames_kept != g->train_frames_kept || T.split != g->allow_split) {
-    sr_status st = make_plan(g, T, W, out_node);
-    if (st != SR_OK) return st;
-  }
+  SrTrainPlan* plan = nullptr;
+  sr_status st = plan_for(g, train_state(g), SrTrainPlan::Key{W, out_node, g->train_tall_from, g->train_frames_kept, g->allow_split}, &plan);
+  if (st != SR_OK) return st;
+  SrTrainPlan& T = *plan;
   hipStream_t s = g->stream;
   const int B = g->batch, N = g->n_nodes, E = g->n_edges, C = g->nodes[out_node].d.channels;
 
@@ -415,7 +443,6 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
     }
     return SR_OK;
   };
-  sr_status st = SR_OK;
   for (size_t k = 0; k < g->inputs.size() && st == SR_OK; ++k) st = set(g->inputs[k], inputs[k], node_floats(g, g->inputs[k]));
   for (int v = 0; v < N && st == SR_OK; ++v)
     if (!g->an.is_input[v]) st = set(T.ids.mask0 + v, masks ? masks[v] : nullptr, node_floats(g, v));
@@ -425,7 +452,7 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
   if (st != SR_OK) return st;
   SR_HIP(g, sr_launch_patch(s, T.tensors, T.dst, patch));
 
-  auto run = [&](const SrRowArgs& rows, const SrTrainState::Launch& l, int backward) -> sr_status {
+  auto run = [&](const SrRowArgs& rows, const SrTrainPlan::Launch& l, int backward) -> sr_status {
     for (const auto& p : l.pools) SR_HIP(g, sr_launch_pool(s, T.tensors, p.first, B, p.second.first, p.second.second));
     SrRowArgs a = rows;
     a.runs = T.runs + l.run0;
@@ -434,11 +461,11 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
     SR_HIP(g, sr_launch_rows_train(s, a, backward, l.shapes));
     return SR_OK;
   };
-  for (const SrTrainState::Launch& l : T.fwd)
+  for (const SrTrainPlan::Launch& l : T.fwd)
     if ((st = run(T.rows_fwd, l, 0)) != SR_OK) return st;
   const float scale = 1.0f / ((float)B * (float)W);
   for (size_t k = 0; k < T.chunks.size(); ++k) {
-    const SrTrainState::Chunk& c = T.chunks[k];
+    const SrTrainPlan::Chunk& c = T.chunks[k];
     SrLossArgs l{};
     l.tensors = T.tensors;
     l.labels = labels;
@@ -455,7 +482,7 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
     l.gate = T.out_is_sink ? 1 : 0;
     l.scale = scale;
     SR_HIP(g, sr_launch_loss(s, l));
-    for (const SrTrainState::Launch& b : c.back)
+    for (const SrTrainPlan::Launch& b : c.back)
       if ((st = run(T.rows_back, b, 1)) != SR_OK) return st;
     SrGradArgs ga{};
     ga.tensors = T.tensors;

@@ -553,3 +553,53 @@ def test_options_set_between_two_windows(option, value):
     assert not torch.equal(after, before)
     dev.close()
     fresh.close()
+
+
+def test_windows_that_alternate_keep_their_plans():
+    # window sizes and out nodes in turn: each call gives the bits of a graph that knows no other window, and once the plans
+    # are made a call only launches -- recorded on the graph's stream, where waiting or allocating would be an error
+    import torch
+    import paper_1806_04965_amd as sr
+    g0 = small_sr_graph(batch=3)
+    g = g0.with_pattern(W.hybrid_pattern(g0))
+    w, b, x = W.make_case(g, seed=23, bias_scale=0.1, frames=6, recipe="uniform")
+    ins = g.input_nodes()
+    labels = torch.tensor([0, 1, 0], device="cuda", dtype=torch.int32)
+
+    def call(dev, Wn, into=None):
+        loss, dth, dbs = dev.window_gradients([xs[Wn][v] for v in ins], labels, Wn, into=into)
+        return loss, dth, dbs
+
+    def flat(r):
+        return torch.cat([r[0]] + [t.flatten() for t in r[1] + [t for t in r[2] if t is not None]]).clone()
+
+    def new():
+        dev = sr.SrGraph(g)
+        dev.set_parameters(w, b)
+        return dev
+
+    xs = {Wn: {v: to_device(x[v][:Wn + 1], "f32") for v in ins} for Wn in (1, 2, 3, 4, 5, 6)}
+    want = {}
+    for Wn in xs:
+        dev = new()
+        want[Wn] = flat(call(dev, Wn))
+        dev.close()
+    dev = new()
+    for Wn in (2, 3, 2, 3, 6, 2, 1, 4, 5, 6, 3, 2, 6, 5):          # more than are kept; the memory grows
+        assert torch.equal(flat(call(dev, Wn)), want[Wn]), Wn
+    into = {Wn: call(dev, Wn) for Wn in (2, 6)}
+    recording = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(recording, stream=dev.stream):
+        for Wn in (2, 6):
+            call(dev, Wn, into=into[Wn])
+    for _ in range(3):
+        for r in into.values():
+            for t in [r[0]] + r[1] + [t for t in r[2] if t is not None]:
+                t.zero_()
+        torch.cuda.synchronize()
+        recording.replay()
+        torch.cuda.synchronize()
+        for Wn in (2, 6):
+            assert torch.equal(flat(into[Wn]), want[Wn]), Wn
+    dev.close()

@@ -336,7 +336,8 @@ sr_status sr_graph_node_kernels(const sr_graph* g, int32_t* kinds);
  *             of input nodes are ignored, a NULL entry skips that node
  * fp32 arithmetic; every sum is taken in a fixed order (no floating-point atomics): the same call
  * gives the same bits.  Device memory for the window's states and
- * gradients (about (2 W + 1) x the graph's node states, plus scratch; see SR_OPT_TRAIN_FRAMES_KEPT) is allocated by the call, kept by the graph and reused by later calls.  The plans of the last
+ * gradients (about (2 W + 1) x the graph's node states, plus scratch; see SR_OPT_TRAIN_FRAMES_KEPT; down to (W + 2) x
+ * where there is no more) is allocated by the call, kept by the graph and reused by later calls.  The plans of the last
  * four combinations of window size, out_node and options are kept too; another one is made, which allocates its tables,
  * and waits for the stream if the memory has to grow or a fifth plan to go.  Asynchronous: the results are complete in the
  * order of the graph's stream; the host arrays are consumed before the call returns.  Every kernel is launched by the

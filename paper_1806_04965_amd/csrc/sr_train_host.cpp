@@ -144,7 +144,8 @@ int make_launches(const std::vector<std::vector<std::pair<int, int>>>& pairs, co
   return most;
 }
 
-sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainPlan::Key& key) {
+// The plan for `key` with the state gradients of at most `most_kept` frames at a time; *kept receives their number.
+sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainPlan::Key& key, int most_kept, int* kept) {
   const int N = g->n_nodes, E = g->n_edges, B = g->batch, W = key.W, out_node = key.out;
   SrTrainIds ids;
   ids.grad0 = N;
@@ -190,6 +191,8 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
   }
   int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(W, std::min<int64_t>(kGradRingBytes / 4 / frame_floats, (1 << 30) / most_pixels)));
   if (key.frames_kept > 0) chunk = std::min(chunk, key.frames_kept);
+  chunk = std::min(chunk, most_kept);
+  *kept = chunk;
   const int ring = chunk + 1;
   const size_t x_at = take(frame_floats * W), dx_at = take(frame_floats * ring);
   const size_t seed_at = take((size_t)W * B * g->nodes[out_node].d.channels);
@@ -383,7 +386,8 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
   return SR_OK;
 }
 
-// The plan of a call: one that is kept, or a new one.
+// The plan of a call: one that is kept, or a new one.  A window whose memory is not to be had gets by with the gradients of
+// fewer frames at a time: at the least W + 2 frames of states.
 sr_status plan_for(sr_graph* g, SrTrainState& S, const SrTrainPlan::Key& key, SrTrainPlan** out) {
   for (size_t k = 0; k < S.plans.size(); ++k)
     if (S.plans[k]->key == key) {
@@ -395,12 +399,20 @@ sr_status plan_for(sr_graph* g, SrTrainState& S, const SrTrainPlan::Key& key, Sr
     SR_HIP(g, hipStreamSynchronize(g->stream));   // its tables may still be in use
     S.plans.pop_back();
   }
-  std::unique_ptr<SrTrainPlan> p(new SrTrainPlan());
-  const sr_status st = make_plan(g, S, *p, key);
-  if (st != SR_OK) return st;
-  S.plans.insert(S.plans.begin(), std::move(p));
-  *out = S.plans[0].get();
-  return SR_OK;
+  for (int most = key.W;;) {
+    std::unique_ptr<SrTrainPlan> p(new SrTrainPlan());
+    int kept = 1;
+    const sr_status st = make_plan(g, S, *p, key, most, &kept);
+    if (st == SR_OK) {
+      S.plans.insert(S.plans.begin(), std::move(p));
+      *out = S.plans[0].get();
+      return SR_OK;
+    }
+    if (st != SR_ERR_OOM) return st;
+    (void)hipGetLastError();   // of the allocation: the next launch would report it
+    if (kept <= 1) return st;
+    most = kept / 2;
+  }
 }
 
 }  // namespace

@@ -603,3 +603,49 @@ def test_windows_that_alternate_keep_their_plans():
         for Wn in (2, 6):
             assert torch.equal(flat(into[Wn]), want[Wn]), Wn
     dev.close()
+
+
+def test_window_that_needs_most_of_the_memory():
+    # 2 W + 1 frames of states and gradients do not fit, W + 2 do: the gradients of fewer frames are kept at a time, and the
+    # graph, which has been refused memory on the way, goes on as usual.  (a hidden node of 128 MiB a frame, window of 16:
+    # 4.1 GiB or 2.3; a frame as a check that nothing of the refusal is left)
+    import torch
+    import paper_1806_04965_amd as sr
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    nodes = [Node("in", 1, 256, 256, ACT_IDENTITY), Node("h", 4, 256, 256), Node("out", 3, 1, 1, ACT_IDENTITY)]
+    edges = [Edge(0, 1, "conv", 1, 1, 1, 0), Edge(1, 1, "conv", 1, 1, 1, 0), Edge(1, 2, "gap_dense", 1, 1, 1, 0)]
+    g0 = Graph("large", nodes, edges, 128, 16, "f32", out_node=2)
+    g = g0.with_pattern(W.streaming_pattern(g0))
+    w, b, _ = W.make_case(replace(g, batch=1), seed=5, bias_scale=0.1, frames=1)
+    w[0], w[1] = np.abs(w[0]), 0.5 * w[1]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.rand((17, 128, 256, 256, 1), generator=gen, device="cuda")
+    labels = torch.arange(128, device="cuda", dtype=torch.int32) % 3
+
+    def flat(r):
+        return torch.cat([r[0]] + [t.flatten() for t in r[1] + [t for t in r[2] if t is not None]]).clone()
+
+    want = []
+    for kept in (0, 1):
+        dev = sr.SrGraph(g, options={9: kept})
+        dev.set_parameters(w, b)
+        want.append(flat(dev.window_gradients([x], labels, 16)))
+        dev.synchronize()
+        dev.close()
+    assert float((want[0] - want[1]).abs().max()) <= 1e-5 * float(want[0].abs().max())
+    assert int((want[0] != 0).sum()) > want[0].numel() // 2
+    dev = sr.SrGraph(g)
+    dev.set_parameters(w, b)
+    into = dev.window_gradients([x[:2]], labels, 1)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    hold = torch.empty(free - (3 << 30), dtype=torch.uint8, device="cuda")
+    got = flat(dev.window_gradients([x], labels, 16, into=into))
+    assert float((got - want[0]).abs().max()) <= 1e-5 * float(want[0].abs().max())
+    dev.reset([x[0]])
+    dev.frame_step([x[1]])
+    assert float(dev.get_state(1).abs().max()) > 0
+    dev.close()
+    del hold
+    torch.cuda.empty_cache()

@@ -122,23 +122,28 @@ SR_HD constexpr int sr_f32_stages(int variant, int shape) {
 // sixteen rows read together hit sixteen different 16-byte columns of the 256-byte LDS line
 SR_HD int sr_f32_piece(int row, int k4) { return k4 ^ ((row >> 2) & 3); }
 
-// A row of a row tile, seen by one segment: where tap (0, 0) lands in the gathered image
-struct SrRowAt { int h, w; uint32_t off; };   // off in floats; h = -SR_FAR: no such row
-#define SR_FAR (1 << 21)
-SR_HD SrRowAt sr_row_at(const SrPhase& p, const SrSeg& g, int i, int b0) {
+// Rows and taps that do not exist: whatever is added to them (images have fewer than 2^30 rows; sums wrap), the result is
+// outside every image
+#define SR_NO_ROW (-(1 << 30))
+#define SR_NO_TAP 0x7fffffff
+
+// A row of a row tile, seen by one segment: where tap (0, 0) lands in the gathered tensor.  A tile's 128 rows may lie in as
+// many images (a phase of a strided edge has few pixels of each), so the offset takes 64 bits; lanes make it once a segment.
+struct SrRowAt { int h, w; long long off; };   // off in floats; h = SR_NO_ROW: no such row
+SR_HD SrRowAt sr_row_at(const SrPhase& p, const SrSeg& g, int i) {
   SrRowAt r;
   const int b = sr_divide(i, p.d_hpwp), rem = i - b * (p.Hp * p.Wp);
   const int hh = sr_divide(rem, p.d_wp), ww = rem - hh * p.Wp;
   if (g.flags & SR_SEG_IMAGE) {
     r.h = 0;
     r.w = 0;
-    r.off = (uint32_t)((b - b0) * g.GC);
+    r.off = (long long)b * g.GC;
   } else {
     r.h = sr_divide(hh, g.d_up) * g.rs + g.r0h;
     r.w = sr_divide(ww, g.d_up) * g.rs + g.r0w;
-    r.off = (uint32_t)(((b - b0) * g.GH + r.h) * g.GW + r.w) * (uint32_t)g.GC;
+    r.off = (((long long)b * g.GH + r.h) * g.GW + r.w) * g.GC;
   }
-  if (i >= p.I) r.h = -SR_FAR;
+  if (i >= p.I) r.h = SR_NO_ROW;
   return r;
 }
 
@@ -150,14 +155,14 @@ SR_HD SrTapAt sr_tap_at(const SrSeg& g, int r) {
   t.c = r - tap * g.GC;
   t.vi = sr_divide(tap, g.d_ntj);
   t.vj = tap - t.vi * g.ntj;
-  if (r >= g.R) t.vi = 2 * SR_FAR;   // past the end: outside every image
+  if (r >= g.R) t.vi = SR_NO_TAP;   // past the end
   return t;
 }
 SR_HD bool sr_gather_ok(const SrSeg& g, const SrRowAt& a, const SrTapAt& t) {
-  return (unsigned)(a.h + g.dir * t.vi) < (unsigned)g.GH && (unsigned)(a.w + g.dir * t.vj) < (unsigned)g.GW;
+  return (unsigned)a.h + (unsigned)g.dir * (unsigned)t.vi < (unsigned)g.GH && (unsigned)(a.w + g.dir * t.vj) < (unsigned)g.GW;
 }
-SR_HD uint32_t sr_gather_off(const SrSeg& g, const SrTapAt& t) {   // added to SrRowAt::off
-  return (uint32_t)(g.dir * (t.vi * g.GW + t.vj)) * (uint32_t)g.GC + (uint32_t)t.c;
+SR_HD long long sr_gather_off(const SrSeg& g, const SrTapAt& t) {   // added to SrRowAt::off
+  return (long long)(int)((unsigned)g.dir * ((unsigned)t.vi * (unsigned)g.GW + (unsigned)t.vj)) * g.GC + t.c;
 }
 // weights, backwards: theta[tap][j][c]
 SR_HD uint32_t sr_weight_off(const SrSeg& g, const SrTapAt& t, int j) {
@@ -208,8 +213,16 @@ SR_HD SrPixAt sr_pix_at(const SrGradEdge& e, int m) {
   const int ho = sr_divide(rem, e.d_wo), wo = rem - ho * e.Wo;
   p.h = sr_divide(ho, e.d_up) * e.stride - e.pad;
   p.w = sr_divide(wo, e.d_up) * e.stride - e.pad;
-  if (m >= e.M) p.h = -SR_FAR;
+  if (m >= e.M) p.h = SR_NO_ROW;
   return p;
+}
+// ... does the tap at row ti, column tj of the window exist, and where is it (floats from the image of the step's first
+// pixel, b0; below 2^32: sr_rows_take_training)?  aoff: of the tap and channel from the window's first element
+SR_HD bool sr_pix_ok(const SrGradEdge& e, const SrPixAt& p, int ti, int tj) {
+  return (unsigned)p.h + (unsigned)ti < (unsigned)e.H && (unsigned)(p.w + tj) < (unsigned)e.W;
+}
+SR_HD uint32_t sr_pix_off(const SrGradEdge& e, const SrPixAt& p, int b0, uint32_t aoff) {
+  return (((uint32_t)(p.b - b0) * (uint32_t)e.H + (uint32_t)p.h) * (uint32_t)e.W + (uint32_t)p.w) * (uint32_t)e.Cin + aoff;
 }
 
 // ---------------------------------------------------------------------------
@@ -315,7 +328,7 @@ struct SrTrainIds {
 };
 // can node v be computed by row tiles (no incoming GAP edge, offsets in 32 bits)?
 bool sr_rows_take_forward(const sr_graph* g, int v);
-// are all tensors of the graph small enough for the tiled kernels of a training window?
+// are all tensors of the graph within the index arithmetic of a training window's kernels?
 bool sr_rows_take_training(const sr_graph* g);
 // Append node v's descriptors; returns its first phase (a forward node has one).  ids = null: frame path, tensors
 // numbered like the nodes.

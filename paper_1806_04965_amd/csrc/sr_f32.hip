@@ -125,8 +125,8 @@ struct SrRowOperands {
   static constexpr bool HALF_B = TJ / (16 * NW) == 0;
 
   SrSeg g;
-  const char* src;           // gathered tensor, image of the tile's first row
-  SrRowAt row[NA];
+  int row_h[NA], row_w[NA];  // this lane's rows: where tap (0, 0) lands ...
+  const char* row_at[NA];    // ... and its address
   int wv, lane, i0, j0;
   int quads, quads_w;
   int turn;                  // ordered: the products of a step go in turn
@@ -135,9 +135,7 @@ struct SrRowOperands {
   __device__ __forceinline__ void enter(const SrPhase& p, const SrTensor* tensors, const SrSlots& sl) {
     SR_CONST4(SrTensor) t = sr_k(tensors) + g.tensor;
     const int slot = sl.lag0 + ((g.flags & SR_SEG_LAG) ? sl.lag1 - sl.lag0 : 0);   // (a select between the fields would go through memory)
-    const int b0 = SR_UNI(sr_divide(i0, p.d_hpwp));
-    const long long image = (g.flags & SR_SEG_IMAGE) ? (long long)g.GC * 4 : (long long)g.GH * g.GW * g.GC * 4;
-    src = sr_uni_ptr((const char*)(unsigned long long)t->base + slot * t->stride + b0 * image);
+    const char* src = sr_uni_ptr((const char*)(unsigned long long)t->base + slot * t->stride);
     quads = SR_UNI((g.flags & SR_SEG_QUADS) && ((unsigned)(unsigned long long)src & 15u) == 0);
     quads_w = SR_UNI((g.ldw & 3) == 0);
     if (FOR == SR_ROWS_ORDERED) turn = !(g.flags & SR_SEG_QUADS);
@@ -145,13 +143,20 @@ struct SrRowOperands {
     for (int n = 0; n < NA; ++n) {
       const int r = quads ? n * 16 * NW + wv * 16 + (lane >> 2)
                           : (TI >= 64 ? (TI == 128 ? (wv & 1) * 64 + lane : lane) : (lane & 31));
-      row[n] = sr_row_at(p, g, i0 + r, b0);
+      const SrRowAt at = sr_row_at(p, g, i0 + r);
+      row_h[n] = at.h;
+      row_w[n] = at.w;
+      row_at[n] = src + at.off * 4;
     }
   }
 
   // may the steps at r0 and r0 + 16 share their addresses (one tap, 16-byte loads)?  stop: end of the segment's share
   __device__ __forceinline__ bool pairs(int r0, int stop) const {
     return quads && (g.GC & 31) == 0 && (r0 & 31) == 0 && r0 + SR_F32_KS < stop && (BACK || quads_w);
+  }
+
+  __device__ __forceinline__ const char* gathered(int n, const SrTapAt& t, long long tap_bytes) const {
+    return sr_gather_ok(g, SrRowAt{row_h[n], row_w[n], 0}, t) ? row_at[n] + tap_bytes : (const char*)sr_zero_line;
   }
 
   // loads of the 16 reduction indices from r0 on, into LDS at `at`; PAIR: and of the next 16, into the stage behind it
@@ -168,17 +173,17 @@ struct SrRowOperands {
       } else {
         t = sr_tap_at(g, r0 + 4 * k4);
       }
-      const uint32_t toff = sr_gather_off(g, t);
+      const long long toff = sr_gather_off(g, t) * 4;
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
-        const char* p = sr_gather_ok(g, row[n], t) ? sr_at(src, row[n].off + toff) : zero;
+        const char* p = gathered(n, t, toff);
         sr_to_lds16(p, at + (n * NW + wv) * 1024);
         if (PAIR) sr_to_lds16(p + 64, at + STAGE + (n * NW + wv) * 1024);
       }
       if (BACK) {
         // (a half-filled wave's rows start at a multiple of eight: its pieces are permuted differently from A's)
         const SrTapAt tb = HALF_B ? sr_tap_at(g, r0 + 4 * sr_f32_piece(wv * 8 + (lane >> 2), lane & 3)) : t;
-        const bool r_ok = tb.vi < SR_FAR;
+        const bool r_ok = tb.vi != SR_NO_TAP;
         const uint32_t woff = sr_weight_off(g, tb, 0);
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
@@ -203,7 +208,7 @@ struct SrRowOperands {
         const int line = TI >= 64 ? id * 64 / TI : 2 * id + (lane >> 5);
         const int k = FOR == SR_ROWS_ORDERED && turn ? sr_in_turn(line) : line;
         const SrTapAt t = sr_tap_at(g, TI >= 64 ? SR_UNI(r0 + k) : r0 + k);
-        const char* p = sr_gather_ok(g, row[0], t) ? sr_at(src, row[0].off + sr_gather_off(g, t)) : zero;
+        const char* p = gathered(0, t, sr_gather_off(g, t) * 4);
         sr_to_lds4(p, at + id * 256);
       }
       if (BACK) {
@@ -213,7 +218,7 @@ struct SrRowOperands {
           const int k = TJ >= 64 ? id * 64 / TJ : 2 * id + (lane >> 5);
           const int j = j0 + (TJ >= 64 ? (TJ == 128 ? (id & 1) * 64 + lane : lane) : (lane & 31));
           const SrTapAt t = sr_tap_at(g, TJ >= 64 ? SR_UNI(r0 + k) : r0 + k);
-          const char* p = (t.vi < SR_FAR && j < g.ldw) ? sr_at((const char*)g.w, sr_weight_off(g, t, j)) : zero;
+          const char* p = (t.vi != SR_NO_TAP && j < g.ldw) ? sr_at((const char*)g.w, sr_weight_off(g, t, j)) : zero;
           sr_to_lds4(p, bt + id * 256);
         }
         return;
@@ -780,7 +785,7 @@ struct SrGradOperands {
     ti = sr_divide(tap, e.d_kw);
     tj = tap - ti * e.kw;
     aoff = (uint32_t)(ti * e.W + tj) * (uint32_t)e.Cin + (uint32_t)ci;
-    if (i >= e.I) ti = 2 * SR_FAR;
+    if (i >= e.I) ti = SR_NO_TAP;
   }
 
   __device__ __forceinline__ void issue(int step, unsigned at) {
@@ -794,18 +799,14 @@ struct SrGradOperands {
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
         const SrPixAt p = sr_pix_at(e, m0 + (n * 4 + wv) * (256 / TI) + lane / (TI / 4));
-        const bool ok = (unsigned)(p.h + ti) < (unsigned)e.H && (unsigned)(p.w + tj) < (unsigned)e.W;
-        const uint32_t off = (uint32_t)(((p.b - b0) * e.H + p.h) * e.W + p.w) * (uint32_t)e.Cin + aoff;
-        sr_to_lds16(ok ? sr_at(xb, off) : zero, at + (n * 4 + wv) * 1024);
+        sr_to_lds16(sr_pix_ok(e, p, ti, tj) ? sr_at(xb, sr_pix_off(e, p, b0, aoff)) : zero, at + (n * 4 + wv) * 1024);
       }
     } else {
 #pragma unroll
       for (int q = 0; q < TI / 16; ++q) {
         const int id = q * 4 + wv;
         const SrPixAt p = sr_pix_at(e, SR_UNI(m0 + id * 64 / TI));
-        const bool ok = (unsigned)(p.h + ti) < (unsigned)e.H && (unsigned)(p.w + tj) < (unsigned)e.W;
-        const uint32_t off = (uint32_t)(((p.b - b0) * e.H + p.h) * e.W + p.w) * (uint32_t)e.Cin + aoff;
-        sr_to_lds4(ok ? sr_at(xb, off) : zero, at + id * 256);
+        sr_to_lds4(sr_pix_ok(e, p, ti, tj) ? sr_at(xb, sr_pix_off(e, p, b0, aoff)) : zero, at + id * 256);
       }
     }
     const unsigned bt = at + TI * 64;
@@ -814,7 +815,7 @@ struct SrGradOperands {
       for (int n = 0; n < NB; ++n) {
         const int id = HALF_B ? wv * 32 + lane : (n * 4 + wv) * 64 + lane;
         const int k = id / (TJ / 4), j = j0 + 4 * (id % (TJ / 4));
-        const char* p = (m0 + k < e.M && j < e.Cout) ? sr_at(yb, (uint32_t)(k * e.Cout + j)) : zero;
+        const char* p = (m0 + k < e.M && j < e.Cout) ? sr_at(yb, (uint32_t)k * (uint32_t)e.Cout + (uint32_t)j) : zero;
         if (HALF_B) {
           if (lane < 32) sr_to_lds16(p, bt + wv * 512);
         } else {
@@ -826,7 +827,7 @@ struct SrGradOperands {
       for (int q = 0; q < TJ / 16; ++q) {
         const int id = (q * 4 + wv) * 64 + lane;
         const int k = id / TJ, j = j0 + id % TJ;
-        sr_to_lds4((m0 + k < e.M && j < e.Cout) ? sr_at(yb, (uint32_t)(k * e.Cout + j)) : zero, bt + (q * 4 + wv) * 256);
+        sr_to_lds4((m0 + k < e.M && j < e.Cout) ? sr_at(yb, (uint32_t)k * (uint32_t)e.Cout + (uint32_t)j) : zero, bt + (q * 4 + wv) * 256);
       }
     }
   }

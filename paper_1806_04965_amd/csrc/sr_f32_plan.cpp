@@ -26,11 +26,16 @@ Geometry geometry(const sr_graph* g, const EdgeRt& e) {
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-// 32-bit offsets (in floats) from the image of a tile's first row, which may touch `images` of them
-bool fits(const sr_graph* g, const sr_node_desc& rows, const sr_node_desc& gathered) {
-  const int64_t pixels = (int64_t)rows.height * rows.width;
-  const int64_t images = std::min<int64_t>(g->batch, 128 / pixels + 2);
-  return (int64_t)g->batch * pixels < ((int64_t)1 << 30) && images * image_floats(gathered) < ((int64_t)1 << 31);
+constexpr int64_t kRows = ((int64_t)1 << 31) - 256;   // rows, columns and reduction indices are ints, some past the last one
+
+// rows of the node, and the rows and columns of its images, are counted in ints
+bool rows_fit(const sr_graph* g, const sr_node_desc& d) {
+  return (int64_t)g->batch * d.height * d.width < kRows && std::max(d.height, d.width) < (1 << 30) && d.channels < (1 << 27);
+}
+
+// theta: offsets in 32 bits; one edge's reduction over (tap, channel) in an int, and a dense edge's source as a row of one
+bool weights_fit(const EdgeRt& e, const Geometry& q) {
+  return (int64_t)e.w_count < ((int64_t)1 << 32) && (int64_t)e.kh * e.kw * std::max(q.Cin, q.Cout) < kRows;
 }
 
 }  // namespace
@@ -38,8 +43,9 @@ bool fits(const sr_graph* g, const sr_node_desc& rows, const sr_node_desc& gathe
 bool sr_rows_take_forward(const sr_graph* g, int v) {
   for (const EdgeRt& e : g->edges) {
     if (e.d.dst != v) continue;
-    if (e.d.kind == SR_EDGE_GAP_DENSE || (int64_t)e.w_count >= ((int64_t)1 << 31)) return false;
-    if (!fits(g, g->nodes[v].d, g->nodes[e.d.src].d)) return false;
+    const sr_node_desc& s = g->nodes[e.d.src].d;
+    if (e.d.kind == SR_EDGE_GAP_DENSE || (e.d.kind == SR_EDGE_DENSE && image_floats(s) >= kRows)) return false;
+    if (!rows_fit(g, g->nodes[v].d) || !rows_fit(g, s) || !weights_fit(e, geometry(g, e))) return false;
   }
   return true;
 }
@@ -47,7 +53,12 @@ bool sr_rows_take_forward(const sr_graph* g, int v) {
 bool sr_rows_take_training(const sr_graph* g) {
   for (const EdgeRt& e : g->edges) {
     const sr_node_desc &s = g->nodes[e.d.src].d, &d = g->nodes[e.d.dst].d;
-    if ((int64_t)e.w_count >= ((int64_t)1 << 31) || !fits(g, d, s) || !fits(g, s, d)) return false;
+    if (e.d.kind == SR_EDGE_DENSE && image_floats(s) >= kRows) return false;
+    const Geometry q = geometry(g, e);
+    if (!rows_fit(g, d) || !rows_fit(g, s) || !weights_fit(e, q)) return false;
+    // a gradient tile's step: 16 pixels of the target, whose windows lie in this many images of the source
+    const int64_t images = std::min<int64_t>(g->batch, 15 / ((int64_t)d.height * d.width) + 2);
+    if (images * q.H * q.W * q.Cin >= ((int64_t)1 << 32)) return false;
   }
   return true;
 }

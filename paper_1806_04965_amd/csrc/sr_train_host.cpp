@@ -189,7 +189,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
     frame_floats += (node_floats(g, v) + 63) / 64 * 64;
     most_pixels = std::max<int64_t>(most_pixels, (int64_t)B * g->nodes[v].d.height * g->nodes[v].d.width);
   }
-  int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(W, std::min<int64_t>(kGradRingBytes / 4 / frame_floats, (1 << 30) / most_pixels)));
+  int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(W, std::min<int64_t>(kGradRingBytes / 4 / frame_floats, ((int64_t)1 << 30) / most_pixels)));
   if (key.frames_kept > 0) chunk = std::min(chunk, key.frames_kept);
   chunk = std::min(chunk, most_kept);
   *kept = chunk;
@@ -436,7 +436,7 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
     if (!g->edges[e].has_w) return sr_gfail(g, SR_ERR_STATE, "edge " + std::to_string(e) + " has no weights");
   if (W > 4096) return sr_gfail(g, SR_ERR_ARG, "sr_window_gradients: window size above 4096");
   if (!sr_rows_take_training(g))
-    return sr_gfail(g, SR_ERR_ARG, "sr_window_gradients: a node or weight tensor of 2^31 or more elements per tile");
+    return sr_gfail(g, SR_ERR_ARG, "sr_window_gradients: a tensor past the limits of sr_window_gradients (sr.h)");
   SrTrainPlan* plan = nullptr;
   sr_status st = plan_for(g, train_state(g), SrTrainPlan::Key{W, out_node, g->train_tall_from, g->train_frames_kept, g->allow_split}, &plan);
   if (st != SR_OK) return st;

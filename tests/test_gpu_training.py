@@ -649,3 +649,56 @@ def test_window_that_needs_most_of_the_memory():
     dev.close()
     del hold
     torch.cuda.empty_cache()
+
+
+def mean_readout_window(batch, size, channels):
+    """One frame of in -> 1x1 convolution, rectifier -> mean over pixels -> scores: the library's gradients and the same
+    in float64 with torch, image by image."""
+    import torch
+    import paper_1806_04965_amd as sr
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    nodes = [Node("in", 1, size, size, ACT_IDENTITY), Node("h", channels, size, size), Node("out", 3, 1, 1, ACT_IDENTITY)]
+    edges = [Edge(0, 1, "conv", 1, 1, 1, 0), Edge(1, 2, "gap_dense", 1, 1, 1, 0)]
+    g0 = Graph("mean", nodes, edges, batch, 1, "f32", out_node=2)
+    g = g0.with_pattern(W.sequential_pattern(g0))
+    w, b, _ = W.make_case(replace(g, batch=1), seed=6, bias_scale=0.3, frames=1)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.rand((2, batch, size, size, 1), generator=gen, device="cuda") - 0.3
+    labels = torch.randint(0, 3, (batch,), generator=gen, device="cuda", dtype=torch.int32)
+    dev = sr.SrGraph(g)
+    dev.set_parameters(w, b)
+    loss, dth, dbs = dev.window_gradients([x], labels, 1)
+    dev.synchronize()
+    got = [loss] + dth + dbs[1:]
+    got = [t.double().cpu().numpy().ravel() for t in got]
+    dev.close()
+
+    w0, w1 = (torch.from_numpy(t).to("cuda").double().reshape(-1, t.shape[-1]) for t in w)
+    b0, b1 = (torch.from_numpy(t).to("cuda").double() for t in b[1:])
+    ref = [torch.zeros(n, device="cuda", dtype=torch.float64) for n in (1, channels, channels * 3, channels, 3)]
+    step = max(1, (1 << 22) // (size * size))
+    for k in range(0, batch, step):
+        xs = x[1, k:k + step].double().flatten(1, 2)                       # [n, pixels, 1]
+        h = torch.relu(xs * w0 + b0)
+        z = h.mean(1) @ w1 + b1
+        lab = labels[k:k + step].long()
+        ref[0] -= torch.log_softmax(z, 1).gather(1, lab[:, None]).sum() / batch
+        dz = (torch.softmax(z, 1) - torch.nn.functional.one_hot(lab, 3)) / batch
+        ref[2] += (h.mean(1).T.contiguous() @ dz).flatten()
+        ref[4] += dz.sum(0)
+        dh = ((dz @ w1.T.contiguous()) / (size * size))[:, None, :] * (h > 0)
+        ref[1] += (dh * xs).sum((0, 1))
+        ref[3] += dh.sum((0, 1))
+    # a bias gradient: one of 512 slices, one of four lanes adds up this many terms of an image, all equal, in float32, each
+    # addition off by up to 2^-24 of the sum (2.6e5 terms: 1.6e-2; measured 1.2e-3)
+    bias_tol = max(GRAD_TOL, batch * size * size / 2048 * 2.0 ** -24)
+    for a, r, (name, tol) in zip(got, ref, (("loss", GRAD_TOL), ("dtheta[0]", GRAD_TOL), ("dtheta[1]", GRAD_TOL), ("dbias[1]", bias_tol),
+                                            ("dbias[2]", GRAD_TOL))):
+        r = r.cpu().numpy()
+        assert np.abs(r).max() > 0
+        assert max_abs_rel(a, r) <= tol, (name, max_abs_rel(a, r))
+
+
+def test_window_over_a_map_that_only_its_mean_is_read_of():
+    # 130 images of 2^24 floats, 8.7 GB a frame: more than 2^31 floats, of which a tile of the scores reads 130 means
+    mean_readout_window(130, 2048, 4)

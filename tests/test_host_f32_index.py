@@ -1,0 +1,109 @@
+"""The index arithmetic of the tiled fp32 kernels (csrc/sr_f32.h: host and device share it), compiled for the host and
+compared with plain 64-bit arithmetic at the ends of its range: offsets past 2^32 floats within one tile, images taller
+than 2^21 rows, rows and taps that do not exist."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include "sr_f32.h"
+
+static long checked = 0;
+#define CHECK(c, ...) do { ++checked; if (!(c)) { std::printf(__VA_ARGS__); std::printf("  (%s)\n", #c); std::exit(1); } } while (0)
+
+struct Shape { int B, Hp, Wp, GH, GW, GC, nti, ntj, rs, r0h, r0w, up, dir; };
+
+static void rows(const Shape& s, const int* is, int n_i, const int* rs, int n_r) {
+  SrPhase p{};
+  p.Hp = s.Hp; p.Wp = s.Wp; p.I = s.B * s.Hp * s.Wp;
+  p.d_wp = sr_div_for(s.Wp); p.d_hpwp = sr_div_for(s.Hp * s.Wp);
+  SrSeg g{};
+  g.GH = s.GH; g.GW = s.GW; g.GC = s.GC; g.rs = s.rs; g.r0h = s.r0h; g.r0w = s.r0w; g.dir = s.dir; g.ntj = s.ntj;
+  g.R = s.nti * s.ntj * s.GC;
+  g.d_gc = sr_div_for(s.GC); g.d_ntj = sr_div_for(s.ntj); g.d_up = sr_div_for(s.up);
+  for (int a = 0; a < n_i; ++a)
+    for (int b = 0; b < n_r; ++b) {
+      const int i = is[a], r = rs[b];
+      const SrRowAt at = sr_row_at(p, g, i);
+      const SrTapAt t = sr_tap_at(g, r);
+      const long long im = i / (s.Hp * s.Wp), hh = i / s.Wp % s.Hp, ww = i % s.Wp;
+      const long long tap = r / s.GC, vi = tap / s.ntj, vj = tap % s.ntj;
+      const long long h = hh / s.up * s.rs + s.r0h + s.dir * vi, w = ww / s.up * s.rs + s.r0w + s.dir * vj;
+      const bool ok = i < p.I && r < g.R && h >= 0 && h < s.GH && w >= 0 && w < s.GW;
+      CHECK(sr_gather_ok(g, at, t) == ok, "B=%d GH=%d i=%d r=%d: h=%lld w=%lld", s.B, s.GH, i, r, h, w);
+      if (ok) {
+        const long long off = ((im * s.GH + h) * s.GW + w) * s.GC + r % s.GC;
+        CHECK(at.off + sr_gather_off(g, t) == off, "B=%d GH=%d GW=%d i=%d r=%d: want %lld", s.B, s.GH, s.GW, i, r, off);
+      }
+    }
+}
+
+static void pixels(int B, int Ho, int Wo, int H, int W, int Cin, int kh, int kw, int stride, int pad, int m0) {
+  SrGradEdge e{};
+  e.Ho = Ho; e.Wo = Wo; e.H = H; e.W = W; e.Cin = Cin; e.kw = kw; e.stride = stride; e.pad = pad;
+  e.I = kh * kw * Cin; e.M = B * Ho * Wo;
+  e.d_cin = sr_div_for(Cin); e.d_kw = sr_div_for(kw); e.d_wo = sr_div_for(Wo); e.d_howo = sr_div_for(Ho * Wo); e.d_up = sr_div_for(1);
+  const int b0 = sr_divide(m0, e.d_howo);
+  const int is[] = {0, 1, Cin - 1, e.I / 2, e.I - 1, e.I, e.I + 127};
+  for (int m = m0; m < m0 + 16; ++m)
+    for (int i : is) {
+      const SrPixAt p = sr_pix_at(e, m);
+      const int tap = sr_divide(i, e.d_cin), ci = i - tap * Cin;
+      int ti = sr_divide(tap, e.d_kw);
+      const int tj = tap - ti * kw;
+      const uint32_t aoff = (uint32_t)(ti * W + tj) * (uint32_t)Cin + (uint32_t)ci;
+      if (i >= e.I) ti = SR_NO_TAP;
+      const long long h = (long long)(m / Wo % Ho) * stride - pad + tap / kw, w = (long long)(m % Wo) * stride - pad + tap % kw;
+      const bool ok = m < e.M && i < e.I && h >= 0 && h < H && w >= 0 && w < W;
+      CHECK(sr_pix_ok(e, p, ti, tj) == ok, "pixel H=%d m=%d i=%d", H, m, i);
+      if (ok) CHECK(sr_pix_off(e, p, b0, aoff) == (((long long)(m / (Ho * Wo) - b0) * H + h) * W + w) * Cin + ci, "pixel offset H=%d m=%d i=%d", H, m, i);
+    }
+}
+
+int main() {
+  for (int dir : {1, -1}) {
+    // one pixel of each image (a phase of a strided edge): 128 rows of a tile lie in 128 images of 2^26 floats
+    { const int is[] = {0, 1, 63, 127, 128, 199, 200, 327}, rs[] = {0, 1, 3, 4, 4 * 4096, 4 * 4 - 1, 16, 31};
+      rows({200, 1, 1, 4096, 4096, 4, 2, 2, 0, dir > 0 ? 0 : 4095, dir > 0 ? 0 : 4095, 1, dir}, is, 8, rs, 8); }
+    // images of 2^22 rows and more: what does not exist stays outside
+    for (int GH : {(1 << 21) + 7, 5000000, (1 << 30) - 1}) {
+      const int n = GH < 6000000 ? GH : 1 << 20;
+      const int is[] = {0, 1, n / 2, n - 1, n, n + 127}, rs[] = {0, 1, 2, 3, 8, 15, 40};
+      rows({1, n, 1, GH, 1, 3, 3, 1, 1, dir > 0 ? -1 : 1, 0, 1, dir}, is, 6, rs, 7);
+      if (GH < 6000000) pixels(1, GH, 1, GH, 1, 3, 3, 1, 1, 1, GH - 8);
+    }
+    // a dense edge: one pixel, the source's elements as channels
+    { const int is[] = {0, 31, 32, 129}, rs[] = {0, 15, 1 << 20, (1 << 24) - 1, 1 << 24};
+      rows({130, 1, 1, 1, 1, 1 << 24, 1, 1, 1, 0, 0, 1, dir}, is, 4, rs, 5); }
+  }
+  pixels(40, 1, 1, 1, 1, 1 << 27, 1, 1, 1, 0, 7);        // 16 images of 2^27 floats in a step
+  pixels(3, 2048, 2048, 4096, 4096, 127, 3, 3, 2, 1, 2048 * 2048 - 8);
+  std::mt19937 rng(1);
+  auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+  for (int k = 0; k < 3000; ++k) {
+    Shape s{pick(1, 9), pick(1, 9), pick(1, 9), pick(1, 12), pick(1, 12), pick(1, 9), pick(1, 4), pick(1, 4), pick(0, 3), pick(-3, 4), pick(-3, 4),
+            pick(1, 3), pick(0, 1) ? 1 : -1};
+    int is[8], rs[8];
+    for (int& i : is) i = pick(0, s.B * s.Hp * s.Wp + 130);
+    for (int& r : rs) r = pick(0, s.nti * s.ntj * s.GC + 64);
+    rows(s, is, 8, rs, 8);
+    const int kk = pick(1, 4), st = pick(1, 3), ho = pick(1, 9), wo = pick(1, 9);
+    pixels(pick(1, 9), ho, wo, pick(1, 12), pick(1, 12), pick(1, 9), kk, pick(1, 4), st, pick(0, 3), pick(0, ho * wo));
+  }
+  std::printf("ok %ld\n", checked);
+}
+"""
+
+
+def test_index_arithmetic_of_the_fp32_tiles(tmp_path):
+    src, exe = tmp_path / "index.cpp", tmp_path / "index"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-fsanitize=undefined", "-fno-sanitize-recover=undefined", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I", os.path.join(ROOT, "paper_1806_04965_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True, timeout=120)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr

@@ -1049,9 +1049,9 @@ __global__ void sr_patch_kernel(SrTensor* __restrict__ tensors, float** __restri
 
 // channel means of a node's state at the frames frame0 .. (the mean read at frame f is that of frame f - lag), a
 // workgroup per 64 channels of one image: four pixel lanes per channel, eight loads in flight
-__global__ __launch_bounds__(256) void sr_pool_kernel(const SrTensor* __restrict__ tensors, SrPool q, int frame0) {
+__global__ __launch_bounds__(256) void sr_pool_kernel(const SrTensor* __restrict__ tensors, SrPool q, int frame0, int image0) {
   __shared__ float lanes[256];
-  const int frame = frame0 + blockIdx.z, b = blockIdx.y, t = threadIdx.x, c = blockIdx.x * 64 + (t & 63), pl = t >> 6;
+  const int frame = frame0 + blockIdx.z, b = image0 + blockIdx.y, t = threadIdx.x, c = blockIdx.x * 64 + (t & 63), pl = t >> 6;
   const SrTensor x = tensors[q.x], mean = tensors[q.mean];
   float acc = 0.f;
   if (c < q.C && !(q.zero0 && frame - q.lag == 0)) {
@@ -1121,13 +1121,14 @@ hipError_t sr_launch_patch(hipStream_t s, SrTensor* tensors, float** dst, const 
 }
 
 hipError_t sr_launch_pool(hipStream_t s, const SrTensor* tensors, const SrPool& p, int B, int frame0, int frames) {
-  // frames and images as grid rows, some thousands at a time (grid y and z are limited to 65535)
-  for (int f = 0; f < frames; f += 4096) {
-    const int nf = frames - f < 4096 ? frames - f : 4096;
-    hipLaunchKernelGGL(sr_pool_kernel, dim3((p.C + 63) / 64, B, nf), dim3(256), 0, s, tensors, p, frame0 + f);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  // images and frames as grid rows, some thousands at a time (grid y and z are limited to 65535)
+  for (int f = 0; f < frames; f += 4096)
+    for (int b = 0; b < B; b += 32768) {
+      hipLaunchKernelGGL(sr_pool_kernel, dim3((p.C + 63) / 64, B - b < 32768 ? B - b : 32768, frames - f < 4096 ? frames - f : 4096), dim3(256),
+                         0, s, tensors, p, frame0 + f, b);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 

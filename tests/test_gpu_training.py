@@ -702,3 +702,8 @@ def mean_readout_window(batch, size, channels):
 def test_window_over_a_map_that_only_its_mean_is_read_of():
     # 130 images of 2^24 floats, 8.7 GB a frame: more than 2^31 floats, of which a tile of the scores reads 130 means
     mean_readout_window(130, 2048, 4)
+
+
+@pytest.mark.parametrize("batch", [32768, 32769, 70000])
+def test_window_of_many_images_read_by_their_means(batch):
+    mean_readout_window(batch, 3, 5)      # a launch takes the means of 32768 images

@@ -342,7 +342,7 @@ sr_status sr_graph_node_kernels(const sr_graph* g, int32_t* kinds);
  * and waits for the stream if the memory has to grow or a fifth plan to go.  Asynchronous: the results are complete in the
  * order of the graph's stream; the host arrays are consumed before the call returns.  Every kernel is launched by the
  * call itself (SR_OPT_USE_HIPGRAPH concerns the frame path only).  No optimiser step is taken.
- * Limits (SR_ERR_ARG past them): W <= 4096, W * B < 2^31; a node's B * H * W below 2^31 - 256, its channels below 2^27; an
+ * Limits (SR_ERR_ARG past them): W <= 4096; a node's B * H * W below 2^31 - 256, its channels below 2^27; an
  * edge's weights below 2^32, its kh * kw * Cin and kh * kw * Cout below 2^31 - 256 (dense: so is the source's H * W * C); and,
  * of a convolution or dense edge, 16 GiB for as many of the source's images as 16 consecutive pixels of the target lie in.
  * Errors: SR_ERR_ARG, SR_ERR_STATE (weights missing), SR_ERR_OOM, SR_ERR_DEVICE. */

@@ -236,6 +236,7 @@ struct SrRowArgs {
   const SrRowTile* tiles;
   const SrRun* runs;              // training: (tile list, frame) pairs of the launch
   int32_t n_runs, n_tiles;        // n_tiles: workgroups
+  int32_t first;                  // training: workgroup that the grid's first one is
   int32_t frame0;                 // training: frame of a run = frame0 + run.frame
   int32_t window;                 // training: W
   int32_t ring;                   // training: gradient tensors keep `ring` frames (slot = frame % ring)
@@ -258,6 +259,7 @@ struct SrLossArgs {
   int32_t frame0, frames;         // of the window, and of this launch
   int32_t B, C, act;
   int32_t x, out, mask;           // tensors: scores, where their gradient goes, dropout (out of the node itself)
+  int32_t first;                  // (frame, sample) pair of the first wave
   int32_t ring, gate;             // gate: `out` is the node's own gradient (apply rectifier and dropout)
   float scale;
 };
@@ -287,8 +289,10 @@ hipError_t sr_launch_rows_frame(hipStream_t s, const SrFrame& f, const SrRowArgs
 hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward, int shapes);
 hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int shapes);
 // destination sums, and (loss != null) loss = scale * sum of the n_terms loss terms
+// (launches of more workgroups than a grid may have -- 2^32 threads, here 2^23 workgroups -- go in pieces)
+#define SR_F32_PIECE (1 << 23)
 hipError_t sr_launch_grad_sum(hipStream_t s, const SrGradSum* sums, int n_sums, int n_blocks, const float* part, float* const* dst,
-                              int accumulate, const float* terms, int n_terms, float scale, float* loss);
+                              int accumulate, const float* terms, long long n_terms, float scale, float* loss);
 hipError_t sr_launch_loss(hipStream_t s, const SrLossArgs& a);
 hipError_t sr_launch_patch(hipStream_t s, SrTensor* tensors, float** dst, const SrPatch& p);
 hipError_t sr_launch_pool(hipStream_t s, const SrTensor* tensors, const SrPool& p, int B, int frame0, int frames);

@@ -21,6 +21,8 @@
 // gives the same bits.  The forward pass of a training window has one order for all sizes and tiles (SR_ROWS_ORDERED);
 // against tiles that take theirs as it comes, and cut long sums, that costs DSR2 1459 -> 1532 us, GTSRB-shaped 5990 -> 6130,
 // MNIST SR 302 -> 360.
+#include <algorithm>
+
 #include "sr_device.h"
 #include "sr_f32.h"
 
@@ -720,11 +722,11 @@ template <bool BACK, int VARIANT>
 __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows_train_kernel(SrRowArgs A) {
   extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
   // the run (tile list, frame) this workgroup belongs to: runs are in order of their first workgroup
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, block = (int)blockIdx.x + A.first;
   int k = 0;
   for (int base = 0; base < A.n_runs; base += 64) {
     const int b0 = base + lane < A.n_runs ? A.runs[base + lane].block0 : 0x7fffffff;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= (int)blockIdx.x);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= block);
     k += __popcll(m);
     if (m != ~0ull) break;
   }
@@ -743,7 +745,7 @@ __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows
     sl.left = frame;
   }
   sl.frame = frame;
-  sr_row_item<BACK ? SR_ROWS_BACK : SR_ROWS_ORDERED, VARIANT>(A, sr_k(A.tiles) + run->tile0 + (blockIdx.x - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
+  sr_row_item<BACK ? SR_ROWS_BACK : SR_ROWS_ORDERED, VARIANT>(A, sr_k(A.tiles) + run->tile0 + (block - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
 }
 
 namespace {
@@ -957,14 +959,14 @@ __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 3) void sr_grad
 // per element (each adds every fourth slice in order, eight loads in flight; then the four in order).  The last
 // workgroup adds up the loss.
 __global__ __launch_bounds__(256) void sr_grad_sum_kernel(const SrGradSum* __restrict__ sums, int n_sums, const float* __restrict__ part,
-                                                          float* const* __restrict__ dst, int accumulate,
-                                                          const float* __restrict__ terms, int n_terms, float scale,
+                                                          float* const* __restrict__ dst, int accumulate, int first, int last,
+                                                          const float* __restrict__ terms, long long n_terms, float scale,
                                                           float* __restrict__ loss) {
   __shared__ float lanes[256];
-  const int t = threadIdx.x;
-  if (loss && blockIdx.x == gridDim.x - 1) {
+  const int t = threadIdx.x, block = (int)blockIdx.x + first;
+  if (block == last) {
     float acc = 0.f;
-    for (int i = t; i < n_terms; i += 256) acc += terms[i];
+    for (long long i = t; i < n_terms; i += 256) acc += terms[i];
     lanes[t] = acc;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
@@ -978,12 +980,12 @@ __global__ __launch_bounds__(256) void sr_grad_sum_kernel(const SrGradSum* __res
   for (int base = 0; base < n_sums; base += 64) {
     const int q = base + (t & 63);
     const int b0 = q < n_sums ? sums[q].block0 : 0x7fffffff;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= (int)blockIdx.x);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= block);
     k += __popcll(m);
     if (m != ~0ull) break;
   }
   SR_CONST4(SrGradSum) s = sr_k(sums) + SR_UNI(k - 1);
-  const long long n = s->n, e = (long long)(blockIdx.x - s->block0) * 64 + (t & 63);
+  const long long n = s->n, e = (long long)(block - s->block0) * 64 + (t & 63);
   const int slices = s->slices, sl = t >> 6;
   const float* p = part + s->part_at;
   float acc = 0.f;
@@ -1009,7 +1011,7 @@ __global__ __launch_bounds__(256) void sr_grad_sum_kernel(const SrGradSum* __res
 // Softmax cross-entropy of every frame of the window (App. A2), a wave per (frame, sample): its term of the loss and
 // the gradient of the scores, (softmax - [class == label]) * scale
 __global__ __launch_bounds__(256) void sr_loss_kernel(SrLossArgs A) {
-  const int lane = threadIdx.x & 63, idx = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, idx = A.first + (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   if (idx >= A.frames * A.B) return;   // a whole wave
   const int fi = idx / A.B, frame = A.frame0 + fi, b = idx - fi * A.B, C = A.C;
   auto at = [&](int id, int slot) -> float* {
@@ -1028,7 +1030,7 @@ __global__ __launch_bounds__(256) void sr_loss_kernel(SrLossArgs A) {
   const float lse = zmax + logf(sum);
   int lab = A.labels[b];
   lab = lab < 0 ? 0 : (lab >= C ? C - 1 : lab);   // the host checks nothing on the device: stay in bounds
-  if (lane == 0) A.terms[(frame - 1) * A.B + b] = lse - z[lab];
+  if (lane == 0) A.terms[(size_t)(frame - 1) * A.B + b] = lse - z[lab];
   for (int c = lane; c < C; c += 64) {
     float v = (expf(z[c] - lse) - (c == lab ? 1.f : 0.f)) * A.scale;
     if (A.gate) {
@@ -1089,8 +1091,14 @@ hipError_t sr_launch_rows_train(hipStream_t s, const SrRowArgs& a, int backward,
   static void (*const kernels[2][3])(SrRowArgs) = {
       {nullptr, sr_rows_train_kernel<false, SR_F32_NARROW>, sr_rows_train_kernel<false, SR_F32_DEEP>},
       {sr_rows_train_kernel<true, SR_F32_WIDE>, sr_rows_train_kernel<true, SR_F32_NARROW>, sr_rows_train_kernel<true, SR_F32_DEEP>}};
-  hipLaunchKernelGGL(kernels[backward ? 1 : 0][sr_f32_variant(shapes)], dim3(a.n_tiles), dim3(256), sr_f32_lds_bytes(shapes), s, a);
-  return hipGetLastError();
+  SrRowArgs piece = a;
+  for (piece.first = 0; piece.first < a.n_tiles; piece.first += SR_F32_PIECE) {
+    hipLaunchKernelGGL(kernels[backward ? 1 : 0][sr_f32_variant(shapes)], dim3(std::min(SR_F32_PIECE, a.n_tiles - piece.first)), dim3(256),
+                       sr_f32_lds_bytes(shapes), s, piece);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int shapes) {
@@ -1102,16 +1110,27 @@ hipError_t sr_launch_grad(hipStream_t s, const SrGradArgs& a, int shapes) {
 }
 
 hipError_t sr_launch_grad_sum(hipStream_t s, const SrGradSum* sums, int n_sums, int n_blocks, const float* part, float* const* dst,
-                              int accumulate, const float* terms, int n_terms, float scale, float* loss) {
-  const int blocks = n_blocks + (loss ? 1 : 0);
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(sr_grad_sum_kernel, dim3(blocks), dim3(256), 0, s, sums, n_sums, part, dst, accumulate, terms, n_terms, scale, loss);
-  return hipGetLastError();
+                              int accumulate, const float* terms, long long n_terms, float scale, float* loss) {
+  const int blocks = n_blocks + (loss ? 1 : 0);   // the last one adds up the loss
+  for (int first = 0; first < blocks; first += SR_F32_PIECE) {
+    hipLaunchKernelGGL(sr_grad_sum_kernel, dim3(std::min(SR_F32_PIECE, blocks - first)), dim3(256), 0, s, sums, n_sums, part, dst, accumulate, first,
+                       n_blocks, terms, n_terms, scale, loss);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t sr_launch_loss(hipStream_t s, const SrLossArgs& a) {
-  hipLaunchKernelGGL(sr_loss_kernel, dim3((a.frames * a.B + 3) / 4), dim3(256), 0, s, a);
-  return hipGetLastError();
+  SrLossArgs piece = a;
+  const long long n = (long long)a.frames * a.B;   // below 2^31
+  for (long long first = 0; first < n; first += 4ll * SR_F32_PIECE) {
+    piece.first = (int)first;
+    hipLaunchKernelGGL(sr_loss_kernel, dim3((unsigned)((std::min(n - first, 4ll * SR_F32_PIECE) + 3) / 4)), dim3(256), 0, s, piece);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t sr_launch_patch(hipStream_t s, SrTensor* tensors, float** dst, const SrPatch& p) {

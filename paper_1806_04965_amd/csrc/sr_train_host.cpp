@@ -508,7 +508,7 @@ sr_status sr_window_gradients(sr_graph* g, int32_t W, const void* const* inputs,
     ga.accumulate = k > 0;
     SR_HIP(g, sr_launch_grad(s, ga, c.grad.shapes));
     const bool final = k + 1 == T.chunks.size();
-    SR_HIP(g, sr_launch_grad_sum(s, c.sums, (int)c.grad.sums.size(), c.grad.sum_blocks, T.part, T.dst, k > 0, T.terms, W * B, scale,
+    SR_HIP(g, sr_launch_grad_sum(s, c.sums, (int)c.grad.sums.size(), c.grad.sum_blocks, T.part, T.dst, k > 0, T.terms, (long long)W * B, scale,
                                  final ? loss : nullptr));
   }
   return SR_OK;
@@ -542,13 +542,18 @@ sr_status sr_rmsprop_step(sr_graph* g, float lr, float rho, float eps, const flo
       *mean = (float*)p;
       SR_HIP(g, sr_launch_fill_zero(g->stream, p, n * sizeof(float)));
     }
+    const long long blocks = ((long long)n + 255) / 256;
+    if (b.count > 0 && b.block0[b.count] + blocks > SR_F32_PIECE) {
+      const sr_status st = flush();
+      if (st != SR_OK) return st;
+    }
     const int k = b.count++;
     b.theta[k] = theta;
     b.mean[k] = *mean;
     b.grad[k] = grad;
     b.n[k] = (long long)n;
     if (k == 0) b.block0[0] = 0;
-    b.block0[k + 1] = b.block0[k] + (int)((n + 255) / 256);
+    b.block0[k + 1] = b.block0[k] + (int)blocks;
     return b.count == SR_RMS_MAX ? flush() : SR_OK;
   };
   sr_status st = SR_OK;

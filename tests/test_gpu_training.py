@@ -707,3 +707,36 @@ def test_window_over_a_map_that_only_its_mean_is_read_of():
 @pytest.mark.parametrize("batch", [32768, 32769, 70000])
 def test_window_of_many_images_read_by_their_means(batch):
     mean_readout_window(batch, 3, 5)      # a launch takes the means of 32768 images
+
+
+def test_window_of_2_to_the_31_loss_terms():
+    # frames x samples past what an int counts: every frame's terms of the loss have their place and all of them are added
+    # (a hidden layer less, so that states, gradients and terms are 50 GB)
+    import torch
+    import paper_1806_04965_amd as sr
+    from workloads.graphs import Node, Edge, Graph, ACT_IDENTITY
+    B, Wn = 1 << 19, 4096
+    g0 = Graph("terms", [Node("in", 1, 1, 1, ACT_IDENTITY), Node("out", 2, 1, 1, ACT_IDENTITY)], [Edge(0, 1, "dense", 1, 1, 1, 0)], B, Wn,
+               "f32", out_node=1)
+    g = g0.with_pattern(W.sequential_pattern(g0))
+    x = torch.empty((Wn + 1, B, 1, 1, 1), device="cuda")
+    x[:] = torch.linspace(-1, 1, Wn + 1, device="cuda").view(-1, 1, 1, 1, 1)
+    labels = torch.zeros(B, dtype=torch.int32, device="cuda")
+    labels[: B // 4] = 1
+    dev = sr.SrGraph(g)
+    w, b = np.array([[[[0.5, -0.25]]]], np.float32), np.array([0.1, 0.2], np.float32)
+    dev.set_parameters([w], [np.zeros(1, np.float32), b])
+    loss, dth, dbs = dev.window_gradients([x], labels, Wn)
+    dev.synchronize()
+    got = [loss.item()] + dth[0].flatten().tolist() + dbs[1].tolist()
+    dev.close()
+    xs = x[1:, 0, 0, 0, 0].double().cpu()
+    z = xs[:, None] * torch.from_numpy(w).double().view(1, 2) + torch.from_numpy(b).double()
+    lp, p = torch.log_softmax(z, 1), torch.softmax(z, 1)
+    d = p - torch.tensor([0.75, 0.25], dtype=torch.float64)
+    ref = [-(0.75 * lp[:, 0] + 0.25 * lp[:, 1]).mean().item()] + (d * xs[:, None]).mean(0).tolist() + d.mean(0).tolist()
+    # 8.4e6 terms a thread, added in float32 one after the other: each addition is off by up to 2^-24 of the sum, so n 2^-24 =
+    # 0.5 at worst; with terms of different frames the errors average out
+    assert abs(got[0] - ref[0]) <= 0.05 * ref[0], (got[0], ref[0])
+    for a, r in zip(got[1:], ref[1:]):
+        assert abs(a - r) <= 1e-3 * max(abs(v) for v in ref[1:]), (got, ref)

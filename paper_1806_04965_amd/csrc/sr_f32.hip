@@ -356,9 +356,8 @@ __device__ __forceinline__ void sr_quarter_products(const unsigned char* st, int
 // Agent-scope accesses throughout: the parts run on different XCDs.
 template <int N>
 __device__ __forceinline__ bool sr_row_split(float (&o)[N], const SrSplitScratch& split, int slot, int part_info, int tid, int* flag) {
-  constexpr int UNITS = N * 256 / 1024;   // slots are counted in 1024 floats
   const int n_parts = part_info >> 16;
-  float* mine = split.slabs + ((size_t)slot + (size_t)(part_info & 0xffff) * UNITS) * 1024 + tid;
+  float* mine = split.slabs + ((size_t)slot + (size_t)(part_info & 0xffff)) * 1024 + tid;
 #pragma unroll
   for (int q = 0; q < N; ++q)
     __hip_atomic_store((unsigned*)(mine + q * 256), __float_as_uint(o[q]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -378,7 +377,7 @@ __device__ __forceinline__ bool sr_row_split(float (&o)[N], const SrSplitScratch
   for (int p = 0; p < n_parts; ++p) {
 #pragma unroll
     for (int q = 0; q < N; ++q)
-      o[q] += __uint_as_float(__hip_atomic_load((const unsigned*)(all + (size_t)p * UNITS * 1024 + q * 256), __ATOMIC_RELAXED,
+      o[q] += __uint_as_float(__hip_atomic_load((const unsigned*)(all + (size_t)p * 1024 + q * 256), __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT));
   }
   return true;
@@ -586,9 +585,11 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[((x * MJ + y) * 16 + v) % NREG] = ORDERED ? sum[ORDERED ? x : 0][ORDERED ? y : 0][v] : acc[x][y][v];
   }
-  if ((part_info >> 16) > 1) {
-    __syncthreads();
-    if (!sr_row_split<NREG>(o, A.split, split_slot, part_info, tid, (int*)lds)) return;
+  if constexpr (SMALL) {   // only these are cut into parts
+    if ((part_info >> 16) > 1) {
+      __syncthreads();
+      if (!sr_row_split<NREG>(o, A.split, split_slot, part_info, tid, (int*)lds)) return;
+    }
   }
 
   // ---- epilogue.  Register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its block (a quarter:

@@ -295,7 +295,7 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
         int slot = -1;
         if (parts > 1) {
           slot = *split_slots;
-          *split_slots += parts * (shape == SR_F32_SMALL ? 1 : ti * tj / 1024);
+          *split_slots += parts;   // 32 x 32 floats each
         }
         for (int part = 0; part < parts; ++part, ++k) {
           SrRowTile t{};

@@ -122,7 +122,8 @@ def test_recording_a_hidden_node():
 
 
 def test_rollout_equals_frame_steps_and_hipgraph_equals_eager():
-    g = W.cifar_sr(batch=2, frames=11)       # 11 frames: one 8-frame graph + 3 single frames
+    # one launch a frame: launched plainly, with and without HIP graphs (frames of more launches: the test below)
+    g = W.cifar_sr(batch=2, frames=11)
     w, b, x = W.make_case(g, seed=5, bias_scale=0.1)
     T = g.frames
     a = gpu_rollout(g, w, b, x, T)
@@ -133,6 +134,39 @@ def test_rollout_equals_frame_steps_and_hipgraph_equals_eager():
     ref = oracle_states(g, w, b, x, T, "bf16", nodes=[g.out_node])[g.out_node]
     for t in range(T):
         assert max_abs_rel(a[t], ref[t]) <= 2e-2
+
+
+@pytest.mark.parametrize("out_node", [7, 3])
+@pytest.mark.parametrize("T", [8, 11])
+def test_recorded_bf16_frames_equal_plain_launches(T, out_node):
+    # a launch per update step (dataflow off), seven a frame: eight frames replayed from a recording and three launched
+    # plainly, against plain launches only; the head records itself, a hidden node has a copy launch behind every frame and,
+    # recorded, the frame counter a launch of its own
+    g = W.cifar_sr(batch=2, frames=T)
+    g = g.with_pattern(W.sequential_pattern(g))
+    assert g.out_node == 7
+    w, b, x = W.make_case(g, seed=5, bias_scale=0.1, frames=T)
+    a, dev = gpu_rollout(g, w, b, x, T, out_node=out_node, options={0: 1, 5: 0}, return_dev=True)
+    assert dev.info()["launches_per_frame"] > 4 and not dev.health()["dependency_driven"]
+    again = gpu_rollout(g, w, b, x, T, out_node=out_node, options={0: 0, 5: 0})
+    np.testing.assert_array_equal(a, again)
+    ref = oracle_states(g, w, b, x, T, "bf16", nodes=[out_node])[out_node]
+    for t in range(T):
+        assert np.abs(ref[t]).max() > 0
+        assert max_abs_rel(a[t], ref[t]) <= 2e-2
+    # one graph object: the other node recorded next, then single frames go on
+    n = g.nodes[10 - out_node]
+    import torch
+    xd = [to_device_(x[v], g.dtype) for v in g.input_nodes()]
+    out = torch.empty((T, g.batch, n.height, n.width, n.channels), dtype=dev.tdtype, device="cuda")
+    dev.rollout([t[:T + 1] for t in xd], T, 10 - out_node, out)
+    dev.synchronize()
+    np.testing.assert_array_equal(out.float().cpu().numpy(), gpu_rollout(g, w, b, x, T, out_node=10 - out_node, options={0: 0, 5: 0}))
+    dev.reset([t[0] for t in xd])
+    for t in range(1, T + 1):
+        dev.frame_step([xi[t] for xi in xd])
+        np.testing.assert_array_equal(dev.get_state(out_node).float().cpu().numpy(), a[t - 1])
+    dev.close()
 
 
 @pytest.mark.parametrize("per_graph", [1, 2, 8])

@@ -130,5 +130,8 @@ def test_random_fp32_graph_direct_kernel(seed):
     g = random_graph(200 + seed, dtype="f32")
     w, b, x = W.make_case(g, seed=seed, bias_scale=0.1, frames=g.frames, recipe="uniform")
     ref = oracle_states(g, w, b, x, g.frames, "f64")
-    got, info, work = gpu_states_by_steps(g, w, b, x, g.frames, None)
-    compare_all(got, ref, 1e-4, g.name)
+    # SR_OPT_FORCE_DIRECT: one thread per output; by default the row tiles
+    for label, options in (("direct", {1: 1}), ("row tiles", None)):
+        got, info, work = gpu_states_by_steps(g, w, b, x, g.frames, options)
+        worst = compare_all(got, ref, 1e-4, f"{g.name}/{label}")
+        print(f"[parity] {g.name}/{label}: worst {worst:.3e}", flush=True)

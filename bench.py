@@ -30,7 +30,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-KERNEL_SOURCES = ["sr_kernels.hip", "sr_host.cpp", "sr_internal.h", "sr_graph.h"]
+KERNEL_SOURCES = ["sr_kernels.hip", "sr_device.h", "sr_host.cpp", "sr_internal.h", "sr_graph.h"]
 
 
 def recorded_traffic(workload, pattern):
@@ -66,7 +66,7 @@ def response_frames(g):
 
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA peak
-PEAK_FP32_VALU_TFLOPS = 157.3  # fp32 vector peak (the fp32 graph runs on plain ALUs)
+PEAK_FP32_VALU_TFLOPS = 157.3  # fp32 peak, the same for vector and matrix instructions
 
 
 def train_window_bench(args, g):
@@ -332,7 +332,9 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"{args.workload} ({args.pattern} rollout)", "batch": B, "frames_per_step": T,
                    "nodes": len(g.nodes), "edges": len(g.edges), "inference_factor": info["inference_factor"],
-                   "launches_per_frame": info["launches_per_frame"], "hipgraph": not args.no_hipgraph},
+                   "launches_per_frame": info["launches_per_frame"],
+                   # frames of up to four launches are never replayed
+                   "hipgraph": not args.no_hipgraph and info["launches_per_frame"] > 4 and T >= 8},
         "us_per_frame": round(ms_per_step * 1e3 / T, 2),
         "frame_latency_us": {"p50": round(float(np.percentile(frame_ms, 50)) * 1e3, 2),
                              "p99": round(float(np.percentile(frame_ms, 99)) * 1e3, 2), "frames": len(frame_ms),

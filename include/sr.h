@@ -116,7 +116,8 @@ typedef enum {
                                /* fp32 contractions (training window, fp32 frames): a contraction takes the taller of its
                                   tile shapes when that launch has at least this many workgroups, else a shorter
                                   one (default 2048; 0: always the taller, 2^30: never).  Same results either way up to
-                                  the order of float sums; for tests of both shapes and for tuning. */
+                                  the order of float sums, which the forward pass of a window does not change; for tests
+                                  of both shapes and for tuning. */
   SR_OPT_TRAIN_FRAMES_KEPT = 9 /* training window: frames whose state gradients are kept at a time; a longer window is swept
                                   in chunks of that many (default 0: as many as 16 GiB hold).  Same results up to the
                                   order of float sums. */
@@ -335,7 +336,8 @@ sr_status sr_graph_node_kernels(const sr_graph* g, int32_t* kinds);
  *   dbias     host array of n_nodes device pointers or NULL; dbias[v]: [C] floats, overwritten; entries
  *             of input nodes are ignored, a NULL entry skips that node
  * fp32 arithmetic; every sum is taken in a fixed order (no floating-point atomics): the same call
- * gives the same bits.  Device memory for the window's states and
+ * gives the same bits.  A rectifier's input that is zero to float32 accuracy takes either derivative by the order of its
+ * sum; the forward pass has one order of sums for all batch and window sizes and options, but for the scores.  Device memory for the window's states and
  * gradients (about (2 W + 1) x the graph's node states, plus scratch; see SR_OPT_TRAIN_FRAMES_KEPT; down to (W + 2) x
  * where there is no more) is allocated by the call, kept by the graph and reused by later calls.  The plans of the last
  * four combinations of window size, out_node and options are kept too; another one is made, which allocates its tables,

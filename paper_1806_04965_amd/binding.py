@@ -225,7 +225,8 @@ class SrGraph:
         return {"dependency_timeouts": t.value, "dependency_driven": bool(d.value)}
 
     def node_kernels(self):
-        """sr_graph_node_kernels: per node 0 input, 1 / 2 tile kernel (4 / 8 waves), 3 one thread per output, 4 head."""
+        """sr_graph_node_kernels: per node 0 input, 1 / 2 tile kernel (4 / 8 waves), 3 fp32 kernels
+        (row tiles; one thread per output where those are not taken), 4 head."""
         k = (C.c_int32 * len(self.g.nodes))()
         _check(self.lib, self.lib.sr_graph_node_kernels(self.h, k), self.h)
         return list(k)

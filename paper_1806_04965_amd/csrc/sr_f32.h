@@ -104,6 +104,7 @@ struct SrRun {
 #define SR_F32_KS 16              // reduction indices per step
 // Variants of the tile kernels, by the shapes that a launch holds (bits 1 << shape):
 //   WIDE    some 128 x 128 tiles: 64 accumulator registers a lane (weight gradients: 128), 48 KiB of LDS, three workgroups per CU
+//           (not in the forward pass of a window: see sr_rows_tiles)
 //   NARROW  none: at most 128 registers and 40 KiB of LDS, four workgroups per CU
 //   DEEP    32 x 32 tiles only: few workgroups and a chain of loads per wave, so three steps ahead instead of two
 // DSR2 window (B=64, W=8) with the weight gradients' tiles all narrow 1557 us, as planned 1575; GTSRB-shaped window without

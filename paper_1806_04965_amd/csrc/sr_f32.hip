@@ -5,16 +5,18 @@
 // step are brought into LDS by direct-to-LDS loads whose lane addresses do the gathering (taps, strides, padding;
 // elements that do not exist are read from a line of zeros), ahead of the step being multiplied: no registers between
 // global memory and LDS.  fp32 matrix instructions are slow (a 32x32x2 product takes 64 cycles of its SIMD); a step's
-// operand traffic (at most 16 bytes per cycle and CU) hides behind them.  What bounds a tile is the fp32 matrix rate, 157
-// TFLOP/s, for 128 x 128 tiles, whose waves have 32 products a step (GTSRB-shaped launches: matrix cores 78 % busy).
-// 64 x 64 and 128 x 32 tiles have 8: there the step's fixed costs (some 70 vector and 120 scalar instructions, a barrier, a
-// wait) take longer than its products (matrix cores 47 % busy with three workgroups per CU).  So these fetch steps in
-// pairs, a barrier per pair and, where a pair lies in one tap, one set of addresses; and launches without 128 x 128 tiles
-// run four workgroups per CU (see the variants in sr_f32.h).
+// operand traffic is 8 bytes per cycle of its products and CU for 128 x 128 tiles, 12 for 128 x 64, 16 for 64 x 64, 20 for
+// 128 x 32 and 32 for 32 x 32.  What bounds a tile is the fp32 matrix rate, 157 TFLOP/s, for 128 x 128 tiles, whose waves have
+// 32 products a step (GTSRB-shaped windows: matrix cores 77 % busy in the reverse sweep, 74 % in the weight gradients; 71 %
+// in the forward pass with its 128 x 64 tiles).  64 x 64 and 128 x 32 tiles have 8: there the step's fixed costs (some 70
+// vector and 120 scalar instructions, a barrier, a wait) take longer than its products (matrix cores 47 % busy with three
+// workgroups per CU).  So these fetch steps in pairs, a barrier per pair and, where a pair lies in one tap, one set of
+// addresses; and launches without 128 x 128 tiles run four workgroups per CU (see the variants in sr_f32.h): 54 % in a DSR2
+// frame, 51 % in the forward pass of its windows.
 //
 // Measured, DSR2 as an fp32 graph (batch 64, 6.4 GFLOP per frame): 1350 us per frame with a thread per output (weights
 // and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s), 100 with pairs; MNIST SR, batch 128:
-// 29 -> 15 us.  Training windows, step by step -> pairs and variants: DSR2 B=64 W=8 1674 -> 1498 us, GTSRB-shaped
+// 31 -> 17 us.  Training windows, step by step -> pairs and variants: DSR2 B=64 W=8 1674 -> 1498 us, GTSRB-shaped
 // B=128 W=4 6270 -> 5970, MNIST SR 317 -> 302.
 //
 // Every sum has a fixed order (reduction index by index within a part, parts in order, waves in order): the same call

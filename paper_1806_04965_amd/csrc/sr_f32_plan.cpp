@@ -245,6 +245,15 @@ double sr_rows_work(const SrRowPlan& p, int phase) {
 // give the launch more workgroups and shorter chains of dependent steps.  A tile may take as long as an even share of
 // the launch's work per compute unit (or some microseconds), else the next smaller shape is tried; below that the
 // reduction is cut into parts.
+// What the constants are worth: each halved and doubled, times of 17 cases (frames of 1 to 128 images, windows; us) --
+//   20000 cycles a tall tile may take            all within noise (0.5 %) either way
+//   12000 of a middle one, 512 of them           noise; a quarter of the workgroups or twice: DSR2 window 1480 -> 1505, 1625
+//   10000 a 32 x 32 tile may take uncut          half: MNIST SR clip 269 -> 237, DSR2 sequential B=1 1136 -> 1058; twice: 359, 1382
+//   5000 fixed                                   half: DSR2 B=1 1187; twice: MNIST SR clip 240, 1117, nothing slower by over 4 %
+//   750 per four steps of 32 x 32 tiles          half: DSR2 clip 1625 -> 2544; twice: 1409, MNIST SR clip 238, small window 221 -> 239
+//   700 a step of middle tiles                   half: noise; twice: DSR2 clip 1745, sequential window 2390 -> 2449
+//   at most 16 parts                             8: DSR2 B=1 1187; 32: noise
+// so 32 x 32 tiles are taken, and left whole, more often than is best for fp32 frames.
 void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split, bool ordered,
                    int* split_slots, std::vector<SrRowTile>* out, int* shapes) {
   double work = 0;

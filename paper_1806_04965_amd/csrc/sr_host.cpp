@@ -1482,6 +1482,7 @@ SrFrame recorded_frame(const sr_graph* g, int offset, int advance) { return SrFr
 // any time, without the library taking part, so its frames have to be the ones that follow whatever has been computed then:
 // their number, and which copy of a state is the last frame's, is known to the device only.
 bool device_counts(sr_graph* g) {
+  if (!g->was_reset) return false;   // nothing is counted yet: the states are those of copy 0
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (!g->replayed && g->stream != nullptr && hipStreamIsCapturing(g->stream, &st) == hipSuccess && st == hipStreamCaptureStatusActive)
     g->replayed = true;
@@ -1670,7 +1671,8 @@ sr_status run_frames(sr_graph* g, int64_t frames, SrCtx c, bool next_frame, cons
   // A replayed launch costs the host 1.5 us instead of up to 9 and starts later on the device: frames of one launch
   // take longer replayed (16 streaming frames: 500 us for 486, CIFAR-shaped; 289 for 282, MNIST SR), of two or four
   // too (453 for 417, MNIST SR hybrid; 1214 for 1140, DSR4 hybrid), and with eight (DSR4 sequential) the time is the
-  // same within 2 % while the host is busy for 209 us instead of 1222.
+  // same within 2 % while the host is busy for 209 us instead of 1222.  A single frame is always launched plainly: with ten
+  // launches (DSR6 sequential fp32, one image) it takes 113 us of the device and 31 of the host.
   if (g->use_hipgraph && !flow && !next_frame && g->launches_per_frame > 4 && left >= g->frames_per_graph && g->frames_per_graph > 1) {
     if ((st = ensure_graph(g)) != SR_OK) return st;
     for (; left >= g->frames_per_graph; left -= g->frames_per_graph) {

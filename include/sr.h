@@ -225,9 +225,9 @@ sr_status sr_frame_step(sr_graph* g, const void* const* inputs_t);
  *    a plain launch on the graph's stream (nothing is captured or instantiated, no memset node), so
  *    the call may itself be captured by the caller.  A recording of one or more calls may be replayed any
  *    number of times, also between calls of any kind: every replay computes the frames that follow the last
- *    one computed on the stream, from what the input buffers hold at that time.  Once a call has been
- *    recorded the device alone counts the frames: sr_get_state, sr_set_state and all frame calls go by its
- *    count, sr_frame_index still counts calls;
+ *    one computed on the stream, from what the input buffers hold at that time.  Once a call that computes
+ *    frames, or sr_reset, has been recorded the device alone counts the frames: sr_get_state, sr_set_state
+ *    and all frame calls go by its count, sr_frame_index still counts calls;
  *  - the partial sums and arrival counters of tiles that are cut along their contraction (the only
  *    device memory a frame needs beyond the graph's states and tables) live in a static device
  *    array of the library, 64 MiB on every GPU the library is loaded on, instead of the graph's own

@@ -1702,6 +1702,7 @@ sr_status do_reset(sr_graph* g, const void* const* input_frame0, SrCtx c) {
   SR_HIP(g, sr_launch_reset(g->stream, g->ctx, c, g->reset_items, g->n_reset_items, g->n_reset_blocks, frame0, g->dtype == SR_BF16));
   g->host_frame = 0;
   g->was_reset = true;
+  device_counts(g);   // recorded, it is done again without the host's count going back
   return SR_OK;
 }
 

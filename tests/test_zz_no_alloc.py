@@ -197,3 +197,53 @@ def test_replays_of_recorded_calls_go_on_with_the_stream(name, calls, hidden_nod
     same(1)
     ref.close()
     dev.close()
+
+
+@pytest.mark.parametrize("what", ["reset and a frame", "rollout"])
+@pytest.mark.parametrize("name", ["bf16 streaming", "bf16 sequential, dependency-driven", "f32 sequential"])
+def test_replays_that_start_again_from_frame_0(name, what):
+    # a recording that resets: a replay puts the stream back to frame 1 (rollout: 2) whatever has been computed since, and
+    # ordinary frames go on from there
+    import torch
+    import paper_1806_04965_amd as sr
+    g = GRAPHS[name]()
+    w, b, x = W.make_case(g, seed=22, bias_scale=0.1, frames=9)
+    xd = [to_device(x[v], g.dtype) for v in g.input_nodes()]
+    ref, dev = sr.SrGraph(g), sr.SrGraph(g)
+    for d in (ref, dev):
+        d.set_parameters(w, b)
+        d.reset([t[0] for t in xd])
+    recorded = 1 if what == "reset and a frame" else 2
+    out = torch.zeros((2, g.batch, 1, 1, g.nodes[g.out_node].channels), dtype=dev.tdtype, device="cuda")
+    head = [t[:3].contiguous() for t in xd]
+    dev.rollout(head, 2, g.out_node, out)     # (the recorded node is set: a rollout that changes it copies a table)
+    dev.synchronize()
+    recording = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(recording, stream=dev.stream):
+        if recorded == 1:
+            dev.reset([t[0] for t in xd])
+            dev.frame_step_static([t[1] for t in xd])
+        else:
+            dev.rollout(head, 2, g.out_node, out)
+    for more in (0, 1, 2, 3):
+        out.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(dev.stream):
+            recording.replay()
+        torch.cuda.synchronize()
+        ref.reset([t[0] for t in xd])
+        for t in range(1, recorded + more + 1):
+            ref.frame_step([xi[t] for xi in xd])
+            if t > recorded:
+                dev.frame_step([xi[t] for xi in xd])
+            if t <= 2 and recorded == 2:
+                ref.synchronize()
+                assert torch.equal(out[t - 1].flatten(), ref.get_state(g.out_node).flatten()), (name, more, t)
+        ref.synchronize()
+        dev.synchronize()
+        for v in range(len(g.nodes)):
+            assert torch.equal(dev.get_state(v), ref.get_state(v)), (name, more, v)
+    assert dev.health()["dependency_timeouts"] == 0
+    ref.close()
+    dev.close()

@@ -21,8 +21,8 @@
 //
 // Every sum has a fixed order (reduction index by index within a part, parts in order, waves in order): the same call
 // gives the same bits.  The forward pass of a training window has one order for all sizes and tiles (SR_ROWS_ORDERED);
-// against tiles that take theirs as it comes, and cut long sums, that costs DSR2 1459 -> 1532 us, GTSRB-shaped 5990 -> 6130,
-// MNIST SR 302 -> 360.
+// against tiles that take theirs as it comes, and cut long sums, that costs DSR2 1459 -> 1480 us, GTSRB-shaped 5990 -> 6180,
+// MNIST SR 302 -> 358.
 #include <algorithm>
 
 #include "sr_device.h"

@@ -65,7 +65,14 @@ struct SrSeg {
   SrDiv d_gc, d_ntj, d_up;
   SrDiv d_wup;            // backwards: gathered positions per tap of an up-sampled edge
   int32_t dist;           // backwards: the gathered node's gradient is zero after frame W - dist
+  int32_t lines;          // first SrLine of the segment's reduction indices; -1: no table
 };
+// A reduction index of a segment whose gathered channel count is no multiple of four: where it is from tap (0, 0), and its tap.
+// Sixteen per step, in the order of the lines of a stage; past the end: a tap outside every image.  (Decoded from the index, 25
+// scalar instructions a line, the five steps of a 5x5x3 edge took a 128 x 32 tile 30 us of 58.)
+SR_HD int sr_in_turn(int line) { return 2 * (line & 7) + (line >> 3); }   // the index of a step that line `line` of its stage holds, if in turn
+#define SR_LINES_MAX 4096   // reduction indices of an edge that gets a table
+struct SrLine { int32_t off, dh, dw, pad_; };
 
 // What a row tile's rows are: the pixels h = hh * S + ph, w = ww * S + pw of a node (S = 1: all of them).
 struct SrPhase {
@@ -88,11 +95,15 @@ struct SrRowNode {
 
 // tile shapes: TI x TJ, of four waves; SR_F32_SMALL: each wave takes every fourth reduction step of a 32 x 32 tile
 enum { SR_F32_128x128 = 0, SR_F32_128x64 = 1, SR_F32_64x64 = 2, SR_F32_128x32 = 3, SR_F32_SMALL = 4 };
-struct SrRowTile {
+struct alignas(128) SrRowTile {
   int32_t phase;                  // < 0: empty slot
   int32_t shape, i0, j0;
   int32_t step_begin, step_end;   // part of the phase's reduction steps
   int32_t split_slot, part;       // K-split as in SrMfmaTile: slot of part 0 (-1: none), part index | parts << 16
+  // The phase itself: a tile then starts on one round trip to memory, then one for segment and node, one for their tensors
+  // (tile -> phase -> segment -> tensor was 2 us of a 32 x 32 tile's 4 to 12, all of it waiting)
+  SrPhase p;
+  int32_t pad_[8];
 };
 
 // A launch over several (tile list, frame) pairs: pair k takes the workgroups from block0 on.
@@ -232,8 +243,8 @@ SR_HD uint32_t sr_pix_off(const SrGradEdge& e, const SrPixAt& p, int b0, uint32_
 struct SrRowArgs {
   const SrTensor* tensors;
   const SrRowNode* nodes;
-  const SrPhase* phases;
   const SrSeg* segs;
+  const SrLine* lines;
   const SrRowTile* tiles;
   const SrRun* runs;              // training: (tile list, frame) pairs of the launch
   int32_t n_runs, n_tiles;        // n_tiles: workgroups
@@ -321,6 +332,7 @@ inline int sr_f32_lds_bytes(int shapes) {   // of a workgroup of a launch with t
 struct sr_graph;
 struct SrRowPlan {
   std::vector<SrSeg> segs;
+  std::vector<SrLine> lines;
   std::vector<SrPhase> phases;
   std::vector<SrRowNode> nodes;
 };

@@ -8,16 +8,21 @@
 // operand traffic is 8 bytes per cycle of its products and CU for 128 x 128 tiles, 12 for 128 x 64, 16 for 64 x 64, 20 for
 // 128 x 32 and 32 for 32 x 32.  What bounds a tile is the fp32 matrix rate, 157 TFLOP/s, for 128 x 128 tiles, whose waves have
 // 32 products a step (GTSRB-shaped windows: matrix cores 77 % busy in the reverse sweep, 74 % in the weight gradients; 71 %
-// in the forward pass with its 128 x 64 tiles).  64 x 64 and 128 x 32 tiles have 8: there the step's fixed costs (some 70
-// vector and 120 scalar instructions, a barrier, a wait) take longer than its products (matrix cores 47 % busy with three
-// workgroups per CU).  So these fetch steps in pairs, a barrier per pair and, where a pair lies in one tap, one set of
-// addresses; and launches without 128 x 128 tiles run four workgroups per CU (see the variants in sr_f32.h): 54 % in a DSR2
-// frame, 51 % in the forward pass of its windows.
+// in the forward pass with its 128 x 64 tiles, before the loop below).  64 x 64 and 128 x 32 tiles have 8: there a step's fixed
+// costs take as long as its products.  So these fetch steps in pairs, a barrier per pair; launches without 128 x 128 tiles run
+// four workgroups per CU (see the variants in sr_f32.h); and the steps of whole segments go through a loop that holds nothing
+// but their loads and products (run_along below: 155 instructions a pair, 16 of them products, where the code that takes any
+// step of any segment has 400).  DSR2 frame: matrix cores 54 % busy before, 58 % since at 0.8 of the time.  What is left there is
+// not the loop (without its loads, or without its LDS reads, a frame takes as long): a 128 x 32 tile of 18 steps spends
+// 12 us of 28 in its tables, first operands and stores while its compute unit's other three do the same.
 //
 // Measured, DSR2 as an fp32 graph (batch 64, 6.4 GFLOP per frame): 1350 us per frame with a thread per output (weights
-// and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s), 100 with pairs; MNIST SR, batch 128:
-// 31 -> 17 us.  Training windows, step by step -> pairs and variants: DSR2 B=64 W=8 1674 -> 1498 us, GTSRB-shaped
-// B=128 W=4 6270 -> 5970, MNIST SR 317 -> 302.
+// and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s), 100 with pairs, 82 with segments' steps back
+// to back; MNIST SR, batch 128: 31 -> 17 -> 14 us.  Training windows, step by step -> pairs and variants -> now: DSR2 B=64 W=8
+// 1674 -> 1480 -> 1430 us, GTSRB-shaped B=128 W=4 6270 -> 6180 -> 5640, MNIST SR 362 -> 362.
+//
+// In the loop a wave's priority is raised but for its products: loads, addresses and set-up of one wave then go ahead of the
+// others' products, which the matrix cores take 64 cycles each for (GTSRB-shaped window 5690 -> 5620 us, DSR2 1437 -> 1423).
 //
 // Every sum has a fixed order (reduction index by index within a part, parts in order, waves in order): the same call
 // gives the same bits.  The forward pass of a training window has one order for all sizes and tiles (SR_ROWS_ORDERED);
@@ -30,6 +35,7 @@
 
 namespace {
 
+typedef int sr_i32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 #define SR_CONST4(T) const __attribute__((address_space(4))) T*
 template <typename T>
@@ -65,6 +71,13 @@ __device__ __forceinline__ unsigned sr_lds_at(const void* p) {
   return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) char*)p;
 }
 
+// the same address, but values read from it are not kept from earlier reads
+template <typename T>
+__device__ __forceinline__ SR_CONST4(T) sr_again(SR_CONST4(T) p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 __device__ __forceinline__ SrDiv sr_load_div(SR_CONST4(SrDiv) d) { return SrDiv{d->mul, d->sh}; }
 __device__ __forceinline__ SrSeg sr_load_seg(SR_CONST4(SrSeg) s) {
   SrSeg g;
@@ -76,7 +89,7 @@ __device__ __forceinline__ SrSeg sr_load_seg(SR_CONST4(SrSeg) s) {
   g.wt0 = s->wt0; g.wti = s->wti; g.wtj = s->wtj;
   g.ldw = s->ldw; g.step0 = s->step0;
   g.d_gc = sr_load_div(&s->d_gc); g.d_ntj = sr_load_div(&s->d_ntj); g.d_up = sr_load_div(&s->d_up);
-  g.d_wup = sr_load_div(&s->d_wup); g.dist = s->dist;
+  g.d_wup = sr_load_div(&s->d_wup); g.dist = s->dist; g.lines = s->lines;
   return g;
 }
 __device__ __forceinline__ SrPhase sr_load_phase(SR_CONST4(SrPhase) s) {
@@ -112,7 +125,6 @@ __device__ __forceinline__ bool sr_seg_counts(const SrSeg& g, const SrSlots& sl)
 // the edges' sums are added in edge order; inside a step the products go 0, 8, 1, 9, .. where all channel counts are
 // multiples of four (SR_SEG_QUADS), else 0, 1, 2, .. (line 8 h + k of its stage then holds index 2 k + h).
 enum { SR_ROWS_FRAME = 0, SR_ROWS_BACK = 1, SR_ROWS_ORDERED = 2 };
-SR_HD int sr_in_turn(int line) { return 2 * (line & 7) + (line >> 3); }
 
 // The operands of a tile: a TI x 16 and a 16 x TJ piece per step, NW waves fetching them together.
 //   rows:  TI (TJ) rows of 16 reduction indices, 64 bytes a row, pieces of four permuted (sr_f32_piece)
@@ -128,20 +140,49 @@ struct SrRowOperands {
   static constexpr int LOADS = NA + NB;                            // fewest loads a wave issues per step
   static constexpr bool HALF_B = TJ / (16 * NW) == 0;
 
-  SrSeg g;
+  // Of the segment: what every step needs.  The rest is read again where it is needed (sr_again): with all of it in registers
+  // the kernels of many shapes kept 150 scalar registers in lanes of vector registers, read back step by step.
+  SR_CONST4(SrSeg) seg;
+  int GH, GW, GC, dir, ntj, R, ldw;
+  int wt0, wti, wtj;         // backwards
+  SrDiv d_wup;
   int row_h[NA], row_w[NA];  // this lane's rows: where tap (0, 0) lands ...
   const char* row_at[NA];    // ... and its address
   int wv, lane, i0, j0;
   int quads, quads_w;
   int turn;                  // ordered: the products of a step go in turn
+  // A step whose indices lie in one tap (channel counts that are multiples of 16) has addresses that go on from those of the
+  // step before: a lane's gathered address by the channels passed, theta by a scalar base under lane offsets that stay for
+  // the segment; only a new tap looks at the image's edges again.  Taking every step's tap and addresses from its number
+  // instead cost a 32 x 32 tile 1000 cycles a step, a frame of the tiny network 11.8 us.
+  const SrLine* lines;       // null: no table
+  int along;                 // A goes that way
+  int at_r, vi, vj, c;       // step that the addresses are for; its tap and first channel
+  const char* cur[NA];
+  unsigned go[NA];           // 4, or 0 where the line of zeros is read: bytes per channel passed
+  const char* wbase;         // theta at column j0, first index (backwards: tap 0, channel 0)
+  const char* wcur;          // backwards: theta at column j0 of the tap and channel
+  uint32_t woff[BACK ? NB : 1];
+  uint32_t wpair;            // a pair's theta by full waves where a step's takes half of each (HALF_B)
+  int wide_w;                // ... whose lane offsets fit 32 bits
 
-  // a new segment: where this lane's rows are in its image
-  __device__ __forceinline__ void enter(const SrPhase& p, const SrTensor* tensors, const SrSlots& sl) {
+  // (a 32 x 32 tile's descriptors stay in registers: its few waves wait for every read)
+  template <typename T>
+  static __device__ __forceinline__ SR_CONST4(T) again(SR_CONST4(T) p) { return NW == 1 ? p : sr_again(p); }
+
+  // a new segment, whose first step will be the one at r0: where this lane's rows are in its image
+  __device__ __forceinline__ void enter(const SrSeg& g, SR_CONST4(SrSeg) at_seg, SR_CONST4(SrPhase) phase, const SrTensor* tensors,
+                                        const SrLine* line_table, const SrSlots& sl, int r0) {
+    const SrPhase p = sr_load_phase(again(phase));
+    seg = at_seg;
+    GH = g.GH; GW = g.GW; GC = g.GC; dir = g.dir; ntj = g.ntj; R = g.R; ldw = g.ldw;
+    if (BACK) { wt0 = g.wt0; wti = g.wti; wtj = g.wtj; d_wup = g.d_wup; }
     SR_CONST4(SrTensor) t = sr_k(tensors) + g.tensor;
     const int slot = sl.lag0 + ((g.flags & SR_SEG_LAG) ? sl.lag1 - sl.lag0 : 0);   // (a select between the fields would go through memory)
     const char* src = sr_uni_ptr((const char*)(unsigned long long)t->base + slot * t->stride);
     quads = SR_UNI((g.flags & SR_SEG_QUADS) && ((unsigned)(unsigned long long)src & 15u) == 0);
     quads_w = SR_UNI((g.ldw & 3) == 0);
+    lines = g.lines >= 0 ? line_table + g.lines : nullptr;
     if (FOR == SR_ROWS_ORDERED) turn = !(g.flags & SR_SEG_QUADS);
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
@@ -152,70 +193,197 @@ struct SrRowOperands {
       row_w[n] = at.w;
       row_at[n] = src + at.off * 4;
     }
+    along = quads && (g.GC & 15) == 0;
+    if (along) {
+      const SrTapAt t0 = sr_tap_at(g, SR_UNI(r0));
+      at_r = r0;
+      vi = t0.vi;
+      vj = t0.vj;
+      c = t0.c;
+      const int k4 = sr_f32_piece(lane >> 2, lane & 3);
+#pragma unroll
+      for (int n = 0; n < NA; ++n) row_at[n] += 16 * k4;
+    }
+    if (BACK) {
+      wide_w = g.GC < (1 << 22);
+      wbase = (const char*)g.w + (unsigned long long)(unsigned)j0 * (unsigned)g.GC * 4;
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        const int row = HALF_B ? wv * 8 + (lane >> 2) : n * 16 * NW + wv * 16 + (lane >> 2);
+        // (a half-filled wave's rows start at a multiple of eight: its pieces are permuted differently from A's; columns that
+        // the node does not have read its last one)
+        woff[n] = ((uint32_t)min(row, g.ldw - 1 - j0) * (uint32_t)g.GC + 4u * (uint32_t)sr_f32_piece(row, lane & 3)) * 4u;
+      }
+    } else {
+      wide_w = g.ldw < (1 << 22);
+      wbase = (const char*)g.w + (unsigned long long)(unsigned)j0 * 4;
+      const int id = HALF_B ? wv * 32 + lane : wv * 64 + lane;
+      if (quads_w) woff[0] = ((uint32_t)(id / (TJ / 4)) * (uint32_t)g.ldw + (uint32_t)min(4 * (id % (TJ / 4)), g.ldw - 4 - j0)) * 4u;
+      else woff[0] = ((uint32_t)((wv * 64 + lane) / TJ) * (uint32_t)g.ldw + (uint32_t)min((wv * 64 + lane) % TJ, g.ldw - 1 - j0)) * 4u;
+    }
+    if (HALF_B) {
+      const int row = (wv & 1) * 16 + (lane >> 2), id = wv * 64 + lane;
+      if (BACK) wpair = ((uint32_t)min(row, ldw - 1 - j0) * (uint32_t)GC + 4u * (uint32_t)sr_f32_piece(row, lane & 3) + 16u * (uint32_t)(wv >> 1)) * 4u;
+      else wpair = ((uint32_t)(id / (TJ / 4)) * (uint32_t)ldw + (uint32_t)min(4 * (id % (TJ / 4)), max(ldw - 4 - j0, 0))) * 4u;
+    }
+    if (along) look();
+  }
+  // the fields above as a descriptor
+  __device__ __forceinline__ SrSeg hot() const {
+    SrSeg g{};
+    g.GH = GH; g.GW = GW; g.GC = GC; g.dir = dir; g.ntj = ntj; g.R = R; g.ldw = ldw;
+    if (BACK) { g.wt0 = wt0; g.wti = wti; g.wtj = wtj; g.d_wup = d_wup; }
+    return g;
   }
 
-  // may the steps at r0 and r0 + 16 share their addresses (one tap, 16-byte loads)?  stop: end of the segment's share
-  __device__ __forceinline__ bool pairs(int r0, int stop) const {
-    return quads && (g.GC & 31) == 0 && (r0 & 31) == 0 && r0 + SR_F32_KS < stop && (BACK || quads_w);
+  // the gathered addresses at tap (vi, vj), channel c
+  __device__ __forceinline__ void look() {
+    const SrSeg g = hot();
+    const SrTapAt t{vi, vj, c};
+    const long long toff = sr_gather_off(g, t) * 4;
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      const bool ok = sr_gather_ok(g, SrRowAt{row_h[n], row_w[n], 0}, t);
+      cur[n] = ok ? row_at[n] + toff : (const char*)sr_zero_line;
+      go[n] = ok ? 4u : 0u;
+    }
+    if (BACK) wcur = wbase + (unsigned long long)sr_weight_off(g, t, 0) * 4;
+  }
+  // ... D channels further on
+  template <int D>
+  __device__ __forceinline__ void advance() {
+    at_r += D;
+    c += D;
+    if (c < GC) {
+#pragma unroll
+      for (int n = 0; n < NA; ++n) cur[n] += D * go[n];
+      if (BACK) wcur += 4 * D;
+      return;
+    }
+    do {
+      c -= GC;
+      if (++vj == ntj) { vj = 0; ++vi; }
+    } while (c >= GC);
+    look();
+  }
+  // ... of the step at r0
+  __device__ __forceinline__ void go_on(int r0) {
+    while (at_r < r0) advance<(NW == 1 ? 4 : 1) * SR_F32_KS>();
   }
 
-  __device__ __forceinline__ const char* gathered(int n, const SrTapAt& t, long long tap_bytes) const {
+  // Do this segment's steps (PAIR: at r0 even pairs of steps) take the loads of issue_along?
+  template <bool PAIR>
+  __device__ __forceinline__ bool all_along(int r0) const {
+    return along && wide_w && (!PAIR || ((GC & 31) == 0 && (r0 & 31) == 0 && (BACK || quads_w)));
+  }
+  // loads of a step all of whose indices exist (PAIR: two of them, in one tap), its gathered addresses at hand; forward: w is theta
+  // at its first index
+  template <bool PAIR>
+  __device__ __forceinline__ void issue_along(unsigned at, const char* w) const {
+    const unsigned bt = at + TI * 64;
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      sr_to_lds16(cur[n], at + (n * NW + wv) * 1024);
+      if (PAIR) sr_to_lds16(cur[n] + 64, at + STAGE + (n * NW + wv) * 1024);
+    }
+    w = sr_uni_ptr(BACK ? wcur : w);
+    const unsigned line = (unsigned)ldw * 4u;
+    if (PAIR && HALF_B) {
+      uint32_t o = wpair;
+      asm volatile("" : "+v"(o));   // keeps the offset 32-bit: scalar base + lane offset addressing
+      sr_to_lds16(w + o, bt + (wv >> 1) * STAGE + (wv & 1) * 1024);
+    } else if (BACK || quads_w) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {   // forward: 256 NW / TJ lines further on each time
+        uint32_t o = woff[BACK ? n : 0];
+        asm volatile("" : "+v"(o));
+        const char* wn = BACK ? w : w + (unsigned long long)(n * (256 * NW / TJ)) * line;
+        if (HALF_B) {
+          if (lane < 32) sr_to_lds16(wn + o, bt + wv * 512);
+        } else {
+          sr_to_lds16(wn + o, bt + (n * NW + wv) * 1024);
+          if (PAIR) sr_to_lds16((BACK ? wn + 64 : wn + (unsigned long long)SR_F32_KS * line) + o, bt + STAGE + (n * NW + wv) * 1024);
+        }
+      }
+    } else {
+      uint32_t o = woff[0];
+      asm volatile("" : "+v"(o));
+#pragma unroll
+      for (int q = 0; q < TJ / 4 / NW; ++q)
+        sr_to_lds4(w + (unsigned long long)(q * (64 * NW) / TJ) * line + o, bt + (q * NW + wv) * 256);
+    }
+  }
+  __device__ __forceinline__ const char* theta(int r0) const { return wbase + (unsigned long long)(unsigned)r0 * ((unsigned)ldw * 4u); }
+
+  // this lane's row at an SrLine
+  __device__ __forceinline__ const char* lined(int off, int dh, int dw) const {
+    const bool ok = (unsigned)row_h[0] + (unsigned)dh < (unsigned)GH && (unsigned)row_w[0] + (unsigned)dw < (unsigned)GW;
+    return ok ? row_at[0] + (long long)off * 4 : (const char*)sr_zero_line;
+  }
+  __device__ __forceinline__ const char* gathered(const SrSeg& g, int n, const SrTapAt& t, long long tap_bytes) const {
     return sr_gather_ok(g, SrRowAt{row_h[n], row_w[n], 0}, t) ? row_at[n] + tap_bytes : (const char*)sr_zero_line;
   }
 
-  // loads of the 16 reduction indices from r0 on, into LDS at `at`; PAIR: and of the next 16, into the stage behind it
-  template <bool PAIR = false>
+  // loads of the 16 reduction indices from r0 on, into LDS at `at`
   __device__ __forceinline__ void issue(int r0, unsigned at) {
     const char* zero = (const char*)sr_zero_line;
     const unsigned bt = at + TI * 64;
-    if (quads) {
-      const int k4 = sr_f32_piece(lane >> 2, lane & 3);
-      SrTapAt t;
-      if ((g.GC & 15) == 0) {   // the step lies inside one tap: its decoding runs on the scalar unit
-        t = sr_tap_at(g, SR_UNI(r0));
-        t.c += 4 * k4;
-      } else {
-        t = sr_tap_at(g, r0 + 4 * k4);
-      }
+    const bool all = r0 + SR_F32_KS <= R;   // all sixteen indices exist (a wave of four may stand past the end of its segment)
+    if (all && all_along<false>(r0)) {
+      go_on(r0);
+      issue_along<false>(at, theta(r0));
+      return;
+    }
+    if (along && all) {
+      go_on(r0);
+#pragma unroll
+      for (int n = 0; n < NA; ++n) sr_to_lds16(cur[n], at + (n * NW + wv) * 1024);
+    } else if (quads) {   // (past the end: of the rows' addresses, which may include k4, none is read)
+      const SrSeg g = sr_load_seg(again(seg));
+      const SrTapAt t = sr_tap_at(g, r0 + 4 * sr_f32_piece(lane >> 2, lane & 3));
       const long long toff = sr_gather_off(g, t) * 4;
 #pragma unroll
-      for (int n = 0; n < NA; ++n) {
-        const char* p = gathered(n, t, toff);
-        sr_to_lds16(p, at + (n * NW + wv) * 1024);
-        if (PAIR) sr_to_lds16(p + 64, at + STAGE + (n * NW + wv) * 1024);
-      }
-      if (BACK) {
-        // (a half-filled wave's rows start at a multiple of eight: its pieces are permuted differently from A's)
-        const SrTapAt tb = HALF_B ? sr_tap_at(g, r0 + 4 * sr_f32_piece(wv * 8 + (lane >> 2), lane & 3)) : t;
-        const bool r_ok = tb.vi != SR_NO_TAP;
-        const uint32_t woff = sr_weight_off(g, tb, 0);
+      for (int n = 0; n < NA; ++n) sr_to_lds16(gathered(g, n, t, toff), at + (n * NW + wv) * 1024);
+    } else if (TI >= 64 && lines != nullptr && r0 < R) {
+      SR_CONST4(sr_i32x16) step = (SR_CONST4(sr_i32x16))(unsigned long long)(lines + r0);
+      const int l0 = TI == 128 ? 8 * (wv >> 1) : 4 * wv;   // this wave's lines, 64 of a line's rows
+#pragma nounroll
+      for (int k = 0; k < TI / 64; ++k) {   // (four lines in scalar registers at a time)
+        const sr_i32x16 x = step[l0 / 4 + k];
 #pragma unroll
-        for (int n = 0; n < NB; ++n) {
-          const int j = j0 + (HALF_B ? wv * 8 + (lane >> 2) : n * 16 * NW + wv * 16 + (lane >> 2));
-          const char* p = (r_ok && j < g.ldw) ? sr_at((const char*)g.w, woff + (uint32_t)j * (uint32_t)g.GC) : zero;
-          if (HALF_B) {
-            if (lane < 32) {
-              sr_to_lds16(p, bt + wv * 512);
-              if (PAIR) sr_to_lds16(p + 64, bt + STAGE + wv * 512);
-            }
-          } else {
-            sr_to_lds16(p, bt + (n * NW + wv) * 1024);
-            if (PAIR) sr_to_lds16(p + 64, bt + STAGE + (n * NW + wv) * 1024);
-          }
-        }
-        return;
+        for (int q = 0; q < 4; ++q) sr_to_lds4(lined(x[4 * q], x[4 * q + 1], x[4 * q + 2]), at + (l0 + 4 * k + q) * (TI * 4) + (TI == 128 ? (wv & 1) * 256 : 0));
       }
     } else {
+      const SrSeg g = sr_load_seg(again(seg));
 #pragma unroll
       for (int q = 0; q < TI / 4 / NW; ++q) {
         const int id = q * NW + wv;
         const int line = TI >= 64 ? id * 64 / TI : 2 * id + (lane >> 5);
         const int k = FOR == SR_ROWS_ORDERED && turn ? sr_in_turn(line) : line;
         const SrTapAt t = sr_tap_at(g, TI >= 64 ? SR_UNI(r0 + k) : r0 + k);
-        const char* p = gathered(0, t, sr_gather_off(g, t) * 4);
+        const char* p = gathered(g, 0, t, sr_gather_off(g, t) * 4);
         sr_to_lds4(p, at + id * 256);
       }
-      if (BACK) {
+    }
+    if (BACK) {
+      if (quads) {
+        // (a half-filled wave's rows start at a multiple of eight: its pieces are permuted differently from A's)
+        const SrSeg g = sr_load_seg(again(seg));
+        const SrTapAt t = sr_tap_at(g, r0 + 4 * sr_f32_piece((HALF_B ? wv * 8 : 0) + (lane >> 2), lane & 3));
+        const bool r_ok = t.vi != SR_NO_TAP;
+        const uint32_t off = sr_weight_off(g, t, 0);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const int j = j0 + (HALF_B ? wv * 8 + (lane >> 2) : n * 16 * NW + wv * 16 + (lane >> 2));
+          const char* p = (r_ok && j < g.ldw) ? sr_at((const char*)g.w, off + (uint32_t)j * (uint32_t)g.GC) : zero;
+          if (HALF_B) {
+            if (lane < 32) sr_to_lds16(p, bt + wv * 512);
+          } else {
+            sr_to_lds16(p, bt + (n * NW + wv) * 1024);
+          }
+        }
+      } else {
+        const SrSeg g = sr_load_seg(again(seg));
 #pragma unroll
         for (int q = 0; q < TJ / 4 / NW; ++q) {
           const int id = q * NW + wv;
@@ -225,10 +393,33 @@ struct SrRowOperands {
           const char* p = (t.vi != SR_NO_TAP && j < g.ldw) ? sr_at((const char*)g.w, sr_weight_off(g, t, j)) : zero;
           sr_to_lds4(p, bt + id * 256);
         }
-        return;
       }
+      return;
     }
     // forward: 16 lines of theta
+    if (all && wide_w && !(FOR == SR_ROWS_ORDERED && turn)) {
+      const unsigned line = (unsigned)ldw * 4u;
+      const char* w = sr_uni_ptr(theta(r0));
+      uint32_t o = woff[0];
+      asm volatile("" : "+v"(o));
+      if (quads_w) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const char* wn = w + (unsigned long long)(n * (256 * NW / TJ)) * line;
+          if (HALF_B) {
+            if (lane < 32) sr_to_lds16(wn + o, bt + wv * 512);
+          } else {
+            sr_to_lds16(wn + o, bt + (n * NW + wv) * 1024);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < TJ / 4 / NW; ++q)
+          sr_to_lds4(w + (unsigned long long)(q * (64 * NW) / TJ) * line + o, bt + (q * NW + wv) * 256);
+      }
+      return;
+    }
+    const SrSeg g = sr_load_seg(again(seg));
     if (FOR == SR_ROWS_ORDERED && turn) {
       if (quads_w) {
 #pragma unroll
@@ -256,17 +447,11 @@ struct SrRowOperands {
       for (int n = 0; n < NB; ++n) {
         const int id = HALF_B ? wv * 32 + lane : (n * NW + wv) * 64 + lane;
         const int r = r0 + id / (TJ / 4), j = j0 + 4 * (id % (TJ / 4));
-        const bool ok = r < g.R && j < g.ldw;
-        const char* p = ok ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
-        const char* p2 = PAIR ? p + (ok ? (uint32_t)g.ldw * (4 * SR_F32_KS) : 0u) : nullptr;
+        const char* p = (r < g.R && j < g.ldw) ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
         if (HALF_B) {
-          if (lane < 32) {
-            sr_to_lds16(p, bt + wv * 512);
-            if (PAIR) sr_to_lds16(p2, bt + STAGE + wv * 512);
-          }
+          if (lane < 32) sr_to_lds16(p, bt + wv * 512);
         } else {
           sr_to_lds16(p, bt + (n * NW + wv) * 1024);
-          if (PAIR) sr_to_lds16(p2, bt + STAGE + (n * NW + wv) * 1024);
         }
       }
     } else {
@@ -392,7 +577,7 @@ struct SrRecord { float* out; };
 // four waves' sums are added in order at the end.  Ordered, four steps go at a time: wave w fetches the w-th, then every
 // wave multiplies all four for a 16 x 16 quarter of the tile -- as long a chain of products per wave.
 template <int TI, int TJ, int WJN, int FOR, bool SMALL, int STAGES>
-__device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p, int i0, int j0, int step_begin, int step_end,
+__device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhase) phase, int i0, int j0, int step_begin, int step_end,
                                             int split_slot, int part_info, const SrSlots& sl, float* record, int rec_node,
                                             unsigned char* lds) {
   constexpr bool BACK = FOR == SR_ROWS_BACK, ORDERED = FOR == SR_ROWS_ORDERED;
@@ -423,27 +608,57 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
   }
   f32x4_t quarter{0.f, 0.f, 0.f, 0.f}, quarter_sum{0.f, 0.f, 0.f, 0.f};
 
+  if (!SMALL) __builtin_amdgcn_s_setprio(2);
+  // where the result goes and what the epilogue reads, fetched while the first operands are on their way
+  SR_CONST4(SrRowNode) nd = sr_k(A.nodes) + phase->node;
+  struct { float* out; const float *mask, *gate, *seed, *bias; int C, act; } end;
+  end.C = nd->C;
+  end.act = nd->act;
+  end.bias = nd->bias;
+  const int id_out = nd->out, id_x = nd->x, id_seed = nd->seed, id_mask = nd->mask;
+  constexpr int YB = SMALL ? 1 : MJ;
+  float bias_j[BACK ? 1 : YB];
+  auto column = [&](int y) { return QUARTERS ? j0 + 16 * (wave & 1) + (lane & 15) : j0 + jw + y * 32 + (lane & 31); };
+  auto prepare_end = [&]() {
+    auto tensor_at = [&](int id, int slot) -> float* {   // (tensor 0 stands in for one that is not there: no branch, so one round trip for all)
+      SR_CONST4(SrTensor) t = sr_k(A.tensors) + max(id, 0);
+      char* b = (char*)(unsigned long long)t->base;
+      return (float*)(id < 0 || b == nullptr ? nullptr : b + slot * t->stride);
+    };
+    end.out = tensor_at(id_out, sl.own);
+    end.mask = FOR == SR_ROWS_FRAME ? nullptr : tensor_at(id_mask, sl.frame);
+    end.gate = BACK && end.act == 1 ? tensor_at(id_x, sl.frame) : nullptr;
+    end.seed = BACK ? tensor_at(id_seed, sl.frame) : nullptr;
+    if constexpr (!BACK) {
+#pragma unroll
+      for (int y = 0; y < YB; ++y) bias_j[y] = end.bias && column(y) < end.C ? end.bias[column(y)] : 0.f;
+    }
+  };
+  const int seg_begin = phase->seg_begin, seg_image = phase->seg_image, seg_last = phase->seg_end;
   // two groups of segments: those that depend on the image only, whose sum is scaled, then the others
-  for (int group = (p.seg_image > p.seg_begin) ? 0 : 1; group < 2; ++group) {
-    int seg = (group == 0 ? p.seg_begin : p.seg_image) - 1;
-    const int seg_end = group == 0 ? p.seg_image : p.seg_end;
+  for (int group = (seg_image > seg_begin) ? 0 : 1; group < 2; ++group) {
+    int seg = (group == 0 ? seg_begin : seg_image) - 1;
+    const int seg_end = group == 0 ? seg_image : seg_last;
     int r = 0, r_stop = 0;   // next step's first index, end of the segment's share
-    // the next step of this workgroup (wave): false when there is none
-    auto next = [&]() -> bool {
-      r += SMALL ? 4 * SR_F32_KS : SR_F32_KS;
+    // r: the next step of this workgroup (wave), in the next segment where this one's share is done; false when there is none
+    auto settle = [&]() -> bool {
       while (r >= r_stop) {
         if (++seg >= seg_end) return false;
-        op.g = sr_load_seg(sr_k(A.segs) + seg);
-        if (!sr_seg_counts<BACK>(op.g, sl)) continue;
-        const int n = (op.g.R + SR_F32_KS - 1) / SR_F32_KS;
-        int lo = max(step_begin - op.g.step0, 0);
-        const int hi = min(step_end - op.g.step0, n);
-        if (ALONE) lo += (wave - (op.g.step0 + lo)) & 3;
+        const SrSeg g = sr_load_seg(sr_k(A.segs) + seg);
+        if (!sr_seg_counts<BACK>(g, sl)) continue;
+        const int n = (g.R + SR_F32_KS - 1) / SR_F32_KS;
+        int lo = max(step_begin - g.step0, 0);
+        const int hi = min(step_end - g.step0, n);
+        if (ALONE) lo += (wave - (g.step0 + lo)) & 3;
         r = lo * SR_F32_KS;
         r_stop = hi * SR_F32_KS;
-        if (r < r_stop) op.enter(p, A.tensors, sl);
+        if (r < r_stop) op.enter(g, sr_k(A.segs) + seg, phase, A.tensors, A.lines, sl, QUARTERS ? r + wave * SR_F32_KS : r);
       }
       return true;
+    };
+    auto next = [&]() -> bool {
+      r += SMALL ? 4 * SR_F32_KS : SR_F32_KS;
+      return settle();
     };
     int issued = 0, done = 0, wr = 0, rd = 0;
     unsigned rows = 0;   // per stage: the gathered operand (backwards: both) lies row by row
@@ -457,20 +672,23 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
     auto issue = [&]() {
       mark(wr);
       // (quarters: the steps of the four that are past the end of the share are zero)
-      op.issue(!QUARTERS ? r : (r + wave * SR_F32_KS < r_stop ? r + wave * SR_F32_KS : op.g.R), at0 + wr * PITCH);
-      wr = wr == STAGES - 1 ? 0 : wr + 1;
+      op.issue(!QUARTERS ? r : (r + wave * SR_F32_KS < r_stop ? r + wave * SR_F32_KS : op.R), at0 + wr * PITCH);
+      if (!PAIRS) wr = wr == STAGES - 1 ? 0 : wr + 1;
       ++issued;
     };
-    auto multiply = [&](int stage) {
+    auto multiply = [&](int stage, bool a_rows) {
+      if (!SMALL) __builtin_amdgcn_s_setprio(0);
       const unsigned char* st = base + stage * PITCH;
-      const bool a_rows = (rows >> stage) & 1;
       if constexpr (QUARTERS) {
         if (a_rows) sr_quarter_products<true>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, quarter);
         else sr_quarter_products<false>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, quarter);
       } else {
         sr_step_products<TI, TJ, MI, MJ>(st, iw, jw, lane, a_rows, BACK && a_rows, acc);
       }
+      if (!SMALL) __builtin_amdgcn_s_setprio(2);
     };
+    // do these stages hold steps that lie row by row, and none that ends a segment?
+    auto plain = [&](unsigned stages) { return (rows & stages) == stages && !(ORDERED && (ends & stages)); };
     auto fold = [&]() {   // a segment is done
       if constexpr (QUARTERS) {
         quarter_sum += quarter;
@@ -487,39 +705,93 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
             }
       }
     };
+    // The steps (pairs) of whole segments back to back, from r on, nothing but their loads and products: as long as there are
+    // such steps, AHEAD of them on the way at a time.  (Every step through the code that takes any step of any segment cost 130
+    // instructions around a pair's 16 products: 98 us of a DSR2 frame of batch 64; the same without them 67.)
+    constexpr int INC = (SMALL ? 4 : PAIRS ? 2 : 1) * SR_F32_KS, AHEAD = PAIRS ? 1 : STAGES - 1;
     bool more = next();
+    auto run_along = [&]() {
+      int n = 0;   // passes to go
+      const char* w = nullptr;
+      auto begin = [&](int least) -> bool {
+        if (!more || !op.template all_along<PAIRS>(r)) return false;
+        n = (r_stop - r + (ALONE ? INC - SR_F32_KS : 0)) / INC;
+        if (n < least) return false;
+        const int r0 = QUARTERS ? r + wave * SR_F32_KS : r;
+        op.go_on(r0);
+        if (!BACK) w = op.theta(r0);
+        return true;
+      };
+      if (!begin(1)) return;
+      bool folding = false;
+      unsigned w_step = (unsigned)op.ldw * (4u * INC);
+      for (;;) {
+        do {
+          if (SMALL && !BACK && !op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::NA + TJ / 4 / NW)>();
+          else sr_wait_loads<PAIRS ? 0 : (AHEAD - 1) * Ops::LOADS>();
+          if (!ALONE) sr_step_barrier();   // everybody's loads of the steps in hand; and the ones before have been read by all
+          op.template issue_along<PAIRS>(at0 + wr * PITCH, w);
+          op.template advance<INC>();
+          if (!BACK) w += w_step;
+          multiply(rd, true);
+          if (PAIRS) multiply(rd + 1, true);
+          r += INC;
+          if (PAIRS) {
+            rd ^= 2;
+            wr ^= 2;
+          } else {
+            rd = rd == STAGES - 1 ? 0 : rd + 1;
+            wr = wr == STAGES - 1 ? 0 : wr + 1;
+          }
+        } while (--n > 0);
+        ends = 0;
+        if (ORDERED && folding) {
+          fold();   // the segment before: its last steps were multiplied while this one's first were on the way
+          folding = false;
+          n = (r_stop - r) / INC;
+          if (n > 0) continue;
+        }
+        if (r < r_stop) break;   // what is less than a pair (four steps)
+        if (ORDERED) ends = 1u << (PAIRS ? rd + 1 : (wr == 0 ? STAGES - 1 : wr - 1));
+        more = settle();
+        if (!begin(ORDERED ? AHEAD : 1)) break;
+        w_step = (unsigned)op.ldw * (4u * INC);
+        if (ORDERED) {
+          folding = true;
+          n = AHEAD;
+        }
+      }
+      rows = (1u << (PAIRS ? 4 : STAGES)) - 1u;
+    };
+    bool first = group == ((seg_image > seg_begin) ? 0 : 1);
     if constexpr (PAIRS) {
       // two steps per barrier: a pair is fetched while the one before it is multiplied
       auto issue_pair = [&](int to) -> int {
-        if (!more) return 0;
-        wr = to;
-        if (op.pairs(r, r_stop)) {
-          mark(wr);
-          op.template issue<true>(r, at0 + wr * Ops::STAGE);
-          r += SR_F32_KS;
-          mark(wr + 1);
+        int n = 0;
+#pragma nounroll
+        for (bool last = false; n < 2 && more && !last; ++n) {
+          wr = to + n;
+          issue();
+          last = ORDERED && ((ends >> (to + n)) & 1);   // a pair lies in one segment
           more = next();
-          return 2;
         }
-        issue();
-        const bool last = ORDERED && ((ends >> to) & 1);   // a pair lies in one segment
-        more = next();
-        if (!more || last) return 1;
-        wr = to + 1;
-        issue();
-        more = next();
-        return 2;
+        return n;
       };
       int cur = issue_pair(0);
+      if (first) prepare_end();
       while (cur > 0) {
         bool end;   // of the loop: ordered, of a segment
         do {
+          if (cur == 2 && plain(3u << rd)) {
+            wr = rd ^ 2;
+            run_along();
+          }
           sr_wait_loads<0>();
           sr_step_barrier();   // everybody's loads of this pair; and the pair before has been read by all
           end = ORDERED && ((ends >> (rd + cur - 1)) & 1);
           const int following = issue_pair(rd ^ 2);
-          multiply(rd);
-          if (cur == 2) multiply(rd + 1);
+          multiply(rd, (rows >> rd) & 1);
+          if (cur == 2) multiply(rd + 1, (rows >> (rd + 1)) & 1);
           rd ^= 2;
           cur = following;
           if (!ORDERED) end = cur == 0;
@@ -527,39 +799,44 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
         fold();
       }
       issued = 0;
-    }
-    for (int k = 0; k < STAGES - 1 && more; ++k) {
-      issue();
-      more = next();
-    }
-    while (done < issued) {
-      bool end;
-      do {
-        if (STAGES > 3 && issued - done >= 3) sr_wait_loads<2 * Ops::LOADS>();
-        else if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
-        else sr_wait_loads<0>();
-        if (!ALONE) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
-        end = ORDERED && ((ends >> rd) & 1);
-        if (more) {
-          issue();
-          more = next();
-        }
-        multiply(rd);
-        rd = rd == STAGES - 1 ? 0 : rd + 1;
-        ++done;
-        if (!ORDERED) end = done == issued;
-      } while (!end);
-      fold();
+    } else {
+#pragma nounroll
+      for (int k = 0; k < STAGES - 1 && more; ++k) {
+        issue();
+        more = next();
+      }
+      if (first) prepare_end();
+      while (done < issued) {
+        bool end;
+        do {
+          if (issued - done == AHEAD && plain(((1u << STAGES) - 1u) & ~(1u << wr))) run_along();
+          if (STAGES > 3 && issued - done >= 3) sr_wait_loads<2 * Ops::LOADS>();
+          else if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
+          else sr_wait_loads<0>();
+          if (!ALONE) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
+          end = ORDERED && ((ends >> rd) & 1);
+          if (more) {
+            issue();
+            more = next();
+          }
+          multiply(rd, (rows >> rd) & 1);
+          rd = rd == STAGES - 1 ? 0 : rd + 1;
+          ++done;
+          if (!ORDERED) end = done == issued;
+        } while (!end);
+        fold();
+      }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (!ALONE) sr_step_barrier();   // the stages are free again
     if (group == 0) {
+      const float image_scale = sr_again(phase)->image_scale;
 #pragma unroll
       for (int x = 0; x < MI; ++x)
 #pragma unroll
         for (int y = 0; y < MJ; ++y)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[x][y][v] *= p.image_scale;
+          for (int v = 0; v < 16; ++v) acc[x][y][v] *= image_scale;
     }
   }
 
@@ -596,69 +873,69 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
 
   // ---- epilogue.  Register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its block (a quarter:
   // row 4 (l / 16) + v, column l % 16).
-  SR_CONST4(SrRowNode) nd = sr_k(A.nodes) + p.node;
-  const int C = nd->C, act = nd->act;
-  auto tensor_at = [&](int id, int slot) -> float* {
-    if (id < 0) return nullptr;
-    SR_CONST4(SrTensor) t = sr_k(A.tensors) + id;
-    char* b = (char*)(unsigned long long)t->base;
-    return b ? (float*)(b + slot * t->stride) : nullptr;
-  };
-  float* out = tensor_at(nd->out, sl.own);
-  const float* mask = tensor_at(nd->mask, sl.frame);
-  const float* gate = (BACK && act == 1) ? tensor_at(nd->x, sl.frame) : nullptr;
-  const float* seed = BACK ? tensor_at(nd->seed, sl.frame) : nullptr;
-  const float* bias = nd->bias;
-  if (rec_node < 0 || nd->gnode != rec_node) record = nullptr;
-  constexpr int XB = SMALL ? 1 : MI, YB = SMALL ? 1 : MJ, VB = SMALL ? 4 : 16;
+  SR_CONST4(SrPhase) ph = sr_again(phase);
+  const int I = ph->I, S = ph->S, C = end.C;
+  if (rec_node < 0 || sr_again(nd)->gnode != rec_node) record = nullptr;
+  constexpr int XB = SMALL ? 1 : MI, VB = SMALL ? 4 : 16;
+  const bool whole = i0 + TI <= I;   // all rows exist
 #pragma unroll
   for (int x = 0; x < XB; ++x) {
+    // the lane's first row; register q is that many rows further on
+    const int row0 = i0 + (QUARTERS ? 16 * (wave >> 1) + 4 * (lane >> 4) : (SMALL ? 8 * wave : iw + x * 32) + 4 * (lane >> 5));
+    auto further = [](int q) { return SMALL ? q : 8 * (q >> 2) + (q & 3); };
     size_t at[VB];
-    bool ok[VB];
+    if (S == 1) {
+      const size_t at0 = (size_t)row0 * C;
 #pragma unroll
-    for (int q = 0; q < VB; ++q) {
-      const int v = SMALL ? 4 * wave + q : q;
-      const int i = QUARTERS ? i0 + 16 * (wave >> 1) + 4 * (lane >> 4) + q : i0 + iw + x * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      ok[q] = i < p.I;
-      size_t px = ok[q] ? (size_t)i : 0;
-      if (p.S != 1 && ok[q]) {
+      for (int q = 0; q < VB; ++q) at[q] = whole || row0 + further(q) < I ? at0 + (size_t)further(q) * C : 0;
+    } else {
+      const SrPhase p = sr_load_phase(ph);
+      const int H = sr_again(nd)->H, W = sr_again(nd)->W;
+#pragma unroll
+      for (int q = 0; q < VB; ++q) {
+        const int i = row0 + further(q) < I ? row0 + further(q) : 0;
         const int b = sr_divide(i, p.d_hpwp), rem = i - b * (p.Hp * p.Wp);
         const int hh = sr_divide(rem, p.d_wp), ww = rem - hh * p.Wp;
-        px = ((size_t)b * nd->H + hh * p.S + p.ph) * nd->W + ww * p.S + p.pw;
+        at[q] = (((size_t)b * H + hh * p.S + p.ph) * W + ww * p.S + p.pw) * C;
       }
-      at[q] = px * C;
     }
 #pragma unroll
     for (int y = 0; y < YB; ++y) {
-      const int j = QUARTERS ? j0 + 16 * (wave & 1) + (lane & 15) : j0 + jw + y * 32 + (lane & 31);
+      const int j = column(y);
       if (j >= C) continue;
-      const float bj = (!BACK && bias) ? bias[j] : 0.f;
       float val[VB];
 #pragma unroll
-      for (int q = 0; q < VB; ++q) val[q] = o[(x * YB + y) * VB + q] + bj;
-      if (seed) {
+      for (int q = 0; q < VB; ++q) val[q] = o[(x * YB + y) * VB + q] + (BACK ? 0.f : bias_j[BACK ? 0 : y]);
+      if (BACK && end.seed) {
 #pragma unroll
-        for (int q = 0; q < VB; ++q) val[q] += seed[at[q] + j];
+        for (int q = 0; q < VB; ++q) val[q] += end.seed[at[q] + j];
       }
       if (BACK) {
-        if (gate) {
+        if (end.gate) {
 #pragma unroll
-          for (int q = 0; q < VB; ++q) val[q] = gate[at[q] + j] > 0.f ? val[q] : 0.f;
+          for (int q = 0; q < VB; ++q) val[q] = end.gate[at[q] + j] > 0.f ? val[q] : 0.f;
         }
-      } else if (act == 1) {
+      } else if (end.act == 1) {
 #pragma unroll
         for (int q = 0; q < VB; ++q) val[q] = fmaxf(val[q], 0.f);
       }
-      if (mask) {
+      if (FOR != SR_ROWS_FRAME && end.mask) {
 #pragma unroll
-        for (int q = 0; q < VB; ++q) val[q] *= mask[at[q] + j];
+        for (int q = 0; q < VB; ++q) val[q] *= end.mask[at[q] + j];
       }
+      if (whole) {
 #pragma unroll
-      for (int q = 0; q < VB; ++q)
-        if (ok[q]) {
-          out[at[q] + j] = val[q];
-          if (record) record[at[q] + j] = val[q];
-        }
+        for (int q = 0; q < VB; ++q) end.out[at[q] + j] = val[q];
+      } else {
+#pragma unroll
+        for (int q = 0; q < VB; ++q)
+          if (row0 + further(q) < I) end.out[at[q] + j] = val[q];
+      }
+      if (record) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q)
+          if (row0 + further(q) < I) record[at[q] + j] = val[q];
+      }
     }
   }
 }
@@ -666,10 +943,10 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, const SrPhase& p
 template <int FOR, int VARIANT>
 __device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowTile) t, int slot0, const SrSlots& sl, float* record,
                                             int rec_node, unsigned char* lds) {
-  const int phase = t->phase;
-  if (phase < 0) return;
-  const SrPhase p = sr_load_phase(sr_k(A.phases) + phase);
-  const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = slot0 + t->split_slot, part = t->part;
+  const sr_i32x16 v = *(SR_CONST4(sr_i32x16))(unsigned long long)t;   // one load
+  if (v[0] < 0) return;
+  SR_CONST4(SrPhase) p = (SR_CONST4(SrPhase))((unsigned long long)t + offsetof(SrRowTile, p));
+  const int shape = v[1], i0 = v[2], j0 = v[3], sb = v[4], se = v[5], slot = slot0 + v[6], part = v[7];
   if constexpr (VARIANT != SR_F32_DEEP) {
     if constexpr (VARIANT == SR_F32_WIDE)
       if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, FOR, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
@@ -726,15 +1003,21 @@ __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows
   extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
   // the run (tile list, frame) this workgroup belongs to: runs are in order of their first workgroup
   const int lane = threadIdx.x & 63, block = (int)blockIdx.x + A.first;
-  int k = 0;
+  // (a lane reads a whole run, so the one found needs no second round trip)
+  SrRun mine{0x7fffffff, 0, 0, 0}, run{0, 0, 0, 0};
   for (int base = 0; base < A.n_runs; base += 64) {
-    const int b0 = base + lane < A.n_runs ? A.runs[base + lane].block0 : 0x7fffffff;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(b0 <= block);
-    k += __popcll(m);
+    mine = SrRun{0x7fffffff, 0, 0, 0};
+    if (base + lane < A.n_runs) mine = A.runs[base + lane];
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(mine.block0 <= block);
+    if (m == 0) break;   // the last one of the 64 before
+    const int k = __popcll(m) - 1;
+    run.block0 = __builtin_amdgcn_readlane(mine.block0, k);
+    run.tile0 = __builtin_amdgcn_readlane(mine.tile0, k);
+    run.frame = __builtin_amdgcn_readlane(mine.frame, k);
+    run.slot0 = __builtin_amdgcn_readlane(mine.slot0, k);
     if (m != ~0ull) break;
   }
-  SR_CONST4(SrRun) run = sr_k(A.runs) + SR_UNI(k - 1);
-  const int frame = A.frame0 + run->frame;
+  const int frame = A.frame0 + run.frame;
   SrSlots sl;
   if (BACK) {
     sl.lag0 = frame % A.ring;
@@ -748,7 +1031,7 @@ __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 2) void sr_rows
     sl.left = frame;
   }
   sl.frame = frame;
-  sr_row_item<BACK ? SR_ROWS_BACK : SR_ROWS_ORDERED, VARIANT>(A, sr_k(A.tiles) + run->tile0 + (block - run->block0), run->slot0, sl, nullptr, -1, sr_rows_lds);
+  sr_row_item<BACK ? SR_ROWS_BACK : SR_ROWS_ORDERED, VARIANT>(A, sr_k(A.tiles) + run.tile0 + (block - run.block0), run.slot0, sl, nullptr, -1, sr_rows_lds);
 }
 
 namespace {

@@ -38,6 +38,29 @@ bool weights_fit(const EdgeRt& e, const Geometry& q) {
   return (int64_t)e.w_count < ((int64_t)1 << 32) && (int64_t)e.kh * e.kw * std::max(q.Cin, q.Cout) < kRows;
 }
 
+// The lines of segment s, in the order in which a step's indices lie in LDS
+void add_lines(SrRowPlan* p, SrSeg* s, bool in_turn) {
+  s->lines = -1;
+  if ((s->flags & SR_SEG_QUADS) || s->R > SR_LINES_MAX) return;
+  s->lines = (int)p->lines.size();
+  for (int r0 = 0; r0 < s->R; r0 += SR_F32_KS)
+    for (int l = 0; l < SR_F32_KS; ++l) {
+      const int r = r0 + (in_turn ? sr_in_turn(l) : l);
+      SrLine x{0, SR_NO_ROW, SR_NO_ROW, 0};
+      if (r < s->R) {
+        const SrTapAt t = sr_tap_at(*s, r);
+        const long long off = sr_gather_off(*s, t);
+        if (off != (int32_t)off) {   // taps of an image of 2^31 floats a row apart and more
+          p->lines.resize(s->lines);
+          s->lines = -1;
+          return;
+        }
+        x = SrLine{(int32_t)off, s->dir * t.vi, s->dir * t.vj, 0};
+      }
+      p->lines.push_back(x);
+    }
+}
+
 }  // namespace
 
 bool sr_rows_take_forward(const sr_graph* g, int v) {
@@ -112,6 +135,7 @@ int sr_rows_forward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds* id
     s.d_up = sr_div_for(q.up);
     s.d_wup = sr_div_for(1);
     ph.steps += ceil_div(s.R, SR_F32_KS);
+    add_lines(p, &s, ids != nullptr);
     p->segs.push_back(s);
   }
   ph.seg_end = (int)p->segs.size();
@@ -186,6 +210,7 @@ int sr_rows_backward(SrRowPlan* p, const sr_graph* g, int v, const SrTrainIds& i
         s.d_ntj = sr_div_for(ntj);
         s.d_up = sr_div_for(1);
         ph.steps += ceil_div(s.R, SR_F32_KS);
+        add_lines(p, &s, false);
         p->segs.push_back(s);
       };
       for (int ei : gap) {
@@ -316,6 +341,7 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
           t.step_end = (int)((int64_t)ph.steps * (part + 1) / parts);
           t.split_slot = slot;
           t.part = part | (parts << 16);
+          t.p = ph;
           per_xcd[k * SR_XCDS / total].push_back(Keyed{latency(shape, (double)ph.steps / parts), t});
         }
       }

@@ -64,6 +64,7 @@ struct sr_graph {
   // options
   bool use_hipgraph = true, force_direct = false;
   int frames_per_graph = 8;
+  bool frames_per_graph_set = false;
 
   // plan
   bool finalized = false, was_reset = false;
@@ -105,8 +106,11 @@ struct sr_graph {
   int32_t* done_counters = nullptr;   // one per graph node
   SrTile4* flow_items = nullptr;      // a frame's work items in dependency order: tiles, and aux items as node = -2 - index
   int n_flow_items = 0;
-  int32_t* flow_order = nullptr;      // (frame, item) pairs of a launch of flow_order_frames frames, by depth (see SrFlow)
-  int n_flow_order = 0, flow_order_frames = 0;
+  // the runs of flow_frames_max frames by depth, and the (frame, item) pairs that launches of flow_order_frames frames take (see SrFlow)
+  struct SrFlowRun* flow_runs = nullptr;
+  int n_flow_runs = 0, flow_frames_max = 0;
+  int32_t* flow_order = nullptr;
+  int flow_order_frames = 0;
   bool flow_depth_order = true;       // SR_OPT_FLOW_ORDER
   std::vector<int> flow_dep_begin, flow_dep_count;
   float* split_scratch = nullptr;

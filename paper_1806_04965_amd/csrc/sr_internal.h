@@ -69,6 +69,9 @@ struct SrFlow {
   const int32_t* order;
 };
 
+// A run of work items of one frame of a dependency-driven launch: items begin .. begin + count - 1 of frame t
+struct SrFlowRun { int32_t begin, count, t, pad_; };
+
 // ---------------------------------------------------------------------------
 // direct path: one thread per output element
 // ---------------------------------------------------------------------------
@@ -300,6 +303,8 @@ hipError_t sr_launch_set_ctx(hipStream_t s, SrCtx* ctx, const SrCtx& values);
 hipError_t sr_launch_reset(hipStream_t s, SrCtx* ctx, const SrCtx& values, const SrResetItem* items, int n_items, int n_blocks,
                            const void* const* frame0, int bf16);
 hipError_t sr_launch_tick(hipStream_t s, SrCtx* ctx, int frames);
+// order[] of a launch of `frames` frames (see SrFlow): the items of the runs with t < frames, run by run
+hipError_t sr_launch_flow_order(hipStream_t s, const SrFlowRun* runs, int n_runs, int frames, int32_t* order);
 hipError_t sr_launch_fill_zero(hipStream_t s, void* p, size_t bytes);
 // dense [px][C] -> pitched [px][Cp], unpack: the other way.  ctx: the pitched side is copy0 or copy1, whichever holds the
 // last frame computed by the device's count; null: copy0.

@@ -86,6 +86,20 @@ __global__ __launch_bounds__(256) void sr_reset_kernel(SrCtx* ctx, SrCtx values,
   }
 }
 
+// A workgroup per run: its items go behind those of the runs before it that belong to one of the launch's frames.
+__global__ __launch_bounds__(256) void sr_flow_order_kernel(const SrFlowRun* __restrict__ runs, int frames, int32_t* __restrict__ order) {
+  __shared__ int sums[4];
+  const SrFlowRun mine = runs[blockIdx.x];
+  if (mine.t >= frames) return;
+  int n = 0;
+  for (int k = threadIdx.x; k < (int)blockIdx.x; k += 256) n += runs[k].t < frames ? runs[k].count : 0;
+  for (int m = 32; m > 0; m >>= 1) n += __shfl_xor(n, m, 64);
+  if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = n;
+  __syncthreads();
+  const int at = sums[0] + sums[1] + sums[2] + sums[3];
+  for (int k = threadIdx.x; k < mine.count; k += 256) order[at + k] = (mine.begin + k) | (mine.t << 24);
+}
+
 __global__ void sr_fill_zero_kernel(uint4* p, size_t n16, unsigned char* tail, size_t ntail) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -1128,6 +1142,12 @@ hipError_t sr_launch_aux(hipStream_t s, const SrFrame& f, const SrAux* aux, int 
   const int vf = sr_vec_floats(smem_bytes);
   if (bf16) hipLaunchKernelGGL(sr_aux_kernel<uint16_t>, dim3(n_aux), dim3(256), smem_bytes, s, f, aux, heads, head_edges, stage_nodes, vf);
   else hipLaunchKernelGGL(sr_aux_kernel<float>, dim3(n_aux), dim3(256), smem_bytes, s, f, aux, heads, head_edges, stage_nodes, vf);
+  return hipGetLastError();
+}
+
+hipError_t sr_launch_flow_order(hipStream_t s, const SrFlowRun* runs, int n_runs, int frames, int32_t* order) {
+  if (n_runs == 0) return hipSuccess;
+  hipLaunchKernelGGL(sr_flow_order_kernel, dim3(n_runs), dim3(256), 0, s, runs, frames, order);
   return hipGetLastError();
 }
 

@@ -484,6 +484,30 @@ def test_depth_ordered_launches_of_other_lengths(frames_per_launch):
     assert np.abs(a[-1]).max() > 0
 
 
+@pytest.mark.parametrize("pattern", [W.sequential_pattern, W.hybrid_pattern])
+def test_depth_ordered_launches_follow_the_rollouts_length(pattern):
+    # one launch for up to 64 frames, launches of equal length beyond (65: 33 + 32, 130: 44 + 43 + 43); rollouts of other
+    # lengths in between, whose launches take other (frame, item) pairs.  All equal one launch per update step.
+    import torch
+    import paper_1806_04965_amd as sr
+    from gpu_util import to_device
+    g0 = W.cifar_sr(batch=2, frames=130)
+    g = g0.with_pattern(pattern(g0))
+    w, b, x = W.make_case(g, seed=64, bias_scale=0.1, frames=130)
+    want = gpu_rollout(g, w, b, x, 130, options={5: 0})
+    dev = sr.SrGraph(g)
+    dev.set_parameters(w, b)
+    xd = [to_device(x[v], g.dtype) for v in g.input_nodes()]
+    for T in (130, 2, 64, 65, 1, 64, 3, 130):
+        out = torch.empty((T, 2, 1, 1, 10), dtype=torch.bfloat16, device="cuda")
+        dev.rollout([t[:T + 1] for t in xd], T, g.out_node, out)
+        dev.synchronize()
+        assert np.array_equal(out.float().cpu().numpy(), want[:T]), T
+    h = dev.health()
+    dev.close()
+    assert h["dependency_driven"] and h["dependency_timeouts"] == 0
+
+
 @pytest.mark.parametrize("batch", [1, 4, 37])
 def test_pooled_slabs_of_several_frames_in_one_launch(batch):
     # a GAP read-out over 12 x 12 pixels is summed in three slabs whose arrival counter is reset by the last one:

@@ -196,9 +196,37 @@ struct SrGradEdge {
   int32_t dst;                    // destination pointer
   long long part_at;              // first float of this edge's partial sums
   SrDiv d_cin, d_kw, d_wo, d_howo, d_up, d_steps;   // d_steps: steps per frame, ceil(M / SR_F32_KS)
-  int32_t steps_per_frame, pad_;
+  int32_t steps_per_frame;
+  int32_t along;                  // a step's pixels can be had from those of the step before (no up-sampling, a frame within 2^31 floats)
 };
-// kind 0: gradient tile; 1: column sums of a gradient tensor (bias gradient), 64 channels x a range of rows
+// From a pixel of a gradient tile's reduction to the one 16 further on, in the coordinates of its window: the digits of 16 in
+// (image, row, column), in steps of the stride, and the floats that they and the two carries stand for (modulo 2^32)
+struct SrPixStep { int32_t w, h, n_w, n_h; uint32_t off, off_w, off_h; };
+SR_HD SrPixStep sr_pix_step(const SrGradEdge& e, int pixels) {
+  const int rows = sr_divide(pixels, e.d_wo), images = sr_divide(pixels, e.d_howo);
+  const int dw = pixels - rows * e.Wo, dh = rows - images * e.Ho;
+  const uint32_t line = (uint32_t)e.W * (uint32_t)e.Cin, image = (uint32_t)e.H * line;
+  SrPixStep s;
+  s.w = dw * e.stride;
+  s.h = dh * e.stride;
+  s.n_w = e.Wo * e.stride;
+  s.n_h = e.Ho * e.stride;
+  s.off = (uint32_t)s.w * (uint32_t)e.Cin + (uint32_t)s.h * line + (uint32_t)images * image;
+  s.off_w = (uint32_t)e.stride * line - (uint32_t)s.n_w * (uint32_t)e.Cin;
+  s.off_h = image - (uint32_t)s.n_h * line;
+  return s;
+}
+// ... the step: (w, h) is a tap of the pixel's window, lim_w and lim_h what they reach one column or row past the target's last
+SR_HD void sr_pix_go(const SrPixStep& s, int stride, int lim_w, int lim_h, int* w, int* h, uint32_t* off) {
+  const int w1 = *w + s.w;
+  const bool cw = w1 >= lim_w;
+  *w = cw ? w1 - s.n_w : w1;
+  const int h1 = *h + s.h + (cw ? stride : 0);
+  const bool ch = h1 >= lim_h;
+  *h = ch ? h1 - s.n_h : h1;
+  *off += s.off + (cw ? s.off_w : 0u) + (ch ? s.off_h : 0u);
+}
+// kind 0: gradient tile; 1: column sums of a gradient tensor (bias gradient), 64 channels x a range of rows; 2: empty slot
 struct SrGradTile {
   int32_t edge, shape, i0, j0;
   int32_t step_begin, step_end;   // steps counted over the edge's frames (kind 1: rows counted over the frames)

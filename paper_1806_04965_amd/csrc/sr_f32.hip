@@ -1049,6 +1049,119 @@ struct SrGradOperands {
   int wv, lane, j0;
   int ti, tj;          // this lane's row (rows i .. i + 3) of A: tap and ...
   uint32_t aoff;       // ... offset from the window's first element
+  // The pixels of the next step, if its frame's steps go on from one another (SrGradEdge::along): where this lane's tap lies in
+  // the source image, and floats from the frame's start.  (Decoded from the step's number, a load cost ten multiplications, at a
+  // quarter of the rate each: windows of DSR2 1480 us, with the pixels so 1443; GTSRB-shaped 5620, 5540.)
+  static constexpr int LINES = TI == 128 ? 8 : 4;   // 4-byte loads: pixels per wave and step, one after the other, 64 rows of each
+  SrPixStep go;                      // 16-byte loads: 16 pixels on
+  int at_h[NA], at_w[NA], lim_h, lim_w;
+  int tap_h;                         // tap row, and how many rows of the image it may lie in: none for a row of theta past the last
+  unsigned in_h;
+  uint32_t at_off[NA], ob;
+  int px_h, px_w;                    // 4-byte loads: the wave's next pixel (scalar)
+  uint32_t px_off;
+  int along, fi, m0;
+  const char *xf, *yf;
+
+  // pixel m's window, at this lane's tap
+  __device__ __forceinline__ void look(int n, int m) {
+    const int b = sr_divide(m, e.d_howo), rem = m - b * (e.Ho * e.Wo), ho = sr_divide(rem, e.d_wo), wo = rem - ho * e.Wo;
+    const int h = ho * e.stride - e.pad, w = wo * e.stride - e.pad;
+    at_off[n] = (((uint32_t)b * (uint32_t)e.H + (uint32_t)h) * (uint32_t)e.W + (uint32_t)w) * (uint32_t)e.Cin + aoff;
+    at_h[n] = h + tap_h;
+    at_w[n] = w + tj;
+  }
+  __device__ __forceinline__ const char* looked(int n) const {
+    return (unsigned)at_h[n] < in_h && (unsigned)at_w[n] < (unsigned)e.W ? sr_at(xf, at_off[n]) : (const char*)sr_zero_line;
+  }
+  // ... that of a later one
+  __device__ __forceinline__ void step_on(int n) {
+    sr_pix_go(go, e.stride, lim_w, lim_h, &at_w[n], &at_h[n], &at_off[n]);
+  }
+
+  // the tile's first step
+  __device__ __forceinline__ void begin(int step) {
+    fi = sr_divide(step, e.d_steps);
+    m0 = (step - fi * e.steps_per_frame) * SR_F32_KS;
+    if (!along) return;
+    go = sr_pix_step(e, SR_F32_KS);
+    tap_h = ti == SR_NO_TAP ? 0 : ti;
+    in_h = ti == SR_NO_TAP ? 0u : (unsigned)e.H;
+    lim_h = e.Ho * e.stride - e.pad + tap_h;
+    lim_w = e.Wo * e.stride - e.pad + tj;
+    const int id = HALF_B ? wv * 32 + lane : wv * 64 + lane;
+    if (quads_b) ob = ((uint32_t)(id / (TJ / 4)) * (uint32_t)e.Cout + (uint32_t)min(4 * (id % (TJ / 4)), e.Cout - 4 - j0)) * 4u;
+    else ob = ((uint32_t)((wv * 64 + lane) / TJ) * (uint32_t)e.Cout + (uint32_t)min((wv * 64 + lane) % TJ, e.Cout - 1 - j0)) * 4u;
+    frame_begin();
+  }
+  __device__ __forceinline__ void frame_begin() {
+    const int frame = e.frame0 + fi;
+    xf = sr_uni_ptr(xb0 + (frame - e.lag) * xs);
+    yf = sr_uni_ptr(yb0 + (frame % ring) * ys + ((long long)m0 * e.Cout + j0) * 4);
+    if (quads_a) {
+#pragma unroll
+      for (int n = 0; n < NA; ++n) look(n, m0 + (n * 4 + wv) * (256 / TI) + lane / (TI / 4));
+    } else {
+      const SrPixAt p = sr_pix_at(e, SR_UNI(m0 + LINES * (TI == 128 ? wv >> 1 : wv)));
+      px_h = p.h;
+      px_w = p.w;
+      px_off = sr_pix_off(e, p, 0, 0);
+    }
+  }
+  // the wave's pixel: some further on
+  __device__ __forceinline__ void px_on(const SrPixStep& s) {
+    sr_pix_go(s, e.stride, s.n_w - e.pad, s.n_h - e.pad, &px_w, &px_h, &px_off);
+  }
+  // loads of the next step
+  __device__ __forceinline__ void issue_next(unsigned at) {
+    const char* zero = (const char*)sr_zero_line;
+    if (!along || m0 + SR_F32_KS > e.M) {
+      issue(fi * e.steps_per_frame + m0 / SR_F32_KS, at);
+    } else {
+      if (quads_a) {
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          sr_to_lds16(looked(n), at + (n * 4 + wv) * 1024);
+          step_on(n);
+        }
+      } else {
+        const SrPixStep one = sr_pix_step(e, 1);
+        const unsigned line = at + LINES * (TI == 128 ? wv >> 1 : wv) * (TI * 4) + (TI == 128 ? (wv & 1) * 256 : 0);
+#pragma nounroll
+        for (int q = 0; q < LINES; ++q) {
+          const bool ok = (unsigned)(px_h + tap_h) < in_h && (unsigned)(px_w + tj) < (unsigned)e.W;
+          sr_to_lds4(ok ? sr_at(xf, px_off + aoff) : zero, line + q * (TI * 4));
+          px_on(one);
+        }
+        px_on(sr_pix_step(e, SR_F32_KS - LINES));
+      }
+      const unsigned bt = at + TI * 64, line = (unsigned)e.Cout * 4u;
+      const char* y = sr_uni_ptr(yf);
+      uint32_t o = ob;
+      asm volatile("" : "+v"(o));   // keeps the offset 32-bit: scalar base + lane offset addressing
+      if (quads_b) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const char* yn = y + (unsigned long long)(n * (1024 / TJ)) * line;
+          if (HALF_B) {
+            if (lane < 32) sr_to_lds16(yn + o, bt + wv * 512);
+          } else {
+            sr_to_lds16(yn + o, bt + (n * 4 + wv) * 1024);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < TJ / 16; ++q) sr_to_lds4(y + (unsigned long long)(q * 256 / TJ) * line + o, bt + (q * 4 + wv) * 256);
+      }
+      yf = y + (unsigned long long)SR_F32_KS * line;
+    }
+    m0 += SR_F32_KS;
+    if (m0 >= e.M) {
+      m0 = 0;
+      ++fi;
+      if (along) frame_begin();
+    }
+  }
 
   __device__ __forceinline__ void enter(SR_CONST4(SrGradEdge) ek, const SrTensor* tensors, int ring_, int i0, int j0_) {
     e.x = ek->x; e.dy = ek->dy; e.lag = ek->lag; e.frame0 = ek->frame0;
@@ -1074,6 +1187,7 @@ struct SrGradOperands {
     tj = tap - ti * e.kw;
     aoff = (uint32_t)(ti * e.W + tj) * (uint32_t)e.Cin + (uint32_t)ci;
     if (i >= e.I) ti = SR_NO_TAP;
+    along = ek->along;
   }
 
   __device__ __forceinline__ void issue(int step, unsigned at) {
@@ -1127,7 +1241,8 @@ struct SrGradOperands {
 template <int TI, int TJ, int WJN>
 __device__ __forceinline__ void sr_grad_tile(const SrGradArgs& A, SR_CONST4(SrGradEdge) ek, int i0, int j0, int step_begin, int step_end,
                                              int slice, unsigned char* lds) {
-  constexpr int WIN = 4 / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN), STAGES = 3;
+  constexpr int WIN = 4 / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
+  constexpr int STAGES = TI * TJ == 4096 ? 4 : 3;   // 64 x 64 and 128 x 32 tiles: a step is 512 cycles of products, so three on the way
   typedef SrGradOperands<TI, TJ> Ops;
   const int tid = threadIdx.x, lane = tid & 63, wv = SR_UNI(tid >> 6);
   const unsigned at0 = sr_lds_at(lds);
@@ -1145,31 +1260,37 @@ __device__ __forceinline__ void sr_grad_tile(const SrGradArgs& A, SR_CONST4(SrGr
       for (int v = 0; v < 16; ++v) acc[x][y][v] = sum[x][y][v] = 0.f;
   const int iw = (wv / WJN) * 32 * MI, jw = (wv % WJN) * 32 * MJ;
   int wr = 0, rd = 0, next = step_begin;
-  for (int k = 0; k < STAGES - 1 && next < step_end; ++k) {
-    op.issue(next++, at0 + wr * Ops::STAGE);
+  op.begin(step_begin);
+#pragma nounroll
+  for (int k = 0; k < STAGES - 1 && next < step_end; ++k, ++next) {
+    op.issue_next(at0 + wr * Ops::STAGE);
     wr = wr == STAGES - 1 ? 0 : wr + 1;
   }
-  for (int s = step_begin; s < step_end; ++s) {
-    if (s + 1 < step_end) sr_wait_loads<Ops::LOADS>();
-    else sr_wait_loads<0>();
-    sr_step_barrier();
-    if (next < step_end) {
-      op.issue(next++, at0 + wr * Ops::STAGE);
-      wr = wr == STAGES - 1 ? 0 : wr + 1;
+  for (int s = step_begin; s < step_end;) {
+    const int block_end = min(s + 128, step_end);
+    for (; s < block_end; ++s) {
+      if (STAGES > 3 && s + 2 < step_end) sr_wait_loads<2 * Ops::LOADS>();
+      else if (s + 1 < step_end) sr_wait_loads<Ops::LOADS>();
+      else sr_wait_loads<0>();
+      sr_step_barrier();
+      if (next < step_end) {
+        ++next;
+        op.issue_next(at0 + wr * Ops::STAGE);
+        wr = wr == STAGES - 1 ? 0 : wr + 1;
+      }
+      sr_step_products<TI, TJ, MI, MJ>(lds + rd * Ops::STAGE, iw, jw, lane, false, false, acc);
+      rd = rd == STAGES - 1 ? 0 : rd + 1;
     }
-    sr_step_products<TI, TJ, MI, MJ>(lds + rd * Ops::STAGE, iw, jw, lane, false, false, acc);
-    rd = rd == STAGES - 1 ? 0 : rd + 1;
-    if (((s - step_begin) & 127) == 127) {
+    // (a loop of its own: a fold that a step may or may not do costs it a move per accumulator)
 #pragma unroll
-      for (int x = 0; x < MI; ++x)
+    for (int x = 0; x < MI; ++x)
 #pragma unroll
-        for (int y = 0; y < MJ; ++y)
+      for (int y = 0; y < MJ; ++y)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            sum[x][y][v] += acc[x][y][v];
-            acc[x][y][v] = 0.f;
-          }
-    }
+        for (int v = 0; v < 16; ++v) {
+          sum[x][y][v] += acc[x][y][v];
+          acc[x][y][v] = 0.f;
+        }
   }
   const int slices = ek->slices;
   const int I = op.e.I, J = op.e.Cout;
@@ -1184,7 +1305,7 @@ __device__ __forceinline__ void sr_grad_tile(const SrGradArgs& A, SR_CONST4(SrGr
         const int i = i0 + iw + x * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), j = j0 + jw + y * 32 + (lane & 31);
         if (i < I && j < J) {
           float* d = out + (size_t)i * J + j;
-          const float r = sum[x][y][v] + acc[x][y][v];
+          const float r = sum[x][y][v];
           *d = add ? *d + r : r;
         }
       }
@@ -1229,6 +1350,7 @@ __global__ __launch_bounds__(256, VARIANT == SR_F32_NARROW ? 4 : 3) void sr_grad
   extern __shared__ __align__(1024) unsigned char sr_rows_lds[];
   SR_CONST4(SrGradTile) t = sr_k(A.tiles) + blockIdx.x;
   const int kind = t->kind, shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slice = t->slice;
+  if (kind == 2) return;
   if (kind == 1) {
     sr_grad_bias(A, sr_k(A.biases) + t->edge, j0, sb, se, slice, (float*)sr_rows_lds);
     return;

@@ -398,6 +398,8 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
     d.d_howo = sr_div_for(d.Ho * d.Wo);
     d.d_up = sr_div_for(q.up);
     d.d_steps = sr_div_for(d.steps_per_frame);
+    d.along = q.up == 1 && (int64_t)g->batch * q.H * q.W * q.Cin < ((int64_t)1 << 31) && q.Cout < (1 << 22) &&
+              std::max(q.Ho, q.Wo) < (1 << 24) / std::max(q.stride, 1);
     Item it{(int)p->edges.size(), 0, 0, 0, d.steps_per_frame * (f1 - f0 + 1), 0};
     p->edges.push_back(d);
     items.push_back(it);
@@ -413,15 +415,20 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
     sr_f32_shape(it.shape, &ti, &tj);
     it.n_i = ceil_div(d.I, ti);
     it.n_j = ceil_div(d.Cout, tj);
-    it.step_cycles = std::max(ti * tj / 8.0, 700.0);
+    // (measured, us a step of three workgroups on a compute unit: 128 x 32 1.55, fetched element by element 2.56; 128 x 64 1.82; 128 x 128 2.8)
+    it.step_cycles = std::max(ti * tj / 8.0, 900.0) * (d.quads_in ? 1.0 : 1.6);
     work += it.step_cycles * it.steps * it.n_i * it.n_j;
     p->shapes |= 1 << it.shape;
   }
-  // The pixel sums are cut into slices so that the launch has about six work items of equal length per compute unit,
-  // none shorter than 16 steps: shorter ones are dominated by filling the pipeline and by their partial sums.
-  const double item_cycles = work / (SR_CUS * 6.0);
+  // The pixel sums are cut into slices so that the launch has about twelve work items of equal length per compute unit,
+  // none shorter than 16 steps: shorter ones are dominated by filling the pipeline and by their partial sums.  (Six, two
+  // generations on the three places of a compute unit, left a fifth of the DSR2 window's launch to the last ones:
+  // 1480 us with 6, 1430 with 12, 1440 with 16; GTSRB-shaped 5630, 5550, 5555.)
+  const double item_cycles = work / (SR_CUS * 12.0);
   struct Keyed { double cost; SrGradTile t; };
-  std::vector<Keyed> list;
+  // Every XCD takes an eighth of each edge's tiles, slice by slice: the tiles of a slice read the same pixels, which then come
+  // through one L2 (workgroup i runs on XCD i % 8).
+  std::vector<std::vector<Keyed>> per_xcd(SR_XCDS);
   for (const Item& it : items) {
     SrGradEdge& d = p->edges[it.edge];
     const int64_t most = std::max(1, it.steps / 16);
@@ -435,9 +442,11 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
     }
     int ti, tj;
     sr_f32_shape(it.shape, &ti, &tj);
+    const int64_t total = (int64_t)d.slices * it.n_i * it.n_j;
+    int64_t k = 0;
     for (int s = 0; s < d.slices; ++s)
       for (int a = 0; a < it.n_i; ++a)
-        for (int b = 0; b < it.n_j; ++b) {
+        for (int b = 0; b < it.n_j; ++b, ++k) {
           SrGradTile t{};
           t.edge = it.edge;
           t.shape = it.shape;
@@ -446,7 +455,7 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
           t.step_begin = (int)((int64_t)it.steps * s / d.slices);
           t.step_end = (int)((int64_t)it.steps * (s + 1) / d.slices);
           t.slice = s;
-          list.push_back(Keyed{it.step_cycles * (t.step_end - t.step_begin), t});
+          per_xcd[k * SR_XCDS / total].push_back(Keyed{it.step_cycles * (t.step_end - t.step_begin), t});
         }
   }
   for (int v = 0; v < g->n_nodes; ++v) {
@@ -476,7 +485,7 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
           t.step_end = (int)(rows * (s + 1) / slices);
           t.slice = s;
           t.kind = 1;
-          list.push_back(Keyed{(t.step_end - t.step_begin) * 8.0, t});
+          per_xcd[(int64_t)s * SR_XCDS / slices].push_back(Keyed{(t.step_end - t.step_begin) * 8.0, t});
         }
       p->biases.push_back(b);
     } else if (!first) {
@@ -485,6 +494,13 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
     p->sums.push_back(sum);
     p->sum_blocks += ceil_div(d.channels, 64);
   }
-  std::stable_sort(list.begin(), list.end(), [](const Keyed& a, const Keyed& b) { return a.cost > b.cost; });
-  for (const Keyed& k : list) p->tiles.push_back(k.t);
+  size_t longest = 0;
+  for (auto& v : per_xcd) {
+    std::stable_sort(v.begin(), v.end(), [](const Keyed& a, const Keyed& b) { return a.cost > b.cost; });
+    longest = std::max(longest, v.size());
+  }
+  SrGradTile none{};
+  none.kind = 2;
+  for (size_t k = 0; k < longest; ++k)
+    for (int x = 0; x < SR_XCDS; ++x) p->tiles.push_back(k < per_xcd[x].size() ? per_xcd[x][k].t : none);
 }

@@ -64,7 +64,37 @@ static void pixels(int B, int Ho, int Wo, int H, int W, int Cin, int kh, int kw,
     }
 }
 
+// pixels of a gradient tile had from one another, against their own coordinates
+static void steps(int B, int Ho, int Wo, int H, int W, int Cin, int stride, int pad, int pixels) {
+  SrGradEdge e{};
+  e.Ho = Ho; e.Wo = Wo; e.H = H; e.W = W; e.Cin = Cin; e.stride = stride; e.pad = pad;
+  e.M = B * Ho * Wo;
+  e.d_wo = sr_div_for(Wo); e.d_howo = sr_div_for(Ho * Wo); e.d_up = sr_div_for(1);
+  const SrPixStep s = sr_pix_step(e, pixels);
+  for (int ti : {0, 2})
+    for (int tj : {0, 1})
+      for (int m0 = 0; m0 < pixels && m0 < e.M; ++m0) {
+        const uint32_t aoff = (uint32_t)(ti * W + tj) * (uint32_t)Cin + 1u;
+        const SrPixAt p0 = sr_pix_at(e, m0);
+        int w = p0.w + tj, h = p0.h + ti;
+        uint32_t off = sr_pix_off(e, p0, 0, aoff);
+        for (int m = m0; m < e.M; m += pixels) {
+          const SrPixAt p = sr_pix_at(e, m);
+          CHECK(w == p.w + tj && h == p.h + ti, "pixel %d of %dx%d stride %d, %d further on: (%d, %d)", m, Ho, Wo, stride, pixels, h, w);
+          CHECK(off == sr_pix_off(e, p, 0, aoff), "offset of pixel %d of %dx%d", m, Ho, Wo);
+          sr_pix_go(s, stride, Wo * stride - pad + tj, Ho * stride - pad + ti, &w, &h, &off);
+        }
+      }
+}
+
 int main() {
+  for (int pixels : {1, 4, 8, 12, 16})
+    for (int stride : {1, 2, 4})
+      for (int pad : {0, 1, 3}) {
+        for (int Wo : {1, 2, 3, 5, 7, 8, 15, 16, 17, 33})
+          for (int Ho : {1, 2, 3, 4, 9}) steps(40, Ho, Wo, Ho * stride, Wo * stride, 3, stride, pad, pixels);
+        steps(3, 64, 64, 64 * stride, 64 * stride, 20, stride, pad, pixels);
+      }
   for (int dir : {1, -1}) {
     // one pixel of each image (a phase of a strided edge): 128 rows of a tile lie in 128 images of 2^26 floats
     { const int is[] = {0, 1, 63, 127, 128, 199, 200, 327}, rs[] = {0, 1, 3, 4, 4 * 4096, 4 * 4 - 1, 16, 31};

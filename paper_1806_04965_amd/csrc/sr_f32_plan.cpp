@@ -270,15 +270,13 @@ double sr_rows_work(const SrRowPlan& p, int phase) {
 // give the launch more workgroups and shorter chains of dependent steps.  A tile may take as long as an even share of
 // the launch's work per compute unit (or some microseconds), else the next smaller shape is tried; below that the
 // reduction is cut into parts.
-// What the constants are worth: each halved and doubled, times of 17 cases (frames of 1 to 128 images, windows; us) --
-//   20000 cycles a tall tile may take            all within noise (0.5 %) either way
-//   12000 of a middle one, 512 of them           noise; a quarter of the workgroups or twice: DSR2 window 1480 -> 1505, 1625
-//   10000 a 32 x 32 tile may take uncut          half: MNIST SR clip 269 -> 237, DSR2 sequential B=1 1136 -> 1058; twice: 359, 1382
-//   5000 fixed                                   half: DSR2 B=1 1187; twice: MNIST SR clip 240, 1117, nothing slower by over 4 %
-//   750 per four steps of 32 x 32 tiles          half: DSR2 clip 1625 -> 2544; twice: 1409, MNIST SR clip 238, small window 221 -> 239
-//   700 a step of middle tiles                   half: noise; twice: DSR2 clip 1745, sequential window 2390 -> 2449
-//   at most 16 parts                             8: DSR2 B=1 1187; 32: noise
-// so 32 x 32 tiles are taken, and left whole, more often than is best for fp32 frames.
+// What the constants are worth (us, with the kernels as they are: live tiny, MNIST SR clip, DSR2 clip, DSR2 sequential B=1, 40x40
+// net hybrid B=9, MNIST S clip B=9, DSR6 clip B=30; windows and the rest within 1 % either way) --
+//   6000 cycles a 32 x 32 tile may take uncut    5000: 33 209 1314 937 451 331 576; 7000: 32 207 1316 949 462 333 579; 10000: 33 223 1315 981 464 361 589
+//   750 per four steps of 32 x 32 tiles          500: 31 225 1717 1055 434 371 556; 1100: 31 207 1315 952 469 341 567 and a 30x30 window 300 -> 324
+//   12000 of a middle one, 512 of them           24000, 256: noise
+//   700 a step of middle tiles                   600, 900: noise
+//   20000 cycles a tall tile may take, 5000 fixed, at most 16 parts   measured when the kernels were slower: noise within 4 %
 void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double work_cycles, int tall_from, bool split, bool ordered,
                    int* split_slots, std::vector<SrRowTile>* out, int* shapes) {
   double work = 0;
@@ -315,7 +313,7 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
     } else if (n_short >= 2 * SR_CUS && latency(mid, ph.steps) <= std::max(share, 12000.0)) {
       shape = mid;
     } else {
-      const double lat = latency(SR_F32_SMALL, ph.steps), want = std::max(share, 10000.0);
+      const double lat = latency(SR_F32_SMALL, ph.steps), want = std::max(share, 6000.0);
       if (split && lat > want) parts = std::max(1, std::min(std::min(ceil_div((int64_t)lat, (int64_t)want), 16), ph.steps / 16));
     }
     int ti, tj;

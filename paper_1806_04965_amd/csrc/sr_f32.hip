@@ -511,12 +511,13 @@ __device__ __forceinline__ void sr_step_products(const unsigned char* st, int iw
 // The products of four steps for a 16 x 16 quarter of a 32 x 32 tile, four reduction indices per instruction, in the order
 // in which the 32x32x2 products take them: 0, 8, 1, 9, ...  Both instructions add their products one after the other, each
 // rounded like a fused multiply-add (300 000 sums compared bit for bit, products below the normal range among them).
+struct SrQuarter { float a[4][4], b[4][4]; };   // operands of four steps
 template <bool A_ROWS>
-__device__ __forceinline__ void sr_quarter_products(const unsigned char* st, int iw, int jw, int lane, f32x4_t& acc) {
+__device__ __forceinline__ void sr_quarter_read(const unsigned char* st, int iw, int jw, int lane, SrQuarter& f4) {
   constexpr int STAGE = 64 * 64;
+  auto &a = f4.a, &b = f4.b;
   const int l = lane & 15, q = lane >> 4;
   const int k0 = 8 * (q & 1) + (q >> 1);   // this lane's index of product m: k0 + 2 m
-  float a[4][4], b[4][4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     if (A_ROWS) {
@@ -533,10 +534,12 @@ __device__ __forceinline__ void sr_quarter_products(const unsigned char* st, int
 #pragma unroll
     for (int m = 0; m < 4; ++m) b[s][m] = p[m * 64];
   }
+}
+__device__ __forceinline__ void sr_quarter_products(const SrQuarter& f, f32x4_t& acc) {
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int m = 0; m < 4; ++m) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][m], b[s][m], acc, 0, 0, 0);
+    for (int m = 0; m < 4; ++m) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[s][m], f.b[s][m], acc, 0, 0, 0);
 }
 
 // K-split: every part leaves its registers in its slab, the part that arrives last adds them up in part order.
@@ -680,8 +683,10 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
       if (!SMALL) __builtin_amdgcn_s_setprio(0);
       const unsigned char* st = base + stage * PITCH;
       if constexpr (QUARTERS) {
-        if (a_rows) sr_quarter_products<true>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, quarter);
-        else sr_quarter_products<false>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, quarter);
+        SrQuarter f;
+        if (a_rows) sr_quarter_read<true>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, f);
+        else sr_quarter_read<false>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, f);
+        sr_quarter_products(f, quarter);
       } else {
         sr_step_products<TI, TJ, MI, MJ>(st, iw, jw, lane, a_rows, BACK && a_rows, acc);
       }
@@ -726,24 +731,51 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
       bool folding = false;
       unsigned w_step = (unsigned)op.ldw * (4u * INC);
       for (;;) {
-        do {
-          if (SMALL && !BACK && !op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::NA + TJ / 4 / NW)>();
-          else sr_wait_loads<PAIRS ? 0 : (AHEAD - 1) * Ops::LOADS>();
-          if (!ALONE) sr_step_barrier();   // everybody's loads of the steps in hand; and the ones before have been read by all
-          op.template issue_along<PAIRS>(at0 + wr * PITCH, w);
-          op.template advance<INC>();
-          if (!BACK) w += w_step;
-          multiply(rd, true);
-          if (PAIRS) multiply(rd + 1, true);
-          r += INC;
-          if (PAIRS) {
-            rd ^= 2;
-            wr ^= 2;
-          } else {
+        if constexpr (QUARTERS && STAGES > 3) {
+          // A quarter's sixteen products are a chain of 512 cycles; the reads of the next four steps' operands go under it.
+          SrQuarter f, g;
+          auto read = [&](SrQuarter& q) {
+            if (!op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::NA + TJ / 4 / NW)>();
+            else sr_wait_loads<(AHEAD - 1) * Ops::LOADS>();
+            sr_step_barrier();   // as below
+            op.template issue_along<false>(at0 + wr * PITCH, w);
+            op.template advance<INC>();
+            w += w_step;
+            sr_quarter_read<true>(base + rd * PITCH, 16 * (wave >> 1), 16 * (wave & 1), lane, q);
+            r += INC;
             rd = rd == STAGES - 1 ? 0 : rd + 1;
             wr = wr == STAGES - 1 ? 0 : wr + 1;
+            --n;
+          };
+          read(f);
+          for (;;) {
+            if (n == 0) { sr_quarter_products(f, quarter); break; }
+            read(g);
+            sr_quarter_products(f, quarter);
+            if (n == 0) { sr_quarter_products(g, quarter); break; }
+            read(f);
+            sr_quarter_products(g, quarter);
           }
-        } while (--n > 0);
+        } else {
+          do {
+            if (SMALL && !BACK && !op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::NA + TJ / 4 / NW)>();
+            else sr_wait_loads<PAIRS ? 0 : (AHEAD - 1) * Ops::LOADS>();
+            if (!ALONE) sr_step_barrier();   // everybody's loads of the steps in hand; and the ones before have been read by all
+            op.template issue_along<PAIRS>(at0 + wr * PITCH, w);
+            op.template advance<INC>();
+            if (!BACK) w += w_step;
+            multiply(rd, true);
+            if (PAIRS) multiply(rd + 1, true);
+            r += INC;
+            if (PAIRS) {
+              rd ^= 2;
+              wr ^= 2;
+            } else {
+              rd = rd == STAGES - 1 ? 0 : rd + 1;
+              wr = wr == STAGES - 1 ? 0 : wr + 1;
+            }
+          } while (--n > 0);
+        }
         ends = 0;
         if (ORDERED && folding) {
           fold();   // the segment before: its last steps were multiplied while this one's first were on the way

@@ -296,7 +296,8 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
     if (shape == SR_F32_SMALL) return steps / 4 * 750.0 + 5000.0;
     return steps * std::max(ti * tj / 8.0, 700.0) + 5000.0;
   };
-  struct Keyed { double cost; SrRowTile t; };
+  struct Keyed { double cost; int tile; };   // (128-byte records are not moved about)
+  std::vector<SrRowTile> tiles;
   std::vector<std::vector<Keyed>> per_xcd(SR_XCDS);
   for (int f : phases) {
     const SrPhase& ph = p.phases[f];
@@ -340,7 +341,8 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
           t.split_slot = slot;
           t.part = part | (parts << 16);
           t.p = ph;
-          per_xcd[k * SR_XCDS / total].push_back(Keyed{latency(shape, (double)ph.steps / parts), t});
+          per_xcd[k * SR_XCDS / total].push_back(Keyed{latency(shape, (double)ph.steps / parts), (int)tiles.size()});
+          tiles.push_back(t);
         }
       }
   }
@@ -353,7 +355,7 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
   SrRowTile none{};
   none.phase = -1;
   for (size_t k = 0; k < longest; ++k)
-    for (int x = 0; x < SR_XCDS; ++x) out->push_back(k < per_xcd[x].size() ? per_xcd[x][k].t : none);
+    for (int x = 0; x < SR_XCDS; ++x) out->push_back(k < per_xcd[x].size() ? tiles[per_xcd[x][k].tile] : none);
 }
 
 void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from) {
@@ -423,7 +425,8 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
   // generations on the three places of a compute unit, left a fifth of the DSR2 window's launch to the last ones:
   // 1480 us with 6, 1430 with 12, 1440 with 16; GTSRB-shaped 5630, 5550, 5555.)
   const double item_cycles = work / (SR_CUS * 12.0);
-  struct Keyed { double cost; SrGradTile t; };
+  struct Keyed { double cost; int tile; };
+  std::vector<SrGradTile> tiles;
   // Every XCD takes an eighth of each edge's tiles, slice by slice: the tiles of a slice read the same pixels, which then come
   // through one L2 (workgroup i runs on XCD i % 8).
   std::vector<std::vector<Keyed>> per_xcd(SR_XCDS);
@@ -453,7 +456,8 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
           t.step_begin = (int)((int64_t)it.steps * s / d.slices);
           t.step_end = (int)((int64_t)it.steps * (s + 1) / d.slices);
           t.slice = s;
-          per_xcd[k * SR_XCDS / total].push_back(Keyed{it.step_cycles * (t.step_end - t.step_begin), t});
+          per_xcd[k * SR_XCDS / total].push_back(Keyed{it.step_cycles * (t.step_end - t.step_begin), (int)tiles.size()});
+          tiles.push_back(t);
         }
   }
   for (int v = 0; v < g->n_nodes; ++v) {
@@ -483,7 +487,8 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
           t.step_end = (int)(rows * (s + 1) / slices);
           t.slice = s;
           t.kind = 1;
-          per_xcd[(int64_t)s * SR_XCDS / slices].push_back(Keyed{(t.step_end - t.step_begin) * 8.0, t});
+          per_xcd[(int64_t)s * SR_XCDS / slices].push_back(Keyed{(t.step_end - t.step_begin) * 8.0, (int)tiles.size()});
+          tiles.push_back(t);
         }
       p->biases.push_back(b);
     } else if (!first) {
@@ -500,5 +505,5 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
   SrGradTile none{};
   none.kind = 2;
   for (size_t k = 0; k < longest; ++k)
-    for (int x = 0; x < SR_XCDS; ++x) p->tiles.push_back(k < per_xcd[x].size() ? per_xcd[x][k].t : none);
+    for (int x = 0; x < SR_XCDS; ++x) p->tiles.push_back(k < per_xcd[x].size() ? tiles[per_xcd[x][k].tile] : none);
 }

@@ -7,8 +7,8 @@
 // global memory and LDS.  fp32 matrix instructions are slow (a 32x32x2 product takes 64 cycles of its SIMD); a step's
 // operand traffic is 8 bytes per cycle of its products and CU for 128 x 128 tiles, 12 for 128 x 64, 16 for 64 x 64, 20 for
 // 128 x 32 and 32 for 32 x 32.  What bounds a tile is the fp32 matrix rate, 157 TFLOP/s, for 128 x 128 tiles, whose waves have
-// 32 products a step (GTSRB-shaped windows: matrix cores 77 % busy in the reverse sweep, 74 % in the weight gradients; 71 %
-// in the forward pass with its 128 x 64 tiles, before the loop below).  64 x 64 and 128 x 32 tiles have 8: there a step's fixed
+// 32 products a step (GTSRB-shaped windows: matrix cores 86 % busy in the reverse sweep, 76 % in the weight gradients, 81 %
+// in the forward pass with its 128 x 64 tiles; 77, 74 and 71 % before the loop below).  64 x 64 and 128 x 32 tiles have 8: there a step's fixed
 // costs take as long as its products.  So these fetch steps in pairs, a barrier per pair; launches without 128 x 128 tiles run
 // four workgroups per CU (see the variants in sr_f32.h); and the steps of whole segments go through a loop that holds nothing
 // but their loads and products (run_along below: 155 instructions a pair, 16 of them products, where the code that takes any
@@ -18,8 +18,8 @@
 //
 // Measured, DSR2 as an fp32 graph (batch 64, 6.4 GFLOP per frame): 1350 us per frame with a thread per output (weights
 // and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s), 100 with pairs, 82 with segments' steps back
-// to back; MNIST SR, batch 128: 31 -> 17 -> 14 us.  Training windows, step by step -> pairs and variants -> now: DSR2 B=64 W=8
-// 1674 -> 1480 -> 1430 us, GTSRB-shaped B=128 W=4 6270 -> 6180 -> 5640, MNIST SR 362 -> 362.
+// to back; MNIST SR, batch 128: 31 -> 17 -> 13 us.  Training windows, step by step -> pairs and variants -> now: DSR2 B=64 W=8
+// 1674 -> 1480 -> 1405 us, GTSRB-shaped B=128 W=4 6270 -> 6180 -> 5550, MNIST SR 362 -> 350.
 //
 // In the loop a wave's priority is raised but for its products: loads, addresses and set-up of one wave then go ahead of the
 // others' products, which the matrix cores take 64 cycles each for (GTSRB-shaped window 5690 -> 5620 us, DSR2 1437 -> 1423).

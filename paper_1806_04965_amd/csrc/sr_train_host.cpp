@@ -8,8 +8,8 @@
 //
 // Measured (launch per edge and per elementwise pass on four streams, state gradients accumulated in memory -> launch
 // per depth, everything fused): MNIST SR B=128 W=8 sequential 250 launches, 1.98 ms -> 25, 0.34; DSR2 B=64 W=8 485,
-// 5.1 -> 22, 1.7; GTSRB-shaped B=128 W=4 52.7 -> 6.3 (a window
-// shorter than the network is deep: an eighth of its nominal operations reach the loss; 94 TFLOP/s on those).
+// 5.1 -> 22, 1.4; GTSRB-shaped B=128 W=4 52.7 -> 5.6 (a window
+// shorter than the network is deep: an eighth of its nominal operations reach the loss; 106 TFLOP/s on those).
 //
 // Values that cannot reach a loss term are not computed: node v is at least dist(v) bridging edges away from the out
 // node, so its states and gradients of the frames after W - dist(v) have no reader.  Nor are the products with the

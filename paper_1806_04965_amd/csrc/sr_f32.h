@@ -95,15 +95,13 @@ struct SrRowNode {
 
 // tile shapes: TI x TJ, of four waves; SR_F32_SMALL: each wave takes every fourth reduction step of a 32 x 32 tile
 enum { SR_F32_128x128 = 0, SR_F32_128x64 = 1, SR_F32_64x64 = 2, SR_F32_128x32 = 3, SR_F32_SMALL = 4 };
-struct alignas(128) SrRowTile {
+// (With its phase in it, 128 bytes, a tile's start saved a round trip and a launch nothing that could be measured; the first window
+// of a graph, which plans and copies them, took longer: MNIST SR 571 -> 606 us, DSR2 1842 -> 1858, GTSRB-shaped 7160 -> 7790.)
+struct SrRowTile {
   int32_t phase;                  // < 0: empty slot
   int32_t shape, i0, j0;
   int32_t step_begin, step_end;   // part of the phase's reduction steps
   int32_t split_slot, part;       // K-split as in SrMfmaTile: slot of part 0 (-1: none), part index | parts << 16
-  // The phase itself: a tile then starts on one round trip to memory, then one for segment and node, one for their tensors
-  // (tile -> phase -> segment -> tensor was 2 us of a 32 x 32 tile's 4 to 12, all of it waiting)
-  SrPhase p;
-  int32_t pad_[8];
 };
 
 // A launch over several (tile list, frame) pairs: pair k takes the workgroups from block0 on.
@@ -271,6 +269,7 @@ SR_HD uint32_t sr_pix_off(const SrGradEdge& e, const SrPixAt& p, int b0, uint32_
 struct SrRowArgs {
   const SrTensor* tensors;
   const SrRowNode* nodes;
+  const SrPhase* phases;
   const SrSeg* segs;
   const SrLine* lines;
   const SrRowTile* tiles;

@@ -975,10 +975,10 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
 template <int FOR, int VARIANT>
 __device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowTile) t, int slot0, const SrSlots& sl, float* record,
                                             int rec_node, unsigned char* lds) {
-  const sr_i32x16 v = *(SR_CONST4(sr_i32x16))(unsigned long long)t;   // one load
-  if (v[0] < 0) return;
-  SR_CONST4(SrPhase) p = (SR_CONST4(SrPhase))((unsigned long long)t + offsetof(SrRowTile, p));
-  const int shape = v[1], i0 = v[2], j0 = v[3], sb = v[4], se = v[5], slot = slot0 + v[6], part = v[7];
+  const int phase = t->phase;
+  if (phase < 0) return;
+  SR_CONST4(SrPhase) p = sr_k(A.phases) + phase;
+  const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = slot0 + t->split_slot, part = t->part;
   if constexpr (VARIANT != SR_F32_DEEP) {
     if constexpr (VARIANT == SR_F32_WIDE)
       if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, FOR, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);

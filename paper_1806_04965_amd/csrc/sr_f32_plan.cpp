@@ -296,7 +296,7 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
     if (shape == SR_F32_SMALL) return steps / 4 * 750.0 + 5000.0;
     return steps * std::max(ti * tj / 8.0, 700.0) + 5000.0;
   };
-  struct Keyed { double cost; int tile; };   // (128-byte records are not moved about)
+  struct Keyed { double cost; int tile; };
   std::vector<SrRowTile> tiles;
   std::vector<std::vector<Keyed>> per_xcd(SR_XCDS);
   for (int f : phases) {
@@ -340,7 +340,6 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
           t.step_end = (int)((int64_t)ph.steps * (part + 1) / parts);
           t.split_slot = slot;
           t.part = part | (parts << 16);
-          t.p = ph;
           per_xcd[k * SR_XCDS / total].push_back(Keyed{latency(shape, (double)ph.steps / parts), (int)tiles.size()});
           tiles.push_back(t);
         }

@@ -122,6 +122,7 @@ struct sr_graph {
   // fp32 graphs: tables of the row tiles (sr_f32.h)
   struct SrTensor* row_tensors = nullptr;
   struct SrRowNode* row_nodes = nullptr;
+  struct SrPhase* row_phases = nullptr;
   struct SrLine* row_lines = nullptr;
   struct SrSeg* row_segs = nullptr;
   struct SrRowTile* row_tiles = nullptr;

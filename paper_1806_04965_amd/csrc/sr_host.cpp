@@ -1204,6 +1204,7 @@ sr_status finalize(sr_graph* g) {
     for (const NodeRt& n : g->nodes) tensors.push_back(SrTensor{(char*)n.state[0], (char*)n.state[1] - (char*)n.state[0]});
     if ((st = upload(g, &g->row_tensors, tensors)) != SR_OK) return st;
     if ((st = upload(g, &g->row_nodes, rows.nodes)) != SR_OK) return st;
+    if ((st = upload(g, &g->row_phases, rows.phases)) != SR_OK) return st;
     if ((st = upload(g, &g->row_lines, rows.lines)) != SR_OK) return st;
     if ((st = upload(g, &g->row_segs, rows.segs)) != SR_OK) return st;
     if ((st = upload(g, &g->row_tiles, row_tiles)) != SR_OK) return st;
@@ -1604,7 +1605,8 @@ sr_status enqueue_frame(sr_graph* g, bool record, FrameTimer* ft, SrSplitScratch
       SR_HIP(g, mark(lp.n_rows > 0 ? 2 : 1));
       if (lp.n_rows > 0) {   // fp32 graphs have no bf16 tiles
         SrRowArgs a{};
-        a.tensors = g->row_tensors; a.nodes = g->row_nodes; a.segs = g->row_segs; a.lines = g->row_lines;
+        a.tensors = g->row_tensors; a.nodes = g->row_nodes; a.phases = g->row_phases; a.segs = g->row_segs;
+        a.lines = g->row_lines;
         a.tiles = g->row_tiles + lp.row_begin;
         a.n_tiles = lp.n_rows;
         a.rec_node = record ? g->rec_node : -1;

@@ -342,8 +342,8 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
 
   Blob blob;
   const size_t o_tensors = blob.add(tensors), o_dst = blob.add(std::vector<float*>(E + N, nullptr)), o_runs = blob.add(runs);
-  const size_t o_fn = blob.add(rf.nodes), o_fl = blob.add(rf.lines), o_fs = blob.add(rf.segs), o_ft = blob.add(tf);
-  const size_t o_bn = blob.add(rb.nodes), o_bl = blob.add(rb.lines), o_bs = blob.add(rb.segs), o_bt = blob.add(tb);
+  const size_t o_fn = blob.add(rf.nodes), o_fp = blob.add(rf.phases), o_fl = blob.add(rf.lines), o_fs = blob.add(rf.segs), o_ft = blob.add(tf);
+  const size_t o_bn = blob.add(rb.nodes), o_bp = blob.add(rb.phases), o_bl = blob.add(rb.lines), o_bs = blob.add(rb.segs), o_bt = blob.add(tb);
   std::vector<std::vector<size_t>> o_chunk;
   for (const SrTrainPlan::Chunk& c : T.chunks)
     o_chunk.push_back({blob.add(c.grad.edges), blob.add(c.grad.biases), blob.add(c.grad.tiles), blob.add(c.grad.sums)});
@@ -363,11 +363,13 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
   T.runs = (const SrRun*)(base + o_runs);
   T.rows_fwd = a;
   T.rows_fwd.nodes = (const SrRowNode*)(base + o_fn);
+  T.rows_fwd.phases = (const SrPhase*)(base + o_fp);
   T.rows_fwd.lines = (const SrLine*)(base + o_fl);
   T.rows_fwd.segs = (const SrSeg*)(base + o_fs);
   T.rows_fwd.tiles = (const SrRowTile*)(base + o_ft);
   T.rows_back = a;
   T.rows_back.nodes = (const SrRowNode*)(base + o_bn);
+  T.rows_back.phases = (const SrPhase*)(base + o_bp);
   T.rows_back.lines = (const SrLine*)(base + o_bl);
   T.rows_back.segs = (const SrSeg*)(base + o_bs);
   T.rows_back.tiles = (const SrRowTile*)(base + o_bt);

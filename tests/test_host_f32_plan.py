@@ -1,0 +1,90 @@
+"""The planner of the tiled fp32 kernels (csrc/sr_f32_plan.cpp), compiled for the host: what its tables hold and how its work
+items are spread."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1806_04965_amd", "csrc")
+
+COMMON = r"""
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include "sr_f32.h"
+#include "sr_graph.h"
+
+#define CHECK(c, ...) do { if (!(c)) { std::printf(__VA_ARGS__); std::printf("  (%s)\n", #c); std::exit(1); } } while (0)
+
+struct N { int channels, size; };
+struct E { int src, dst, kind, k, stride, pad; };
+static sr_graph* graph(int batch, std::vector<N> nodes, std::vector<E> edges) {   // every edge bridges
+  sr_graph* g = new sr_graph();
+  g->batch = batch;
+  g->n_nodes = (int)nodes.size();
+  g->n_edges = (int)edges.size();
+  for (const N& n : nodes) {
+    NodeRt r;
+    r.d.channels = n.channels; r.d.height = r.d.width = n.size; r.d.act = 1;
+    g->nodes.push_back(r);
+  }
+  g->an.is_input.assign(nodes.size(), 1);
+  for (const E& e : edges) {
+    EdgeRt r;
+    r.d.src = e.src; r.d.dst = e.dst; r.d.kind = e.kind; r.d.bridge = 1; r.d.upsample = 1;
+    r.d.stride = e.stride; r.d.pad = e.pad;
+    r.kh = r.kw = e.kind == SR_EDGE_DENSE ? nodes[e.src].size : (e.kind == SR_EDGE_CONV ? e.k : 1);
+    r.w_count = (size_t)r.kh * r.kw * nodes[e.src].channels * nodes[e.dst].channels;
+    g->edges.push_back(r);
+    g->an.is_input[e.dst] = 0;
+  }
+  return g;
+}
+// tensor numbers of a window with its loss at node `out`
+static SrTrainIds train_ids(const sr_graph* g, int out) {
+  SrTrainIds ids;
+  ids.grad0 = g->n_nodes; ids.mask0 = 2 * g->n_nodes; ids.seed = -1; ids.out_node = out;
+  int n = 3 * g->n_nodes + 1;
+  ids.mean.assign(g->n_edges, -1);
+  for (int e = 0; e < g->n_edges; ++e)
+    if (g->edges[e].d.kind == SR_EDGE_GAP_DENSE) ids.mean[e] = n++;
+  ids.dist.assign(g->n_nodes, -1);
+  ids.dist[out] = 0;
+  for (bool changed = true; changed;) {
+    changed = false;
+    for (const EdgeRt& e : g->edges)
+      if (ids.dist[e.d.dst] >= 0 && (ids.dist[e.d.src] < 0 || ids.dist[e.d.src] > ids.dist[e.d.dst] + 1)) {
+        ids.dist[e.d.src] = ids.dist[e.d.dst] + 1;
+        changed = true;
+      }
+  }
+  return ids;
+}
+"""
+
+TILE_RECORD = COMMON + r"""
+int main() {
+  // Planned by the ten thousands in the first window of a graph, sorted, and copied to the device: a record has what tells a
+  // workgroup its part, not the descriptors that many of them share.
+  CHECK(sizeof(SrRowTile) <= 32, "a tile's record has %zu bytes", sizeof(SrRowTile));
+  std::printf("ok\n");
+}
+"""
+
+
+def run(tmp_path, program):
+    src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
+    src.write_text(program)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-fsanitize=undefined", "-fno-sanitize-recover=undefined", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-I", CSRC, str(src), os.path.join(CSRC, "sr_f32_plan.cpp"), "-o", str(exe)],
+                   check=True, timeout=120)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+    return r.stdout
+
+
+def test_tile_records_are_small(tmp_path):
+    run(tmp_path, TILE_RECORD)

@@ -126,14 +126,15 @@ __device__ __forceinline__ bool sr_seg_counts(const SrSeg& g, const SrSlots& sl)
 // multiples of four (SR_SEG_QUADS), else 0, 1, 2, .. (line 8 h + k of its stage then holds index 2 k + h).
 enum { SR_ROWS_FRAME = 0, SR_ROWS_BACK = 1, SR_ROWS_ORDERED = 2 };
 
-// The operands of a tile: a TI x 16 and a 16 x TJ piece per step, NW waves fetching them together.
+// The operands of a tile of four waves: a TI x 16 and a 16 x TJ piece per step, the waves fetching them together.
 //   rows:  TI (TJ) rows of 16 reduction indices, 64 bytes a row, pieces of four permuted (sr_f32_piece)
 //   k-major: 16 lines of TI (TJ) elements
 // A is rows when the gathered channel count is a multiple of four (16-byte loads), else k-major (4-byte loads); B is
 // k-major in the forward direction, where theta's columns are contiguous, and like A backwards.
-template <int TI, int TJ, int NW, int FOR>
+template <int TI, int TJ, int FOR>
 struct SrRowOperands {
   static constexpr bool BACK = FOR == SR_ROWS_BACK;
+  static constexpr int NW = 4;
   static constexpr int NA = TI / (16 * NW);                        // 16-byte loads of A per wave and step
   static constexpr int NB = TJ / (16 * NW) > 0 ? TJ / (16 * NW) : 1;   // ... of B (TJ = 32 of four waves: half the lanes)
   static constexpr int STAGE = (TI + TJ) * 64;                     // bytes of one step in LDS
@@ -153,8 +154,7 @@ struct SrRowOperands {
   int turn;                  // ordered: the products of a step go in turn
   // A step whose indices lie in one tap (channel counts that are multiples of 16) has addresses that go on from those of the
   // step before: a lane's gathered address by the channels passed, theta by a scalar base under lane offsets that stay for
-  // the segment; only a new tap looks at the image's edges again.  Taking every step's tap and addresses from its number
-  // instead cost a 32 x 32 tile 1000 cycles a step, a frame of the tiny network 11.8 us.
+  // the segment; only a new tap looks at the image's edges again.
   const SrLine* lines;       // null: no table
   int along;                 // A goes that way
   int at_r, vi, vj, c;       // step that the addresses are for; its tap and first channel
@@ -166,14 +166,10 @@ struct SrRowOperands {
   uint32_t wpair;            // a pair's theta by full waves where a step's takes half of each (HALF_B)
   int wide_w;                // ... whose lane offsets fit 32 bits
 
-  // (a 32 x 32 tile's descriptors stay in registers: its few waves wait for every read)
-  template <typename T>
-  static __device__ __forceinline__ SR_CONST4(T) again(SR_CONST4(T) p) { return NW == 1 ? p : sr_again(p); }
-
   // a new segment, whose first step will be the one at r0: where this lane's rows are in its image
   __device__ __forceinline__ void enter(const SrSeg& g, SR_CONST4(SrSeg) at_seg, SR_CONST4(SrPhase) phase, const SrTensor* tensors,
                                         const SrLine* line_table, const SrSlots& sl, int r0) {
-    const SrPhase p = sr_load_phase(again(phase));
+    const SrPhase p = sr_load_phase(sr_again(phase));
     seg = at_seg;
     GH = g.GH; GW = g.GW; GC = g.GC; dir = g.dir; ntj = g.ntj; R = g.R; ldw = g.ldw;
     if (BACK) { wt0 = g.wt0; wti = g.wti; wtj = g.wtj; d_wup = g.d_wup; }
@@ -187,7 +183,7 @@ struct SrRowOperands {
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
       const int r = quads ? n * 16 * NW + wv * 16 + (lane >> 2)
-                          : (TI >= 64 ? (TI == 128 ? (wv & 1) * 64 + lane : lane) : (lane & 31));
+                          : (TI == 128 ? (wv & 1) * 64 + lane : lane);
       const SrRowAt at = sr_row_at(p, g, i0 + r);
       row_h[n] = at.h;
       row_w[n] = at.w;
@@ -268,7 +264,7 @@ struct SrRowOperands {
   }
   // ... of the step at r0
   __device__ __forceinline__ void go_on(int r0) {
-    while (at_r < r0) advance<(NW == 1 ? 4 : 1) * SR_F32_KS>();
+    while (at_r < r0) advance<SR_F32_KS>();
   }
 
   // Do this segment's steps (PAIR: at r0 even pairs of steps) take the loads of issue_along?
@@ -328,7 +324,7 @@ struct SrRowOperands {
   __device__ __forceinline__ void issue(int r0, unsigned at) {
     const char* zero = (const char*)sr_zero_line;
     const unsigned bt = at + TI * 64;
-    const bool all = r0 + SR_F32_KS <= R;   // all sixteen indices exist (a wave of four may stand past the end of its segment)
+    const bool all = r0 + SR_F32_KS <= R;   // all sixteen indices exist
     if (all && all_along<false>(r0)) {
       go_on(r0);
       issue_along<false>(at, theta(r0));
@@ -339,12 +335,12 @@ struct SrRowOperands {
 #pragma unroll
       for (int n = 0; n < NA; ++n) sr_to_lds16(cur[n], at + (n * NW + wv) * 1024);
     } else if (quads) {   // (past the end: of the rows' addresses, which may include k4, none is read)
-      const SrSeg g = sr_load_seg(again(seg));
+      const SrSeg g = sr_load_seg(sr_again(seg));
       const SrTapAt t = sr_tap_at(g, r0 + 4 * sr_f32_piece(lane >> 2, lane & 3));
       const long long toff = sr_gather_off(g, t) * 4;
 #pragma unroll
       for (int n = 0; n < NA; ++n) sr_to_lds16(gathered(g, n, t, toff), at + (n * NW + wv) * 1024);
-    } else if (TI >= 64 && lines != nullptr && r0 < R) {
+    } else if (lines != nullptr) {
       SR_CONST4(sr_i32x16) step = (SR_CONST4(sr_i32x16))(unsigned long long)(lines + r0);
       const int l0 = TI == 128 ? 8 * (wv >> 1) : 4 * wv;   // this wave's lines, 64 of a line's rows
 #pragma nounroll
@@ -354,13 +350,13 @@ struct SrRowOperands {
         for (int q = 0; q < 4; ++q) sr_to_lds4(lined(x[4 * q], x[4 * q + 1], x[4 * q + 2]), at + (l0 + 4 * k + q) * (TI * 4) + (TI == 128 ? (wv & 1) * 256 : 0));
       }
     } else {
-      const SrSeg g = sr_load_seg(again(seg));
+      const SrSeg g = sr_load_seg(sr_again(seg));
 #pragma unroll
       for (int q = 0; q < TI / 4 / NW; ++q) {
         const int id = q * NW + wv;
-        const int line = TI >= 64 ? id * 64 / TI : 2 * id + (lane >> 5);
+        const int line = id * 64 / TI;
         const int k = FOR == SR_ROWS_ORDERED && turn ? sr_in_turn(line) : line;
-        const SrTapAt t = sr_tap_at(g, TI >= 64 ? SR_UNI(r0 + k) : r0 + k);
+        const SrTapAt t = sr_tap_at(g, SR_UNI(r0 + k));
         const char* p = gathered(g, 0, t, sr_gather_off(g, t) * 4);
         sr_to_lds4(p, at + id * 256);
       }
@@ -368,7 +364,7 @@ struct SrRowOperands {
     if (BACK) {
       if (quads) {
         // (a half-filled wave's rows start at a multiple of eight: its pieces are permuted differently from A's)
-        const SrSeg g = sr_load_seg(again(seg));
+        const SrSeg g = sr_load_seg(sr_again(seg));
         const SrTapAt t = sr_tap_at(g, r0 + 4 * sr_f32_piece((HALF_B ? wv * 8 : 0) + (lane >> 2), lane & 3));
         const bool r_ok = t.vi != SR_NO_TAP;
         const uint32_t off = sr_weight_off(g, t, 0);
@@ -383,7 +379,7 @@ struct SrRowOperands {
           }
         }
       } else {
-        const SrSeg g = sr_load_seg(again(seg));
+        const SrSeg g = sr_load_seg(sr_again(seg));
 #pragma unroll
         for (int q = 0; q < TJ / 4 / NW; ++q) {
           const int id = q * NW + wv;
@@ -419,7 +415,7 @@ struct SrRowOperands {
       }
       return;
     }
-    const SrSeg g = sr_load_seg(again(seg));
+    const SrSeg g = sr_load_seg(sr_again(seg));
     if (FOR == SR_ROWS_ORDERED && turn) {
       if (quads_w) {
 #pragma unroll
@@ -462,6 +458,194 @@ struct SrRowOperands {
         const char* p = (r < g.R && j < g.ldw) ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : zero;
         sr_to_lds4(p, bt + id * 256);
       }
+    }
+  }
+};
+
+// The operands of a 32 x 32 tile, laid out as above and fetched by one wave.  A launch of such tiles is one generation of them, a
+// wave takes one to ten steps of a segment, and the instructions in a row from a tile's start to its end are what it takes: a
+// scalar one 5 to 8 cycles.  So a segment's descriptor stays in registers, a step is decoded from its number, and addresses that
+// go on from step to step (as above) are set up where the loop that uses them starts.  (Set up with every segment, 270 more
+// scalar instructions a tile: windows MNIST SR 343 -> 327 us, DSR1 B=3 273 -> 255, DSR5 B=1 486 -> 454; 16 frames of the
+// CIFAR-shaped graph B=7 514 -> 494, of 33x33 images in 16 channels 224 -> 214.  Segments and steps as two loops, or filling,
+// running and draining the stages as one, made the kernels a third smaller and 3 to 10 % slower: copies of accumulators and
+// descriptors between the parts.)
+template <int FOR>
+struct SrSmallOperands {
+  static constexpr bool BACK = FOR == SR_ROWS_BACK;
+  static constexpr int N = 2;                // 16-byte loads of A, and of B, per step
+  static constexpr int STAGE = 64 * 64, LOADS = 2 * N;
+
+  SrSeg g;
+  int row_h[N], row_w[N];    // this lane's rows: where tap (0, 0) lands ...
+  const char* row_at[N];     // ... and its address
+  int lane, i0, j0;
+  int quads, quads_w;
+  int turn;                  // ordered: the products of a step go in turn
+
+  // a new segment: where this lane's rows are in its image
+  __device__ __forceinline__ void enter(const SrPhase& p, const SrTensor* tensors, const SrSlots& sl) {
+    SR_CONST4(SrTensor) t = sr_k(tensors) + g.tensor;
+    const int slot = sl.lag0 + ((g.flags & SR_SEG_LAG) ? sl.lag1 - sl.lag0 : 0);   // (a select between the fields would go through memory)
+    const char* src = sr_uni_ptr((const char*)(unsigned long long)t->base + slot * t->stride);
+    quads = SR_UNI((g.flags & SR_SEG_QUADS) && ((unsigned)(unsigned long long)src & 15u) == 0);
+    quads_w = SR_UNI((g.ldw & 3) == 0);
+    if (FOR == SR_ROWS_ORDERED) turn = !(g.flags & SR_SEG_QUADS);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const SrRowAt at = sr_row_at(p, g, i0 + (quads ? n * 16 + (lane >> 2) : (lane & 31)));
+      row_h[n] = at.h;
+      row_w[n] = at.w;
+      row_at[n] = src + at.off * 4;
+    }
+  }
+
+  __device__ __forceinline__ const char* gathered(int n, const SrTapAt& t, long long tap_bytes) const {
+    return sr_gather_ok(g, SrRowAt{row_h[n], row_w[n], 0}, t) ? row_at[n] + tap_bytes : (const char*)sr_zero_line;
+  }
+  // theta at row r, column j (forward)
+  __device__ __forceinline__ const char* theta(int r, int j) const {
+    const bool ok = (r < g.R) & (j < g.ldw);   // (&& is a branch here: 2 % of a frame)
+    return ok ? sr_at((const char*)g.w, (uint32_t)r * (uint32_t)g.ldw + (uint32_t)j) : (const char*)sr_zero_line;
+  }
+
+  // loads of the 16 reduction indices from r0 on, into LDS at `at`
+  __device__ __forceinline__ void issue(int r0, unsigned at) {
+    const char* zero = (const char*)sr_zero_line;
+    const unsigned bt = at + 32 * 64;
+    if (quads) {
+      const int k4 = sr_f32_piece(lane >> 2, lane & 3);
+      SrTapAt t;
+      if ((g.GC & 15) == 0) {   // the step lies inside one tap: its decoding runs on the scalar unit
+        t = sr_tap_at(g, SR_UNI(r0));
+        t.c += 4 * k4;
+      } else {
+        t = sr_tap_at(g, r0 + 4 * k4);
+      }
+      const long long toff = sr_gather_off(g, t) * 4;
+#pragma unroll
+      for (int n = 0; n < N; ++n) sr_to_lds16(gathered(n, t, toff), at + n * 1024);
+      if (BACK) {
+        const bool r_ok = t.vi != SR_NO_TAP;
+        const uint32_t woff = sr_weight_off(g, t, 0);
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+          const int j = j0 + n * 16 + (lane >> 2);
+          sr_to_lds16(r_ok && j < g.ldw ? sr_at((const char*)g.w, woff + (uint32_t)j * (uint32_t)g.GC) : zero, bt + n * 1024);
+        }
+        return;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int line = 2 * q + (lane >> 5);
+        const SrTapAt t = sr_tap_at(g, r0 + (FOR == SR_ROWS_ORDERED && turn ? sr_in_turn(line) : line));
+        sr_to_lds4(gathered(0, t, sr_gather_off(g, t) * 4), at + q * 256);
+      }
+      if (BACK) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int j = j0 + (lane & 31);
+          const SrTapAt t = sr_tap_at(g, r0 + 2 * q + (lane >> 5));
+          sr_to_lds4(t.vi != SR_NO_TAP && j < g.ldw ? sr_at((const char*)g.w, sr_weight_off(g, t, j)) : zero, bt + q * 256);
+        }
+        return;
+      }
+    }
+    // forward: 16 lines of theta
+    if (FOR == SR_ROWS_ORDERED && turn) {
+      if (quads_w) {
+#pragma unroll
+        for (int n = 0; n < N; ++n) sr_to_lds16(theta(r0 + sr_in_turn(n * 8 + lane / 8), j0 + 4 * (lane % 8)), bt + n * 1024);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sr_to_lds4(theta(r0 + sr_in_turn(q * 2 + lane / 32), j0 + lane % 32), bt + q * 256);
+      }
+    } else if (quads_w) {
+#pragma unroll
+      for (int n = 0; n < N; ++n) sr_to_lds16(theta(r0 + n * 8 + lane / 8, j0 + 4 * (lane % 8)), bt + n * 1024);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sr_to_lds4(theta(r0 + q * 2 + lane / 32, j0 + lane % 32), bt + q * 256);
+    }
+  }
+
+  // Addresses that go on from one of a wave's steps to the next, each in one tap.
+  int vi, vj, c;             // tap and first channel of the step that the addresses are for
+  const char* row_k[N];      // row_at, at this lane's channels of a step
+  const char* cur[N];
+  unsigned go[N];            // 4, or 0 where the line of zeros is read: bytes per channel passed
+  const char* w;             // forward: theta at the step's first index, column j0; backwards: at its tap and channel, row j0
+  uint32_t woff[BACK ? N : 1];
+
+  // can the segment's steps go that way? (channels in sixteens; theta's lane offsets fit 32 bits)
+  __device__ __forceinline__ bool goes_along() const { return quads && (g.GC & 15) == 0 && (BACK ? g.GC : g.ldw) < (1 << 22); }
+  __device__ __forceinline__ void begin_along(int r0) {
+    const SrTapAt t = sr_tap_at(g, SR_UNI(r0));
+    vi = t.vi;
+    vj = t.vj;
+    c = t.c;
+#pragma unroll
+    for (int n = 0; n < N; ++n) row_k[n] = row_at[n] + 16 * sr_f32_piece(lane >> 2, lane & 3);
+    if (BACK) {   // (columns that the node does not have read its last one)
+#pragma unroll
+      for (int n = 0; n < N; ++n)
+        woff[n] = ((uint32_t)min(n * 16 + (lane >> 2), g.ldw - 1 - j0) * (uint32_t)g.GC + 4u * (uint32_t)sr_f32_piece(lane >> 2, lane & 3)) * 4u;
+    } else {
+      w = (const char*)g.w + ((unsigned long long)(unsigned)r0 * (unsigned)g.ldw + (unsigned)j0) * 4;
+      woff[0] = quads_w ? ((uint32_t)(lane / 8) * (uint32_t)g.ldw + (uint32_t)min(4 * (lane % 8), g.ldw - 4 - j0)) * 4u
+                        : ((uint32_t)(lane / 32) * (uint32_t)g.ldw + (uint32_t)min(lane % 32, g.ldw - 1 - j0)) * 4u;
+    }
+    look();
+  }
+  // the addresses at tap (vi, vj), channel c
+  __device__ __forceinline__ void look() {
+    const SrTapAt t{vi, vj, c};
+    const long long toff = sr_gather_off(g, t) * 4;
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const bool ok = sr_gather_ok(g, SrRowAt{row_h[n], row_w[n], 0}, t);
+      cur[n] = ok ? row_k[n] + toff : (const char*)sr_zero_line;
+      go[n] = ok ? 4u : 0u;
+    }
+    if (BACK) w = (const char*)g.w + (unsigned long long)(unsigned)j0 * (unsigned)g.GC * 4 + (unsigned long long)sr_weight_off(g, t, 0) * 4;
+  }
+  // ... four steps further on
+  __device__ __forceinline__ void advance() {
+    constexpr int D = 4 * SR_F32_KS;
+    if (!BACK) w += (unsigned long long)((unsigned)g.ldw * (4u * D));
+    c += D;
+    if (c < g.GC) {
+#pragma unroll
+      for (int n = 0; n < N; ++n) cur[n] += D * go[n];
+      if (BACK) w += 4 * D;
+      return;
+    }
+    do {
+      c -= g.GC;
+      if (++vj == g.ntj) { vj = 0; ++vi; }
+    } while (c >= g.GC);
+    look();
+  }
+  // loads of a step all of whose indices exist, at the addresses in hand
+  __device__ __forceinline__ void issue_along(unsigned at) const {
+    const unsigned bt = at + 32 * 64;
+#pragma unroll
+    for (int n = 0; n < N; ++n) sr_to_lds16(cur[n], at + n * 1024);
+    const char* wu = sr_uni_ptr(w);
+    const unsigned line = (unsigned)g.ldw * 4u;
+    if (BACK || quads_w) {
+#pragma unroll
+      for (int n = 0; n < N; ++n) {   // forward: eight lines further on each time
+        uint32_t o = woff[BACK ? n : 0];
+        asm volatile("" : "+v"(o));   // keeps the offset 32-bit: scalar base + lane offset addressing
+        sr_to_lds16((BACK ? wu : wu + (unsigned long long)(n * 8) * line) + o, bt + n * 1024);
+      }
+    } else {
+      uint32_t o = woff[0];
+      asm volatile("" : "+v"(o));
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sr_to_lds4(wu + (unsigned long long)(q * 2) * line + o, bt + q * 256);
     }
   }
 };
@@ -573,174 +757,211 @@ __device__ __forceinline__ bool sr_row_split(float (&o)[N], const SrSplitScratch
   return true;
 }
 
-// where a recorded node's values go as well (frame path)
-struct SrRecord { float* out; };
-
-// A row tile.  SMALL: every wave takes every fourth step of a 32 x 32 tile through LDS of its own (no barriers); the
-// four waves' sums are added in order at the end.  Ordered, four steps go at a time: wave w fetches the w-th, then every
-// wave multiplies all four for a 16 x 16 quarter of the tile -- as long a chain of products per wave.
-template <int TI, int TJ, int WJN, int FOR, bool SMALL, int STAGES>
-__device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhase) phase, int i0, int j0, int step_begin, int step_end,
-                                            int split_slot, int part_info, const SrSlots& sl, float* record, int rec_node,
-                                            unsigned char* lds) {
-  constexpr bool BACK = FOR == SR_ROWS_BACK, ORDERED = FOR == SR_ROWS_ORDERED;
-  constexpr bool PAIRS = STAGES == SR_F32_PAIRS, ALONE = SMALL && !ORDERED, QUARTERS = SMALL && ORDERED;
-  constexpr int NW = SMALL ? 1 : 4, WIN = NW / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
-  typedef SrRowOperands<TI, TJ, NW, FOR> Ops;
-  const int tid = threadIdx.x, lane = tid & 63, wave = SR_UNI(tid >> 6);
-  const int iw = (wave / WJN) * 32 * MI * (SMALL ? 0 : 1), jw = (wave % WJN) * 32 * MJ * (SMALL ? 0 : 1);
-  constexpr int PITCH = (QUARTERS ? 4 : 1) * Ops::STAGE;   // from one stage to the next
-  unsigned char* base = ALONE ? lds + wave * ((PAIRS ? 4 : STAGES) * Ops::STAGE) : lds;
-  const unsigned at0 = sr_lds_at(base) + (QUARTERS ? wave * Ops::STAGE : 0);
-
-  Ops op;
-  op.wv = SMALL ? 0 : wave; op.lane = lane; op.i0 = i0; op.j0 = j0;
-  f32x16_t acc[MI][MJ];
-#pragma unroll
-  for (int x = 0; x < MI; ++x)
-#pragma unroll
-    for (int y = 0; y < MJ; ++y)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
-  f32x16_t sum[ORDERED ? MI : 1][ORDERED ? MJ : 1];   // of the segments that are done
-  if constexpr (ORDERED) {
-#pragma unroll
-    for (int x = 0; x < MI; ++x)
-#pragma unroll
-      for (int y = 0; y < MJ; ++y) sum[x][y] = acc[x][y];
+// Where a tile's sums go and what is applied to them on the way: open() reads the node, locate() the tensors, a round trip each.
+template <int FOR, int YB>
+struct SrRowEnd {
+  static constexpr bool BACK = FOR == SR_ROWS_BACK;
+  float* out;
+  const float *mask, *gate, *seed;
+  int C, act, id_out, id_mask, id_x, id_seed;
+  const float* biases;
+  float bias[BACK ? 1 : YB];   // of this lane's columns j0, j0 + 32, ..
+  __device__ __forceinline__ void open(SR_CONST4(SrRowNode) nd) {
+    C = nd->C;
+    act = nd->act;
+    id_out = nd->out;
+    id_mask = nd->mask;
+    id_x = nd->x;
+    id_seed = nd->seed;
+    biases = nd->bias;
   }
-  f32x4_t quarter{0.f, 0.f, 0.f, 0.f}, quarter_sum{0.f, 0.f, 0.f, 0.f};
-
-  if (!SMALL) __builtin_amdgcn_s_setprio(2);
-  // where the result goes and what the epilogue reads, fetched while the first operands are on their way
-  SR_CONST4(SrRowNode) nd = sr_k(A.nodes) + phase->node;
-  struct { float* out; const float *mask, *gate, *seed, *bias; int C, act; } end;
-  end.C = nd->C;
-  end.act = nd->act;
-  end.bias = nd->bias;
-  const int id_out = nd->out, id_x = nd->x, id_seed = nd->seed, id_mask = nd->mask;
-  constexpr int YB = SMALL ? 1 : MJ;
-  float bias_j[BACK ? 1 : YB];
-  auto column = [&](int y) { return QUARTERS ? j0 + 16 * (wave & 1) + (lane & 15) : j0 + jw + y * 32 + (lane & 31); };
-  auto prepare_end = [&]() {
+  __device__ __forceinline__ void locate(const SrRowArgs& A, const SrSlots& sl, int j0) {
     auto tensor_at = [&](int id, int slot) -> float* {   // (tensor 0 stands in for one that is not there: no branch, so one round trip for all)
       SR_CONST4(SrTensor) t = sr_k(A.tensors) + max(id, 0);
       char* b = (char*)(unsigned long long)t->base;
       return (float*)(id < 0 || b == nullptr ? nullptr : b + slot * t->stride);
     };
-    end.out = tensor_at(id_out, sl.own);
-    end.mask = FOR == SR_ROWS_FRAME ? nullptr : tensor_at(id_mask, sl.frame);
-    end.gate = BACK && end.act == 1 ? tensor_at(id_x, sl.frame) : nullptr;
-    end.seed = BACK ? tensor_at(id_seed, sl.frame) : nullptr;
+    out = tensor_at(id_out, sl.own);
+    mask = FOR == SR_ROWS_FRAME ? nullptr : tensor_at(id_mask, sl.frame);
+    gate = BACK && act == 1 ? tensor_at(id_x, sl.frame) : nullptr;
+    seed = BACK ? tensor_at(id_seed, sl.frame) : nullptr;
     if constexpr (!BACK) {
 #pragma unroll
-      for (int y = 0; y < YB; ++y) bias_j[y] = end.bias && column(y) < end.C ? end.bias[column(y)] : 0.f;
+      for (int y = 0; y < YB; ++y) bias[y] = biases && j0 + y * 32 < C ? biases[j0 + y * 32] : 0.f;
     }
-  };
-  const int seg_begin = phase->seg_begin, seg_image = phase->seg_image, seg_last = phase->seg_end;
-  // two groups of segments: those that depend on the image only, whose sum is scaled, then the others
-  for (int group = (seg_image > seg_begin) ? 0 : 1; group < 2; ++group) {
-    int seg = (group == 0 ? seg_begin : seg_image) - 1;
-    const int seg_end = group == 0 ? seg_image : seg_last;
+  }
+};
+
+// Bias, loss term, rectifier, gate and mask over a tile's sums o, and their store.  A lane has XB x YB blocks 32 rows and columns
+// apart, in each VB values of column j0, from row row0 on (VB = 16: rows 8 (v / 4) + v % 4 further on).  i_end: the tile's end.
+template <int FOR, int XB, int YB, int VB>
+__device__ __forceinline__ void sr_row_store(const SrRowArgs& A, const SrRowEnd<FOR, YB>& end, SR_CONST4(SrPhase) ph, float* record, int rec_node,
+                                             const float* o, int row0, int j0, int i_end) {
+  constexpr bool BACK = FOR == SR_ROWS_BACK;
+  SR_CONST4(SrRowNode) nd = sr_k(A.nodes) + ph->node;
+  const int I = ph->I, S = ph->S, C = end.C;
+  if (rec_node < 0 || nd->gnode != rec_node) record = nullptr;
+  const bool whole = i_end <= I;   // all rows exist
+  auto further = [](int q) { return VB == 4 ? q : 8 * (q >> 2) + (q & 3); };
+#pragma unroll
+  for (int x = 0; x < XB; ++x) {
+    const int row = row0 + x * 32;
+    size_t at[VB];
+    if (S == 1) {
+      const size_t at0 = (size_t)row * C;
+#pragma unroll
+      for (int q = 0; q < VB; ++q) at[q] = whole || row + further(q) < I ? at0 + (size_t)further(q) * C : 0;
+    } else {
+      const SrPhase p = sr_load_phase(ph);
+      const int H = nd->H, W = nd->W;
+#pragma unroll
+      for (int q = 0; q < VB; ++q) {
+        const int i = row + further(q) < I ? row + further(q) : 0;
+        const int b = sr_divide(i, p.d_hpwp), rem = i - b * (p.Hp * p.Wp);
+        const int hh = sr_divide(rem, p.d_wp), ww = rem - hh * p.Wp;
+        at[q] = (((size_t)b * H + hh * p.S + p.ph) * W + ww * p.S + p.pw) * C;
+      }
+    }
+#pragma unroll
+    for (int y = 0; y < YB; ++y) {
+      const int j = j0 + y * 32;
+      if (j >= C) continue;
+      float val[VB];
+#pragma unroll
+      for (int q = 0; q < VB; ++q) val[q] = o[(x * YB + y) * VB + q] + (BACK ? 0.f : end.bias[BACK ? 0 : y]);
+      if (end.seed) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q) val[q] += end.seed[at[q] + j];
+      }
+      if (BACK) {
+        if (end.gate) {
+#pragma unroll
+          for (int q = 0; q < VB; ++q) val[q] = end.gate[at[q] + j] > 0.f ? val[q] : 0.f;
+        }
+      } else if (end.act == 1) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q) val[q] = fmaxf(val[q], 0.f);
+      }
+      if (end.mask) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q) val[q] *= end.mask[at[q] + j];
+      }
+      if (whole) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q) end.out[at[q] + j] = val[q];
+      } else {
+#pragma unroll
+        for (int q = 0; q < VB; ++q)
+          if (row + further(q) < I) end.out[at[q] + j] = val[q];
+      }
+      if (record) {
+#pragma unroll
+        for (int q = 0; q < VB; ++q)
+          if (row + further(q) < I) record[at[q] + j] = val[q];
+      }
+    }
+  }
+}
+
+// A 32 x 32 tile.  Every wave takes every fourth step through LDS of its own (no barriers); the four waves' sums are added in order
+// at the end.  Ordered, four steps go at a time: wave w fetches the w-th, then every wave multiplies all four for a 16 x 16
+// quarter of the tile -- as long a chain of products per wave.
+template <int FOR, int STAGES>
+__device__ __forceinline__ void sr_small_tile(const SrRowArgs& A, SR_CONST4(SrPhase) phase, int i0, int j0, int step_begin, int step_end,
+                                              int split_slot, int part_info, const SrSlots& sl, float* record, int rec_node,
+                                              unsigned char* lds) {
+  constexpr bool BACK = FOR == SR_ROWS_BACK, QUARTERS = FOR == SR_ROWS_ORDERED;
+  typedef SrSmallOperands<FOR> Ops;
+  const int tid = threadIdx.x, lane = tid & 63, wave = SR_UNI(tid >> 6);
+  constexpr int PITCH = (QUARTERS ? 4 : 1) * Ops::STAGE;   // from one stage to the next
+  unsigned char* base = QUARTERS ? lds : lds + wave * (STAGES * Ops::STAGE);
+  const unsigned at0 = sr_lds_at(base) + (QUARTERS ? wave * Ops::STAGE : 0);
+  const SrPhase p = sr_load_phase(phase);
+
+  Ops op;
+  op.lane = lane; op.i0 = i0; op.j0 = j0;
+  f32x16_t acc[1][1];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+  f32x4_t quarter{0.f, 0.f, 0.f, 0.f}, quarter_sum{0.f, 0.f, 0.f, 0.f};   // ordered: of the segment, of those that are done
+
+  // two groups of segments: those that depend on the image only (backwards), whose sum is scaled, then the others
+#pragma nounroll
+  for (int group = BACK && p.seg_image > p.seg_begin ? 0 : 1; group < 2; ++group) {
+    int seg = (group == 0 ? p.seg_begin : p.seg_image) - 1;
+    const int seg_end = group == 0 ? p.seg_image : p.seg_end;
+    constexpr int INC = 4 * SR_F32_KS, AHEAD = STAGES - 1;
     int r = 0, r_stop = 0;   // next step's first index, end of the segment's share
-    // r: the next step of this workgroup (wave), in the next segment where this one's share is done; false when there is none
+    // r: the next step of this wave (quarters: four steps), in the next segment where this one's share is done; false when there is none
     auto settle = [&]() -> bool {
       while (r >= r_stop) {
         if (++seg >= seg_end) return false;
-        const SrSeg g = sr_load_seg(sr_k(A.segs) + seg);
-        if (!sr_seg_counts<BACK>(g, sl)) continue;
-        const int n = (g.R + SR_F32_KS - 1) / SR_F32_KS;
-        int lo = max(step_begin - g.step0, 0);
-        const int hi = min(step_end - g.step0, n);
-        if (ALONE) lo += (wave - (g.step0 + lo)) & 3;
+        op.g = sr_load_seg(sr_k(A.segs) + seg);
+        if (!sr_seg_counts<BACK>(op.g, sl)) continue;
+        const int n = (op.g.R + SR_F32_KS - 1) / SR_F32_KS;
+        int lo = max(step_begin - op.g.step0, 0);
+        const int hi = min(step_end - op.g.step0, n);
+        if (!QUARTERS) lo += (wave - (op.g.step0 + lo)) & 3;
         r = lo * SR_F32_KS;
         r_stop = hi * SR_F32_KS;
-        if (r < r_stop) op.enter(g, sr_k(A.segs) + seg, phase, A.tensors, A.lines, sl, QUARTERS ? r + wave * SR_F32_KS : r);
+        if (r < r_stop) op.enter(p, A.tensors, sl);
       }
       return true;
     };
     auto next = [&]() -> bool {
-      r += SMALL ? 4 * SR_F32_KS : SR_F32_KS;
+      r += INC;
       return settle();
     };
     int issued = 0, done = 0, wr = 0, rd = 0;
     unsigned rows = 0;   // per stage: the gathered operand (backwards: both) lies row by row
     unsigned ends = 0;   // ordered, per stage: it is the last one of its segment
-    auto mark = [&](int stage) {   // what the step at r, about to be fetched into `stage`, is
-      const unsigned bit = 1u << stage;
-      rows = op.quads ? rows | bit : rows & ~bit;
-      if constexpr (ORDERED)
-        ends = r + (QUARTERS ? 4 : 1) * SR_F32_KS >= r_stop ? ends | bit : ends & ~bit;
-    };
     auto issue = [&]() {
-      mark(wr);
+      const unsigned bit = 1u << wr;
+      rows = op.quads ? rows | bit : rows & ~bit;
+      if constexpr (QUARTERS) ends = r + INC >= r_stop ? ends | bit : ends & ~bit;
       // (quarters: the steps of the four that are past the end of the share are zero)
-      op.issue(!QUARTERS ? r : (r + wave * SR_F32_KS < r_stop ? r + wave * SR_F32_KS : op.R), at0 + wr * PITCH);
-      if (!PAIRS) wr = wr == STAGES - 1 ? 0 : wr + 1;
+      op.issue(!QUARTERS ? r : (r + wave * SR_F32_KS < r_stop ? r + wave * SR_F32_KS : op.g.R), at0 + wr * PITCH);
+      wr = wr == STAGES - 1 ? 0 : wr + 1;
       ++issued;
     };
-    auto multiply = [&](int stage, bool a_rows) {
-      if (!SMALL) __builtin_amdgcn_s_setprio(0);
-      const unsigned char* st = base + stage * PITCH;
+    auto multiply = [&](bool a_rows) {   // the stage at rd
+      const unsigned char* st = base + rd * PITCH;
       if constexpr (QUARTERS) {
         SrQuarter f;
         if (a_rows) sr_quarter_read<true>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, f);
         else sr_quarter_read<false>(st, 16 * (wave >> 1), 16 * (wave & 1), lane, f);
         sr_quarter_products(f, quarter);
       } else {
-        sr_step_products<TI, TJ, MI, MJ>(st, iw, jw, lane, a_rows, BACK && a_rows, acc);
+        sr_step_products<32, 32, 1, 1>(st, 0, 0, lane, a_rows, BACK && a_rows, acc);
       }
-      if (!SMALL) __builtin_amdgcn_s_setprio(2);
     };
-    // do these stages hold steps that lie row by row, and none that ends a segment?
-    auto plain = [&](unsigned stages) { return (rows & stages) == stages && !(ORDERED && (ends & stages)); };
     auto fold = [&]() {   // a segment is done
-      if constexpr (QUARTERS) {
-        quarter_sum += quarter;
-        quarter = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      } else if constexpr (ORDERED) {
-#pragma unroll
-        for (int x = 0; x < MI; ++x)
-#pragma unroll
-          for (int y = 0; y < MJ; ++y)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              sum[x][y][v] += acc[x][y][v];
-              acc[x][y][v] = 0.f;
-            }
-      }
+      quarter_sum += quarter;
+      quarter = f32x4_t{0.f, 0.f, 0.f, 0.f};
     };
-    // The steps (pairs) of whole segments back to back, from r on, nothing but their loads and products: as long as there are
-    // such steps, AHEAD of them on the way at a time.  (Every step through the code that takes any step of any segment cost 130
-    // instructions around a pair's 16 products: 98 us of a DSR2 frame of batch 64; the same without them 67.)
-    constexpr int INC = (SMALL ? 4 : PAIRS ? 2 : 1) * SR_F32_KS, AHEAD = PAIRS ? 1 : STAGES - 1;
     bool more = next();
+    // The steps of whole segments back to back, from r on, nothing but their loads and products: as long as there are
+    // such steps, AHEAD of them on the way at a time.
     auto run_along = [&]() {
       int n = 0;   // passes to go
-      const char* w = nullptr;
       auto begin = [&](int least) -> bool {
-        if (!more || !op.template all_along<PAIRS>(r)) return false;
-        n = (r_stop - r + (ALONE ? INC - SR_F32_KS : 0)) / INC;
-        if (n < least) return false;
-        const int r0 = QUARTERS ? r + wave * SR_F32_KS : r;
-        op.go_on(r0);
-        if (!BACK) w = op.theta(r0);
+        n = (r_stop - r + (QUARTERS ? 0 : INC - SR_F32_KS)) / INC;
+        if (!more || n < least || !op.goes_along()) return false;
+        op.begin_along(QUARTERS ? r + wave * SR_F32_KS : r);
         return true;
       };
       if (!begin(1)) return;
       bool folding = false;
-      unsigned w_step = (unsigned)op.ldw * (4u * INC);
       for (;;) {
         if constexpr (QUARTERS && STAGES > 3) {
           // A quarter's sixteen products are a chain of 512 cycles; the reads of the next four steps' operands go under it.
           SrQuarter f, g;
           auto read = [&](SrQuarter& q) {
-            if (!op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::NA + TJ / 4 / NW)>();
+            if (!op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::N + 8)>();
             else sr_wait_loads<(AHEAD - 1) * Ops::LOADS>();
             sr_step_barrier();   // as below
-            op.template issue_along<false>(at0 + wr * PITCH, w);
-            op.template advance<INC>();
-            w += w_step;
+            op.issue_along(at0 + wr * PITCH);
+            op.advance();
             sr_quarter_read<true>(base + rd * PITCH, 16 * (wave >> 1), 16 * (wave & 1), lane, q);
             r += INC;
             rd = rd == STAGES - 1 ? 0 : rd + 1;
@@ -758,24 +979,231 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
           }
         } else {
           do {
-            if (SMALL && !BACK && !op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::NA + TJ / 4 / NW)>();
-            else sr_wait_loads<PAIRS ? 0 : (AHEAD - 1) * Ops::LOADS>();
-            if (!ALONE) sr_step_barrier();   // everybody's loads of the steps in hand; and the ones before have been read by all
-            op.template issue_along<PAIRS>(at0 + wr * PITCH, w);
-            op.template advance<INC>();
-            if (!BACK) w += w_step;
-            multiply(rd, true);
-            if (PAIRS) multiply(rd + 1, true);
+            if (!BACK && !op.quads_w) sr_wait_loads<(AHEAD - 1) * (Ops::N + 8)>();
+            else sr_wait_loads<(AHEAD - 1) * Ops::LOADS>();
+            if (QUARTERS) sr_step_barrier();   // everybody's loads of the steps in hand; and the ones before have been read by all
+            op.issue_along(at0 + wr * PITCH);
+            op.advance();
+            multiply(true);
             r += INC;
-            if (PAIRS) {
-              rd ^= 2;
-              wr ^= 2;
-            } else {
-              rd = rd == STAGES - 1 ? 0 : rd + 1;
-              wr = wr == STAGES - 1 ? 0 : wr + 1;
-            }
+            rd = rd == STAGES - 1 ? 0 : rd + 1;
+            wr = wr == STAGES - 1 ? 0 : wr + 1;
           } while (--n > 0);
         }
+        ends = 0;
+        if (QUARTERS && folding) {
+          fold();   // the segment before: its last steps were multiplied while this one's first were on the way
+          folding = false;
+          n = (r_stop - r) / INC;
+          if (n > 0) continue;
+        }
+        if (r < r_stop) break;   // what is less than four steps
+        if (QUARTERS) ends = 1u << (wr == 0 ? STAGES - 1 : wr - 1);
+        more = settle();
+        if (!begin(QUARTERS ? AHEAD : 1)) break;
+        if (QUARTERS) {
+          folding = true;
+          n = AHEAD;
+        }
+      }
+      rows = (1u << STAGES) - 1u;
+    };
+#pragma nounroll
+    for (int k = 0; k < AHEAD && more; ++k) {
+      issue();
+      more = next();
+    }
+    while (done < issued) {
+      bool end;   // of the loop: ordered, of a segment
+      do {
+        if (issued - done == AHEAD && r < r_stop) {
+          const unsigned others = ((1u << STAGES) - 1u) & ~(1u << wr);   // the stages on the way: row by row, and none ends a segment?
+          if ((rows & others) == others && !(QUARTERS && (ends & others))) run_along();
+        }
+        if (STAGES > 3 && issued - done >= 3) sr_wait_loads<2 * Ops::LOADS>();
+        else if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
+        else sr_wait_loads<0>();
+        if (QUARTERS) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
+        end = QUARTERS && ((ends >> rd) & 1);
+        if (more) {
+          issue();
+          more = next();
+        }
+        multiply((rows >> rd) & 1);
+        rd = rd == STAGES - 1 ? 0 : rd + 1;
+        ++done;
+        if (!QUARTERS) end = done == issued;
+      } while (!end);
+      if (QUARTERS) fold();
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (QUARTERS) sr_step_barrier();   // the stages are free again
+    if (BACK && group == 0) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[0][0][v] *= p.image_scale;
+    }
+  }
+
+  // register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 (a quarter: row 4 (l / 16) + v, column l % 16)
+  float o[4];
+  if constexpr (QUARTERS) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = quarter_sum[q];
+  } else {
+    __syncthreads();
+    float* red = (float*)lds;   // [wave][register][lane]
+#pragma unroll
+    for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float* s = red + (4 * wave + q) * 64 + lane;
+      o[q] = ((s[0] + s[16 * 64]) + s[32 * 64]) + s[48 * 64];
+    }
+  }
+  if ((part_info >> 16) > 1) {
+    __syncthreads();
+    if (!sr_row_split<4>(o, A.split, split_slot, part_info, tid, (int*)lds)) return;
+  }
+  const int row = i0 + (QUARTERS ? 16 * (wave >> 1) + 4 * (lane >> 4) : 8 * wave + 4 * (lane >> 5));
+  const int column = j0 + (QUARTERS ? 16 * (wave & 1) + (lane & 15) : (lane & 31));
+  SrRowEnd<FOR, 1> end;
+  end.open(sr_k(A.nodes) + p.node);
+  end.locate(A, sl, column);
+  sr_row_store<FOR, 1, 1, 4>(A, end, phase, record, rec_node, o, row, column, i0 + 32);
+}
+
+// A tile of four waves.
+template <int TI, int TJ, int WJN, int FOR, int STAGES>
+__device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhase) phase, int i0, int j0, int step_begin, int step_end,
+                                            const SrSlots& sl, float* record, int rec_node, unsigned char* lds) {
+  constexpr bool BACK = FOR == SR_ROWS_BACK, ORDERED = FOR == SR_ROWS_ORDERED;
+  constexpr bool PAIRS = STAGES == SR_F32_PAIRS;
+  constexpr int WIN = 4 / WJN, MI = TI / (32 * WIN), MJ = TJ / (32 * WJN);
+  typedef SrRowOperands<TI, TJ, FOR> Ops;
+  const int tid = threadIdx.x, lane = tid & 63, wave = SR_UNI(tid >> 6);
+  const int iw = (wave / WJN) * 32 * MI, jw = (wave % WJN) * 32 * MJ;
+  const unsigned at0 = sr_lds_at(lds);
+
+  Ops op;
+  op.wv = wave; op.lane = lane; op.i0 = i0; op.j0 = j0;
+  f32x16_t acc[MI][MJ];
+#pragma unroll
+  for (int x = 0; x < MI; ++x)
+#pragma unroll
+    for (int y = 0; y < MJ; ++y)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.f;
+  f32x16_t sum[ORDERED ? MI : 1][ORDERED ? MJ : 1];   // of the segments that are done
+  if constexpr (ORDERED) {
+#pragma unroll
+    for (int x = 0; x < MI; ++x)
+#pragma unroll
+      for (int y = 0; y < MJ; ++y) sum[x][y] = acc[x][y];
+  }
+
+  __builtin_amdgcn_s_setprio(2);
+  const int seg_begin = phase->seg_begin, seg_image = phase->seg_image, seg_last = phase->seg_end;
+  SrRowEnd<FOR, MJ> end;
+  const int column = j0 + jw + (lane & 31);
+  end.open(sr_k(A.nodes) + phase->node);
+  // two groups of segments: those that depend on the image only (backwards), whose sum is scaled, then the others
+  const int first = BACK && seg_image > seg_begin ? 0 : 1;
+  for (int group = first; group < 2; ++group) {
+    int seg = (group == 0 ? seg_begin : seg_image) - 1;
+    const int seg_end = group == 0 ? seg_image : seg_last;
+    int r = 0, r_stop = 0;   // next step's first index, end of the segment's share
+    // r: the next step of this workgroup (wave), in the next segment where this one's share is done; false when there is none
+    auto settle = [&]() -> bool {
+      while (r >= r_stop) {
+        if (++seg >= seg_end) return false;
+        const SrSeg g = sr_load_seg(sr_k(A.segs) + seg);
+        if (!sr_seg_counts<BACK>(g, sl)) continue;
+        const int n = (g.R + SR_F32_KS - 1) / SR_F32_KS;
+        const int lo = max(step_begin - g.step0, 0);
+        const int hi = min(step_end - g.step0, n);
+        r = lo * SR_F32_KS;
+        r_stop = hi * SR_F32_KS;
+        if (r < r_stop) op.enter(g, sr_k(A.segs) + seg, phase, A.tensors, A.lines, sl, r);
+      }
+      return true;
+    };
+    auto next = [&]() -> bool {
+      r += SR_F32_KS;
+      return settle();
+    };
+    int issued = 0, done = 0, wr = 0, rd = 0;
+    unsigned rows = 0;   // per stage: the gathered operand (backwards: both) lies row by row
+    unsigned ends = 0;   // ordered, per stage: it is the last one of its segment
+    auto mark = [&](int stage) {   // what the step at r, about to be fetched into `stage`, is
+      const unsigned bit = 1u << stage;
+      rows = op.quads ? rows | bit : rows & ~bit;
+      if constexpr (ORDERED)
+        ends = r + SR_F32_KS >= r_stop ? ends | bit : ends & ~bit;
+    };
+    auto issue = [&]() {
+      mark(wr);
+      op.issue(r, at0 + wr * Ops::STAGE);
+      if (!PAIRS) wr = wr == STAGES - 1 ? 0 : wr + 1;
+      ++issued;
+    };
+    auto multiply = [&](int stage, bool a_rows) {
+      __builtin_amdgcn_s_setprio(0);
+      sr_step_products<TI, TJ, MI, MJ>(lds + stage * Ops::STAGE, iw, jw, lane, a_rows, BACK && a_rows, acc);
+      __builtin_amdgcn_s_setprio(2);
+    };
+    // do these stages hold steps that lie row by row, and none that ends a segment?
+    auto plain = [&](unsigned stages) { return (rows & stages) == stages && !(ORDERED && (ends & stages)); };
+    auto fold = [&]() {   // a segment is done
+      if constexpr (ORDERED) {
+#pragma unroll
+        for (int x = 0; x < MI; ++x)
+#pragma unroll
+          for (int y = 0; y < MJ; ++y)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              sum[x][y][v] += acc[x][y][v];
+              acc[x][y][v] = 0.f;
+            }
+      }
+    };
+    // The steps (pairs) of whole segments back to back, from r on, nothing but their loads and products: as long as there are
+    // such steps, AHEAD of them on the way at a time.  (Every step through the code that takes any step of any segment cost 130
+    // instructions around a pair's 16 products: 98 us of a DSR2 frame of batch 64; the same without them 67.)
+    constexpr int INC = (PAIRS ? 2 : 1) * SR_F32_KS, AHEAD = PAIRS ? 1 : STAGES - 1;
+    bool more = next();
+    auto run_along = [&]() {
+      int n = 0;   // passes to go
+      const char* w = nullptr;
+      auto begin = [&](int least) -> bool {
+        if (!more || !op.template all_along<PAIRS>(r)) return false;
+        n = (r_stop - r) / INC;
+        if (n < least) return false;
+        op.go_on(r);
+        if (!BACK) w = op.theta(r);
+        return true;
+      };
+      if (!begin(1)) return;
+      bool folding = false;
+      unsigned w_step = (unsigned)op.ldw * (4u * INC);
+      for (;;) {
+        do {
+          sr_wait_loads<PAIRS ? 0 : (AHEAD - 1) * Ops::LOADS>();
+          sr_step_barrier();   // everybody's loads of the steps in hand; and the ones before have been read by all
+          op.template issue_along<PAIRS>(at0 + wr * Ops::STAGE, w);
+          op.template advance<INC>();
+          if (!BACK) w += w_step;
+          multiply(rd, true);
+          if (PAIRS) multiply(rd + 1, true);
+          r += INC;
+          if (PAIRS) {
+            rd ^= 2;
+            wr ^= 2;
+          } else {
+            rd = rd == STAGES - 1 ? 0 : rd + 1;
+            wr = wr == STAGES - 1 ? 0 : wr + 1;
+          }
+        } while (--n > 0);
         ends = 0;
         if (ORDERED && folding) {
           fold();   // the segment before: its last steps were multiplied while this one's first were on the way
@@ -783,7 +1211,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
           n = (r_stop - r) / INC;
           if (n > 0) continue;
         }
-        if (r < r_stop) break;   // what is less than a pair (four steps)
+        if (r < r_stop) break;   // what is less than a pair
         if (ORDERED) ends = 1u << (PAIRS ? rd + 1 : (wr == 0 ? STAGES - 1 : wr - 1));
         more = settle();
         if (!begin(ORDERED ? AHEAD : 1)) break;
@@ -795,7 +1223,6 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
       }
       rows = (1u << (PAIRS ? 4 : STAGES)) - 1u;
     };
-    bool first = group == ((seg_image > seg_begin) ? 0 : 1);
     if constexpr (PAIRS) {
       // two steps per barrier: a pair is fetched while the one before it is multiplied
       auto issue_pair = [&](int to) -> int {
@@ -810,7 +1237,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
         return n;
       };
       int cur = issue_pair(0);
-      if (first) prepare_end();
+      if (group == first) end.locate(A, sl, column);
       while (cur > 0) {
         bool end;   // of the loop: ordered, of a segment
         do {
@@ -837,15 +1264,14 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
         issue();
         more = next();
       }
-      if (first) prepare_end();
+      if (group == first) end.locate(A, sl, column);
       while (done < issued) {
         bool end;
         do {
           if (issued - done == AHEAD && plain(((1u << STAGES) - 1u) & ~(1u << wr))) run_along();
-          if (STAGES > 3 && issued - done >= 3) sr_wait_loads<2 * Ops::LOADS>();
-          else if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
+          if (issued - done >= 2) sr_wait_loads<Ops::LOADS>();
           else sr_wait_loads<0>();
-          if (!ALONE) sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
+          sr_step_barrier();   // everybody's loads of this step; and the step before has been read by all
           end = ORDERED && ((ends >> rd) & 1);
           if (more) {
             issue();
@@ -860,8 +1286,8 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (!ALONE) sr_step_barrier();   // the stages are free again
-    if (group == 0) {
+    sr_step_barrier();   // the stages are free again
+    if (BACK && group == 0) {
       const float image_scale = sr_again(phase)->image_scale;
 #pragma unroll
       for (int x = 0; x < MI; ++x)
@@ -872,104 +1298,15 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
     }
   }
 
-  constexpr int NREG = SMALL ? 4 : MI * MJ * 16;
-  float o[NREG];
-  if constexpr (QUARTERS) {
+  // register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its block
+  float o[MI * MJ * 16];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = quarter_sum[q];
-  } else if (SMALL) {
-    __syncthreads();
-    float* red = (float*)lds;   // [wave][register][lane]
+  for (int x = 0; x < MI; ++x)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
-    __syncthreads();
+    for (int y = 0; y < MJ; ++y)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float* s = red + (4 * wave + q) * 64 + lane;
-      o[q] = ((s[0] + s[16 * 64]) + s[32 * 64]) + s[48 * 64];
-    }
-  } else {
-#pragma unroll
-    for (int x = 0; x < MI; ++x)
-#pragma unroll
-      for (int y = 0; y < MJ; ++y)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[((x * MJ + y) * 16 + v) % NREG] = ORDERED ? sum[ORDERED ? x : 0][ORDERED ? y : 0][v] : acc[x][y][v];
-  }
-  if constexpr (SMALL) {   // only these are cut into parts
-    if ((part_info >> 16) > 1) {
-      __syncthreads();
-      if (!sr_row_split<NREG>(o, A.split, split_slot, part_info, tid, (int*)lds)) return;
-    }
-  }
-
-  // ---- epilogue.  Register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32 of its block (a quarter:
-  // row 4 (l / 16) + v, column l % 16).
-  SR_CONST4(SrPhase) ph = sr_again(phase);
-  const int I = ph->I, S = ph->S, C = end.C;
-  if (rec_node < 0 || sr_again(nd)->gnode != rec_node) record = nullptr;
-  constexpr int XB = SMALL ? 1 : MI, VB = SMALL ? 4 : 16;
-  const bool whole = i0 + TI <= I;   // all rows exist
-#pragma unroll
-  for (int x = 0; x < XB; ++x) {
-    // the lane's first row; register q is that many rows further on
-    const int row0 = i0 + (QUARTERS ? 16 * (wave >> 1) + 4 * (lane >> 4) : (SMALL ? 8 * wave : iw + x * 32) + 4 * (lane >> 5));
-    auto further = [](int q) { return SMALL ? q : 8 * (q >> 2) + (q & 3); };
-    size_t at[VB];
-    if (S == 1) {
-      const size_t at0 = (size_t)row0 * C;
-#pragma unroll
-      for (int q = 0; q < VB; ++q) at[q] = whole || row0 + further(q) < I ? at0 + (size_t)further(q) * C : 0;
-    } else {
-      const SrPhase p = sr_load_phase(ph);
-      const int H = sr_again(nd)->H, W = sr_again(nd)->W;
-#pragma unroll
-      for (int q = 0; q < VB; ++q) {
-        const int i = row0 + further(q) < I ? row0 + further(q) : 0;
-        const int b = sr_divide(i, p.d_hpwp), rem = i - b * (p.Hp * p.Wp);
-        const int hh = sr_divide(rem, p.d_wp), ww = rem - hh * p.Wp;
-        at[q] = (((size_t)b * H + hh * p.S + p.ph) * W + ww * p.S + p.pw) * C;
-      }
-    }
-#pragma unroll
-    for (int y = 0; y < YB; ++y) {
-      const int j = column(y);
-      if (j >= C) continue;
-      float val[VB];
-#pragma unroll
-      for (int q = 0; q < VB; ++q) val[q] = o[(x * YB + y) * VB + q] + (BACK ? 0.f : bias_j[BACK ? 0 : y]);
-      if (BACK && end.seed) {
-#pragma unroll
-        for (int q = 0; q < VB; ++q) val[q] += end.seed[at[q] + j];
-      }
-      if (BACK) {
-        if (end.gate) {
-#pragma unroll
-          for (int q = 0; q < VB; ++q) val[q] = end.gate[at[q] + j] > 0.f ? val[q] : 0.f;
-        }
-      } else if (end.act == 1) {
-#pragma unroll
-        for (int q = 0; q < VB; ++q) val[q] = fmaxf(val[q], 0.f);
-      }
-      if (FOR != SR_ROWS_FRAME && end.mask) {
-#pragma unroll
-        for (int q = 0; q < VB; ++q) val[q] *= end.mask[at[q] + j];
-      }
-      if (whole) {
-#pragma unroll
-        for (int q = 0; q < VB; ++q) end.out[at[q] + j] = val[q];
-      } else {
-#pragma unroll
-        for (int q = 0; q < VB; ++q)
-          if (row0 + further(q) < I) end.out[at[q] + j] = val[q];
-      }
-      if (record) {
-#pragma unroll
-        for (int q = 0; q < VB; ++q)
-          if (row0 + further(q) < I) record[at[q] + j] = val[q];
-      }
-    }
-  }
+      for (int v = 0; v < 16; ++v) o[(x * MJ + y) * 16 + v] = ORDERED ? sum[ORDERED ? x : 0][ORDERED ? y : 0][v] : acc[x][y][v];
+  sr_row_store<FOR, MI, MJ, 16>(A, end, sr_again(phase), record, rec_node, o, i0 + iw + 4 * (lane >> 5), column, i0 + TI);
 }
 
 template <int FOR, int VARIANT>
@@ -981,13 +1318,13 @@ __device__ __forceinline__ void sr_row_item(const SrRowArgs& A, SR_CONST4(SrRowT
   const int shape = t->shape, i0 = t->i0, j0 = t->j0, sb = t->step_begin, se = t->step_end, slot = slot0 + t->split_slot, part = t->part;
   if constexpr (VARIANT != SR_F32_DEEP) {
     if constexpr (VARIANT == SR_F32_WIDE)
-      if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, FOR, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-    if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, FOR, false, 3>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-    else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, FOR, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
-    else if (shape == SR_F32_128x32) sr_row_tile<128, 32, 1, FOR, false, SR_F32_PAIRS>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+      if (shape == SR_F32_128x128) sr_row_tile<128, 128, 2, FOR, 3>(A, p, i0, j0, sb, se, sl, record, rec_node, lds);
+    if (shape == SR_F32_128x64) sr_row_tile<128, 64, 2, FOR, 3>(A, p, i0, j0, sb, se, sl, record, rec_node, lds);
+    else if (shape == SR_F32_64x64) sr_row_tile<64, 64, 2, FOR, SR_F32_PAIRS>(A, p, i0, j0, sb, se, sl, record, rec_node, lds);
+    else if (shape == SR_F32_128x32) sr_row_tile<128, 32, 1, FOR, SR_F32_PAIRS>(A, p, i0, j0, sb, se, sl, record, rec_node, lds);
   }
   if (shape == SR_F32_SMALL)
-    sr_row_tile<32, 32, 1, FOR, true, sr_f32_stages(VARIANT, SR_F32_SMALL)>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
+    sr_small_tile<FOR, sr_f32_stages(VARIANT, SR_F32_SMALL)>(A, p, i0, j0, sb, se, slot, part, sl, record, rec_node, lds);
 }
 
 }  // namespace

@@ -1104,9 +1104,13 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
 
   __builtin_amdgcn_s_setprio(2);
   const int seg_begin = phase->seg_begin, seg_image = phase->seg_image, seg_last = phase->seg_end;
+  // Located while the first operands are on their way (24x24 frames of 40 channels 995 -> 965 us; DSR6 571 -> 567), but at the end in the
+  // forward pass of a window: there it took registers that its sums need (a first depth of 2 to 5 steps a tile: GTSRB-shaped 59 -> 47
+  // us, DSR2 31 -> 28)
+  constexpr bool EARLY = !ORDERED;
   SrRowEnd<FOR, MJ> end;
   const int column = j0 + jw + (lane & 31);
-  end.open(sr_k(A.nodes) + phase->node);
+  if (EARLY) end.open(sr_k(A.nodes) + phase->node);
   // two groups of segments: those that depend on the image only (backwards), whose sum is scaled, then the others
   const int first = BACK && seg_image > seg_begin ? 0 : 1;
   for (int group = first; group < 2; ++group) {
@@ -1237,7 +1241,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
         return n;
       };
       int cur = issue_pair(0);
-      if (group == first) end.locate(A, sl, column);
+      if (EARLY && group == first) end.locate(A, sl, column);
       while (cur > 0) {
         bool end;   // of the loop: ordered, of a segment
         do {
@@ -1264,7 +1268,7 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
         issue();
         more = next();
       }
-      if (group == first) end.locate(A, sl, column);
+      if (EARLY && group == first) end.locate(A, sl, column);
       while (done < issued) {
         bool end;
         do {
@@ -1306,6 +1310,10 @@ __device__ __forceinline__ void sr_row_tile(const SrRowArgs& A, SR_CONST4(SrPhas
     for (int y = 0; y < MJ; ++y)
 #pragma unroll
       for (int v = 0; v < 16; ++v) o[(x * MJ + y) * 16 + v] = ORDERED ? sum[ORDERED ? x : 0][ORDERED ? y : 0][v] : acc[x][y][v];
+  if (!EARLY) {
+    end.open(sr_k(A.nodes) + sr_again(phase)->node);
+    end.locate(A, sl, column);
+  }
   sr_row_store<FOR, MI, MJ, 16>(A, end, sr_again(phase), record, rec_node, o, i0 + iw + 4 * (lane >> 5), column, i0 + TI);
 }
 

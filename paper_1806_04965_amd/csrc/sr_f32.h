@@ -16,6 +16,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <array>
+#include <map>
 #include <vector>
 
 #include "sr_internal.h"
@@ -360,6 +362,7 @@ struct sr_graph;
 struct SrRowPlan {
   std::vector<SrSeg> segs;
   std::vector<SrLine> lines;
+  std::map<std::array<int, 6>, int> line_tables;   // gathered channels, columns, taps per row, indices, direction, in turn -> its first line
   std::vector<SrPhase> phases;
   std::vector<SrRowNode> nodes;
 };

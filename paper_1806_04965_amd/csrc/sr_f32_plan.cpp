@@ -38,11 +38,18 @@ bool weights_fit(const EdgeRt& e, const Geometry& q) {
   return (int64_t)e.w_count < ((int64_t)1 << 32) && (int64_t)e.kh * e.kw * std::max(q.Cin, q.Cout) < kRows;
 }
 
-// The lines of segment s, in the order in which a step's indices lie in LDS
+// The lines of segment s, in the order in which a step's indices lie in LDS.  Segments that differ in nothing that a line holds
+// share a table: a node that a convolution and a dense edge read has a phase, and a segment of either, per pixel.
 void add_lines(SrRowPlan* p, SrSeg* s, bool in_turn) {
   s->lines = -1;
   if ((s->flags & SR_SEG_QUADS) || s->R > SR_LINES_MAX) return;
-  s->lines = (int)p->lines.size();
+  const auto known = p->line_tables.emplace(std::array<int, 6>{s->GC, s->GW, s->ntj, s->R, s->dir, in_turn}, -1);
+  int& at = known.first->second;
+  if (!known.second) {
+    s->lines = at;
+    return;
+  }
+  const int first = (int)p->lines.size();
   for (int r0 = 0; r0 < s->R; r0 += SR_F32_KS)
     for (int l = 0; l < SR_F32_KS; ++l) {
       const int r = r0 + (in_turn ? sr_in_turn(l) : l);
@@ -51,14 +58,14 @@ void add_lines(SrRowPlan* p, SrSeg* s, bool in_turn) {
         const SrTapAt t = sr_tap_at(*s, r);
         const long long off = sr_gather_off(*s, t);
         if (off != (int32_t)off) {   // taps of an image of 2^31 floats a row apart and more
-          p->lines.resize(s->lines);
-          s->lines = -1;
+          p->lines.resize(first);
           return;
         }
         x = SrLine{(int32_t)off, s->dir * t.vi, s->dir * t.vj, 0};
       }
       p->lines.push_back(x);
     }
+  at = s->lines = first;
 }
 
 }  // namespace

@@ -74,6 +74,46 @@ int main() {
 }
 """
 
+LINE_TABLES = COMMON + r"""
+static long checked = 0;
+// every segment's table against the indices decoded one by one
+static void compare(const SrRowPlan& p, bool in_turn) {
+  for (const SrSeg& s : p.segs) {
+    if (s.lines < 0) continue;
+    CHECK((s.R + 15) / 16 * 16 + (size_t)s.lines <= p.lines.size(), "a table past the end");
+    for (int k = 0; k < (s.R + 15) / 16 * 16; ++k) {
+      const int r = k / 16 * 16 + (in_turn ? sr_in_turn(k % 16) : k % 16);
+      const SrLine& x = p.lines[s.lines + k];
+      const SrTapAt t = sr_tap_at(s, r);
+      ++checked;
+      if (r >= s.R) CHECK(x.dh == SR_NO_ROW && x.dw == SR_NO_ROW, "an index that does not exist");
+      else CHECK(x.off == sr_gather_off(s, t) && x.dh == s.dir * t.vi && x.dw == s.dir * t.vj, "index %d of %d", r, s.R);
+    }
+  }
+}
+int main() {
+  // 96 x 96 pixels of 43 channels, read by two convolutions (stride 1 and 3) and a dense edge: a phase per pixel backwards
+  sr_graph* g = graph(2, {{3, 96}, {43, 96}, {43, 96}, {43, 32}, {10, 1}},
+                      {{0, 1, SR_EDGE_CONV, 5, 1, 2}, {1, 2, SR_EDGE_CONV, 3, 1, 1}, {1, 3, SR_EDGE_CONV, 3, 3, 0}, {1, 4, SR_EDGE_DENSE, 0, 1, 0},
+                       {2, 4, SR_EDGE_GAP_DENSE, 0, 1, 0}, {3, 4, SR_EDGE_GAP_DENSE, 0, 1, 0}, {2, 2, SR_EDGE_CONV, 3, 1, 1}, {3, 3, SR_EDGE_CONV, 7, 1, 3}});
+  const SrTrainIds ids = train_ids(g, 4);
+  for (int train = 0; train < 2; ++train) {
+    SrRowPlan f;
+    for (int v = 1; v < 4; ++v) sr_rows_forward(&f, g, v, train ? &ids : nullptr);
+    compare(f, train == 1);
+    std::printf("forward %zu segments, %zu lines\n", f.segs.size(), f.lines.size());
+  }
+  SrRowPlan b;
+  for (int v = 1; v < 4; ++v) sr_rows_backward(&b, g, v, ids);
+  compare(b, false);
+  std::printf("backwards %zu phases, %zu segments, %zu lines, %ld checked\n", b.phases.size(), b.segs.size(), b.lines.size(), checked);
+  // tables of 3 x 3, 1 x 1 (stride 3: its only tap row and column), 7 x 7 taps of 43 channels and of 10: 400, 48 and 2112 lines and 16
+  CHECK(b.segs.size() > 9216 * 2, "as many segments as expected");
+  CHECK(b.lines.size() <= 8192, "%zu lines", b.lines.size());
+  std::printf("ok\n");
+}
+"""
+
 
 def run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
@@ -82,9 +122,13 @@ def run(tmp_path, program):
                     "-I/opt/rocm/include", "-I", CSRC, str(src), os.path.join(CSRC, "sr_f32_plan.cpp"), "-o", str(exe)],
                    check=True, timeout=120)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
-    assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+    assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
     return r.stdout
 
 
 def test_tile_records_are_small(tmp_path):
     run(tmp_path, TILE_RECORD)
+
+
+def test_segments_share_tables_of_lines(tmp_path):
+    print(run(tmp_path, LINE_TABLES))

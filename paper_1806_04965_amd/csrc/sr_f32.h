@@ -399,6 +399,20 @@ struct SrGradPlan {
   int sum_blocks = 0, shapes = 0;
   long long part_floats = 0;
 };
-void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from);
+// items: work items per compute unit that the pixel sums are cut for
+void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from, int items);
+// What a window's plan may take: state gradients of so many frames at a time, and partial sums for so many work items per compute unit.
+#define SR_GRAD_ITEMS 12
+struct SrTrainRoom {
+  int frames, items;
+  // less than a plan that kept `kept` frames and whose memory was not to be had; false: there is nothing to take back
+  bool shrink(int kept) {
+    if (items == SR_GRAD_ITEMS) items /= 2;   // (cheapest: half the partial sums for 1.5 % of a GTSRB-shaped window)
+    else if (kept > 1) frames = kept / 2;
+    else if (items > 1) items = 1;
+    else return false;
+    return true;
+  }
+};
 
 #endif  // SR_F32_H_

@@ -364,7 +364,7 @@ void sr_rows_tiles(const SrRowPlan& p, const std::vector<int>& phases, double wo
     for (int x = 0; x < SR_XCDS; ++x) out->push_back(k < per_xcd[x].size() ? tiles[per_xcd[x][k].tile] : none);
 }
 
-void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from) {
+void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W, int lo, int hi, bool first, int tall_from, int items_per_cu) {
   // columns of work: per edge its shape, tiles, steps
   struct Item { int edge, shape, n_i, n_j, steps; double step_cycles; };
   std::vector<Item> items;
@@ -426,11 +426,11 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
     work += it.step_cycles * it.steps * it.n_i * it.n_j;
     p->shapes |= 1 << it.shape;
   }
-  // The pixel sums are cut into slices so that the launch has about twelve work items of equal length per compute unit,
+  // The pixel sums are cut into slices so that the launch has about items_per_cu (SR_GRAD_ITEMS: 12) work items of equal length per compute unit,
   // none shorter than 16 steps: shorter ones are dominated by filling the pipeline and by their partial sums.  (Six, two
   // generations on the three places of a compute unit, left a fifth of the DSR2 window's launch to the last ones:
   // 1480 us with 6, 1430 with 12, 1440 with 16; GTSRB-shaped 5630, 5550, 5555.)
-  const double item_cycles = work / (SR_CUS * 12.0);
+  const double item_cycles = work / (SR_CUS * (double)items_per_cu);
   struct Keyed { double cost; int tile; };
   std::vector<SrGradTile> tiles;
   // Every XCD takes an eighth of each edge's tiles, slice by slice: the tiles of a slice read the same pixels, which then come

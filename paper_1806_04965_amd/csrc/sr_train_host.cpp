@@ -144,8 +144,8 @@ int make_launches(const std::vector<std::vector<std::pair<int, int>>>& pairs, co
   return most;
 }
 
-// The plan for `key` with the state gradients of at most `most_kept` frames at a time; *kept receives their number.
-sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainPlan::Key& key, int most_kept, int* kept) {
+// The plan for `key` within `room`; *kept receives the number of frames whose state gradients it keeps at a time.
+sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainPlan::Key& key, const SrTrainRoom& room, int* kept) {
   const int N = g->n_nodes, E = g->n_edges, B = g->batch, W = key.W, out_node = key.out;
   SrTrainIds ids;
   ids.grad0 = N;
@@ -191,7 +191,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
   }
   int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(W, std::min<int64_t>(kGradRingBytes / 4 / frame_floats, ((int64_t)1 << 30) / most_pixels)));
   if (key.frames_kept > 0) chunk = std::min(chunk, key.frames_kept);
-  chunk = std::min(chunk, most_kept);
+  chunk = std::min(chunk, room.frames);
   *kept = chunk;
   const int ring = chunk + 1;
   const size_t x_at = take(frame_floats * W), dx_at = take(frame_floats * ring);
@@ -304,7 +304,7 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
           put(d, i, v);
         }
       slots = std::max(slots, make_launches(pairs, nb, &runs, &c.back));
-      sr_grad_plan(&c.grad, g, ids, W, c.lo, c.hi, hi == W, key.tall_from);
+      sr_grad_plan(&c.grad, g, ids, W, c.lo, c.hi, hi == W, key.tall_from, room.items);
       T.chunks.push_back(std::move(c));
     }
   }
@@ -388,8 +388,8 @@ sr_status make_plan(sr_graph* g, SrTrainState& S, SrTrainPlan& T, const SrTrainP
   return SR_OK;
 }
 
-// The plan of a call: one that is kept, or a new one.  A window whose memory is not to be had gets by with the gradients of
-// fewer frames at a time: at the least W + 2 frames of states.
+// The plan of a call: one that is kept, or a new one.  A window whose memory is not to be had gets by with fewer partial
+// sums and the gradients of fewer frames at a time: at the least W + 2 frames of states.
 sr_status plan_for(sr_graph* g, SrTrainState& S, const SrTrainPlan::Key& key, SrTrainPlan** out) {
   for (size_t k = 0; k < S.plans.size(); ++k)
     if (S.plans[k]->key == key) {
@@ -401,10 +401,10 @@ sr_status plan_for(sr_graph* g, SrTrainState& S, const SrTrainPlan::Key& key, Sr
     SR_HIP(g, hipStreamSynchronize(g->stream));   // its tables may still be in use
     S.plans.pop_back();
   }
-  for (int most = key.W;;) {
+  for (SrTrainRoom room{key.W, SR_GRAD_ITEMS};;) {
     std::unique_ptr<SrTrainPlan> p(new SrTrainPlan());
     int kept = 1;
-    const sr_status st = make_plan(g, S, *p, key, most, &kept);
+    const sr_status st = make_plan(g, S, *p, key, room, &kept);
     if (st == SR_OK) {
       S.plans.insert(S.plans.begin(), std::move(p));
       *out = S.plans[0].get();
@@ -412,8 +412,7 @@ sr_status plan_for(sr_graph* g, SrTrainState& S, const SrTrainPlan::Key& key, Sr
     }
     if (st != SR_ERR_OOM) return st;
     (void)hipGetLastError();   // of the allocation: the next launch would report it
-    if (kept <= 1) return st;
-    most = kept / 2;
+    if (!room.shrink(kept)) return st;
   }
 }
 

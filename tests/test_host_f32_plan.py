@@ -114,6 +114,44 @@ int main() {
 }
 """
 
+LITTLE_MEMORY = COMMON + r"""
+int main() {
+  // deep sums of large edges: as many slices as there are work items to make
+  sr_graph* g = graph(64, {{64, 16}, {256, 16}, {256, 16}, {512, 8}, {10, 1}},
+                      {{0, 1, SR_EDGE_CONV, 3, 1, 1}, {1, 2, SR_EDGE_CONV, 3, 1, 1}, {2, 3, SR_EDGE_CONV, 3, 2, 1}, {3, 3, SR_EDGE_CONV, 3, 1, 1},
+                       {1, 1, SR_EDGE_CONV, 3, 1, 1}, {3, 4, SR_EDGE_GAP_DENSE, 0, 1, 0}});
+  const SrTrainIds ids = train_ids(g, 4);
+  const int W = 8;
+  auto part_bytes = [&](const SrTrainRoom& r) {   // the largest chunk's, as a plan allocates them
+    long long most = 0;
+    for (int hi = W; hi >= 1; hi -= r.frames) {
+      SrGradPlan p;
+      sr_grad_plan(&p, g, ids, W, std::max(1, hi - r.frames + 1), hi, hi == W, 2048, r.items);
+      most = std::max(most, p.part_floats * 4);
+    }
+    return most;
+  };
+  // a room whose memory is not to be had is followed by a smaller one: partial sums for half as many work items before any frame is
+  // given up and with every number of frames after that, and for one a compute unit at the very end
+  SrTrainRoom r{W, SR_GRAD_ITEMS};
+  long long before = part_bytes(r);
+  const long long full = before;
+  int turns = 0, last_frames = W;
+  while (r.shrink(r.frames)) {
+    const long long now = part_bytes(r);
+    std::printf("%d frames, %d items: %lld bytes of partial sums\n", r.frames, r.items, now);
+    CHECK(r.frames <= last_frames && r.items < SR_GRAD_ITEMS, "%d frames, %d items", r.frames, r.items);
+    CHECK(turns > 0 || (r.frames == W && now <= full * 5 / 8), "the first turn: %d frames, %lld of %lld bytes", r.frames, now, full);
+    CHECK(r.frames < last_frames || now < before, "no less than before");
+    last_frames = r.frames;
+    before = now;
+    CHECK(++turns < 20, "no end");
+  }
+  CHECK(r.frames == 1 && r.items == 1 && before <= full / 6, "%d frames, %d items, %lld of %lld bytes at the end", r.frames, r.items, before, full);
+  std::printf("ok\n");
+}
+"""
+
 
 def run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
@@ -132,3 +170,7 @@ def test_tile_records_are_small(tmp_path):
 
 def test_segments_share_tables_of_lines(tmp_path):
     print(run(tmp_path, LINE_TABLES))
+
+
+def test_a_window_that_does_not_fit_takes_fewer_partial_sums(tmp_path):
+    print(run(tmp_path, LITTLE_MEMORY))

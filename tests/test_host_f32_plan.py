@@ -152,6 +152,54 @@ int main() {
 }
 """
 
+SPREAD = COMMON + r"""
+// cycles of the weight gradients' work items per XCD (workgroup i runs on XCD i % 8), by the planner's own measure
+static double spread(const char* name, sr_graph* g, int out, int W, double limit) {
+  const SrTrainIds ids = train_ids(g, out);
+  SrGradPlan p;
+  sr_grad_plan(&p, g, ids, W, 1, W, true, 2048, SR_GRAD_ITEMS);
+  double load[8] = {}, all = 0, longest = 0;
+  int items = 0;
+  for (size_t k = 0; k < p.tiles.size(); ++k) {
+    const SrGradTile& t = p.tiles[k];
+    if (t.kind == 2) continue;
+    int ti, tj;
+    sr_f32_shape(t.shape, &ti, &tj);
+    const double c = t.kind == 1 ? (t.step_end - t.step_begin) * 8.0
+                                 : std::max(ti * tj / 8.0, 900.0) * (p.edges[t.edge].quads_in ? 1.0 : 1.6) * (t.step_end - t.step_begin);
+    load[k % 8] += c;
+    all += c;
+    longest = std::max(longest, c);
+    ++items;
+  }
+  const double most = *std::max_element(load, load + 8), mean = all / 8;
+  std::printf("%s: %d items in %zu workgroups, most / mean %.3f, longest / mean %.3f\n", name, items, p.tiles.size(), most / mean, longest / mean);
+  // no XCD has more than the limit, unless a single item is that long
+  CHECK(most <= std::max(limit * mean, longest * 1.001), "%s", name);
+  CHECK(p.tiles.size() <= items * 3 / 2 + 16, "%s: %zu workgroups for %d items", name, p.tiles.size(), items);
+  return most / mean;
+}
+static sr_graph* mnist(int batch) {
+  return graph(batch, {{1, 28}, {16, 7}, {128, 1}, {10, 1}},
+               {{0, 1, SR_EDGE_CONV, 7, 4, 3}, {1, 2, SR_EDGE_DENSE, 0, 1, 0}, {2, 3, SR_EDGE_DENSE, 0, 1, 0}, {1, 3, SR_EDGE_DENSE, 0, 1, 0},
+                {1, 1, SR_EDGE_CONV, 3, 1, 1}});
+}
+static sr_graph* chain(int batch, int size, int width) {
+  return graph(batch, {{3, size}, {width, size}, {2 * width, size / 2}, {2 * width, size / 2}, {4 * width, size / 4}, {10, 1}},
+               {{0, 1, SR_EDGE_CONV, 3, 1, 1}, {1, 2, SR_EDGE_CONV, 3, 2, 1}, {2, 3, SR_EDGE_CONV, 3, 1, 1}, {1, 3, SR_EDGE_CONV, 3, 2, 1},
+                {3, 4, SR_EDGE_CONV, 3, 2, 1}, {2, 4, SR_EDGE_CONV, 3, 2, 1}, {2, 2, SR_EDGE_CONV, 3, 1, 1}, {4, 4, SR_EDGE_CONV, 3, 1, 1},
+                {4, 5, SR_EDGE_GAP_DENSE, 0, 1, 0}});
+}
+int main() {
+  spread("mnist_sr B=1", mnist(1), 3, 4, 1.3);
+  spread("mnist_sr B=16", mnist(16), 3, 8, 1.15);
+  spread("mnist_sr B=128", mnist(128), 3, 8, 1.1);
+  for (int width : {8, 24, 64})
+    for (int batch : {1, 5, 64}) spread("chain", chain(batch, 32, width), 5, 6, batch == 1 ? 1.25 : 1.15);
+  std::printf("ok\n");
+}
+"""
+
 
 def run(tmp_path, program):
     src, exe = tmp_path / "plan.cpp", tmp_path / "plan"
@@ -174,3 +222,7 @@ def test_segments_share_tables_of_lines(tmp_path):
 
 def test_a_window_that_does_not_fit_takes_fewer_partial_sums(tmp_path):
     print(run(tmp_path, LITTLE_MEMORY))
+
+
+def test_weight_gradients_are_spread_over_the_chip(tmp_path):
+    print(run(tmp_path, SPREAD))

@@ -216,6 +216,10 @@ SR_HD SrPixStep sr_pix_step(const SrGradEdge& e, int pixels) {
   s.off_h = image - (uint32_t)s.n_h * line;
   return s;
 }
+// ... to the next pixel, of a step's own terms: one column on, whose carry is the same
+SR_HD SrPixStep sr_pix_one(const SrGradEdge& e, const SrPixStep& s) {
+  return SrPixStep{e.stride, 0, s.n_w, s.n_h, (uint32_t)e.stride * (uint32_t)e.Cin, s.off_w, s.off_h};
+}
 // ... the step: (w, h) is a tap of the pixel's window, lim_w and lim_h what they reach one column or row past the target's last
 SR_HD void sr_pix_go(const SrPixStep& s, int stride, int lim_w, int lim_h, int* w, int* h, uint32_t* off) {
   const int w1 = *w + s.w;

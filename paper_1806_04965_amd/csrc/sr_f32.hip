@@ -1437,7 +1437,7 @@ struct SrGradOperands {
   uint32_t at_off[NA], ob;
   int px_h, px_w;                    // 4-byte loads: the wave's next pixel (scalar)
   uint32_t px_off;
-  int along, fi, m0;
+  int along, fi, m0, fresh;
   const char *xf, *yf;
 
   // pixel m's window, at this lane's tap
@@ -1460,6 +1460,7 @@ struct SrGradOperands {
   __device__ __forceinline__ void begin(int step) {
     fi = sr_divide(step, e.d_steps);
     m0 = (step - fi * e.steps_per_frame) * SR_F32_KS;
+    fresh = 0;
     if (!along) return;
     go = sr_pix_step(e, SR_F32_KS);
     tap_h = ti == SR_NO_TAP ? 0 : ti;
@@ -1469,7 +1470,7 @@ struct SrGradOperands {
     const int id = HALF_B ? wv * 32 + lane : wv * 64 + lane;
     if (quads_b) ob = ((uint32_t)(id / (TJ / 4)) * (uint32_t)e.Cout + (uint32_t)min(4 * (id % (TJ / 4)), e.Cout - 4 - j0)) * 4u;
     else ob = ((uint32_t)((wv * 64 + lane) / TJ) * (uint32_t)e.Cout + (uint32_t)min((wv * 64 + lane) % TJ, e.Cout - 1 - j0)) * 4u;
-    frame_begin();
+    fresh = 1;
   }
   __device__ __forceinline__ void frame_begin() {
     const int frame = e.frame0 + fi;
@@ -1485,13 +1486,13 @@ struct SrGradOperands {
       px_off = sr_pix_off(e, p, 0, 0);
     }
   }
-  // the wave's pixel: some further on
-  __device__ __forceinline__ void px_on(const SrPixStep& s) {
-    sr_pix_go(s, e.stride, s.n_w - e.pad, s.n_h - e.pad, &px_w, &px_h, &px_off);
-  }
   // loads of the next step
   __device__ __forceinline__ void issue_next(unsigned at) {
     const char* zero = (const char*)sr_zero_line;
+    if (fresh) {
+      frame_begin();
+      fresh = 0;
+    }
     if (!along || m0 + SR_F32_KS > e.M) {
       issue(fi * e.steps_per_frame + m0 / SR_F32_KS, at);
     } else {
@@ -1502,15 +1503,17 @@ struct SrGradOperands {
           step_on(n);
         }
       } else {
-        const SrPixStep one = sr_pix_step(e, 1);
+        const SrPixStep one = sr_pix_one(e, go);
+        int h = px_h, w = px_w;   // the wave's pixels one after the other
+        uint32_t off = px_off;
         const unsigned line = at + LINES * (TI == 128 ? wv >> 1 : wv) * (TI * 4) + (TI == 128 ? (wv & 1) * 256 : 0);
 #pragma nounroll
         for (int q = 0; q < LINES; ++q) {
-          const bool ok = (unsigned)(px_h + tap_h) < in_h && (unsigned)(px_w + tj) < (unsigned)e.W;
-          sr_to_lds4(ok ? sr_at(xf, px_off + aoff) : zero, line + q * (TI * 4));
-          px_on(one);
+          const bool ok = (unsigned)(h + tap_h) < in_h && (unsigned)(w + tj) < (unsigned)e.W;
+          sr_to_lds4(ok ? sr_at(xf, off + aoff) : zero, line + q * (TI * 4));
+          sr_pix_go(one, e.stride, one.n_w - e.pad, one.n_h - e.pad, &w, &h, &off);
         }
-        px_on(sr_pix_step(e, SR_F32_KS - LINES));
+        sr_pix_go(go, e.stride, go.n_w - e.pad, go.n_h - e.pad, &px_w, &px_h, &px_off);
       }
       const unsigned bt = at + TI * 64, line = (unsigned)e.Cout * 4u;
       const char* y = sr_uni_ptr(yf);
@@ -1536,7 +1539,7 @@ struct SrGradOperands {
     if (m0 >= e.M) {
       m0 = 0;
       ++fi;
-      if (along) frame_begin();
+      fresh = along;
     }
   }
 

@@ -404,7 +404,7 @@ void sr_grad_plan(SrGradPlan* p, const sr_graph* g, const SrTrainIds& ids, int W
     d.d_howo = sr_div_for(d.Ho * d.Wo);
     d.d_up = sr_div_for(q.up);
     d.d_steps = sr_div_for(d.steps_per_frame);
-    d.along = q.up == 1 && (int64_t)g->batch * q.H * q.W * q.Cin < ((int64_t)1 << 31) && q.Cout < (1 << 22) &&
+    d.along = q.up == 1 && d.M >= SR_F32_KS && (int64_t)g->batch * q.H * q.W * q.Cin < ((int64_t)1 << 31) && q.Cout < (1 << 22) &&
               std::max(q.Ho, q.Wo) < (1 << 24) / std::max(q.stride, 1);
     Item it{(int)p->edges.size(), 0, 0, 0, d.steps_per_frame * (f1 - f0 + 1), 0};
     p->edges.push_back(d);

@@ -70,21 +70,22 @@ static void steps(int B, int Ho, int Wo, int H, int W, int Cin, int stride, int 
   e.Ho = Ho; e.Wo = Wo; e.H = H; e.W = W; e.Cin = Cin; e.stride = stride; e.pad = pad;
   e.M = B * Ho * Wo;
   e.d_wo = sr_div_for(Wo); e.d_howo = sr_div_for(Ho * Wo); e.d_up = sr_div_for(1);
-  const SrPixStep s = sr_pix_step(e, pixels);
-  for (int ti : {0, 2})
-    for (int tj : {0, 1})
-      for (int m0 = 0; m0 < pixels && m0 < e.M; ++m0) {
-        const uint32_t aoff = (uint32_t)(ti * W + tj) * (uint32_t)Cin + 1u;
-        const SrPixAt p0 = sr_pix_at(e, m0);
-        int w = p0.w + tj, h = p0.h + ti;
-        uint32_t off = sr_pix_off(e, p0, 0, aoff);
-        for (int m = m0; m < e.M; m += pixels) {
-          const SrPixAt p = sr_pix_at(e, m);
-          CHECK(w == p.w + tj && h == p.h + ti, "pixel %d of %dx%d stride %d, %d further on: (%d, %d)", m, Ho, Wo, stride, pixels, h, w);
-          CHECK(off == sr_pix_off(e, p, 0, aoff), "offset of pixel %d of %dx%d", m, Ho, Wo);
-          sr_pix_go(s, stride, Wo * stride - pad + tj, Ho * stride - pad + ti, &w, &h, &off);
+  // (one pixel on: the step that a step of sixteen has the terms of, too)
+  for (const SrPixStep& s : {sr_pix_step(e, pixels), pixels == 1 ? sr_pix_one(e, sr_pix_step(e, 16)) : sr_pix_step(e, pixels)})
+    for (int ti : {0, 2})
+      for (int tj : {0, 1})
+        for (int m0 = 0; m0 < pixels && m0 < e.M; ++m0) {
+          const uint32_t aoff = (uint32_t)(ti * W + tj) * (uint32_t)Cin + 1u;
+          const SrPixAt p0 = sr_pix_at(e, m0);
+          int w = p0.w + tj, h = p0.h + ti;
+          uint32_t off = sr_pix_off(e, p0, 0, aoff);
+          for (int m = m0; m < e.M; m += pixels) {
+            const SrPixAt p = sr_pix_at(e, m);
+            CHECK(w == p.w + tj && h == p.h + ti, "pixel %d of %dx%d stride %d, %d further on: (%d, %d)", m, Ho, Wo, stride, pixels, h, w);
+            CHECK(off == sr_pix_off(e, p, 0, aoff), "offset of pixel %d of %dx%d", m, Ho, Wo);
+            sr_pix_go(s, stride, Wo * stride - pad + tj, Ho * stride - pad + ti, &w, &h, &off);
+          }
         }
-      }
 }
 
 int main() {

@@ -94,8 +94,6 @@ sr_status analyse_pattern(int n_nodes, const sr_edge_desc* edges, int n_edges, c
   return SR_OK;
 }
 
-constexpr int kFlowFrames = 64;   // frames of a dependency-driven launch
-
 inline int conv_out(int size, int k, int stride, int pad) { return (size + 2 * pad - k) / stride + 1; }
 
 inline uint16_t f2bf(float f) {
@@ -1339,8 +1337,7 @@ sr_status finalize(sr_graph* g) {
       // runs.  Every wait still refers to an earlier workgroup, and update steps of consecutive frames that do not
       // depend on one another are dispatched side by side instead of frame after frame.
       {
-        // (16 MiB of pairs at most)
-        const int n_frames = (int)std::min<int64_t>(kFlowFrames, ((int64_t)4 << 20) / std::max(g->n_flow_items, 1));
+        const int n_frames = sr_flow_frames(g->frames_per_graph_set ? g->frames_per_graph : 0, g->n_flow_items);
         run_begin.push_back((int)items.size());
         const int n_runs = (int)run_begin.size() - 1;
         std::vector<std::vector<int>> run_nodes(n_runs);
@@ -1356,7 +1353,7 @@ sr_status finalize(sr_graph* g) {
             }
             if (v >= 0 && run_of[v] != r) { run_of[v] = r; run_nodes[r].push_back(v); }
           }
-        bool ok = n_frames >= 2 && g->n_flow_items < (1 << 24);
+        bool ok = n_frames >= 2;
         std::vector<std::vector<int>> depth(n_frames, std::vector<int>(n_runs, 0));
         for (int t = 0; ok && t < n_frames; ++t)
           for (int r = 0; ok && r < n_runs; ++r) {
@@ -1695,7 +1692,7 @@ sr_status run_frames(sr_graph* g, int64_t frames, SrCtx c, bool next_frame, cons
   // Dependency-driven frames: launches of equal length, as few as may be, for each fills and drains the chip through all depths
   // of its frames (CIFAR-shaped sequential, 16 frames: two launches of 14 depths 897 us, one of 22 781; GTSRB-shaped 10970 -> 10630, hi-res 7100 -> 6340).
   int flow_most = g->frames_per_graph;
-  if (g->flow_depth_order && g->flow_frames_max > 1) flow_most = g->frames_per_graph_set ? std::min(flow_most, g->flow_frames_max) : g->flow_frames_max;
+  if (g->flow_depth_order && g->flow_frames_max > 1) flow_most = g->flow_frames_max;
   int64_t flow_launches = (left + flow_most - 1) / flow_most;
   for (; left > 0; --flow_launches) {
     const int n = flow ? (int)((left + flow_launches - 1) / flow_launches) : 1;

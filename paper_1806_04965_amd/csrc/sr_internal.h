@@ -69,6 +69,22 @@ struct SrFlow {
   const int32_t* order;
 };
 
+// Frames of a depth-ordered launch of graphs with `items` work items a frame, at most.  wanted: SR_OPT_FRAMES_PER_GRAPH if the caller
+// set it, else 0.  An entry of SrFlow::order holds a frame below 256 and an item below 2^24; a grid has at most 2^32 threads, here
+// 2^23 workgroups; unasked, the order takes no more than 16 MiB past eight frames.  64: us a frame
+// of 255 frames in launches of 8 / 32 / 64 / 128, CIFAR-shaped sequential B=64 54.7 / 42.7 / 42.4 / 40.3, hybrid B=3 26.6 / 23.8 / 23.7 / 23.3,
+// DSR4 sequential B=20 55.8 / 45.4 / 43.6 / 42.9; the order and the host's plan of it grow with the frames.
+#define SR_FLOW_FRAMES 64
+inline int sr_flow_frames(int wanted, int64_t items) {
+  int64_t n = wanted < 255 ? wanted : 255;
+  if (wanted == 0) {
+    n = ((int64_t)4 << 20) / (items > 0 ? items : 1);
+    n = n < 8 ? 8 : (n > SR_FLOW_FRAMES ? SR_FLOW_FRAMES : n);
+  }
+  const int64_t most = items < (1 << 24) ? ((int64_t)1 << 23) / (items > 0 ? items : 1) : 0;
+  return (int)(n < most ? n : most);
+}
+
 // A run of work items of one frame of a dependency-driven launch: items begin .. begin + count - 1 of frame t
 struct SrFlowRun { int32_t begin, count, t, pad_; };
 

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void sr_flow_order_kernel(const SrFlowRun* __r
   if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = n;
   __syncthreads();
   const int at = sums[0] + sums[1] + sums[2] + sums[3];
-  for (int k = threadIdx.x; k < mine.count; k += 256) order[at + k] = (mine.begin + k) | (mine.t << 24);
+  for (int k = threadIdx.x; k < mine.count; k += 256) order[at + k] = (int32_t)((unsigned)(mine.begin + k) | ((unsigned)mine.t << 24));
 }
 
 __global__ void sr_fill_zero_kernel(uint4* p, size_t n16, unsigned char* tail, size_t ntail) {

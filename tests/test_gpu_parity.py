@@ -473,8 +473,8 @@ def test_depth_ordered_multi_frame_launch_equals_frame_after_frame(name):
 
 @pytest.mark.parametrize("frames_per_launch", [1, 2, 5, 16])
 def test_depth_ordered_launches_of_other_lengths(frames_per_launch):
-    # the order table is built for the configured number of frames per launch; a rollout whose length is no
-    # multiple of it finishes with single-frame launches.  All of them equal one launch per update step.
+    # launches of at most the configured number of frames, of equal length or one apart (13 frames: 13 of 1; 6 of 2 and 1; 5, 4, 4;
+    # one of 13); the pairs are written for each length.  All of them equal one launch per update step.
     g0 = W.cifar_sr(batch=3, frames=13)
     g = g0.with_pattern(W.sequential_pattern(g0))
     w, b, x = W.make_case(g, seed=62, bias_scale=0.1, frames=13)
@@ -506,6 +506,18 @@ def test_depth_ordered_launches_follow_the_rollouts_length(pattern):
     h = dev.health()
     dev.close()
     assert h["dependency_driven"] and h["dependency_timeouts"] == 0
+
+
+@pytest.mark.parametrize("wanted", [100, 255, 1024])
+def test_launches_of_more_than_64_frames(wanted):
+    # frames from 128 on set the sign bit of a (frame, item) pair; 255 in one launch at most (260 frames: 3 of 87, 87, 86; 2 of 130)
+    g0 = W.cifar_sr(batch=1, frames=260)
+    g = g0.with_pattern(W.sequential_pattern(g0))
+    w, b, x = W.make_case(g, seed=65, bias_scale=0.1, frames=260)
+    a = gpu_rollout(g, w, b, x, 260, options={2: wanted})
+    c = gpu_rollout(g, w, b, x, 260, options={5: 0})
+    assert np.array_equal(a, c)
+    assert np.abs(a[-1]).max() > 0
 
 
 @pytest.mark.parametrize("batch", [1, 4, 37])

@@ -247,3 +247,55 @@ def test_replays_that_start_again_from_frame_0(name, what):
     assert dev.health()["dependency_timeouts"] == 0
     ref.close()
     dev.close()
+
+
+@pytest.mark.parametrize("pattern", [W.sequential_pattern, W.hybrid_pattern])
+def test_replays_of_recorded_rollouts_between_rollouts_of_other_lengths(pattern):
+    # a dependency-driven launch of several frames takes its work items in an order that is written for its number of frames:
+    # recordings of two lengths bring their own along, and ordinary rollouts between the replays write theirs again.  All equal
+    # one launch per update step, bit for bit.
+    import torch
+    import paper_1806_04965_amd as sr
+    g0 = W.cifar_sr(batch=2, frames=70)
+    g = g0.with_pattern(pattern(g0))
+    w, b, x = W.make_case(g, seed=23, bias_scale=0.1, frames=70)
+    xd = [to_device(x[v], g.dtype) for v in g.input_nodes()]
+    classes = g.nodes[g.out_node].channels
+    ref, dev = sr.SrGraph(g, options={5: 0}), sr.SrGraph(g)
+    want = torch.zeros((70, g.batch, 1, 1, classes), dtype=dev.tdtype, device="cuda")
+    for d in (ref, dev):
+        d.set_parameters(w, b)
+    ref.rollout(xd, 70, g.out_node, want)
+    ref.synchronize()
+    assert float(want[-1].abs().max()) > 0
+
+    def ordinary(T):
+        out = torch.zeros((T, g.batch, 1, 1, classes), dtype=dev.tdtype, device="cuda")
+        dev.rollout([t[:T + 1].contiguous() for t in xd], T, g.out_node, out)
+        dev.synchronize()
+        assert torch.equal(out, want[:T]), T
+
+    ordinary(20)                       # the order of the first recording's length is there when it is recorded
+    recordings = []
+    for T in (20, 7):
+        out, head = torch.zeros((T, g.batch, 1, 1, classes), dtype=dev.tdtype, device="cuda"), [t[:T + 1].contiguous() for t in xd]
+        recording = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(recording, stream=dev.stream):
+            dev.rollout(head, T, g.out_node, out)
+        recordings.append((recording, out, head))
+    for turn, lengths in enumerate([(), (70,), (20,), (7, 3), (64, 2, 20), (1,), (33, 70)]):
+        for T in lengths:
+            ordinary(T)
+        for recording, out, _ in recordings if turn % 2 else recordings[::-1]:
+            out.zero_()
+            torch.ones(1 << 20, device="cuda").cumsum(0)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(dev.stream):
+                recording.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want[:out.shape[0]]), (turn, out.shape[0])
+    h = dev.health()
+    assert h["dependency_driven"] and h["dependency_timeouts"] == 0
+    ref.close()
+    dev.close()

@@ -69,7 +69,7 @@ struct SrSeg {
   int32_t dist;           // backwards: the gathered node's gradient is zero after frame W - dist
   int32_t lines;          // first SrLine of the segment's reduction indices; -1: no table
 };
-// A reduction index of a segment whose gathered channel count is no multiple of four: where it is from tap (0, 0), and its tap.
+// A reduction index of a segment without SR_SEG_QUADS (a channel count that is no multiple of four): where it is from tap (0, 0), and its tap.
 // Sixteen per step, in the order of the lines of a stage; past the end: a tap outside every image.  (Decoded from the index, 25
 // scalar instructions a line, the five steps of a 5x5x3 edge took a 128 x 32 tile 30 us of 58.)
 SR_HD int sr_in_turn(int line) { return 2 * (line & 7) + (line >> 3); }   // the index of a step that line `line` of its stage holds, if in turn

@@ -12,14 +12,17 @@
 // costs take as long as its products.  So these fetch steps in pairs, a barrier per pair; launches without 128 x 128 tiles run
 // four workgroups per CU (see the variants in sr_f32.h); and the steps of whole segments go through a loop that holds nothing
 // but their loads and products (run_along below: 155 instructions a pair, 16 of them products, where the code that takes any
-// step of any segment has 400).  DSR2 frame: matrix cores 54 % busy before, 58 % since at 0.8 of the time.  What is left there is
-// not the loop (without its loads, or without its LDS reads, a frame takes as long): a 128 x 32 tile of 18 steps spends
-// 12 us of 28 in its tables, first operands and stores while its compute unit's other three do the same.
+// step of any segment has 400).  DSR2 frame: matrix cores 54 % busy before, 58 % since at 0.8 of the time.  Pairs are of consecutive
+// steps, whatever their segments (but for ordered sums, whose pairs end with a segment): behind a segment of an odd number of steps
+// the next one's pairs lie across the loop's, and none of them goes through it.  DSR2's largest node is such a one (5 steps of a
+// 5x5x3 edge, then 18 of its self edge: a quarter of a frame's operations), so what the loop is worth to a frame is not known from
+// a frame of DSR2; beside it a 128 x 32 tile of 18 steps spends 12 us of 28 in its tables, first operands and stores, while its
+// compute unit's other three do the same.
 //
 // Measured, DSR2 as an fp32 graph (batch 64, 6.4 GFLOP per frame): 1350 us per frame with a thread per output (weights
 // and taps through global loads, no matrix cores), 104 with row tiles (62 TFLOP/s), 100 with pairs, 82 with segments' steps back
-// to back; MNIST SR, batch 128: 31 -> 17 -> 13 us.  Training windows, step by step -> pairs and variants -> now: DSR2 B=64 W=8
-// 1674 -> 1480 -> 1405 us, GTSRB-shaped B=128 W=4 6270 -> 6180 -> 5550, MNIST SR 362 -> 350.
+// to back; MNIST SR, batch 128: 31 -> 17 -> 13 us.  Training windows, pairs and variants -> now, on one card: DSR2 B=64 W=8
+// 1479 -> 1380 us, GTSRB-shaped B=128 W=4 6174 -> 5492, MNIST SR B=128 W=8 362 -> 330.
 //
 // In the loop a wave's priority is raised but for its products: loads, addresses and set-up of one wave then go ahead of the
 // others' products, which the matrix cores take 64 cycles each for (GTSRB-shaped window 5690 -> 5620 us, DSR2 1437 -> 1423).

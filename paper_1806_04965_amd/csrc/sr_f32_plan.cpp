@@ -277,10 +277,12 @@ double sr_rows_work(const SrRowPlan& p, int phase) {
 // give the launch more workgroups and shorter chains of dependent steps.  A tile may take as long as an even share of
 // the launch's work per compute unit (or some microseconds), else the next smaller shape is tried; below that the
 // reduction is cut into parts.
-// What the constants are worth (us, with the kernels as they are: live tiny, MNIST SR clip, DSR2 clip, DSR2 sequential B=1, 40x40
-// net hybrid B=9, MNIST S clip B=9, DSR6 clip B=30; windows and the rest within 1 % either way) --
-//   6000 cycles a 32 x 32 tile may take uncut    5000: 33 209 1314 937 451 331 576; 7000: 32 207 1316 949 462 333 579; 10000: 33 223 1315 981 464 361 589
-//   750 per four steps of 32 x 32 tiles          500: 31 225 1717 1055 434 371 556; 1100: 31 207 1315 952 469 341 567 and a 30x30 window 300 -> 324
+// What the constants are worth (us; clips of MNIST SR B=128 T=16, DSR2 B=64 T=16, DSR2 sequential B=1 T=16, MNIST S B=9 T=32, DSR6 B=4 T=8,
+// windows of MNIST SR B=128 W=8, DSR2 B=16 W=4, DSR5 B=1 W=4; as they are 208 1306 1019 321 264 324 225 181) --
+//   6000 cycles a 32 x 32 tile may take uncut    5000: all within noise; 10000: 221 1305 1057 354 265 327 227 184
+//   750 per four steps of 32 x 32 tiles          500: 207 1724 1037 325 257 325 220 183; 1100: 208 1306 1019 321 278 325 224 180
+// The reverse launches alone, of 10000 cycles for 6000: MNIST SR B=128 11.0-11.8 -> 11.2-12.7 each, DSR2 B=64 and GTSRB-shaped equal.
+// Measured when the kernels were slower:
 //   12000 of a middle one, 512 of them           24000, 256: noise
 //   700 a step of middle tiles                   600, 900: noise
 //   20000 cycles a tall tile may take, 5000 fixed, at most 16 parts   measured when the kernels were slower: noise within 4 %

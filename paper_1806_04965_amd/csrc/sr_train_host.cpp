@@ -7,9 +7,9 @@
 // and state gradients are kept, so that all weight and bias gradients are one launch behind the sweep.
 //
 // Measured (launch per edge and per elementwise pass on four streams, state gradients accumulated in memory -> launch
-// per depth, everything fused): MNIST SR B=128 W=8 sequential 250 launches, 1.98 ms -> 25, 0.34; DSR2 B=64 W=8 485,
-// 5.1 -> 22, 1.4; GTSRB-shaped B=128 W=4 52.7 -> 5.6 (a window
-// shorter than the network is deep: an eighth of its nominal operations reach the loss; 106 TFLOP/s on those).
+// per depth, everything fused): MNIST SR B=128 W=8 sequential 250 launches, 1.98 ms -> 22, 0.33; DSR2 B=64 W=8 485,
+// 5.1 -> 18, 1.4; GTSRB-shaped B=128 W=4 52.7 -> 10, 5.5 (a window
+// shorter than the network is deep: an eighth of its nominal operations reach the loss; 107 TFLOP/s on those).
 //
 // Values that cannot reach a loss term are not computed: node v is at least dist(v) bridging edges away from the out
 // node, so its states and gradients of the frames after W - dist(v) have no reader.  Nor are the products with the
